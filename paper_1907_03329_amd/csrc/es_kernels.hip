@@ -7,6 +7,7 @@
 
 #include "device_utils.h"
 #include "esrnn_internal.h"
+#include "three_term.h"
 
 namespace esrnn {
 
@@ -90,73 +91,83 @@ struct PackLstmArgs {
     const float *W, *b;
     float *fwd, *bias, *bwd;
     int h, in_dim, HT, KXT;
-    int narrow;          // operand order of the 4-series kernels (4x4x1 MFMA) instead
+    int narrow_fwd, narrow_bwd;   // operand orders of the 4-series kernels (4x4x1 MFMA) instead
+
+    // element of W for gate `gate` of hidden unit `unit` and row `u` of the layer input or the recurrent state; zero
+    // in the padding
+    __device__ float at(int gate, int unit, bool in_x, int u) const
+    {
+        const bool exists = unit < h && u < (in_x ? in_dim : h);
+        return exists ? W[(size_t)(gate * h + unit) * (in_dim + h) + (in_x ? u : in_dim + u)] : 0.0f;
+    }
+    // the same for a row of [x ; h] in whole unit tiles
+    __device__ float at_row(int gate, int unit, int row) const
+    {
+        const int KX = 4 * KXT;
+        return row < KX ? at(gate, unit, true, row) : row < KX + 4 * HT ? at(gate, unit, false, row - KX) : 0.0f;
+    }
 };
 
 // Operands of the 4-series kernels.  v_mfma_f32_4x4x1: lane l supplies A[l%4] of block l/4.
 //   forward  [wave][column k of x ; h][lane]: gate l%4 of unit wave*HT + min(l/4, HT-1) (the blocks past HT
 //            repeat the last unit, so that all lanes do the same work on the same addresses)
 //   reverse  [wave][group g][k-step 4*u + gate][lane]: W[gate, unit wave*HT + u][column 64*g + l]
-__device__ void pack_lstm_narrow_body(const PackLstmArgs &a)
+__device__ void pack_forward_narrow(const PackLstmArgs &a)
 {
-    const int KX = 4 * a.KXT, KT4 = KX + 4 * a.HT, NG = (KT4 + 63) / 64, ld = a.in_dim + a.h;
-    const int n_fwd = 4 * KT4 * 64, n_bwd = 4 * NG * 4 * a.HT * 64;
-    auto user_col = [&](int k) {
-        if (k < KX) return k < a.in_dim ? k : -1;
-        if (k < KT4) return k - KX < a.h ? a.in_dim + k - KX : -1;
-        return -1;
-    };
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n_fwd + n_bwd; idx += gridDim.x * 256) {
-        if (idx < n_fwd) {
-            const int lane = idx & 63, k = (idx >> 6) % KT4, w = (idx >> 6) / KT4;
-            const int blk = min(lane >> 2, a.HT - 1), gate = lane & 3, unit = w * a.HT + blk, col = user_col(k);
-            a.fwd[idx] = (unit < a.h && col >= 0) ? a.W[(size_t)(gate * a.h + unit) * ld + col] : 0.0f;
-        } else {
-            const int j = idx - n_fwd;
-            const int lane = j & 63, ks = (j >> 6) % (4 * a.HT), g = ((j >> 6) / (4 * a.HT)) % NG, w = (j >> 6) / (4 * a.HT * NG);
-            const int unit = w * a.HT + (ks >> 2), gate = ks & 3, col = user_col(64 * g + lane);
-            a.bwd[j] = (unit < a.h && col >= 0) ? a.W[(size_t)(gate * a.h + unit) * ld + col] : 0.0f;
-        }
+    const int KT4 = 4 * (a.KXT + a.HT), n = 4 * KT4 * 64;
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+        const int lane = idx & 63, k = (idx >> 6) % KT4, w = (idx >> 6) / KT4;
+        a.fwd[idx] = a.at_row(lane & 3, w * a.HT + min(lane >> 2, a.HT - 1), k);
+    }
+}
+__device__ void pack_backward_narrow(const PackLstmArgs &a)
+{
+    const int NG = (4 * (a.KXT + a.HT) + 63) / 64, n = 4 * NG * 4 * a.HT * 64;
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+        const int lane = idx & 63, ks = (idx >> 6) % (4 * a.HT), g = ((idx >> 6) / (4 * a.HT)) % NG, w = (idx >> 6) / (4 * a.HT * NG);
+        a.bwd[idx] = a.at_row(ks & 3, w * a.HT + (ks >> 2), 64 * g + lane);
+    }
+}
+
+// Operands of the 16-series forward kernel: three bf16 parts of W (three_term.h) as [unit tile][quads of x, then of
+// h][lane][dword], and the bias as [unit tile][unit][gate].  Row 4g+r of unit tile mt is gate r of unit 4mt+g; lane
+// group k of a pair of input tiles stands for unit k of each.
+__device__ void pack_forward(const PackLstmArgs &a)
+{
+    const int npx = (a.KXT + 1) / 2, nph = (a.HT + 1) / 2, qx = tt_a_quads(npx), quads = qx + tt_a_quads(nph);
+    const int n = a.HT * quads * 256;
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+        const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, mt = (idx >> 8) / quads;
+        const int i = lane & 15, k = lane >> 4, unit = 4 * mt + (i >> 2), gate = i & 3;
+        const bool in_x = q < qx;
+        const TtDword w = tt_a_dword(in_x ? npx : nph, in_x ? q : q - qx, d);
+        const Parts p = split_pair(a.at(gate, unit, in_x, 8 * w.pair + k), a.at(gate, unit, in_x, 8 * w.pair + 4 + k));
+        reinterpret_cast<unsigned *>(a.fwd)[idx] = part_of(p, w.part);
+    }
+    for (int j = blockIdx.x * 256 + threadIdx.x; j < a.HT * 16; j += gridDim.x * 256) {
+        const int gate = j & 3, unit = j >> 2;   // (mt*4+g)*4 + r  ->  unit = 4mt+g
+        a.bias[j] = unit < a.h ? a.b[gate * a.h + unit] : 0.0f;
+    }
+}
+
+// Operands of the 16-series reverse kernels.  Transposed contraction: k-step 4mt+gate, lane group = unit within
+// tile; output row 4g+r of tile mb is row g of input unit tile 4mb+r.
+__device__ void pack_backward(const PackLstmArgs &a)
+{
+    const int MB = (a.KXT + a.HT + 3) / 4, n = MB * 4 * a.HT * 64;
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+        const int lane = idx & 63, ks = (idx >> 6) % (4 * a.HT), mb = (idx >> 6) / (4 * a.HT);
+        const int i = lane & 15;
+        a.bwd[idx] = a.at_row(ks & 3, 4 * (ks >> 2) + (lane >> 4), 4 * (4 * mb + (i & 3)) + (i >> 2));
     }
 }
 
 __device__ void pack_lstm_body(const PackLstmArgs &a)
 {
-    if (a.narrow) {
-        pack_lstm_narrow_body(a);
-        return;
-    }
-    const int KT = a.KXT + a.HT, MB = (KT + 3) / 4, ld = a.in_dim + a.h;
-    const int n_fwd = a.HT * KT * 64, n_bias = a.HT * 16, n_bwd = MB * 4 * a.HT * 64;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n_fwd + n_bias + n_bwd; idx += gridDim.x * 256) {
-        if (idx < n_fwd) {
-            // gate contraction: row 4g+r of unit tile mt is gate r of unit 4mt+g
-            const int lane = idx & 63, ks = (idx >> 6) % KT, mt = (idx >> 6) / KT;
-            const int i = lane & 15, kk = lane >> 4;
-            const int unit = 4 * mt + (i >> 2), gate = i & 3;
-            int col = -1;
-            if (ks < a.KXT) { const int xc = 4 * ks + kk; if (xc < a.in_dim) col = xc; }
-            else { const int hu = 4 * (ks - a.KXT) + kk; if (hu < a.h) col = a.in_dim + hu; }
-            a.fwd[idx] = (unit < a.h && col >= 0) ? a.W[(size_t)(gate * a.h + unit) * ld + col] : 0.0f;
-        } else if (idx < n_fwd + n_bias) {
-            const int j = idx - n_fwd;
-            const int gate = j & 3, unit = j >> 2;   // (mt*4+g)*4 + r  ->  unit = 4mt+g
-            a.bias[j] = unit < a.h ? a.b[gate * a.h + unit] : 0.0f;
-        } else {
-            // transposed contraction: k-step 4mt+gate, lane group = unit within tile;
-            // output row 4g+r of tile mb is row g of input unit tile 4mb+r
-            const int j = idx - n_fwd - n_bias;
-            const int lane = j & 63, ks = (j >> 6) % (4 * a.HT), mb = (j >> 6) / (4 * a.HT);
-            const int i = lane & 15, gk = lane >> 4;
-            const int mt = ks >> 2, gate = ks & 3;
-            const int unit = 4 * mt + gk;
-            const int q = 4 * mb + (i & 3), gi = i >> 2;
-            int col = -1;
-            if (q < a.KXT) { const int xc = 4 * q + gi; if (xc < a.in_dim) col = xc; }
-            else if (q < KT) { const int hu = 4 * (q - a.KXT) + gi; if (hu < a.h) col = a.in_dim + hu; }
-            a.bwd[j] = (unit < a.h && col >= 0) ? a.W[(size_t)(gate * a.h + unit) * ld + col] : 0.0f;
-        }
-    }
+    if (a.narrow_fwd) pack_forward_narrow(a);
+    else pack_forward(a);
+    if (a.narrow_bwd) pack_backward_narrow(a);
+    else pack_backward(a);
 }
 
 struct PackHeadArgs {
@@ -1166,10 +1177,8 @@ hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *wei
     for (int l = 0; l < pl.L; ++l) {
         const LayerPlan &lp = pl.layer[l];
         a.lstm[l] = PackLstmArgs{weights + lp.w_off, weights + lp.b_off, ws + lp.wpack_fwd, ws + lp.bias_pack,
-                                 ws + lp.wpack_bwd, pl.h, lp.in_dim, pl.HT, lp.KXT, lp.narrow};
-        const int KT = lp.KXT + pl.HT, MB = (KT + 3) / 4;
-        max_total = std::max(max_total, lp.narrow ? 4 * 4 * KT * 64 + 4 * ((4 * KT + 63) / 64) * 4 * pl.HT * 64
-                                                  : pl.HT * KT * 64 + pl.HT * 16 + MB * 4 * pl.HT * 64);
+                                 ws + lp.wpack_bwd, pl.h, lp.in_dim, pl.HT, lp.KXT, lp.narrow_fwd, lp.narrow_bwd};
+        max_total = std::max(max_total, 4 * pl.HT * 64 * (lp.KXT + pl.HT));     // (about the larger of the two operands)
     }
     const HeadPack hp = head_pack_layout(pl);
     float *f = ws + pl.head_fwd_pack, *b = ws + pl.head_bwd_pack;

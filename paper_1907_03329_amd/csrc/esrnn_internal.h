@@ -33,7 +33,7 @@ struct LayerPlan {
     int KXT;             // unit tiles of the layer input (x part of the contraction)
     size_t w_off, b_off; // offsets into the caller's flat weight vector
     // forward operands (offsets in floats into the workspace)
-    size_t wpack_fwd;    // [HT][KXT+HT][64]  A operands of the gate contraction
+    size_t wpack_fwd;    // [HT][quads][64][4] A operands of the gate contraction, split in three (three_term.h)
     size_t bias_pack;    // [HT][4][4]        bias of (unit tile, unit, gate)
     size_t xsrc;         // TL(4*KXT) input
     size_t gates, c, hid;
@@ -43,12 +43,14 @@ struct LayerPlan {
     size_t gsrc[4];      // TL(HP): the gradient arriving at this layer's hidden output is the sum of these
     int n_gsrc;
     size_t gdst;         // TL(4*KXT) gradient with respect to the layer input
-    int chains;          // workgroups per series tile (per 4 series if narrow); each walks the residue classes r, r+chains, ... (mod dil)
+    int chains;          // forward workgroups per series tile (per 4 series if narrow_fwd); each walks the residue classes
+                         // r, r+chains, ... (mod dil)
     int chains_bwd;      // the same for the reverse kernel
     int split_bwd;       // 1: reverse kernel with eight waves, the weight gradient on waves of its own, one workgroup per compute unit
-    int narrow;          // 1: the layer runs on the 4-series kernels (lstm_narrow_fwd.h, lstm_narrow_bwd.h): wpack_fwd is
-                         // [4][4*(KXT+HT)][64], wpack_bwd [4][NG][4*HT][64], bias_pack unused, and the
-                         // weight-gradient partials are indexed by 4*NB*chains workgroups
+    int narrow_fwd;      // 1: forward pass on the 4-series kernel (lstm_narrow_fwd.h): wpack_fwd is [4][4*(KXT+HT)][64],
+                         // bias_pack unused
+    int narrow_bwd;      // 1: reverse pass on the 4-series kernel (lstm_narrow_bwd.h): wpack_bwd is [4][NG][4*HT][64], and the
+                         // weight-gradient partials are indexed by 4*NB*chains_bwd workgroups
     size_t dw_partial;   // [NB*chains][HT*MB][4][64] per-workgroup weight-gradient tiles
     size_t db_partial;   // [NB*chains][HT][4][4]
     size_t dw_reduced, db_reduced;   // [kReduceSplits][...] first reduction stage
@@ -91,8 +93,8 @@ struct Plan {
     int head_dw_stride;
     size_t head_dw_reduced;
     int es_blocks;
-    int partial_groups(const LayerPlan &lp) const { return (lp.narrow ? 4 * NB : NB) * lp.chains_bwd; }   // producers of weight-gradient partials
-    int forward_groups(const LayerPlan &lp) const { return (lp.narrow ? 4 * NB : NB) * lp.chains; }        // workgroups of the forward kernel
+    int partial_groups(const LayerPlan &lp) const { return (lp.narrow_bwd ? 4 * NB : NB) * lp.chains_bwd; }   // producers of weight-gradient partials
+    int forward_groups(const LayerPlan &lp) const { return (lp.narrow_fwd ? 4 * NB : NB) * lp.chains; }        // workgroups of the forward kernel
     size_t es_window_floats;   // prefix of the workspace used by the smoothing and window stages alone
     size_t total_floats;
 };
@@ -124,6 +126,7 @@ hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *leng
 hipError_t launch_window_forward(const Plan &pl, const int32_t *categories, float *ws, hipStream_t st);
 hipError_t launch_lstm_forward(const Plan &pl, int layer, const int32_t *lengths, const float *weights, float *ws,
                                hipStream_t st);
+hipError_t launch_lstm_forward_residual(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
 // 4-series kernels for layers with few workgroups (called by the two launchers above and below)
 hipError_t launch_lstm_forward_narrow(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
                                       float *ws, hipStream_t st);
@@ -159,7 +162,9 @@ hipError_t launch_forecast_metrics(const Plan &pl, const float *forecasts, const
 // Device address and size of the library's own scratch array on the current device (static_scratch.hip).
 hipError_t static_scratch(void **ptr, size_t *bytes);
 
-// Supported (HT, KXT) instantiations of the LSTM kernels.
+// Supported (HT, KXT) instantiations of the LSTM kernels: padded hidden size and layer input in unit tiles.
+#define ESRNN_LSTM_SHAPES(X) \
+    X(2, 1) X(2, 2) X(8, 2) X(8, 3) X(8, 8) X(10, 1) X(10, 3) X(10, 6) X(10, 8) X(10, 10) X(13, 3) X(13, 5) X(13, 13) X(16, 16)
 bool lstm_shape_supported(int HT, int KXT);
 
 }  // namespace esrnn

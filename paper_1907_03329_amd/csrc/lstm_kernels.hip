@@ -1,207 +1,14 @@
-// Dilated LSTM layer, forward and reverse (Section 3.2, Table 1), one launch per
-// layer.
+// Reverse pass of a dilated LSTM layer (Section 3.2, Table 1), one launch per layer, 16 series per workgroup (the
+// forward pass: lstm_forward.h; the same parallel structure).
 //
-// Parallel structure.  Series never interact, and a layer with dilation d is d
-// independent recurrences over the interleaved position classes p = r (mod d).
-// A workgroup of four waves (eight in one variant of the reverse pass, see
-// there) therefore owns 16 series and one or more residue classes r (grid =
-// series tiles x chains) and walks each class in order with the recurrent state
-// on chip: h through LDS, c in registers.  There is no grid-level
-// synchronisation and no recurrent traffic through global memory.
-//
-// Arithmetic.  The gate contraction runs on the 16x16x4 fp32 MFMA with the
-// weights as the A operand, held in registers for the whole launch, and the
-// activations [x_p ; h_{p-d}] of 16 series as the B operand.  Row order of the
-// A operand: row 4g+r of unit tile mt is gate r of hidden unit 4mt+g.  A lane
-// then holds the four gate pre-activations of one unit for one series (cell
-// update without cross-lane traffic), and the hidden state it produces for unit
-// tile mt is, as it stands, the B operand of k-step mt of the next position.
+// Arithmetic.  fp32 MFMA (16x16x4) with the transposed weights as the A operand, held in registers for the whole
+// launch, and the gate gradients of 16 series as the B operand.
 #include "device_utils.h"
 #include "esrnn_internal.h"
 
 namespace esrnn {
 
 namespace {
-
-struct LstmFwdArgs {
-    const float *wpack;   // [HT][KT][64]
-    const float *bpack;   // [HT][4][4]
-    const float *xsrc;    // TL(4*KXT)
-    float *gates;         // [P][NB][HT][64][4]
-    float *c, *hid;       // TL(HP)
-    const float *resid;   // TL(HP) or null
-    float *out;           // TL(HP) or null: resid + hid
-    int P, NB, d;
-    const int32_t *pmax;  // [NB] positions the longest series of a tile has: the tile's chains stop there
-    // cell-state penalty (Section 8.4) of a block's first layer, kernels instantiated with CP only
-    const int32_t *lengths;
-    float *cs_partial;    // [NB * gridDim.y] sums of squared cell states over valid window positions
-    int B, T, I, H;
-};
-
-template <int HT, int KXT, bool CP>
-__global__ void __launch_bounds__(64 * kLstmWaves, 2) lstm_forward_kernel(LstmFwdArgs a)
-{
-    constexpr int KT = KXT + HT;
-    constexpr int MTW = (HT + kLstmWaves - 1) / kLstmWaves;   // unit tiles per wave
-    // Waves 0 .. NX-1 own one unit tile more than the others.  Where that is at most two waves, wave s + 2
-    // takes over the input part of the last tile of wave s (bias included) and hands the accumulators over
-    // through LDS one position ahead: the input part does not depend on the recurrence, and the matrix work
-    // per position becomes (nearly) the same on every wave.
-    constexpr int NX = HT - kLstmWaves * (MTW - 1);
-    constexpr bool kHelp = kLstmWaves == 4 && KXT >= 2 && MTW >= 2 && NX <= 2;
-    __shared__ float hbuf[2][HT * 64];
-    __shared__ f32x4 xfer[2][kHelp ? 2 : 1][64];
-
-    const int lane = threadIdx.x & 63, bt = blockIdx.x;
-    const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, known to be uniform
-    const int Pt = a.pmax[bt];      // positions past the tile's longest series are never computed (nor read later)
-    const bool last_tile = s < NX;                              // this wave's last tile exists
-    const bool helper = kHelp && s >= 2 && s - 2 < NX;          // its last slot holds the input part of wave s-2's last tile
-    const bool last_x = kHelp ? helper : true;                  // input part of the last slot computed here
-
-    float wreg[MTW][KT];
-    f32x4 bias[MTW];
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) {
-        const int mt = (helper && j == MTW - 1 ? s - 2 : s) + kLstmWaves * j;
-        const bool valid = mt < HT;
-#pragma unroll
-        for (int ks = 0; ks < KT; ++ks) wreg[j][ks] = valid ? a.wpack[((size_t)mt * KT + ks) * 64 + lane] : 0.0f;
-        const float4 bv = valid ? *reinterpret_cast<const float4 *>(a.bpack + (mt * 4 + (lane >> 4)) * 4)
-                                : make_float4(0.f, 0.f, 0.f, 0.f);
-        bias[j] = f32x4{bv.x, bv.y, bv.z, bv.w};
-    }
-    const size_t xtile = (size_t)KXT * 64;
-    // positions below this take part in the loss for this lane's series (CP only)
-    int n_valid = 0;
-    float csq = 0.0f;
-    if constexpr (CP) {
-        const int col = bt * kTileN + (lane & 15);
-        const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
-        n_valid = len - a.I - a.H + 1;
-    }
-
-    for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y) {
-        // start of a chain: zero state
-        float creg[MTW];
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) creg[j] = 0.0f;
-        for (int i = threadIdx.x; i < HT * 64; i += 64 * kLstmWaves) hbuf[0][i] = 0.0f;
-
-        // input part of the first position
-        float bx[KXT];
-#pragma unroll
-        for (int ks = 0; ks < KXT; ++ks) bx[ks] = (a.xsrc + ((size_t)r * a.NB + bt) * xtile + ks * 64)[lane];
-        const unsigned lane4 = 4 * lane, lane16 = 16 * lane;   // this lane's bytes inside a tile
-        f32x4 acc[MTW];
-        // input part (with the bias) of one position; a helper's share first, so that it is complete when it
-        // goes to LDS after the rest
-        auto input_part = [&](int buf) {
-#pragma unroll
-            for (int j = 0; j < MTW; ++j) acc[j] = bias[j];
-            if (last_x) {
-#pragma unroll
-                for (int ks = 0; ks < KXT; ++ks) acc[MTW - 1] = mfma16(wreg[MTW - 1][ks], bx[ks], acc[MTW - 1]);
-            }
-#pragma unroll
-            for (int ks = 0; ks < KXT; ++ks)
-#pragma unroll
-                for (int j = 0; j < MTW - 1; ++j) acc[j] = mfma16(wreg[j][ks], bx[ks], acc[j]);
-            if (helper) xfer[buf][kHelp ? s - 2 : 0][lane] = acc[MTW - 1];
-        };
-        input_part(0);
-        {
-            const buf_rsrc rx = make_rsrc(a.xsrc + ((size_t)min(r + a.d, Pt - 1) * a.NB + bt) * xtile);
-#pragma unroll
-            for (int ks = 0; ks < KXT; ++ks) bx[ks] = buf_load(rx, lane4, ks * 256);
-        }
-        // residual input of the block (last layer of a block >= 1), one position ahead like the input
-        float res[MTW];
-#pragma unroll
-        for (int j = 0; j < MTW; ++j)
-            res[j] = a.out ? (a.resid + (((size_t)r * a.NB + bt) * HT + min(s + kLstmWaves * j, HT - 1)) * 64)[lane] : 0.0f;
-        lds_barrier();
-
-        int it = 0;
-        for (int p = r; p < Pt; p += a.d, ++it) {
-            const size_t pb = (size_t)p * a.NB + bt;
-            // this position's tiles of the stash and the outputs: scalar bases, scalar tile offsets
-            const buf_rsrc r_gates = make_rsrc(a.gates + pb * HT * 256), r_c = make_rsrc(a.c + pb * HT * 64);
-            const buf_rsrc r_hid = make_rsrc(a.hid + pb * HT * 64), r_out = make_rsrc(a.out + (a.out ? pb * HT * 64 : 0));
-            float res_next[MTW];
-            if (a.out) {
-                const buf_rsrc rr = make_rsrc(a.resid + ((size_t)min(p + a.d, Pt - 1) * a.NB + bt) * HT * 64);
-#pragma unroll
-                for (int j = 0; j < MTW; ++j) res_next[j] = buf_load(rr, lane4, min(s + kLstmWaves * j, HT - 1) * 256);
-            }
-            // recurrent part
-            const float *hb = hbuf[it & 1];
-            float bh[HT];
-#pragma unroll
-            for (int ks = 0; ks < HT; ++ks) bh[ks] = hb[ks * 64 + lane];
-            if (kHelp && last_tile) acc[MTW - 1] = xfer[it & 1][kHelp ? s : 0][lane];
-            float *hn_buf = hbuf[(it + 1) & 1];
-            // Tile by tile, one tile ahead on the matrix pipe: the MFMAs of tile j+1 are issued before the
-            // activations of tile j, whose accumulator is complete by then (no drain of the pipe per tile).
-            auto tile_mfma = [&](int j) {
-#pragma unroll
-                for (int ks = 0; ks < HT; ++ks) acc[j] = mfma16(wreg[j][KXT + ks], bh[ks], acc[j]);
-            };
-            auto tile_act = [&](int j) {
-                const int mt = s + kLstmWaves * j;
-                const float gi = sigmoid_f(acc[j][0]);
-                const float gf = sigmoid_f(acc[j][1]);
-                const float gg = tanh_f(acc[j][2]);
-                const float go = sigmoid_f(acc[j][3]);
-                const float cn = gf * creg[j] + gi * gg;
-                const float hn = go * tanh_f(cn);
-                creg[j] = cn;
-                if constexpr (CP) csq += p < n_valid ? cn * cn : 0.0f;
-                hn_buf[mt * 64 + lane] = hn;
-                // gates and cell state are read again only by the reverse pass: streaming stores
-                buf_store4<true>(r_gates, lane16, mt * 1024, f32x4{gi, gf, gg, go});
-                buf_store<true>(r_c, lane4, mt * 256, cn);
-                buf_store(r_hid, lane4, mt * 256, hn);
-                if (a.out) buf_store(r_out, lane4, mt * 256, res[j] + hn);
-            };
-            // (with a one-tile input, KXT = 1, the plain order measured faster and is kept)
-            constexpr bool kAhead = KXT >= 2;
-            if (kAhead) tile_mfma(0);
-#pragma unroll
-            for (int j = 0; j < MTW; ++j) {
-                if (kAhead) {
-                    if (j + 1 < MTW - 1 || (j + 1 == MTW - 1 && last_tile)) tile_mfma(j + 1);
-                } else {
-                    if (j < MTW - 1 || last_tile) tile_mfma(j);
-                }
-                if (j < MTW - 1 || last_tile) tile_act(j);
-            }
-            // input part of the next position of the chain: independent of the
-            // recurrence, so it runs on the matrix pipe while the waves meet at
-            // the barrier
-            if (p + a.d < Pt) {
-                input_part((it + 1) & 1);
-                const buf_rsrc rx = make_rsrc(a.xsrc + ((size_t)min(p + 2 * a.d, Pt - 1) * a.NB + bt) * xtile);
-#pragma unroll
-                for (int ks = 0; ks < KXT; ++ks) bx[ks] = buf_load(rx, lane4, ks * 256);
-            }
-            if (a.out) {
-#pragma unroll
-                for (int j = 0; j < MTW; ++j) res[j] = res_next[j];
-            }
-            lds_barrier();
-        }
-    }
-    if constexpr (CP) {
-        __shared__ float s_cs[kLstmWaves];
-        const float tot = wave_sum(csq);
-        if (lane == 0) s_cs[s] = tot;
-        __syncthreads();
-        if (threadIdx.x == 0)
-            a.cs_partial[blockIdx.x * gridDim.y + blockIdx.y] = (s_cs[0] + s_cs[1]) + (s_cs[2] + s_cs[3]);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Reverse pass of one layer.  Per position p of a chain (descending):
@@ -812,14 +619,6 @@ __global__ void __launch_bounds__(256) sum_sources_kernel(const float4 *__restri
 }
 
 template <int HT, int KXT>
-hipError_t run_fwd(const LstmFwdArgs &a, int chains, hipStream_t st)
-{
-    if (a.cs_partial) lstm_forward_kernel<HT, KXT, true><<<dim3(a.NB, chains), 64 * kLstmWaves, 0, st>>>(a);
-    else lstm_forward_kernel<HT, KXT, false><<<dim3(a.NB, chains), 64 * kLstmWaves, 0, st>>>(a);
-    return hipGetLastError();
-}
-
-template <int HT, int KXT>
 hipError_t run_bwd(const LstmBwdArgs &a, int chains, bool split, hipStream_t st)
 {
     if (split || HT >= kSplitBwdFromHT) {
@@ -832,26 +631,7 @@ hipError_t run_bwd(const LstmBwdArgs &a, int chains, bool split, hipStream_t st)
     return hipGetLastError();
 }
 
-#define ESRNN_LSTM_SHAPES(X) \
-    X(2, 1) X(2, 2) X(8, 2) X(8, 3) X(8, 8) X(10, 1) X(10, 3) X(10, 6) X(10, 8) X(10, 10) X(13, 3) X(13, 5) X(13, 13) X(16, 16)
-
 }  // namespace
-
-hipError_t launch_lstm_forward(const Plan &pl, int layer, const int32_t *lengths, const float *weights, float *ws,
-                               hipStream_t st)
-{
-    const LayerPlan &lp = pl.layer[layer];
-    if (lp.narrow) return launch_lstm_forward_narrow(pl, layer, lengths, weights, ws, st);
-    const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
-    LstmFwdArgs a{ws + lp.wpack_fwd, ws + lp.bias_pack, ws + lp.xsrc, ws + lp.gates, ws + lp.c, ws + lp.hid,
-                  lp.out ? ws + lp.resid : nullptr, lp.out ? ws + lp.out : nullptr, pl.P, pl.NB, lp.dil,
-                  reinterpret_cast<const int32_t *>(ws + pl.pmax),
-                  lengths, cp ? ws + lp.cs_partial : nullptr, pl.B, pl.T, pl.I, pl.H};
-#define X(HT_, KXT_) if (pl.HT == HT_ && lp.KXT == KXT_) return run_fwd<HT_, KXT_>(a, lp.chains, st);
-    ESRNN_LSTM_SHAPES(X)
-#undef X
-    return hipErrorInvalidValue;
-}
 
 hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st)
 {
@@ -878,7 +658,7 @@ hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *length
         if (e != hipSuccess) return e;
         a.gsrc[1] = ws + pl.gsum;
     }
-    if (lp.narrow) return launch_lstm_backward_narrow(pl, layer, lengths, ws, st);
+    if (lp.narrow_bwd) return launch_lstm_backward_narrow(pl, layer, lengths, ws, st);
     a.gdst = ws + lp.gdst; a.dw_partial = ws + lp.dw_partial; a.db_partial = ws + lp.db_partial;
     a.sink = ws + pl.sink;
     a.P = pl.P; a.NB = pl.NB; a.d = lp.dil;

@@ -99,9 +99,6 @@ __device__ __forceinline__ void quad_transpose(f32x4 &v, int j)
 // workgroups along x: groups of 32 = 8 tiles x 4 quarters
 inline int narrow_grid_x(int NB) { return ((NB + 7) / 8) * 32; }
 
-#define ESRNN_LSTM_SHAPES(X) \
-    X(2, 1) X(2, 2) X(8, 2) X(8, 3) X(8, 8) X(10, 1) X(10, 3) X(10, 6) X(10, 8) X(10, 10) X(13, 3) X(13, 5) X(13, 13) X(16, 16)
-
 }  // namespace
 
 }  // namespace esrnn

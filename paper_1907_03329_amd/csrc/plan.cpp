@@ -5,6 +5,7 @@
 #include <cstring>
 
 #include "esrnn_internal.h"
+#include "three_term.h"
 
 namespace esrnn {
 
@@ -22,7 +23,12 @@ struct Bump {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-constexpr int kNarrowBelowDefault = 160;
+// Layers whose 16-series grid has fewer workgroups than this run on the 4-series kernels, separately for the two
+// directions.  A workgroup of the forward kernel needs 0.60 us a position at hidden 40 and 16 series, 0.49 us at 4,
+// and with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each: 64
+// workgroups (1024 series of the quarterly shape, first layer) take 40 us against 35 us, 128 (hourly shape, second
+// layer) 131 us against 175 us.
+constexpr int kNarrowForwardBelow = 96, kNarrowBackwardBelow = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
 // 16384 tiles, streaming 0.053 / 0.079 / 0.25 ms; a wave of the streaming kernel is a chain of dependent memory
@@ -43,10 +49,9 @@ int pick_ht(int hidden)
 
 bool lstm_shape_supported(int HT, int KXT)
 {
-    static const int pairs[][2] = {{2, 1}, {2, 2}, {8, 2}, {8, 3}, {8, 8}, {10, 1}, {10, 3}, {10, 6}, {10, 8}, {10, 10},
-                                   {13, 3}, {13, 5}, {13, 13}, {16, 16}};
-    for (auto &p : pairs)
-        if (p[0] == HT && p[1] == KXT) return true;
+#define X(HT_, KXT_) if (HT == HT_ && KXT == KXT_) return true;
+    ESRNN_LSTM_SHAPES(X)
+#undef X
     return false;
 }
 
@@ -69,10 +74,9 @@ HeadPack head_pack_layout(const Plan &pl)
 esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
 {
     std::memset(&pl, 0, sizeof(pl));
-    // Layers whose 16-series grid has fewer workgroups than this run on the 4-series kernels.
-    // ESRNN_NARROW_BELOW overrides the threshold (0: never, a large number: always), for measurements.
-    int narrow_below = kNarrowBelowDefault;
-    if (const char *env = std::getenv("ESRNN_NARROW_BELOW")) narrow_below = std::atoi(env);
+    // ESRNN_NARROW_BELOW overrides both thresholds (0: never, a large number: always), for measurements.
+    int narrow_fwd_below = kNarrowForwardBelow, narrow_bwd_below = kNarrowBackwardBelow;
+    if (const char *env = std::getenv("ESRNN_NARROW_BELOW")) narrow_fwd_below = narrow_bwd_below = std::atoi(env);
     // The window adjoint streams tile by tile from this many series tiles on (one wave per tile needs enough
     // tiles to hide memory latency); ESRNN_WINDOW_STREAM_FROM overrides, for measurements.
     int window_stream_from = kWindowStreamFromDefault;
@@ -185,32 +189,32 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         const int KT = lp.KXT + pl.HT;
         const int MB = ceil_div(KT, 4);
         // Few workgroups (small batch, small dilation): four series per workgroup instead of sixteen.
-        // `narrow_below`: use the 4-series kernels when the 16-series grid would have fewer workgroups.
-        const int wide_chains = std::min(std::min(lp.dil, pl.P), std::max(1, ceil_div(512, pl.NB)));
-        lp.narrow = pl.NB * wide_chains < narrow_below ? 1 : 0;
-        const int groups = lp.narrow ? 4 * pl.NB : pl.NB;
-        // enough workgroups to put several on every compute unit, without more
-        // weight-gradient partials than the reduction can read cheaply
-        const int max_chains = std::max(1, ceil_div(512, groups));
-        lp.chains = std::min(std::min(lp.dil, pl.P), max_chains);
+        // Enough workgroups to put several on every compute unit, without more weight-gradient partials than
+        // the reduction can read cheaply.
+        const int most_chains = std::min(lp.dil, pl.P);
+        auto chains_for = [&](int groups, int fill) { return std::min(most_chains, std::max(1, ceil_div(fill, groups))); };
+        const int wide_groups = pl.NB * chains_for(pl.NB, 512);
+        lp.narrow_fwd = wide_groups < narrow_fwd_below ? 1 : 0;
+        lp.narrow_bwd = wide_groups < narrow_bwd_below ? 1 : 0;
+        lp.chains = chains_for(lp.narrow_fwd ? 4 * pl.NB : pl.NB, 512);
+        const int groups = lp.narrow_bwd ? 4 * pl.NB : pl.NB;
+        lp.chains_bwd = chains_for(groups, 512);
         // Reverse kernels with eight waves, the weight gradient on waves of its own: one workgroup per compute
         // unit.  The faster kind where the grid has at most one workgroup per compute unit anyway, and for the
         // 16-series kernel with the larger hidden sizes (whose four-wave workgroup would be alone on its
         // compute unit for its registers).
-        const bool one_per_cu = groups * lp.chains <= 256;
-        lp.split_bwd = (one_per_cu || (!lp.narrow && pl.HT >= kSplitBwdFromHT)) ? 1 : 0;
-        lp.chains_bwd = (lp.split_bwd && !lp.narrow) ? std::min(std::min(lp.dil, pl.P), std::max(1, ceil_div(256, groups)))
-                                                      : lp.chains;
-        if (lp.narrow) {
-            const int KT4 = 4 * KT, NG = ceil_div(KT4, 64);
-            lp.wpack_fwd = ws.take((size_t)4 * KT4 * 64);
+        const bool one_per_cu = groups * lp.chains_bwd <= 256;
+        lp.split_bwd = (one_per_cu || (!lp.narrow_bwd && pl.HT >= kSplitBwdFromHT)) ? 1 : 0;
+        if (lp.split_bwd && !lp.narrow_bwd) lp.chains_bwd = chains_for(groups, 256);
+        if (lp.narrow_fwd) {
+            lp.wpack_fwd = ws.take((size_t)4 * 4 * KT * 64);
             lp.bias_pack = lp.wpack_fwd;                       // unused: the kernels read the caller's bias
-            lp.wpack_bwd = ws.take((size_t)4 * NG * 4 * pl.HT * 64);
         } else {
-            lp.wpack_fwd = ws.take((size_t)pl.HT * KT * 64);
+            lp.wpack_fwd = ws.take((size_t)pl.HT * (tt_a_quads((lp.KXT + 1) / 2) + tt_a_quads((pl.HT + 1) / 2)) * 256);
             lp.bias_pack = ws.take((size_t)pl.HT * 16);
-            lp.wpack_bwd = ws.take((size_t)MB * 4 * pl.HT * 64);
         }
+        lp.wpack_bwd = lp.narrow_bwd ? ws.take((size_t)4 * ceil_div(4 * KT, 64) * 4 * pl.HT * 64)
+                                     : ws.take((size_t)MB * 4 * pl.HT * 64);
         lp.gates = ws.take(PN * tileH * 4);
         lp.c = ws.take(PN * tileH);
         lp.hid = ws.take(PN * tileH);
