@@ -42,6 +42,7 @@ __device__ __forceinline__ float buf_load(buf_rsrc r, unsigned lane_bytes, unsig
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, lane_bytes, tile_bytes, 0));
 }
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 buf_load4(buf_rsrc r, unsigned lane_bytes, unsigned tile_bytes)
 {

@@ -150,9 +150,29 @@ __device__ void pack_forward(const PackLstmArgs &a)
     }
 }
 
-// Operands of the 16-series reverse kernels.  Transposed contraction: k-step 4mt+gate, lane group = unit within
-// tile; output row 4g+r of tile mb is row g of input unit tile 4mb+r.
+// Operands of the 16-series reverse kernel: three bf16 parts of W^T as [row tile][unit tile][part][lane][dword].  Lane
+// group k of unit tile t is unit 4t+k, its dwords are the gate pairs (0, 1) and (2, 3); row 4g+r of a row tile is unit
+// g of its unit tile r.  The row tiles of x come first; the unit tiles of the others are those of h and then the
+// merged ones of x (three_term.h).
 __device__ void pack_backward(const PackLstmArgs &a)
+{
+    const int rx = bwd_x_row_tiles(a.HT, a.KXT), ml = bwd_merged_tiles(a.HT, a.KXT), tiles = 2 * bwd_chain_waves(a.HT);
+    const int n = bwd_pack_dwords(a.HT, a.KXT);
+    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+        const int d = idx & 1, lane = (idx >> 1) & 63, part = (idx >> 7) % 3, t = (idx / 384) % tiles, rt = idx / (384 * tiles);
+        const int i = lane & 15, unit = 4 * t + (lane >> 4);
+        const int slot = 4 * (rt < rx ? rt : rt - rx) + (i & 3);
+        const bool merged = rt >= rx && slot >= a.HT, exists = !merged || slot < a.HT + ml;
+        const bool in_x = rt < rx || merged;
+        const int row = 4 * (merged ? 4 * rx + slot - a.HT : slot) + (i >> 2);
+        const Parts p = split_pair(exists ? a.at(2 * d, unit, in_x, row) : 0.0f, exists ? a.at(2 * d + 1, unit, in_x, row) : 0.0f);
+        reinterpret_cast<unsigned *>(a.bwd)[idx] = part_of(p, part);
+    }
+}
+
+// The same for the fp32 kernel (hidden sizes above 52).  Transposed contraction: k-step 4mt+gate, lane group = unit within
+// tile; output row 4g+r of tile mb is row g of input unit tile 4mb+r.
+__device__ void pack_backward_fp32(const PackLstmArgs &a)
 {
     const int MB = (a.KXT + a.HT + 3) / 4, n = MB * 4 * a.HT * 64;
     for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
@@ -167,7 +187,8 @@ __device__ void pack_lstm_body(const PackLstmArgs &a)
     if (a.narrow_fwd) pack_forward_narrow(a);
     else pack_forward(a);
     if (a.narrow_bwd) pack_backward_narrow(a);
-    else pack_backward(a);
+    else if (bwd_three_term(a.HT)) pack_backward(a);
+    else pack_backward_fp32(a);
 }
 
 struct PackHeadArgs {

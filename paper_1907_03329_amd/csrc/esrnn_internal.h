@@ -16,7 +16,6 @@ constexpr int kTileN = 16;       // series per tile (N of the 16x16x4 fp32 MFMA)
 constexpr int kMaxLayers = ESRNN_MAX_BLOCKS * ESRNN_MAX_LAYERS_PER_BLOCK;
 constexpr int kLstmWaves = 4;    // waves per workgroup in the LSTM kernels
 constexpr int kSinkLines = 256;  // 256-byte lines of the store sink
-constexpr int kSplitBwdFromHT = 13;   // hidden unit tiles from which the 16-series reverse kernel always puts the weight gradient on waves of its own
 constexpr int kReduceSplits = 16; // subsets of producers in the first stage of the weight-gradient reduction
 // Row stride of the LDS arrays [row][16 series] that are read transposed (lane = row n, column 4k + g).  With 18
 // the 32 lanes of a half wave (16 rows x 2 columns) hit 32 different banks: (18 n + g) mod 32 takes every value
@@ -39,14 +38,15 @@ struct LayerPlan {
     size_t gates, c, hid;
     size_t resid, out;   // out = resid + hid for the last layer of a block >= 1 (0 = none)
     // backward operands
-    size_t wpack_bwd;    // [MB][4*HT][64]    A operands of the transposed contraction
+    size_t wpack_bwd;    // [row tiles of x, of h][unit tiles][3][64][2] A operands of the transposed contraction, split in
+                         // three (lstm_backward.h; hidden sizes above 52: [MB][4*HT][64] in fp32)
     size_t gsrc[4];      // TL(HP): the gradient arriving at this layer's hidden output is the sum of these
     int n_gsrc;
     size_t gdst;         // TL(4*KXT) gradient with respect to the layer input
     int chains;          // forward workgroups per series tile (per 4 series if narrow_fwd); each walks the residue classes
                          // r, r+chains, ... (mod dil)
     int chains_bwd;      // the same for the reverse kernel
-    int split_bwd;       // 1: reverse kernel with eight waves, the weight gradient on waves of its own, one workgroup per compute unit
+    int split_bwd;       // 1: 4-series reverse kernel with eight waves, the weight gradient on waves of its own, one workgroup per compute unit
     int narrow_fwd;      // 1: forward pass on the 4-series kernel (lstm_narrow_fwd.h): wpack_fwd is [4][4*(KXT+HT)][64],
                          // bias_pack unused
     int narrow_bwd;      // 1: reverse pass on the 4-series kernel (lstm_narrow_bwd.h): wpack_bwd is [4][NG][4*HT][64], and the
@@ -140,6 +140,15 @@ hipError_t launch_forecasts(const Plan &pl, const int32_t *lengths, float *ws, f
 hipError_t launch_loss_finalize(const Plan &pl, float *ws, float *loss, hipStream_t st);
 
 hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
+// the gradient arriving at a layer's hidden output is the sum of n (1 or 2) arrays; g[1] repeats g[0] when there is one
+struct LstmBwdSources {
+    const float *g[2];
+    int n;
+};
+hipError_t launch_lstm_backward_three_term(const Plan &pl, int layer, const LstmBwdSources &src, const int32_t *lengths,
+                                           float *ws, hipStream_t st);
+hipError_t launch_lstm_backward_three_term_large(const Plan &pl, int layer, const LstmBwdSources &src,
+                                                 const int32_t *lengths, float *ws, hipStream_t st);
 hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st);
 hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *lengths, const float *es,
                               float *ws, float *grad_es, hipStream_t st);

@@ -1,17 +1,19 @@
-// Reverse pass of a dilated LSTM layer (Section 3.2, Table 1), one launch per layer, 16 series per workgroup (the
-// forward pass: lstm_forward.h; the same parallel structure).
+// Reverse pass of a dilated LSTM layer (Section 3.2, Table 1), one launch per layer, 16 series per workgroup: the
+// launcher, and the kernel for hidden sizes above 52 (lstm_backward.h has the one for the others; the forward pass
+// and the parallel structure: lstm_forward.h).
 //
 // Arithmetic.  fp32 MFMA (16x16x4) with the transposed weights as the A operand, held in registers for the whole
 // launch, and the gate gradients of 16 series as the B operand.
 #include "device_utils.h"
 #include "esrnn_internal.h"
+#include "three_term.h"
 
 namespace esrnn {
 
 namespace {
 
 // ---------------------------------------------------------------------------
-// Reverse pass of one layer.  Per position p of a chain (descending):
+// Per position p of a chain (descending):
 //   A. every lane turns (dh, dc) of its hidden unit into the four gate
 //      pre-activation gradients da (registers), and leaves them in LDS next to
 //      [x_p ; h_{p-d}] for step C;
@@ -25,15 +27,19 @@ namespace {
 //      lanes;
 //   C. weight gradient dW += da (x) [x_p ; h_{p-d}]: contraction over the 16
 //      series on the MFMA, both operands read transposed from LDS; whole rows
-//      of tiles per wave, in accumulators for the whole launch.  Rows go to the
-//      waves in reverse order of unit ownership, which evens out the MFMA
-//      count of B plus C.
-// The loop is software-pipelined: the MFMAs of C(p) are issued together with
-// the elementwise work of A(p-d), whose global operands were requested one
-// position earlier.  fp32 MFMAs and vector instructions of a SIMD do not run at
-// the same time on this chip (esrnn_probe_issue_overlap measures it): what the
-// elementwise work and the address arithmetic cost is taken from the matrix
-// pipe, so both are kept short.
+//      of tiles per wave, in accumulators for the whole launch.
+// Steps A and B are the recurrence: position p - d cannot start before the
+// recurrent dh of p is summed.  Step C only consumes what A leaves in LDS.
+// Four "chain" waves do A and B, and four "dW" waves do C one position behind
+// them: after the barrier that completes position p they read da and [x ; h] of
+// p from one LDS copy while the chain waves fill the other copy with p - d.
+// One workgroup of eight waves per compute unit; one barrier per position,
+// taken by all eight waves.
+//
+// fp32 MFMAs and vector instructions of a SIMD do not run at the same time on
+// this chip (esrnn_probe_issue_overlap measures it): what the elementwise work
+// and the address arithmetic cost is taken from the matrix pipe, so both are
+// kept short.
 // ---------------------------------------------------------------------------
 struct LstmBwdArgs {
     const float *wpack;   // [MB][4*HT][64]
@@ -54,289 +60,6 @@ struct LstmBwdArgs {
     int B, T, I, H;
 };
 
-template <int HT, int KXT, bool CP>
-__global__ void __launch_bounds__(64 * kLstmWaves, (HT <= 10 ? 2 : 1)) lstm_backward_kernel(LstmBwdArgs a)
-{
-    constexpr int W = kLstmWaves;
-    constexpr int KT = KXT + HT;
-    constexpr int MB = (KT + 3) / 4;                 // 16-row tiles of [x ; h]
-    constexpr int MTW = (HT + W - 1) / W;            // unit tiles per wave
-    constexpr int QXW = (KXT + W - 1) / W;           // input unit tiles finalised per wave
-    constexpr int NT = 64 * W;
-    constexpr int DA_ROWS = 16 * W * MTW;            // includes dummy rows for tiles past HT
-    constexpr int XH_PER_THREAD = (KT * 64 + NT - 1) / NT;
-    constexpr int XH_ROWS = (16 * MB > 16 * XH_PER_THREAD) ? 16 * MB : 16 * XH_PER_THREAD;
-
-    __shared__ float da_lds[DA_ROWS * kLdsPad];      // [mt][4*gate + unit][series]
-    __shared__ float xh_lds[XH_ROWS * kLdsPad];      // [row of x ; h][series]; rows past 4*KT are scratch
-    __shared__ float part_lds[W][MB * 4][64];        // partial d[x ; h] of every wave
-    static_assert((DA_ROWS * kLdsPad + XH_ROWS * kLdsPad + W * MB * 4 * 64) * 4 <= 128 * 1024, "LDS budget of the reverse kernel");
-
-    const int lane = threadIdx.x & 63, bt = blockIdx.x;
-    const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, known to be uniform
-    const int Pt = a.pmax[bt];      // the chains of this tile stop at its longest series
-    const int g = lane >> 4, n = lane & 15;
-    const bool last_own_valid = s + W * (MTW - 1) < HT;           // unit tile s + 4(MTW-1)
-    const bool last_row_valid = (W - 1 - s) + W * (MTW - 1) < HT; // dW row (3-s) + 4(MTW-1)
-    const bool last_qx_valid = s + W * (QXW - 1) < KXT;
-    float *sink_line = a.sink + ((bt + blockIdx.y * 61) % kSinkLines) * 64;
-
-    // W^T operands of the k-steps this wave owns: k-step 4*mt + gate, mt = s + 4j
-    float wreg[MB][4 * MTW];
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) {
-            const int mt = s + W * j;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = a.wpack[((size_t)mb * 4 * HT + 4 * min(mt, HT - 1) + r) * 64 + lane];
-                wreg[mb][4 * j + r] = mt < HT ? w : 0.0f;
-            }
-        }
-    f32x4 dw[MTW][MB];
-    f32x4 dbacc[MTW];
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) {
-        dbacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int nbk = 0; nbk < MB; ++nbk) dw[j][nbk] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    for (int i = threadIdx.x; i < XH_ROWS * kLdsPad; i += NT) xh_lds[i] = 0.0f;
-    for (int i = threadIdx.x; i < DA_ROWS * kLdsPad; i += NT) da_lds[i] = 0.0f;
-
-    const size_t xtile = (size_t)KXT * 64, htile = (size_t)HT * 64;
-
-    // ---- operands of one position, requested one position ahead.  Branch-free:
-    // tiles past HT alias the last tile, a missing predecessor aliases p itself,
-    // elements past the end of [x ; h] alias its last element.
-    float4 pf_gt[MTW];
-    float pf_c[MTW], pf_cp[MTW], pf_g[MTW], pf_g2[MTW], pf_xh[XH_PER_THREAD];
-    // `first`: the chain's first request.  Later ones follow a request for position p + d, whose predecessor
-    // cell state c[p] is still in registers: it is not read from memory a second time.
-    // The requests of a position go out piece by piece, each as soon as the registers it fills are free:
-    // [x ; h] after it has gone to LDS, the operands of unit tile j after the elementwise step of tile j.
-    // Buffer addressing: the tiles of a position sit behind scalar bases, a tile is a scalar byte offset, the
-    // lane's share a fixed 32-bit offset - no address arithmetic on the vector ALU.
-    const unsigned lane4 = 4 * lane, lane16 = 16 * lane;
-    auto fetch_xh = [&](int p) {
-        const size_t pb = (size_t)p * a.NB + bt;
-        const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
-#pragma unroll
-        for (int i = 0; i < XH_PER_THREAD; ++i) {
-            // unit tile s + W*i of [x ; h]; tiles past the end alias the last one.  One request whichever array
-            // the tile is in (a scalar choice of the base, no branch around the request)
-            const int q = min(s + W * i, KT - 1);
-            const float *src = q < KXT ? a.xsrc + pb * xtile + q * 64 : a.hid + pbd * htile + (q - KXT) * 64;
-            pf_xh[i] = buf_load(make_rsrc(src), lane4, 0);
-        }
-    };
-    auto fetch_tile = [&](int j, int p, bool first) {
-        const size_t pb = (size_t)p * a.NB + bt;
-        const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
-        const int mt = __builtin_amdgcn_readfirstlane(min(s + W * j, HT - 1));   // (known to be uniform)
-        const f32x4 gt = buf_load4(make_rsrc(a.gates + pb * htile * 4), lane16, mt * 1024);
-        pf_gt[j] = make_float4(gt[0], gt[1], gt[2], gt[3]);
-        pf_c[j] = first ? buf_load(make_rsrc(a.c + pb * htile), lane4, mt * 256) : pf_cp[j];
-        pf_cp[j] = buf_load(make_rsrc(a.c + pbd * htile), lane4, mt * 256);
-        pf_g[j] = buf_load(make_rsrc(a.gsrc[0] + pb * htile), lane4, mt * 256);
-        pf_g2[j] = buf_load(make_rsrc(a.gsrc[1] + pb * htile), lane4, mt * 256);   // gsrc[1] repeats gsrc[0] when there is one source (ignored then)
-    };
-    auto fetch = [&](int p, bool first) {
-        fetch_xh(p);
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) fetch_tile(j, p, first);
-    };
-
-    const float g2_scale = a.n_gsrc >= 2 ? 1.0f : 0.0f;
-    // d/dc of lambda * c^2 / n over the valid window positions of this lane's series (CP only)
-    int n_valid = 0;
-    float pen = 0.0f;
-    if constexpr (CP) {
-        const int col = bt * kTileN + n;
-        const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
-        n_valid = len - a.I - a.H + 1;
-        pen = a.two_lambda_cs * a.sc->inv_n_cs;
-    }
-    float dcreg[MTW], dhreg[MTW];
-    float da[MTW][4];
-    // ---- step A, tile j of the fetched position: gate gradients to registers and LDS
-    auto step_a_tile = [&](int j, bool has_prev, int p_cur) {
-        const float4 gt = pf_gt[j];
-        const float dh = pf_g[j] + g2_scale * pf_g2[j] + dhreg[j];
-        const float tc = tanh_f(pf_c[j]);
-        // (products shared between the terms are formed once: the vector ALU's cycles are the matrix pipe's)
-        const float dh_o = dh * gt.w;
-        float dc = dcreg[j] + dh_o * (1.0f - tc * tc);
-        if constexpr (CP) dc += p_cur < n_valid ? pen * pf_c[j] : 0.0f;
-        const float cp = has_prev ? pf_cp[j] : 0.0f;
-        const float dc_i = dc * gt.x, dc_f = dc * gt.y;
-        da[j][0] = dc_i * gt.z * (1.0f - gt.x);
-        da[j][1] = dc_f * cp * (1.0f - gt.y);
-        da[j][2] = dc_i * (1.0f - gt.z * gt.z);
-        da[j][3] = dh_o * tc * (1.0f - gt.w);
-        dcreg[j] = dc_f;
-        float *dst = da_lds + ((s + W * j) * 16 + g) * kLdsPad + n;   // dummy rows for tiles past HT
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            dst[r * 4 * kLdsPad] = da[j][r];
-            dbacc[j][r] += da[j][r];
-        }
-    };
-    auto store_xh = [&](bool has_prev) {
-#pragma unroll
-        for (int i = 0; i < XH_PER_THREAD; ++i) {
-            const int e = threadIdx.x + i * NT;
-            xh_lds[(e >> 4) * kLdsPad + (e & 15)] = (e < KXT * 64 || has_prev) ? pf_xh[i] : 0.0f;
-        }
-    };
-    // ---- step B: partial W^T da over this wave's k-steps, into LDS
-    auto step_b = [&]() {
-        f32x4 acc[MB];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < MTW - 1; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma16(wreg[mb][4 * j + r], da[j][r], acc[mb]);
-        if (last_own_valid) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[mb] = mfma16(wreg[mb][4 * (MTW - 1) + r], da[MTW - 1][r], acc[mb]);
-        }
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) part_lds[s][mb * 4 + r][lane] = acc[mb][r];
-    };
-    // ---- end of position p: sum the partials this wave needs (recurrent dh of its
-    // units) or stores (input gradient), and pull the operands of step C into registers
-    float xb[MB][4], ar[MTW][4], dxv[QXW];
-    auto finish = [&](int p) {
-        lds_barrier();              // partials, da, [x ; h] of position p complete
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) {
-            const int q = min(KXT + s + W * j, KT - 1);   // row of part_lds = unit tile of [x ; h]
-            dhreg[j] = (part_lds[0][q][lane] + part_lds[1][q][lane]) + (part_lds[2][q][lane] + part_lds[3][q][lane]);
-        }
-#pragma unroll
-        for (int j = 0; j < QXW; ++j) {
-            const int q = min(s + W * j, KXT - 1);
-            dxv[j] = (part_lds[0][q][lane] + part_lds[1][q][lane]) + (part_lds[2][q][lane] + part_lds[3][q][lane]);
-        }
-#pragma unroll
-        for (int nbk = 0; nbk < MB; ++nbk)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) xb[nbk][ks] = xh_lds[(nbk * 16 + n) * kLdsPad + 4 * ks + g];
-#pragma unroll
-        for (int j = 0; j < MTW; ++j)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                ar[j][ks] = da_lds[(((W - 1 - s) + W * j) * 16 + n) * kLdsPad + 4 * ks + g];
-        lds_barrier();              // everything of position p has been read
-    };
-    // Memory operations complete in order, and the compiler's wait for the operands requested one
-    // position ahead counts the stores issued since with the smallest number any wave issues.  Every
-    // wave therefore issues the same number of stores: one without an input tile for its last store
-    // writes to a sink.  The stores go out right after the sums, behind the requests already in flight
-    // (which then do not wait for them) and a whole position ahead of the next wait.
-    auto store_dx = [&](int p) {
-        const size_t pb = (size_t)p * a.NB + bt;
-        const buf_rsrc r_dx = make_rsrc(a.gdst + pb * xtile), r_sink = make_rsrc(sink_line);
-#pragma unroll
-        for (int j = 0; j < QXW; ++j) {
-            if (j < QXW - 1 || last_qx_valid) buf_store(r_dx, lane4, (s + W * j) * 256, dxv[j]);
-            else buf_store(r_sink, lane4, 0, dxv[j]);
-        }
-    };
-    auto dw_row = [&](int j) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-            for (int nbk = 0; nbk < MB; ++nbk) dw[j][nbk] = mfma16(ar[j][ks], xb[nbk][ks], dw[j][nbk]);
-    };
-
-    for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
-        const int p_last = r0 + ((Pt - 1 - r0) / a.d) * a.d;
-        // start of a chain: no gradient arrives from later positions
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) { dcreg[j] = 0.0f; dhreg[j] = 0.0f; }
-        __syncthreads();            // LDS free (previous chain / initial clearing)
-        fetch(p_last, true);
-        store_xh(p_last >= a.d);
-#pragma unroll
-        for (int j = 0; j < MTW; ++j) step_a_tile(j, p_last >= a.d, p_last);
-        fetch(max(p_last - a.d, r0), false);
-        step_b();
-
-        for (int p = p_last; p >= a.d; p -= a.d) {
-            finish(p);
-            store_dx(p);
-            // gate gradients of position p - d (elementwise) interleaved with the dW MFMAs of p and with
-            // the requests for position p - 2d
-            const bool has_prev = p >= 2 * a.d;
-            const int p_next = max(p - 2 * a.d, r0);
-            store_xh(has_prev);
-            fetch_xh(p_next);
-#pragma unroll
-            for (int j = 0; j < MTW - 1; ++j) {
-                step_a_tile(j, has_prev, p - a.d);
-                fetch_tile(j, p_next, false);
-                dw_row(j);
-            }
-            step_a_tile(MTW - 1, has_prev, p - a.d);
-            fetch_tile(MTW - 1, p_next, false);
-            if (last_row_valid) dw_row(MTW - 1);
-            step_b();
-        }
-        finish(r0);
-        store_dx(r0);
-#pragma unroll
-        for (int j = 0; j < MTW - 1; ++j) dw_row(j);
-        if (last_row_valid) dw_row(MTW - 1);
-    }
-
-    // per-workgroup partial results
-    const size_t part = (size_t)bt * gridDim.y + blockIdx.y;
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) {
-        const int row = (W - 1 - s) + W * j;
-        if (row < HT) {
-#pragma unroll
-            for (int nbk = 0; nbk < MB; ++nbk) {
-                float *dst = a.dw_partial + (part * (HT * MB) + row * MB + nbk) * 256 + lane;
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) dst[rr * 64] = dw[j][nbk][rr];
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < MTW; ++j) {
-        const int mt = s + W * j;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const float tot = group16_sum(dbacc[j][rr]);
-            if (n == 0 && mt < HT) a.db_partial[(part * HT + mt) * 16 + g * 4 + rr] = tot;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Reverse pass with the weight gradient on waves of its own.  Steps A and B are
-// the recurrence: position p - d cannot start before the recurrent dh of p is
-// summed.  Step C only consumes what A leaves in LDS.  Here four "chain" waves
-// do A and B exactly as above, and four "dW" waves do C one position behind
-// them: after the barrier that completes position p they read da and [x ; h] of
-// p from one LDS copy while the chain waves fill the other copy with p - d.
-// The matrix pipe of a SIMD then has the dW wave's work whenever its chain wave
-// waits (barrier, LDS round trip, accumulator read-out), and the chain waves
-// carry half the MFMAs per position.  One workgroup of eight waves per compute
-// unit; one barrier per position, taken by all eight waves.
-// ---------------------------------------------------------------------------
 template <int HT, int KXT, bool CP>
 __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kernel(LstmBwdArgs a)
 {
@@ -442,7 +165,8 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
     for (int j = 0; j < MTW; ++j) dbacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const size_t xtile = (size_t)KXT * 64, htile = (size_t)HT * 64;
 
-    // operands of one position, requested one position ahead (branch-free, see the kernel above)
+    // operands of one position, requested one position ahead.  Branch-free: tiles past HT alias the last tile, a
+    // missing predecessor aliases p itself, elements past the end of [x ; h] alias its last element.
     float4 pf_gt[MTW];
     float pf_c[MTW], pf_cp[MTW], pf_g[MTW], pf_g2[MTW], pf_xh[XH_PER_THREAD];
     // The requests of a position go out piece by piece, each as soon as the registers it fills are free:
@@ -552,7 +276,10 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
             dxv[j] = (pt[0][q][lane] + pt[1][q][lane]) + (pt[2][q][lane] + pt[3][q][lane]);
         }
     };
-    auto store_dx = [&](int p) {     // every wave issues the same number of stores (see the kernel above)
+    // Every wave issues the same number of stores (one without an input tile for its last store writes to a sink):
+    // memory operations complete in order, and the compiler's wait for the operands requested one position ahead
+    // counts the stores issued since with the smallest number any wave issues.
+    auto store_dx = [&](int p) {
         const size_t pb = (size_t)p * a.NB + bt;
 #pragma unroll
         for (int j = 0; j < QXW; ++j) {
@@ -619,15 +346,10 @@ __global__ void __launch_bounds__(256) sum_sources_kernel(const float4 *__restri
 }
 
 template <int HT, int KXT>
-hipError_t run_bwd(const LstmBwdArgs &a, int chains, bool split, hipStream_t st)
+hipError_t run_bwd(const LstmBwdArgs &a, int chains, hipStream_t st)
 {
-    if (split || HT >= kSplitBwdFromHT) {
-        if (a.sc) lstm_backward_split_kernel<HT, KXT, true><<<dim3(a.NB, chains), 128 * kLstmWaves, 0, st>>>(a);
-        else lstm_backward_split_kernel<HT, KXT, false><<<dim3(a.NB, chains), 128 * kLstmWaves, 0, st>>>(a);
-    } else if constexpr (HT < kSplitBwdFromHT) {   // (the four-wave kernel is not built for the larger hidden sizes)
-        if (a.sc) lstm_backward_kernel<HT, KXT, true><<<dim3(a.NB, chains), 64 * kLstmWaves, 0, st>>>(a);
-        else lstm_backward_kernel<HT, KXT, false><<<dim3(a.NB, chains), 64 * kLstmWaves, 0, st>>>(a);
-    }
+    if (a.sc) lstm_backward_split_kernel<HT, KXT, true><<<dim3(a.NB, chains), 128 * kLstmWaves, 0, st>>>(a);
+    else lstm_backward_split_kernel<HT, KXT, false><<<dim3(a.NB, chains), 128 * kLstmWaves, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -636,16 +358,7 @@ hipError_t run_bwd(const LstmBwdArgs &a, int chains, bool split, hipStream_t st)
 hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st)
 {
     const LayerPlan &lp = pl.layer[layer];
-    LstmBwdArgs a{};
-    const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
-    a.lengths = lengths;
-    a.sc = cp ? reinterpret_cast<const Scalars *>(ws + pl.scalars) : nullptr;
-    a.two_lambda_cs = 2.0f * pl.cfg.lambda_cs;
-    a.B = pl.B; a.T = pl.T; a.I = pl.I; a.H = pl.H;
-    a.wpack = ws + lp.wpack_bwd; a.xsrc = ws + lp.xsrc; a.gates = ws + lp.gates; a.c = ws + lp.c; a.hid = ws + lp.hid;
-    a.n_gsrc = lp.n_gsrc < 2 ? lp.n_gsrc : 2;
-    a.gsrc[0] = ws + lp.gsrc[0];
-    a.gsrc[1] = ws + lp.gsrc[lp.n_gsrc >= 2 ? 1 : 0];
+    LstmBwdSources src{{ws + lp.gsrc[0], ws + lp.gsrc[lp.n_gsrc >= 2 ? 1 : 0]}, std::min(lp.n_gsrc, 2)};
     if (lp.n_gsrc > 2) {
         // three or more residual blocks: the sources past the first are summed into a buffer of their
         // own first (they stay intact for the layers that consume them separately)
@@ -656,14 +369,25 @@ hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *length
             reinterpret_cast<const float4 *>(s3), reinterpret_cast<float4 *>(ws + pl.gsum), n4);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        a.gsrc[1] = ws + pl.gsum;
+        src.g[1] = ws + pl.gsum;
     }
     if (lp.narrow_bwd) return launch_lstm_backward_narrow(pl, layer, lengths, ws, st);
+    if (bwd_three_term(pl.HT)) return launch_lstm_backward_three_term(pl, layer, src, lengths, ws, st);
+    LstmBwdArgs a{};
+    const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
+    a.lengths = lengths;
+    a.sc = cp ? reinterpret_cast<const Scalars *>(ws + pl.scalars) : nullptr;
+    a.two_lambda_cs = 2.0f * pl.cfg.lambda_cs;
+    a.B = pl.B; a.T = pl.T; a.I = pl.I; a.H = pl.H;
+    a.wpack = ws + lp.wpack_bwd; a.xsrc = ws + lp.xsrc; a.gates = ws + lp.gates; a.c = ws + lp.c; a.hid = ws + lp.hid;
+    a.n_gsrc = src.n;
+    a.gsrc[0] = src.g[0];
+    a.gsrc[1] = src.g[1];
     a.gdst = ws + lp.gdst; a.dw_partial = ws + lp.dw_partial; a.db_partial = ws + lp.db_partial;
     a.sink = ws + pl.sink;
     a.P = pl.P; a.NB = pl.NB; a.d = lp.dil;
     a.pmax = reinterpret_cast<const int32_t *>(ws + pl.pmax);
-#define X(HT_, KXT_) if (pl.HT == HT_ && lp.KXT == KXT_) return run_bwd<HT_, KXT_>(a, lp.chains_bwd, lp.split_bwd != 0, st);
+#define X(HT_, KXT_) if constexpr (!bwd_three_term(HT_)) if (pl.HT == HT_ && lp.KXT == KXT_) return run_bwd<HT_, KXT_>(a, lp.chains_bwd, st);
     ESRNN_LSTM_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;

@@ -198,14 +198,10 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.narrow_bwd = wide_groups < narrow_bwd_below ? 1 : 0;
         lp.chains = chains_for(lp.narrow_fwd ? 4 * pl.NB : pl.NB, 512);
         const int groups = lp.narrow_bwd ? 4 * pl.NB : pl.NB;
-        lp.chains_bwd = chains_for(groups, 512);
-        // Reverse kernels with eight waves, the weight gradient on waves of its own: one workgroup per compute
-        // unit.  The faster kind where the grid has at most one workgroup per compute unit anyway, and for the
-        // 16-series kernel with the larger hidden sizes (whose four-wave workgroup would be alone on its
-        // compute unit for its registers).
-        const bool one_per_cu = groups * lp.chains_bwd <= 256;
-        lp.split_bwd = (one_per_cu || (!lp.narrow_bwd && pl.HT >= kSplitBwdFromHT)) ? 1 : 0;
-        if (lp.split_bwd && !lp.narrow_bwd) lp.chains_bwd = chains_for(groups, 256);
+        // 16-series reverse kernels have one workgroup per compute unit.  The 4-series one has two, or one of eight
+        // waves, the weight gradient on waves of its own: the faster kind where the grid has no more than that.
+        lp.chains_bwd = chains_for(groups, lp.narrow_bwd ? 512 : 256);
+        lp.split_bwd = lp.narrow_bwd && groups * lp.chains_bwd <= 256 ? 1 : 0;
         if (lp.narrow_fwd) {
             lp.wpack_fwd = ws.take((size_t)4 * 4 * KT * 64);
             lp.bias_pack = lp.wpack_fwd;                       // unused: the kernels read the caller's bias
@@ -214,7 +210,8 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
             lp.bias_pack = ws.take((size_t)pl.HT * 16);
         }
         lp.wpack_bwd = lp.narrow_bwd ? ws.take((size_t)4 * ceil_div(4 * KT, 64) * 4 * pl.HT * 64)
-                                     : ws.take((size_t)MB * 4 * pl.HT * 64);
+                       : bwd_three_term(pl.HT) ? ws.take((size_t)bwd_pack_dwords(pl.HT, lp.KXT))
+                                               : ws.take((size_t)MB * 4 * pl.HT * 64);
         lp.gates = ws.take(PN * tileH * 4);
         lp.c = ws.take(PN * tileH);
         lp.hid = ws.take(PN * tileH);

@@ -64,6 +64,25 @@ constexpr TtPair tt_mfma(int np, int i)
     return {3 * full + i, 3 * full + (i == 2 ? 1 : 0)};
 }
 
+// ---- how the reverse kernel (lstm_backward.h) deals its work (host and device) ----
+// Up to 13 unit tiles; at 16 its weights and sums do not fit the registers of 16 waves.
+constexpr bool bwd_three_term(int HT) { return HT <= 13; }
+constexpr int bwd_chain_waves(int HT) { return (HT + 1) / 2; }
+constexpr int bwd_dw_waves(int HT) { return HT / 2; }
+constexpr int bwd_h_row_tiles(int HT) { return (HT + 3) / 4; }
+// unit tiles of x that do not fill a 16-row tile and find room in the last one of h
+constexpr int bwd_merged_tiles(int HT, int KXT)
+{
+    return KXT >= 4 && KXT % 4 <= 4 * bwd_h_row_tiles(HT) - HT ? KXT % 4 : 0;
+}
+constexpr int bwd_x_row_tiles(int HT, int KXT) { return bwd_merged_tiles(HT, KXT) ? KXT / 4 : (KXT + 3) / 4; }
+constexpr int bwd_waves(int HT, int KXT) { return bwd_chain_waves(HT) + bwd_dw_waves(HT) + bwd_x_row_tiles(HT, KXT); }
+// dwords of its A operands: [row tiles of x, then of h][unit tile][part][64][2]
+constexpr int bwd_pack_dwords(int HT, int KXT)
+{
+    return (bwd_x_row_tiles(HT, KXT) + bwd_h_row_tiles(HT)) * 2 * bwd_chain_waves(HT) * 3 * 128;
+}
+
 __device__ __forceinline__ unsigned bf16_pack(float a, float b)     // round to nearest even; a in the low half
 {
     bf16x2 v;
