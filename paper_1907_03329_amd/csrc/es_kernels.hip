@@ -156,7 +156,7 @@ __device__ void pack_forward(const PackLstmArgs &a)
 // merged ones of x (three_term.h).
 __device__ void pack_backward(const PackLstmArgs &a)
 {
-    const int rx = bwd_x_row_tiles(a.HT, a.KXT), ml = bwd_merged_tiles(a.HT, a.KXT), tiles = 2 * bwd_chain_waves(a.HT);
+    const int rx = bwd_x_row_tiles(a.HT, a.KXT), ml = bwd_merged_tiles(a.HT, a.KXT), tiles = bwd_even_tiles(a.HT);
     const int n = bwd_pack_dwords(a.HT, a.KXT);
     for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
         const int d = idx & 1, lane = (idx >> 1) & 63, part = (idx >> 7) % 3, t = (idx / 384) % tiles, rt = idx / (384 * tiles);

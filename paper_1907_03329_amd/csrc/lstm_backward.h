@@ -8,19 +8,31 @@
 //   C. dW += da (x) [x ; h], contraction over the 16 series, in accumulators for the whole launch.
 // All products run on the bf16 matrix pipe with fp32 accuracy (three_term.h).
 //
-// Three kinds of waves, one barrier per position:
-//   chain waves (two unit tiles each) carry the recurrence: A, and B for the h rows, split over the waves along the
-//     contraction, so that a wave multiplies what it has just computed in registers; the partial results meet in
-//     LDS and every wave sums those of its own units.  Whatever of A does not depend on the recurrent gradient is
-//     formed one position ahead, so that between the barrier and the first product there are a dozen dependent
-//     instructions.  They also leave the three parts of da in LDS.
+// Kinds of waves, one barrier per position:
+//   chain waves (two or three unit tiles each) carry the recurrence: A, and B for the h rows, split over the waves along
+//     the contraction, so that a wave multiplies what it has just computed in registers; the partial results meet in
+//     LDS and every wave sums those of its own units.  They also leave the three parts of da in LDS.
+//   factor waves (hidden sizes up to 40) read the stash and form whatever of A does not depend on the recurrent
+//     gradient, two positions ahead; a chain wave then has a dozen dependent instructions between the barrier and its
+//     first product.  At 13 unit tiles the sixteen waves of a workgroup are taken: there seven chain waves of two tiles
+//     do it themselves, one position ahead.
 //   dx waves (one 16-row tile each) do B for the x rows, which nothing in the recurrence waits for, one position
 //     behind, from the parts in LDS.  If the last tile of h rows has room for the x tiles that do not fill a tile of
 //     their own, the chain waves' products carry them, and a dx wave sums and stores them.
 //   dW waves (two rows of tiles each) do C one position behind.  They bring [x ; h], two positions ahead; both
 //     operands are needed transposed (series along the contraction) and are read with the LDS transpose load.
-// Chain waves only load, dx waves only store (a dx wave brings a tile of [x ; h] where the dW waves do not suffice),
-// so that no wait for a request covers a store.
+// No wave waits for its own stores: those that load do not store, except a dx wave that brings a tile of [x ; h] where the
+// dW waves do not suffice.
+//
+// What bounds it.  Hidden 40, 4096 series, 61 positions: 90 - 94 us a layer (fp32 kernel: 128 - 131 us), first layer 70 -
+// 73 us (103 us), i.e. 1.45 us a position with 320 MB of traffic, of which the memory needs 52 us.  Without the dW waves'
+// part it is 69 us, without dx and dW 61 us; without the dW products alone 82 us: the reads of transposed operands from LDS
+// (80 of 195 KB a position) weigh more than the products (matrix pipe busy 40 %).  Hidden 50, 240 steps: 440 - 470 us (780 -
+// 810 us), first layer 340 us (517 us).  Tried without gain: chain waves that form their own factors (12 waves: 90 us, first
+// layer 74 us; alone on the chip 1.03 us a position against 0.92), five chain waves of two tiles (two of them share a
+// SIMD), raised priority of the chain waves (+2 %), all operands of a consumer read at once (+3 %), dW waves that own 32
+// columns and read them from memory with 32x32 products (54 KB less through LDS, but 97 us, first layer 85 us: three waves
+// are then the longest of a position).
 //
 // LDS home of 16 rows x 16 series in one of the three parts: the four rows of a lane group as one 8-byte chunk per
 // lane, [chunk][series], so that the wave that computes them writes whole chunks; the second half is shifted by 32
@@ -56,28 +68,36 @@ struct LstmBwdArgs {
 };
 
 // The positions of a workgroup in order: residue classes r, r + step, ..., each from its last position down.  Scalar,
-// without branches.
+// without branches and without 64-bit arithmetic (what a chain wave spends on it is on the critical path).
 struct ChainWalk {
-    int p, r, step, d, top, top_mod, classes;
-    __device__ ChainWalk(int first, int step_, int d_, int positions)
-        : r(first), step(step_), d(d_), top(positions - 1), top_mod((positions - 1) % d_), classes(min(d_, positions))
+    int p;                          // position
+    int r, step, d, base, top_mod, classes, NB, bt;
+    __device__ ChainWalk(int first, int step_, int d_, int positions, int NB_, int bt_)
+        : r(first), step(step_), d(d_), top_mod((positions - 1) % d_), classes(min(d_, positions)), NB(NB_), bt(bt_)
     {
+        base = positions - 1 - top_mod;
         p = first < classes ? last(first) : 0;
     }
-    __device__ int last(int rr) const { return top - (top_mod - rr + (top_mod >= rr ? 0 : d)); }
-    __device__ int count() const        // (of a walk at its start)
+    __device__ int last(int rr) const { return base + rr - (rr > top_mod ? d : 0); }
+    __device__ unsigned tile() const { return (unsigned)p * NB + bt; }      // (P NB < 2^31: B T is at most 2^30)
+    __device__ int count() const    // (of a walk at its start)
     {
         if (r >= classes) return 0;
         const int n = (classes - 1 - r) / step + 1, longer = r <= top_mod ? (top_mod - r) / step + 1 : 0;
-        return n * (top / d) + longer;
+        return n * (base / d) + longer;
     }
-    __device__ void next()              // stays at the last one
+    __device__ void next()          // stays at the last one
     {
         const int r2 = r + step, below = p - d, over = r2 < classes ? last(r2) : p;
         r = below < 0 && r2 < classes ? r2 : r;
         p = below >= 0 ? below : over;
     }
 };
+// tile `tile` of an array of tiles of `floats` floats
+__device__ __forceinline__ const char *tile_at(const float *array, unsigned tile, unsigned floats)
+{
+    return reinterpret_cast<const char *>(array) + (unsigned long long)tile * (4u * floats);
+}
 // f(0), f(1), f(0), ... n times (arguments are compile-time constants): which half of a double buffer a position uses.
 // Straight runs without an exit in between, or registers of requests in flight are copied - and waited for - there.
 template <class F>
@@ -107,44 +127,45 @@ __device__ __forceinline__ u32x2 lds_read_transposed(const char *at)
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at)));
 }
 
-// Workgroups are alone on their compute unit (for their registers), so the waves of one fill it: three or four per SIMD.
+// Workgroups are alone on their compute unit (for their registers), so the waves of one fill it: four per SIMD.
 template <int HT, int KXT, bool CP>
 __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) + 3) / 4) lstm_backward_kernel(LstmBwdArgs a)
 {
     constexpr int KT = KXT + HT, MB = (KT + 3) / 4;        // unit tiles and 16-column tiles of [x ; h]
     constexpr int RX = bwd_x_row_tiles(HT, KXT), RH = bwd_h_row_tiles(HT), ML = bwd_merged_tiles(HT, KXT);
-    constexpr int NC = bwd_chain_waves(HT), NW = bwd_dw_waves(HT), HTE = 2 * NC;
+    constexpr int NC = bwd_chain_waves(HT), NW = bwd_dw_waves(HT), NF = bwd_factor_waves(HT), HTE = bwd_even_tiles(HT);
     constexpr int HM = HT + ML;                            // unit tiles the chain waves' products give
     constexpr bool kTail = HT % 2 != 0;                    // a last row of dW tiles, dealt to the dW waves by columns
     constexpr int XC = (MB + NW - 1) / NW;                 // columns of it per wave
     constexpr int D = HT <= 10 ? 2 : 1;                    // positions the stash is requested ahead
+    constexpr bool kReadAhead = HT <= 10;                  // dW and dx waves read operands from LDS one tile ahead (registers)
     static_assert(MB <= NW + RX, "every column tile needs a wave that brings it");
 
     __shared__ __align__(16) char da_lds[2][HTE * 3 * kPartBytes];   // [pair of unit tiles][part][unit tile of the pair]
     __shared__ __align__(16) char xh_lds[2][MB * 3 * kPartBytes];
     __shared__ float part_lds[2][NC][HM][64];
-    static_assert(sizeof(da_lds) + sizeof(xh_lds) + sizeof(part_lds) <= 128 * 1024, "LDS budget of the reverse kernel");
+    __shared__ f32x4 factor_lds[NF > 0 ? 2 : 1][NF > 0 ? HT : 1][2][64];
+    static_assert(sizeof(da_lds) + sizeof(xh_lds) + sizeof(part_lds) + sizeof(factor_lds) <= 128 * 1024,
+                  "LDS budget of the reverse kernel");
 
     const int lane = threadIdx.x & 63, bt = blockIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, known to be uniform
     const int g = lane >> 4, n = lane & 15;
     const int Pt = a.pmax[bt];      // the chains of this tile stop at its longest series
     const size_t part = (size_t)bt * gridDim.y + blockIdx.y;
-    constexpr size_t xtile = (size_t)KXT * 64, htile = (size_t)HT * 64;
+    constexpr unsigned xtile = KXT * 64, htile = HT * 64;
     const unsigned lane4 = 4 * lane, lane16 = 16 * lane;
     auto da_at = [](int mt, int q) { return ((mt >> 1) * 6 + 2 * q + (mt & 1)) * kPartBytes; };
     const int own = 8 * lane + 32 * (lane >> 5);           // this lane's chunk inside a part
-    const ChainWalk start(blockIdx.y, gridDim.y, a.d, Pt);
+    const ChainWalk start(blockIdx.y, gridDim.y, a.d, Pt, a.NB, bt);
     const int n_steps = start.count();
 
     // ---- [x ; h] of one position, column tile nb: requested two positions ahead, split, left in LDS.
     float xraw[2][4];
-    auto request_xh = [&](int set, int nb, int p) {
-        const size_t pb = (size_t)p * a.NB + bt;
-        const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
+    auto request_xh = [&](int set, int nb, const ChainWalk &at) {
         // scalar choices of a base, no branch around a request; tiles past the end alias the last one
-        const char *x = reinterpret_cast<const char *>(a.xsrc + pb * xtile);
-        const char *h = reinterpret_cast<const char *>(a.hid + pbd * htile) - KXT * 256;
+        const char *x = tile_at(a.xsrc, at.tile(), xtile);
+        const char *h = tile_at(a.hid, at.tile() - (at.p >= a.d ? (unsigned)a.d * a.NB : 0u), htile) - KXT * 256;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int q = min(4 * nb + e, KT - 1);
@@ -164,148 +185,180 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
         *reinterpret_cast<u32x2 *>(dst + kPartBytes) = u32x2{p0.mid, p1.mid};
         *reinterpret_cast<u32x2 *>(dst + 2 * kPartBytes) = u32x2{p0.lo, p1.lo};
     };
-    // A wave that consumes what the chain waves leave: `work(buf, p)` after the barrier that completes position p.
-    // LOAD: it also brings column tile nb.  Every wave of the workgroup meets the same barriers.
+    // A wave that consumes what the chain waves leave: `work(buf, tile, aside)` after the barrier that completes a
+    // position.  LOAD: it also brings column tile nb, in `aside`, which `work` calls once its first operands are on
+    // their way from LDS.  Every wave of the workgroup meets the same barriers.
     auto consumer = [&](auto load, int nb, auto &&work) {
         constexpr bool LOAD = decltype(load)::value;
         if (n_steps == 0) return;
-        ChainWalk now = start, bring = start, ask = start;
+        if constexpr (NF > 0) lds_barrier();               // (the first factors)
+        ChainWalk now = start, ask = start;
+        int at[3];                                         // LOAD: the next three positions, the last one ask's
         if constexpr (LOAD) {
-            request_xh(0, nb, ask.p);
-            ask.next();
-            __builtin_amdgcn_sched_barrier(0);
-            request_xh(1, nb, ask.p);
-            ask.next();
-            store_xh(0, 0, nb, bring.p >= a.d);
-            __builtin_amdgcn_sched_barrier(0);
-            request_xh(0, nb, ask.p);
+            const bool first = start.p >= a.d;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                if (i == 2) store_xh(0, 0, nb, first);
+                __builtin_amdgcn_sched_barrier(0);
+                request_xh(i % 2, nb, ask);
+                ask.next();
+                at[i] = ask.p;
+            }
         }
         alternate(n_steps, [&](auto u) {
             constexpr int U = decltype(u)::value;
             lds_barrier();
-            if constexpr (LOAD) {
-                bring.next();
-                store_xh(U ^ 1, U ^ 1, nb, bring.p >= a.d);
-                __builtin_amdgcn_sched_barrier(0);
-                ask.next();
-                request_xh(U ^ 1, nb, ask.p);
-            }
-            work(U, now.p);
+            work(U, now.tile(), [&]() {
+                if constexpr (LOAD) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    store_xh(U ^ 1, U ^ 1, nb, at[0] >= a.d);
+                    __builtin_amdgcn_sched_barrier(0);
+                    request_xh(U ^ 1, nb, ask);
+                    ask.next();
+                    at[0] = at[1];
+                    at[1] = at[2];
+                    at[2] = ask.p;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
             now.next();
             __builtin_amdgcn_sched_barrier(0);
         });
     };
 
+    // ---- what a position's step A needs of the stash, for unit tiles t0 and t0 + 1: requested D positions ahead of
+    // its use.  With the gates and the arriving gradients comes the cell state of the position that follows in the walk:
+    // inside a chain that is the predecessor's, which this position needs too.
+    f32x4 gt[D][2];
+    float cnext[D][2], ga[D][2], gb[D][2], ccur[2];
+    auto request = [&](int set, int t0, auto njc, unsigned tile, unsigned next_tile) {
+        constexpr int nj = decltype(njc)::value;
+        const buf_rsrc r_g = make_rsrc(tile_at(a.gates, tile, 4 * htile)), r_c = make_rsrc(tile_at(a.c, next_tile, htile));
+        const buf_rsrc r_a = make_rsrc(tile_at(a.gsrc[0], tile, htile)), r_b = make_rsrc(tile_at(a.gsrc[1], tile, htile));
+#pragma unroll
+        for (int j = 0; j < nj; ++j) {
+            gt[set][j] = buf_load4(r_g, lane16, (t0 + j) * 1024);
+            cnext[set][j] = buf_load(r_c, lane4, (t0 + j) * 256);
+            ga[set][j] = buf_load(r_a, lane4, (t0 + j) * 256);
+            gb[set][j] = buf_load(r_b, lane4, (t0 + j) * 256);
+        }
+    };
+    auto request_first_c = [&](int t0, auto njc, unsigned tile) {
+        constexpr int nj = decltype(njc)::value;
+        const buf_rsrc r_c = make_rsrc(tile_at(a.c, tile, htile));
+#pragma unroll
+        for (int j = 0; j < nj; ++j) ccur[j] = buf_load(r_c, lane4, (t0 + j) * 256);
+    };
+    const float g2_scale = a.n_gsrc >= 2 ? 1.0f : 0.0f;
+    int n_valid = 0;                    // positions below this take part in the loss for this lane's series (CP only)
+    float pen = 0.0f;
+    if constexpr (CP) {
+        const int col = bt * kTileN + n;
+        const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
+        n_valid = len - a.I - a.H + 1;
+        pen = a.two_lambda_cs * a.sc->inv_n_cs;
+    }
+    // factors of step A that do not depend on the recurrent gradient, as two quads:
+    // dc = dcreg + (gs + dhreg) ad + pc;  da = (dc ki, dc kf, dc kg, (gs + dhreg) ko);  dcreg = dc f
+    auto factors = [&](int set, int j, int p, f32x4 (&f)[2]) {
+        const f32x4 v = gt[set][j];                        // input, forget, candidate, output gate
+        const float tc = tanh_f(ccur[j]), cp = p >= a.d ? cnext[set][j] : 0.0f;
+        f[0] = f32x4{v[0] * v[2] * (1.0f - v[0]), v[1] * cp * (1.0f - v[1]), v[0] * (1.0f - v[2] * v[2]),
+                     v[3] * tc * (1.0f - v[3])};           // ki, kf, kg, ko
+        f[1] = f32x4{own_register(ga[set][j]) + g2_scale * gb[set][j], v[3] * (1.0f - tc * tc), own_register(v[1]),
+                     CP && p < n_valid ? pen * ccur[j] : 0.0f};   // gs, ad, f, pc
+        ccur[j] = own_register(cnext[set][j]);
+    };
+
     if (wv < NC) {
         // =========================== chain waves ===========================
-        __builtin_amdgcn_s_setprio(3);
         const int s = wv;
         auto chains = [&](auto njc) {
-            constexpr int NJ = decltype(njc)::value;       // unit tiles 2 s .. 2 s + NJ - 1
-            u32x4 w[RH][3];
+            // NJ unit tiles: 2 s and 2 s + 1, whose products take whole groups of four pairs, and 2 NC + s, a rest of two pairs
+            constexpr int NJ = decltype(njc)::value, NP = NJ < 2 ? NJ : 2;
+            constexpr std::integral_constant<int, NP> np;
+            auto tile_of = [&](int j) { return j < 2 ? 2 * s + j : 2 * NC + s; };
+            u32x4 w[RH][3], w3[RH][2];
 #pragma unroll
-            for (int mb = 0; mb < RH; ++mb)
+            for (int mb = 0; mb < RH; ++mb) {
+                const u32x2 *src = a.wpack + ((size_t)RX + mb) * HTE * 3 * 64 + lane;
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    const u32x2 *src = a.wpack + ((((size_t)RX + mb) * HTE + 2 * s) * 3 + q) * 64 + lane;
-                    const u32x2 w0 = src[0], w1 = src[3 * 64];
+                    const u32x2 w0 = src[(2 * s * 3 + q) * 64], w1 = src[((2 * s + 1) * 3 + q) * 64];
                     w[mb][q] = u32x4{w0[0], w0[1], w1[0], w1[1]};
                 }
+                if constexpr (NJ > 2) {
+                    const u32x2 *t = src + (2 * NC + s) * 3 * 64;
+                    const u32x2 hi = t[0], mid = t[64], lo = t[128];
+                    w3[mb][0] = u32x4{hi[0], hi[1], mid[0], mid[1]};
+                    w3[mb][1] = u32x4{hi[0], hi[1], lo[0], lo[1]};
+                }
+            }
 #pragma unroll
-            for (int mb = 0; mb < RH; ++mb)
+            for (int mb = 0; mb < RH; ++mb) {
 #pragma unroll
                 for (int q = 0; q < 3; ++q) arrived(w[mb][q]);
-            const float g2_scale = a.n_gsrc >= 2 ? 1.0f : 0.0f;
-            int n_valid = 0;            // positions below this take part in the loss for this lane's series (CP only)
-            float pen = 0.0f;
-            if constexpr (CP) {
-                const int col = bt * kTileN + n;
-                const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
-                n_valid = len - a.I - a.H + 1;
-                pen = a.two_lambda_cs * a.sc->inv_n_cs;
+                if constexpr (NJ > 2) { arrived(w3[mb][0]); arrived(w3[mb][1]); }
             }
-            // what is requested for a position: gates, arriving gradients, and the cell state of the position that
-            // follows in the walk - inside a chain that is the predecessor's, which this position needs too
-            f32x4 gt[D][2];
-            float cnext[D][2], ga[D][2], gb[D][2], ccur[2];
-            auto request = [&](int set, int p, int p_next) {
-                const size_t pb = (size_t)p * a.NB + bt, pn = (size_t)p_next * a.NB + bt;
-                const buf_rsrc r_g = make_rsrc(a.gates + pb * htile * 4), r_c = make_rsrc(a.c + pn * htile);
-                const buf_rsrc r_a = make_rsrc(a.gsrc[0] + pb * htile), r_b = make_rsrc(a.gsrc[1] + pb * htile);
+            float dhreg[NJ], dcreg[NJ], db[NJ][4];
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const int mt = 2 * s + j;
-                    gt[set][j] = buf_load4(r_g, lane16, mt * 1024);
-                    cnext[set][j] = buf_load(r_c, lane4, mt * 256);
-                    ga[set][j] = buf_load(r_a, lane4, mt * 256);
-                    gb[set][j] = buf_load(r_b, lane4, mt * 256);
+            for (int j = 0; j < NJ; ++j) {
+                dhreg[j] = dcreg[j] = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) db[j][r] = 0.0f;
+            }
+            f32x4 f[NJ][2];
+            // at[i]: the position i steps from now.  Without factor waves the walk is D + 2 positions ahead, and `ask` is
+            // the next tile to request; its successor is the walk's.
+            constexpr int AT = NF > 0 ? 2 : D + 2;
+            ChainWalk walk = start;
+            int at[AT];
+            unsigned ask = walk.tile();
+            if constexpr (NF > 0) {
+                at[0] = walk.p;
+                walk.next();
+                at[1] = walk.p;
+                if (n_steps > 0) {
+                    lds_barrier();                         // factors of the first two positions complete
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) { f[j][0] = factor_lds[0][tile_of(j)][0][lane]; f[j][1] = factor_lds[0][tile_of(j)][1][lane]; }
                 }
-            };
-            // factors of a position that do not depend on the recurrent gradient:
-            // dc = dcreg + dh ad + pc;  da = (dc ki, dc kf, dc kg, dh ko);  dcreg = dc f
-            float gs[2], ad[2], ki[2], kf[2], kg[2], ko[2], ff[2], pc[2];
-            auto factors = [&](int set, int p) {
-                const bool has_prev = p >= a.d;
+            } else if (n_steps > 0) {
+                request_first_c(2 * s, np, ask);
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const f32x4 v = gt[set][j];            // input, forget, candidate, output gate
-                    const float tc = tanh_f(ccur[j]), cp = has_prev ? cnext[set][j] : 0.0f;
-                    gs[j] = own_register(ga[set][j]) + g2_scale * gb[set][j];
-                    ad[j] = v[3] * (1.0f - tc * tc);
-                    ki[j] = v[0] * v[2] * (1.0f - v[0]);
-                    kf[j] = v[1] * cp * (1.0f - v[1]);
-                    kg[j] = v[0] * (1.0f - v[2] * v[2]);
-                    ko[j] = v[3] * tc * (1.0f - v[3]);
-                    ff[j] = own_register(v[1]);
-                    if constexpr (CP) pc[j] = p < n_valid ? pen * ccur[j] : 0.0f;
-                    ccur[j] = own_register(cnext[set][j]);
-                }
-            };
-            float dhreg[2] = {0.f, 0.f}, dcreg[2] = {0.f, 0.f};
-            float db[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-            // `now`: the position whose factors are ready; `ask`, `after`: the next one to request and its successor
-            ChainWalk now = start, ask = start, after = start;
-            if (n_steps > 0) {
-                after.next();
-                const buf_rsrc r_c = make_rsrc(a.c + ((size_t)start.p * a.NB + bt) * htile);
+                for (int i = 0; i <= D; ++i) {
+                    at[i] = walk.p;
+                    walk.next();
+                    if (i == D) {
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) ccur[j] = buf_load(r_c, lane4, (2 * s + j) * 256);
-#pragma unroll
-                for (int i = 0; i < D; ++i) {
-                    request(i, ask.p, after.p);
-                    ask.next();
-                    after.next();
+                        for (int j = 0; j < NP; ++j) factors(0, j, at[0], f[j]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    request(i % D, 2 * s, np, ask, walk.tile());
+                    ask = walk.tile();
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                factors(0, now.p);
-                __builtin_amdgcn_sched_barrier(0);
-                request(0, ask.p, after.p);
-                ask.next();
-                after.next();
+                at[D + 1] = walk.p;
             }
             alternate(n_steps, [&](auto u) {
-                constexpr int U = decltype(u)::value, set = (U + 1) % D;
+                constexpr int U = decltype(u)::value;
                 // A: gate gradients, their parts to LDS and into the operand of B
-                u32x4 b[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q) b[q] = u32x4{0u, 0u, 0u, 0u};
+                float da[NJ][4];
+                unsigned parts[NJ][3][2];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    const float dh = gs[j] + dhreg[j];
-                    float dc = dcreg[j] + dh * ad[j];
-                    if constexpr (CP) dc += pc[j];
-                    const float da[4] = {dc * ki[j], dc * kf[j], dc * kg[j], dh * ko[j]};
-                    dcreg[j] = dc * ff[j];
-                    const Parts p0 = split_pair(da[0], da[1]), p1 = split_pair(da[2], da[3]);
-                    char *dst = da_lds[U] + da_at(2 * s + j, 0) + own;
+                    const float dh = f[j][1][0] + dhreg[j];
+                    float dc = dcreg[j] + dh * f[j][1][1];
+                    if constexpr (CP) dc += f[j][1][3];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        b[q][2 * j] = part_of(p0, q);
-                        b[q][2 * j + 1] = part_of(p1, q);
-                        *reinterpret_cast<u32x2 *>(dst + 2 * q * kPartBytes) = u32x2{part_of(p0, q), part_of(p1, q)};
-                    }
+                    for (int r = 0; r < 3; ++r) da[j][r] = dc * f[j][0][r];
+                    da[j][3] = dh * f[j][0][3];
+                    dcreg[j] = dc * f[j][1][2];
+                    const Parts p0 = split_pair(da[j][0], da[j][1]), p1 = split_pair(da[j][2], da[j][3]);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) db[j][r] += da[r];
+                    for (int q = 0; q < 3; ++q) { parts[j][q][0] = part_of(p0, q); parts[j][q][1] = part_of(p1, q); }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) db[j][r] += da[j][r];
                 }
                 // (The scheduler sees one position at a time.  Left alone it moves the uses of what was requested two
                 // positions ago to the top of a position, and requests in between the uses of the registers they
@@ -315,18 +368,57 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                 f32x4 acc[RH];
 #pragma unroll
                 for (int mb = 0; mb < RH; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-                static_for<0, 6>([&](auto ic) {
-                    constexpr TtPair t = tt_mfma(4, decltype(ic)::value);
+                u32x4 b[3];
 #pragma unroll
-                    for (int mb = 0; mb < RH; ++mb) acc[mb] = mfma_bf16(w[mb][t.a], b[t.b], acc[mb]);
-                });
-                const bool last_of_chain = now.p < a.d;
-                now.next();
-                factors(set, now.p);
-                __builtin_amdgcn_sched_barrier(0);
-                request(set, ask.p, after.p);
-                ask.next();
-                after.next();
+                for (int q = 0; q < 3; ++q)
+                    b[q] = u32x4{parts[0][q][0], parts[0][q][1], NP > 1 ? parts[NP - 1][q][0] : 0u, NP > 1 ? parts[NP - 1][q][1] : 0u};
+                auto pairs = [&](auto from, auto to) {
+                    static_for<decltype(from)::value, decltype(to)::value>([&](auto ic) {
+                        constexpr TtPair t = tt_mfma(4, decltype(ic)::value);
+#pragma unroll
+                        for (int mb = 0; mb < RH; ++mb) acc[mb] = mfma_bf16(w[mb][t.a], b[t.b], acc[mb]);
+                    });
+                };
+                auto third = [&](int k) {                  // (hi, lo) (lo, hi);  (hi, mid) mid;  (hi, mid) hi
+                    if constexpr (NJ > 2) {
+                        const unsigned (&p)[3][2] = parts[NJ - 1];
+                        const int q0 = 2 - k, q1 = k == 1 ? 1 : 0;
+                        const u32x4 bb = u32x4{p[q0][0], p[q0][1], p[q1][0], p[q1][1]};
+#pragma unroll
+                        for (int mb = 0; mb < RH; ++mb) acc[mb] = mfma_bf16(w3[mb][k == 0], bb, acc[mb]);
+                    }
+                };
+                third(0);                                  // smallest terms first: fewer roundings of the large sum
+                third(1);
+                pairs(std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
+                third(2);
+                pairs(std::integral_constant<int, 5>{}, std::integral_constant<int, 6>{});
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        *reinterpret_cast<u32x2 *>(da_lds[U] + da_at(tile_of(j), q) + own) = u32x2{parts[j][q][0], parts[j][q][1]};
+                }
+                const bool last_of_chain = at[0] < a.d;
+                if constexpr (NF > 0) {
+                    __builtin_amdgcn_sched_barrier(0);     // (the factors take the registers of the operands)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) { f[j][0] = factor_lds[U ^ 1][tile_of(j)][0][lane]; f[j][1] = factor_lds[U ^ 1][tile_of(j)][1][lane]; }
+                    walk.next();
+                    at[0] = at[1];
+                    at[1] = walk.p;
+                } else {
+                    constexpr int set = (U + 1) % D;
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) factors(set, j, at[1], f[j]);
+                    walk.next();
+#pragma unroll
+                    for (int i = 0; i <= D; ++i) at[i] = at[i + 1];
+                    at[D + 1] = walk.p;
+                    __builtin_amdgcn_sched_barrier(0);
+                    request(set, 2 * s, np, ask, walk.tile());
+                    ask = walk.tile();
+                }
 #pragma unroll
                 for (int mb = 0; mb < RH; ++mb)
 #pragma unroll
@@ -336,11 +428,9 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
-                    float t = 0.0f;
+                    float t = part_lds[U][0][tile_of(j)][lane];
 #pragma unroll
-                    for (int i = 0; i < NC; i += 2)
-                        t += i + 1 < NC ? part_lds[U][i][2 * s + j][lane] + part_lds[U][i + 1][2 * s + j][lane]
-                                        : part_lds[U][i][2 * s + j][lane];
+                    for (int i = 1; i < NC; ++i) t += part_lds[U][i][tile_of(j)][lane];
                     dhreg[j] = last_of_chain ? 0.0f : t;
                     dcreg[j] = last_of_chain ? 0.0f : dcreg[j];
                 }
@@ -350,10 +440,11 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float tot = group16_sum(db[j][r]);
-                    if (n == 0) a.db_partial[(part * HT + 2 * s + j) * 16 + g * 4 + r] = tot;
+                    if (n == 0) a.db_partial[(part * HT + tile_of(j)) * 16 + g * 4 + r] = tot;
                 }
         };
-        if (kTail && s == NC - 1) chains(std::integral_constant<int, 1>{});
+        if (HT > 2 * NC && s < HT - 2 * NC) chains(std::integral_constant<int, (HT > 2 * NC ? 3 : 2)>{});
+        else if (kTail && s == NC - 1) chains(std::integral_constant<int, 1>{});
         else chains(std::integral_constant<int, 2>{});
     } else if (wv < NC + NW) {
         // =========================== dW waves ===========================
@@ -373,34 +464,41 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
             const u32x2 v0 = lds_read_transposed(at), v1 = lds_read_transposed(at + 32);
             return u32x4{v0[0], v0[1], v1[0], v1[1]};
         };
-        auto work = [&](int buf, int) {
-            u32x4 ar[2][3];                                // (hi | hi), (mid | mid), (hi | lo) of da
-            auto read_row = [&](int row, u32x4 (&v)[3]) {
+        auto work = [&](int buf, unsigned, auto &&aside) {
+            auto read_row = [&](int row, u32x4 (&v)[3]) {  // (hi | hi), (mid | mid), (hi | lo) of da
                 const char *base = da_lds[buf] + da_at(row, 0);
                 v[0] = quad(base + tr);
                 v[1] = quad(base + tr + 2 * kPartBytes);
                 v[2] = quad(base + hl);
             };
+            u32x4 ar[2][3], xb[2][2];                      // (hi | mid), (lo | hi) of [x ; h], one column tile ahead
+            auto read_column = [&](int nb) {
+                const char *base = xh_lds[buf] + nb * 3 * kPartBytes;
+                xb[nb & 1][0] = quad(base + hm);
+                xb[nb & 1][1] = quad(base + lh);
+            };
+            if constexpr (kReadAhead) read_column(0);
             read_row(2 * s, ar[0]);
             read_row(2 * s + 1, ar[1]);
+            aside();
+            static_for<0, MB>([&](auto nbc) {
+                constexpr int nb = decltype(nbc)::value;
+                if constexpr (!kReadAhead) read_column(nb);
+                else if constexpr (nb + 1 < MB) read_column(nb + 1);
+                const u32x4 (&x)[2] = xb[nb & 1];
 #pragma unroll
-            for (int nb = 0; nb < MB; ++nb) {
-                const char *base = xh_lds[buf] + nb * 3 * kPartBytes;
-                const u32x4 b_hm = quad(base + hm), b_lh = quad(base + lh);
-                auto product = [&](const u32x4 (&v)[3], f32x4 acc) {
-                    acc = mfma_bf16(v[0], b_hm, acc);
-                    acc = mfma_bf16(v[1], b_hm, acc);
-                    return mfma_bf16(v[2], b_lh, acc);
-                };
-                dw[0][nb] = product(ar[0], dw[0][nb]);
-                dw[1][nb] = product(ar[1], dw[1][nb]);
+                for (int k = 0; k < 3; ++k)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) dw[j][nb] = mfma_bf16(ar[j][k], x[k == 2], dw[j][nb]);
                 if constexpr (kTail)
                     if (nb % NW == s) {
                         u32x4 at[3];
                         read_row(HT - 1, at);
-                        dwt[nb / NW] = product(at, dwt[nb / NW]);
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) dwt[nb / NW] = mfma_bf16(at[k], x[k == 2], dwt[nb / NW]);
                     }
-            }
+                if constexpr (kReadAhead) __builtin_amdgcn_sched_barrier(0);   // (or the reads end up right before their uses)
+            });
         };
         if (s < MB) consumer(std::true_type{}, s, work);
         else consumer(std::false_type{}, 0, work);
@@ -418,12 +516,62 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
             put(2 * s + 1, nb, dw[1][nb]);
             if (kTail && nb % NW == s) put(HT - 1, nb, dwt[nb / NW]);
         }
+    } else if (NF > 0 && wv >= NC + NW + RX) {
+        // =========================== factor waves ===========================
+        // Unit tiles 2 s and 2 s + 1; the factors of a position are complete two positions ahead of the step.
+        const int s = wv - NC - NW - RX;
+        constexpr std::integral_constant<int, 2> two;
+        ChainWalk walk = start;
+        int at[3];                                         // positions whose factors come next
+        unsigned ask = walk.tile();
+        auto advance = [&](int set) {                      // requests `ask`, whose successor becomes the walk's position
+            walk.next();
+            __builtin_amdgcn_sched_barrier(0);
+            request(set, 2 * s, two, ask, walk.tile());
+            ask = walk.tile();
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto leave = [&](int buf, int set, int p) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                f32x4 f[2];
+                factors(set, j, p, f);
+                factor_lds[buf][2 * s + j][0][lane] = f[0];
+                factor_lds[buf][2 * s + j][1][lane] = f[1];
+            }
+        };
+        if (n_steps > 0) {
+            request_first_c(2 * s, two, ask);
+            const int p0 = walk.p;
+            advance(0);
+            const int p1 = walk.p;
+            advance(1);
+            at[0] = walk.p;
+            leave(0, 0, p0);
+            advance(0);
+            at[1] = walk.p;
+            leave(1, 1, p1);
+            advance(1);
+            at[2] = walk.p;
+            lds_barrier();
+        }
+        alternate(n_steps, [&](auto u) {
+            constexpr int U = decltype(u)::value;
+            leave(U, U, at[0]);
+            advance(U);
+            at[0] = at[1];
+            at[1] = at[2];
+            at[2] = walk.p;
+            lds_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        });
     } else {
         // =========================== dx waves ===========================
         const int s = wv - NC - NW;                        // 16-row tile of x
-        u32x4 w[NC][3];
+        constexpr int NT = HTE / 2;                        // pairs of unit tiles
+        u32x4 w[NT][3];
 #pragma unroll
-        for (int t = 0; t < NC; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 const u32x2 *src = a.wpack + (((size_t)s * HTE + 2 * t) * 3 + q) * 64 + lane;
@@ -431,31 +579,44 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                 w[t][q] = u32x4{w0[0], w0[1], w1[0], w1[1]};
             }
 #pragma unroll
-        for (int t = 0; t < NC; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int q = 0; q < 3; ++q) arrived(w[t][q]);
         // S: the wave's number, a compile-time constant so that it knows which tiles it stores
         auto role = [&](auto sc) {
             constexpr int S = decltype(sc)::value;
-            auto work = [&](int buf, int p) {
-                f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-                static_for<0, NC>([&](auto tc) {
-                    constexpr int t = decltype(tc)::value;
-                    u32x4 b[3];
+            auto work = [&](int buf, unsigned tile, auto &&aside) {
+                // accumulators for terms of like size: small sums do not round the large one, and consecutive products do
+                // not wait for each other
+                f32x4 acc[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                u32x4 b[2][3];                             // one pair of unit tiles ahead
+                auto read_pair = [&](int t) {
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const char *at = da_lds[buf] + da_at(2 * t, q) + own;
                         const u32x2 b0 = *reinterpret_cast<const u32x2 *>(at);
                         const u32x2 b1 = 2 * t + 1 < HT ? *reinterpret_cast<const u32x2 *>(at + kPartBytes) : u32x2{0u, 0u};
-                        b[q] = u32x4{b0[0], b0[1], b1[0], b1[1]};
+                        b[t & 1][q] = u32x4{b0[0], b0[1], b1[0], b1[1]};
                     }
+                };
+                if constexpr (kReadAhead) read_pair(0);
+                aside();
+                static_for<0, NT>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    if constexpr (!kReadAhead) read_pair(t);
+                    else if constexpr (t + 1 < NT) read_pair(t + 1);
                     static_for<0, 6>([&](auto ic) {
-                        constexpr TtPair m = tt_mfma(4, decltype(ic)::value);
-                        acc[t & 1] = mfma_bf16(w[t][m.a], b[m.b], acc[t & 1]);
+                        constexpr int i = decltype(ic)::value;
+                        constexpr TtPair m = tt_mfma(4, i);
+                        constexpr int size = i < 2 ? 0 : i < 5 ? 1 : 2;   // hi lo, lo hi; mid mid, hi mid, mid hi; hi hi
+                        acc[size] = mfma_bf16(w[t][m.a], b[t & 1][m.b], acc[size]);
                     });
+                    if constexpr (kReadAhead) __builtin_amdgcn_sched_barrier(0);
                 });
-                const f32x4 dx = acc[0] + acc[1];
-                const buf_rsrc r_dx = make_rsrc(a.gdst + ((size_t)p * a.NB + bt) * xtile);
+                const f32x4 dx = acc[0] + acc[1] + acc[2];
+                const buf_rsrc r_dx = make_rsrc(tile_at(a.gdst, tile, xtile));
                 static_for<0, 4>([&](auto rc) {
                     constexpr int r = decltype(rc)::value;
                     if constexpr (4 * S + r < KXT) buf_store(r_dx, lane4, (4 * S + r) * 256, dx[r]);

@@ -28,12 +28,31 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // and with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each: 64
 // workgroups (1024 series of the quarterly shape, first layer) take 40 us against 35 us, 128 (hourly shape, second
 // layer) 131 us against 175 us.
-constexpr int kNarrowForwardBelow = 96, kNarrowBackwardBelow = 160;
+// In reverse the 16-series kernel needs 0.96 us a position at hidden 40 and one workgroup per compute unit, the
+// 4-series one 0.75 us with one workgroup per compute unit and 1.05 us with two: 64 groups (1024 series of the
+// quarterly shape, first layer) take 59 us against 53 us, 80 groups 58 us against 73 us, 128 (hourly shape, second
+// layer) 195 us against 288 us.
+constexpr int kNarrowForwardBelow = 96, kNarrowBackwardBelow = 65;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
 // 16384 tiles, streaming 0.053 / 0.079 / 0.25 ms; a wave of the streaming kernel is a chain of dependent memory
 // round trips and needs about sixteen waves per SIMD to hide them.
 constexpr int kWindowStreamFromDefault = 4096;
+
+// Chains of the 16-series reverse kernels, which have one workgroup per compute unit: the fewest that take the least
+// time, counted in rounds of 256 workgroups times classes each walks (80 groups, four classes: 320 workgroups with
+// four chains are two rounds, 49 us; with two chains one round of two classes, 44 us).  No more than fill the chip
+// once: every workgroup leaves a block of weight-gradient partials to be reduced.
+int wide_reverse_chains(int groups, int classes)
+{
+    int best = 1;
+    long long best_cost = -1;
+    for (int c = 1; c <= classes && (c == 1 || groups * c <= 256); ++c) {
+        const long long cost = (long long)ceil_div(groups * c, 256) * ceil_div(classes, c);
+        if (best_cost < 0 || cost < best_cost) { best = c; best_cost = cost; }
+    }
+    return best;
+}
 
 // hidden sizes are padded to one of the instantiated unit-tile counts
 int pick_ht(int hidden)
@@ -198,9 +217,9 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.narrow_bwd = wide_groups < narrow_bwd_below ? 1 : 0;
         lp.chains = chains_for(lp.narrow_fwd ? 4 * pl.NB : pl.NB, 512);
         const int groups = lp.narrow_bwd ? 4 * pl.NB : pl.NB;
-        // 16-series reverse kernels have one workgroup per compute unit.  The 4-series one has two, or one of eight
-        // waves, the weight gradient on waves of its own: the faster kind where the grid has no more than that.
-        lp.chains_bwd = chains_for(groups, lp.narrow_bwd ? 512 : 256);
+        // The 4-series reverse kernel has two workgroups per compute unit, or one of eight waves, the weight gradient
+        // on waves of its own: the faster kind where the grid has no more than that.
+        lp.chains_bwd = lp.narrow_bwd ? chains_for(groups, 512) : wide_reverse_chains(groups, most_chains);
         lp.split_bwd = lp.narrow_bwd && groups * lp.chains_bwd <= 256 ? 1 : 0;
         if (lp.narrow_fwd) {
             lp.wpack_fwd = ws.take((size_t)4 * 4 * KT * 64);

@@ -56,10 +56,11 @@ constexpr TtPair tt_mfma(int np, int i)
     const int full = tt_full(np);
     if (i < 6 * full) {
         const int g = 3 * (i / 6), k = i % 6;
-        const int a[6] = {0, 1, 0, 1, 2, 0}, b[6] = {0, 0, 1, 1, 0, 2};
+        const int a[6] = {0, 2, 1, 0, 1, 0}, b[6] = {2, 0, 1, 1, 0, 0};    // smallest first: fewer roundings of the large sum
         return {g + a[k], g + b[k]};
     }
     i -= 6 * full;
+    i = tt_rest(np) - i;
     if (tt_rest(np) == 1) return {3 * full + i, 3 * full};
     return {3 * full + i, 3 * full + (i == 2 ? 1 : 0)};
 }
@@ -67,7 +68,10 @@ constexpr TtPair tt_mfma(int np, int i)
 // ---- how the reverse kernel (lstm_backward.h) deals its work (host and device) ----
 // Up to 13 unit tiles; at 16 its weights and sums do not fit the registers of 16 waves.
 constexpr bool bwd_three_term(int HT) { return HT <= 13; }
-constexpr int bwd_chain_waves(int HT) { return (HT + 1) / 2; }
+constexpr int bwd_even_tiles(int HT) { return HT + HT % 2; }
+// Waves that carry the recurrence: one per SIMD where sixteen waves leave room for others that form its factors.
+constexpr int bwd_chain_waves(int HT) { return HT <= 10 ? (HT >= 8 ? 4 : 1) : (HT + 1) / 2; }
+constexpr int bwd_factor_waves(int HT) { return HT <= 10 ? HT / 2 : 0; }
 constexpr int bwd_dw_waves(int HT) { return HT / 2; }
 constexpr int bwd_h_row_tiles(int HT) { return (HT + 3) / 4; }
 // unit tiles of x that do not fill a 16-row tile and find room in the last one of h
@@ -76,11 +80,14 @@ constexpr int bwd_merged_tiles(int HT, int KXT)
     return KXT >= 4 && KXT % 4 <= 4 * bwd_h_row_tiles(HT) - HT ? KXT % 4 : 0;
 }
 constexpr int bwd_x_row_tiles(int HT, int KXT) { return bwd_merged_tiles(HT, KXT) ? KXT / 4 : (KXT + 3) / 4; }
-constexpr int bwd_waves(int HT, int KXT) { return bwd_chain_waves(HT) + bwd_dw_waves(HT) + bwd_x_row_tiles(HT, KXT); }
+constexpr int bwd_waves(int HT, int KXT)
+{
+    return bwd_chain_waves(HT) + bwd_dw_waves(HT) + bwd_x_row_tiles(HT, KXT) + bwd_factor_waves(HT);
+}
 // dwords of its A operands: [row tiles of x, then of h][unit tile][part][64][2]
 constexpr int bwd_pack_dwords(int HT, int KXT)
 {
-    return (bwd_x_row_tiles(HT, KXT) + bwd_h_row_tiles(HT)) * 2 * bwd_chain_waves(HT) * 3 * 128;
+    return (bwd_x_row_tiles(HT, KXT) + bwd_h_row_tiles(HT)) * bwd_even_tiles(HT) * 3 * 128;
 }
 
 __device__ __forceinline__ unsigned bf16_pack(float a, float b)     // round to nearest even; a in the low half
@@ -88,7 +95,9 @@ __device__ __forceinline__ unsigned bf16_pack(float a, float b)     // round to 
     bf16x2 v;
     v[0] = (__bf16)a;
     v[1] = (__bf16)b;
-    return __builtin_bit_cast(unsigned, v);
+    unsigned r = __builtin_bit_cast(unsigned, v);
+    asm("" : "+v"(r));      // (keeps the compiler from rounding a second time to get at the low half)
+    return r;
 }
 
 struct Parts { unsigned hi, mid, lo; };      // two bf16 each
