@@ -105,7 +105,10 @@ esrnn_status esrnn_set_categories(esrnn_handle *h, const int32_t *categories);
 
 /* Callers that only evaluate (loss and forecasts of esrnn_forward, no esrnn_backward): with on != 0 the output
  * stage of esrnn_forward skips its reverse pass (Sections 3.4, 3.5 forward only) and esrnn_backward returns
- * ESRNN_ERR_ORDER until it is switched off again.  Off by default.  esrnn_predict never runs that reverse pass. */
+ * ESRNN_ERR_ORDER until it is switched off again.  Off by default.  esrnn_predict never runs that reverse pass.
+ * Neither such a forward pass nor esrnn_predict is bound to leave the gates and cell states of the LSTM layers in the
+ * workspace, and esrnn_predict computes hidden states and outputs only where its forecasts depend on them
+ * (esrnn_workspace_buffer finds them complete after an esrnn_forward that esrnn_backward may follow). */
 esrnn_status esrnn_set_forward_only(esrnn_handle *h, int32_t on);
 
 /* Sizes the caller needs to allocate buffers. */

@@ -64,6 +64,17 @@ __device__ __forceinline__ void buf_store4(buf_rsrc r, unsigned lane_bytes, f32x
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, lane_bytes, 0, kStream ? 2 : 0);
 }
 
+// Which of the residue classes r, r + step, ... below d a forward pass has to compute for a series tile: bit i for class
+// r + i step, the same in every lane (all ones without masks, or where there are more classes than bits).
+constexpr int kNeedWords = 8, kNeedMost = 32 * kNeedWords;
+__device__ __forceinline__ unsigned long long needed_classes(const unsigned *masks, int tile, int r, int step, int d)
+{
+    if (!masks || d > kNeedMost || d > 64 * step) return ~0ull;
+    const int mine = r + (int)(threadIdx.x & 63) * step;
+    const bool want = mine < d && ((masks[(size_t)tile * kNeedWords + (min(mine, d - 1) >> 5)] >> (mine & 31)) & 1);
+    return __ballot(want);
+}
+
 // Workgroup barrier that orders LDS traffic only: global loads and stores in
 // flight are not waited for.
 __device__ __forceinline__ void lds_barrier()

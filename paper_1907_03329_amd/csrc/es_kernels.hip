@@ -3,6 +3,7 @@
 // (forward and adjoint), loss reduction and weight-gradient reduction.
 #include <algorithm>
 #include <mutex>
+#include <numeric>
 #include <type_traits>
 
 #include "device_utils.h"
@@ -24,6 +25,9 @@ struct PrepArgs {
     int32_t *pmax;       // [NB] window positions needed by the longest series of every 16-series tile
     int NB;
     int B, T, I, H;
+    // residue classes that the outputs at the last windows depend on (ForwardMode; null: not wanted)
+    unsigned *need;
+    int L, dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: of the dilations of layers l and l + 1
     int cs_per_window;   // cell-state values per valid window in the cell-state penalty: hidden * blocks
 };
 
@@ -69,16 +73,47 @@ __device__ void prep_body(const PrepArgs &pa)
 }
 
 // Ragged batches (Section 8.1: padding multiplies the iterations of the recursions): every later kernel
-// stops a 16-series tile at the number of window positions its longest series has.  One thread per tile.
+// stops a 16-series tile at the number of window positions its longest series has.  One thread per series, sixteen of a
+// tile next to each other.
 __device__ void pmax_body(const PrepArgs &pa, int first_block, int n_blocks)
 {
-    for (int bt = (blockIdx.x - first_block) * 256 + threadIdx.x; bt < pa.NB; bt += n_blocks * 256) {
-        int best = 0;
-        for (int k = 0; k < kTileN; ++k) {
-            const int b = bt * kTileN + k;
-            if (b < pa.B) best = max(best, clamp_len(pa.lengths[b], pa.T) - pa.I - pa.H + 1);
+    __shared__ unsigned s_masks[2][16][kNeedWords];
+    const int k = threadIdx.x & 15;
+    for (int t0 = ((int)blockIdx.x - first_block) * 16; t0 < pa.NB; t0 += n_blocks * 16) {
+        const int bt = t0 + (threadIdx.x >> 4), b = bt * kTileN + k;
+        const int windows = b < pa.B ? max(clamp_len(pa.lengths[b], pa.T) - pa.I - pa.H + 1, 0) : 0;
+        int best = windows;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
+        if (k == 0 && bt < pa.NB) pa.pmax[bt] = best;
+        if (!pa.need) continue;
+        // Top layer: the classes of the last windows.  Below: a layer is read at the positions of the classes above it,
+        // which fall into every class congruent to one of those modulo the common divisor g of the two dilations.
+        unsigned (*s_need)[16][kNeedWords] = s_masks;                  // [this layer, the one above][tile][word]
+        const int grp = threadIdx.x >> 4;
+        for (int l = pa.L - 1; l >= 0; --l) {
+            const int d = pa.dil[l];
+            unsigned *mine = s_need[l & 1][grp];
+            const unsigned *over = s_need[(l + 1) & 1][grp];
+            __syncthreads();
+            if (k < kNeedWords) mine[k] = 0u;
+            __syncthreads();
+            if (d <= kNeedMost) {
+                const int above = l + 1 < pa.L ? pa.dil[l + 1] : 0, g = pa.gcd_above[l];
+                if (l == pa.L - 1) {
+                    if (windows > 0) atomicOr(&mine[(windows - 1) % d >> 5], 1u << ((windows - 1) % d & 31));
+                } else {
+                    for (int r = k; r < g; r += 16) {
+                        bool any = above > kNeedMost;
+                        for (int q = r; q < above && !any; q += g) any = (over[q >> 5] >> (q & 31)) & 1;
+                        if (any)
+                            for (int q = r; q < d; q += g) atomicOr(&mine[q >> 5], 1u << (q & 31));
+                    }
+                }
+            }
+            __syncthreads();
+            if (k < kNeedWords && bt < pa.NB) pa.need[((size_t)l * pa.NB + bt) * kNeedWords + k] = mine[k];
         }
-        pa.pmax[bt] = best;
     }
 }
 
@@ -1182,16 +1217,27 @@ hipError_t allow_large_lds(const void *kernel, size_t lds)
 }
 }  // namespace
 
-hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, hipStream_t st)
+hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode,
+                        hipStream_t st)
 {
     SetupArgs a{};
     a.L = pl.L;
     a.pack = weights != nullptr;
-    a.prep = PrepArgs{lengths, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
-                      pl.B, pl.T, pl.I, pl.H, pl.h * pl.cfg.n_blocks};
+    a.prep.lengths = lengths;
+    a.prep.sc = reinterpret_cast<Scalars *>(ws + pl.scalars);
+    a.prep.pmax = reinterpret_cast<int32_t *>(ws + pl.pmax);
+    a.prep.NB = pl.NB;
+    a.prep.B = pl.B; a.prep.T = pl.T; a.prep.I = pl.I; a.prep.H = pl.H;
+    a.prep.cs_per_window = pl.h * pl.cfg.n_blocks;
+    a.prep.need = mode.need;
+    a.prep.L = pl.L;
+    for (int l = 0; l < pl.L; ++l) {
+        a.prep.dil[l] = pl.layer[l].dil;
+        a.prep.gcd_above[l] = l + 1 < pl.L ? std::gcd(pl.layer[l].dil, pl.layer[l + 1].dil) : 0;
+    }
     if (!a.pack) {
         // block 0 counts the loss normalisers, the others find the position bound of every tile
-        setup_kernel<<<dim3(1 + std::min((pl.NB + 255) / 256, 63), 1, 1), 256, 0, st>>>(a);
+        setup_kernel<<<dim3(1 + std::min((pl.NB + 15) / 16, 63), 1, 1), 256, 0, st>>>(a);
         return hipGetLastError();
     }
     int max_total = 256;

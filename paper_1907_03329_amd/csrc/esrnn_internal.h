@@ -120,22 +120,33 @@ hipError_t launch_probe_issue_overlap(int mode, int iterations, int per_cu, floa
 esrnn_status build_plan(const esrnn_config &cfg, Plan &pl);
 
 // ---- kernel launchers (each returns hipGetLastError()) -----------------------------------
-hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, hipStream_t st);
+// What a forward pass is for.  `stash`: a reverse pass may follow, so gates and cell states are written.  `need` (null:
+// everything): only the outputs at the last window of every series are wanted; [L][NB][8] bit masks of the residue classes
+// of every layer and series tile that those outputs depend on, by setup.
+struct ForwardMode {
+    bool stash;
+    unsigned *need;
+};
+hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode,
+                        hipStream_t st);
 hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *lengths, const float *es,
                              float *ws, hipStream_t st);
 hipError_t launch_window_forward(const Plan &pl, const int32_t *categories, float *ws, hipStream_t st);
 hipError_t launch_lstm_forward(const Plan &pl, int layer, const int32_t *lengths, const float *weights, float *ws,
-                               hipStream_t st);
-hipError_t launch_lstm_forward_residual(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
+                               const ForwardMode &mode, hipStream_t st);
+hipError_t launch_lstm_forward_residual(const Plan &pl, int layer, const int32_t *lengths, float *ws, const ForwardMode &mode,
+                                        hipStream_t st);
 // 4-series kernels for layers with few workgroups (called by the two launchers above and below)
 hipError_t launch_lstm_forward_narrow(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
-                                      float *ws, hipStream_t st);
+                                      float *ws, const ForwardMode &mode, hipStream_t st);
 hipError_t launch_lstm_forward_narrow_residual(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
-                                      float *ws, hipStream_t st);
+                                      float *ws, const ForwardMode &mode, hipStream_t st);
 hipError_t launch_lstm_backward_narrow(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
 hipError_t launch_lstm_backward_narrow_split(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
 // output stage, forward and reverse in one launch (needs the loss normalisers of launch_setup)
 hipError_t launch_head(const Plan &pl, const int32_t *lengths, float *ws, bool reverse, hipStream_t st);
+// output stage at the last window of every series only, forward
+hipError_t launch_head_last(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st);
 hipError_t launch_forecasts(const Plan &pl, const int32_t *lengths, float *ws, float *forecasts, hipStream_t st);
 hipError_t launch_loss_finalize(const Plan &pl, float *ws, float *loss, hipStream_t st);
 

@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
             const int q = 4 * nb + e;
             v[e] = q < KXT || (q < KT && has_prev) ? xraw[set][e] : 0.0f;
         }
-        const Parts p0 = split_pair(v[0], v[1]), p1 = split_pair(v[2], v[3]);
+        const Parts p0 = split_pair<true>(v[0], v[1]), p1 = split_pair<true>(v[2], v[3]);
         char *dst = xh_lds[buf] + nb * 3 * kPartBytes + own;
         *reinterpret_cast<u32x2 *>(dst) = u32x2{p0.hi, p1.hi};
         *reinterpret_cast<u32x2 *>(dst + kPartBytes) = u32x2{p0.mid, p1.mid};
@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                     for (int r = 0; r < 3; ++r) da[j][r] = dc * f[j][0][r];
                     da[j][3] = dh * f[j][0][3];
                     dcreg[j] = dc * f[j][1][2];
-                    const Parts p0 = split_pair(da[j][0], da[j][1]), p1 = split_pair(da[j][2], da[j][3]);
+                    const Parts p0 = split_pair<true>(da[j][0], da[j][1]), p1 = split_pair<true>(da[j][2], da[j][3]);
 #pragma unroll
                     for (int q = 0; q < 3; ++q) { parts[j][q][0] = part_of(p0, q); parts[j][q][1] = part_of(p1, q); }
 #pragma unroll
@@ -374,7 +374,7 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                     b[q] = u32x4{parts[0][q][0], parts[0][q][1], NP > 1 ? parts[NP - 1][q][0] : 0u, NP > 1 ? parts[NP - 1][q][1] : 0u};
                 auto pairs = [&](auto from, auto to) {
                     static_for<decltype(from)::value, decltype(to)::value>([&](auto ic) {
-                        constexpr TtPair t = tt_mfma(4, decltype(ic)::value);
+                        constexpr TtPair t = tt_group_rising(decltype(ic)::value);
 #pragma unroll
                         for (int mb = 0; mb < RH; ++mb) acc[mb] = mfma_bf16(w[mb][t.a], b[t.b], acc[mb]);
                     });
@@ -609,7 +609,7 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                     else if constexpr (t + 1 < NT) read_pair(t + 1);
                     static_for<0, 6>([&](auto ic) {
                         constexpr int i = decltype(ic)::value;
-                        constexpr TtPair m = tt_mfma(4, i);
+                        constexpr TtPair m = tt_group_rising(i);
                         constexpr int size = i < 2 ? 0 : i < 5 ? 1 : 2;   // hi lo, lo hi; mid mid, hi mid, mid hi; hi hi
                         acc[size] = mfma_bf16(w[t][m.a], b[t & 1][m.b], acc[size]);
                     });

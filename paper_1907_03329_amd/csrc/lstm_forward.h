@@ -48,6 +48,8 @@ struct LstmFwdArgs {
     const int32_t *lengths;
     float *cs_partial;    // [NB * gridDim.y] sums of squared cell states over valid window positions
     int B, T, I, H;
+    int stash;            // 0: no reverse pass follows, gates and cell states stay on chip
+    const unsigned *need; // [NB][kNeedWords] residue classes to compute (null: all)
 };
 
 // LDS home of the three parts of a 4-row operand tile, [quad][dword][lane] with two bf16 per dword.  SEG: the tiles
@@ -84,8 +86,10 @@ struct TileHome {
 constexpr int fwd_waves(int HT) { return HT <= 10 ? 8 : HT; }
 
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the block
-// input, writes the block output).
-template <int HT, int KXT, bool CP, bool OUT>
+// input, writes the block output); STASH: a reverse pass may follow - without it gates and cell states stay on chip, and
+// only the residue classes that are asked for are computed.  (An instantiation of its own: a switch at run time cost the
+// layers of a training step 3 us each.)
+template <int HT, int KXT, bool CP, bool OUT, bool STASH>
 __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(LstmFwdArgs a)
 {
     constexpr int W = fwd_waves(HT);
@@ -100,6 +104,11 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, known to be uniform
     const int sx = W - 1 - s;                                        // first input tile of this wave
     const int Pt = a.pmax[bt];      // positions past the tile's longest series are never computed (nor read later)
+    unsigned long long need = ~0ull;
+    if constexpr (!STASH) {
+        need = needed_classes(a.need, bt, blockIdx.y, gridDim.y, a.d);
+        if (need == 0) return;                                       // (before any barrier)
+    }
 
     u32x4 wx[MTW][AX], wh[MTW][AH];
     f32x4 bias[MTW];
@@ -179,6 +188,11 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
         };
 
         for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y) {
+            if constexpr (!STASH) {
+                const bool want = need & 1;
+                need = need >> 1 | 1ull << 63;
+                if (!want) continue;
+            }
             // start of a chain: zero state, input part of the first position, parts of the second input in LDS
             float creg[MTW], xv[XTW], x1[XTW];
 #pragma unroll
@@ -227,8 +241,10 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
                     if constexpr (CP) csq += p < n_valid ? cn * cn : 0.0f;
                     TileHome<NPH, SH + j>::store(h_lds[par ^ 1], h_at[j], hn);
                     // gates and cell state are read again only by the reverse pass: streaming stores
-                    buf_store4<true>(make_rsrc(a.gates + (pb * HT + mt) * 256), lane16, f32x4{gi, gf, gg, go});
-                    buf_store<true>(r_c, lane4, mt * 256, cn);
+                    if constexpr (STASH) {
+                        buf_store4<true>(make_rsrc(a.gates + (pb * HT + mt) * 256), lane16, f32x4{gi, gf, gg, go});
+                        buf_store<true>(r_c, lane4, mt * 256, cn);
+                    }
                     buf_store(r_hid, lane4, mt * 256, hn);
                     if constexpr (OUT) buf_store(make_rsrc(a.out + pb * HT * 64), lane4, mt * 256, res[j] + hn);
                 });
@@ -272,19 +288,22 @@ template <int HT, int KXT, bool OUT>
 hipError_t run_fwd(const LstmFwdArgs &a, int chains, hipStream_t st)
 {
     const dim3 grid(a.NB, chains);
-    if (a.cs_partial) lstm_forward_kernel<HT, KXT, true, OUT><<<grid, 64 * fwd_waves(HT), 0, st>>>(a);
-    else lstm_forward_kernel<HT, KXT, false, OUT><<<grid, 64 * fwd_waves(HT), 0, st>>>(a);
+    // (with the cell-state penalty there is only the general kernel: it writes the stash and computes every class)
+    if (a.cs_partial) lstm_forward_kernel<HT, KXT, true, OUT, true><<<grid, 64 * fwd_waves(HT), 0, st>>>(a);
+    else if (a.stash) lstm_forward_kernel<HT, KXT, false, OUT, true><<<grid, 64 * fwd_waves(HT), 0, st>>>(a);
+    else lstm_forward_kernel<HT, KXT, false, OUT, false><<<grid, 64 * fwd_waves(HT), 0, st>>>(a);
     return hipGetLastError();
 }
 
-inline LstmFwdArgs forward_args(const Plan &pl, int layer, const int32_t *lengths, float *ws)
+inline LstmFwdArgs forward_args(const Plan &pl, int layer, const int32_t *lengths, float *ws, const ForwardMode &mode)
 {
     const LayerPlan &lp = pl.layer[layer];
     const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
     return LstmFwdArgs{reinterpret_cast<const u32x4 *>(ws + lp.wpack_fwd), ws + lp.bias_pack, ws + lp.xsrc, ws + lp.gates,
                        ws + lp.c, ws + lp.hid, lp.out ? ws + lp.resid : nullptr, lp.out ? ws + lp.out : nullptr, pl.P, pl.NB,
                        lp.dil, reinterpret_cast<const int32_t *>(ws + pl.pmax), lengths, cp ? ws + lp.cs_partial : nullptr,
-                       pl.B, pl.T, pl.I, pl.H};
+                       pl.B, pl.T, pl.I, pl.H, mode.stash ? 1 : 0,
+                       mode.need ? mode.need + (size_t)layer * pl.NB * kNeedWords : nullptr};
 }
 
 }  // namespace

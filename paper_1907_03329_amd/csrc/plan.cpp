@@ -26,13 +26,13 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // Layers whose 16-series grid has fewer workgroups than this run on the 4-series kernels, separately for the two
 // directions.  A workgroup of the forward kernel needs 0.60 us a position at hidden 40 and 16 series, 0.49 us at 4,
 // and with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each: 64
-// workgroups (1024 series of the quarterly shape, first layer) take 40 us against 35 us, 128 (hourly shape, second
-// layer) 131 us against 175 us.
+// workgroups (1024 series of the quarterly shape, first layer) take 40 us against 35 us, 72 47 us against 51 us, 80 48 us
+// against 53 us, 128 (hourly shape, second layer) 131 us against 175 us.
 // In reverse the 16-series kernel needs 0.96 us a position at hidden 40 and one workgroup per compute unit, the
 // 4-series one 0.75 us with one workgroup per compute unit and 1.05 us with two: 64 groups (1024 series of the
 // quarterly shape, first layer) take 59 us against 53 us, 80 groups 58 us against 73 us, 128 (hourly shape, second
 // layer) 195 us against 288 us.
-constexpr int kNarrowForwardBelow = 96, kNarrowBackwardBelow = 65;
+constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
 // 16384 tiles, streaming 0.053 / 0.079 / 0.25 ms; a wave of the streaming kernel is a chain of dependent memory

@@ -56,11 +56,10 @@ constexpr TtPair tt_mfma(int np, int i)
     const int full = tt_full(np);
     if (i < 6 * full) {
         const int g = 3 * (i / 6), k = i % 6;
-        const int a[6] = {0, 2, 1, 0, 1, 0}, b[6] = {2, 0, 1, 1, 0, 0};    // smallest first: fewer roundings of the large sum
+        const int a[6] = {0, 1, 0, 1, 2, 0}, b[6] = {0, 0, 1, 1, 0, 2};
         return {g + a[k], g + b[k]};
     }
     i -= 6 * full;
-    i = tt_rest(np) - i;
     if (tt_rest(np) == 1) return {3 * full + i, 3 * full};
     return {3 * full + i, 3 * full + (i == 2 ? 1 : 0)};
 }
@@ -90,27 +89,38 @@ constexpr int bwd_pack_dwords(int HT, int KXT)
     return (bwd_x_row_tiles(HT, KXT) + bwd_h_row_tiles(HT)) * bwd_even_tiles(HT) * 3 * 128;
 }
 
-__device__ __forceinline__ unsigned bf16_pack(float a, float b)     // round to nearest even; a in the low half
+// quads of instruction i of one full group, smallest terms first: fewer roundings of the large sum
+constexpr TtPair tt_group_rising(int i)
+{
+    const int a[6] = {0, 2, 1, 0, 1, 0}, b[6] = {2, 0, 1, 1, 0, 0};
+    return {a[i], b[i]};
+}
+
+// Round to nearest even; a in the low half.  kOnce keeps the compiler from rounding a second time to get at the low half:
+// two instructions fewer a pair, but a fixed order (the reverse kernel gains 3 %, the forward kernel loses as much).
+template <bool kOnce = false>
+__device__ __forceinline__ unsigned bf16_pack(float a, float b)
 {
     bf16x2 v;
     v[0] = (__bf16)a;
     v[1] = (__bf16)b;
     unsigned r = __builtin_bit_cast(unsigned, v);
-    asm("" : "+v"(r));      // (keeps the compiler from rounding a second time to get at the low half)
+    if constexpr (kOnce) asm("" : "+v"(r));
     return r;
 }
 
 struct Parts { unsigned hi, mid, lo; };      // two bf16 each
 
+template <bool kOnce = false>
 __device__ __forceinline__ Parts split_pair(float a, float b)
 {
 #pragma clang fp contract(off)      // (the differences below are of the rounded a and b, not of what they were formed from)
     Parts p;
-    p.hi = bf16_pack(a, b);
+    p.hi = bf16_pack<kOnce>(a, b);
     const float a1 = a - __builtin_bit_cast(float, p.hi << 16), b1 = b - __builtin_bit_cast(float, p.hi & 0xffff0000u);
-    p.mid = bf16_pack(a1, b1);
+    p.mid = bf16_pack<kOnce>(a1, b1);
     const float a2 = a1 - __builtin_bit_cast(float, p.mid << 16), b2 = b1 - __builtin_bit_cast(float, p.mid & 0xffff0000u);
-    p.lo = bf16_pack(a2, b2);
+    p.lo = bf16_pack<kOnce>(a2, b2);
     return p;
 }
 

@@ -52,6 +52,19 @@ def test_predict_shapes_of_the_workloads(name):
     run_case(cfg, seed=31)
 
 
+# Only the residue classes that the last windows depend on are computed: dilations with and without a common divisor, in
+# both orders, more classes than windows, more than 32 and 64 (words of a mask, classes a workgroup walks), at and past the
+# 256 a mask holds; on either kind of LSTM kernel.
+@pytest.mark.parametrize("blocks", [((1, 2), (4, 8)), ((2, 3), (5, 7)), ((8, 4), (6, 1)), ((3,), (9,), (6, 40)),
+                                    ((1, 90), (7, 70)), ((2, 256), (3,)), ((5, 257), (64,))])
+@pytest.mark.parametrize("narrow", ["0", "100000"])
+def test_predict_with_any_dilations(blocks, narrow, monkeypatch):
+    monkeypatch.setenv("ESRNN_NARROW_BELOW", narrow)
+    cfg = CONFIGS["tiny_quarterly"].with_(B=35, T=300, hidden=33, blocks=blocks)
+    run_case(cfg, seed=37)
+    run_case(cfg.with_(T=90), seed=38, ragged=False)
+
+
 def test_predict_horizon_longer_than_the_period_and_logit_space():
     cfg = CONFIGS["tiny_quarterly"].with_(B=21, H=11, T=60, param_space=1)
     inp = synth.make_inputs(cfg.with_(param_space=0), seed=5)
