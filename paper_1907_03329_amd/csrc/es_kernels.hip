@@ -25,9 +25,6 @@ struct PrepArgs {
     int32_t *pmax;       // [NB] window positions needed by the longest series of every 16-series tile
     int NB;
     int B, T, I, H;
-    // residue classes that the outputs at the last windows depend on (ForwardMode; null: not wanted)
-    unsigned *need;
-    int L, dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: of the dilations of layers l and l + 1
     int cs_per_window;   // cell-state values per valid window in the cell-state penalty: hidden * blocks
 };
 
@@ -73,47 +70,16 @@ __device__ void prep_body(const PrepArgs &pa)
 }
 
 // Ragged batches (Section 8.1: padding multiplies the iterations of the recursions): every later kernel
-// stops a 16-series tile at the number of window positions its longest series has.  One thread per series, sixteen of a
-// tile next to each other.
+// stops a 16-series tile at the number of window positions its longest series has.  One thread per tile.
 __device__ void pmax_body(const PrepArgs &pa, int first_block, int n_blocks)
 {
-    __shared__ unsigned s_masks[2][16][kNeedWords];
-    const int k = threadIdx.x & 15;
-    for (int t0 = ((int)blockIdx.x - first_block) * 16; t0 < pa.NB; t0 += n_blocks * 16) {
-        const int bt = t0 + (threadIdx.x >> 4), b = bt * kTileN + k;
-        const int windows = b < pa.B ? max(clamp_len(pa.lengths[b], pa.T) - pa.I - pa.H + 1, 0) : 0;
-        int best = windows;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
-        if (k == 0 && bt < pa.NB) pa.pmax[bt] = best;
-        if (!pa.need) continue;
-        // Top layer: the classes of the last windows.  Below: a layer is read at the positions of the classes above it,
-        // which fall into every class congruent to one of those modulo the common divisor g of the two dilations.
-        unsigned (*s_need)[16][kNeedWords] = s_masks;                  // [this layer, the one above][tile][word]
-        const int grp = threadIdx.x >> 4;
-        for (int l = pa.L - 1; l >= 0; --l) {
-            const int d = pa.dil[l];
-            unsigned *mine = s_need[l & 1][grp];
-            const unsigned *over = s_need[(l + 1) & 1][grp];
-            __syncthreads();
-            if (k < kNeedWords) mine[k] = 0u;
-            __syncthreads();
-            if (d <= kNeedMost) {
-                const int above = l + 1 < pa.L ? pa.dil[l + 1] : 0, g = pa.gcd_above[l];
-                if (l == pa.L - 1) {
-                    if (windows > 0) atomicOr(&mine[(windows - 1) % d >> 5], 1u << ((windows - 1) % d & 31));
-                } else {
-                    for (int r = k; r < g; r += 16) {
-                        bool any = above > kNeedMost;
-                        for (int q = r; q < above && !any; q += g) any = (over[q >> 5] >> (q & 31)) & 1;
-                        if (any)
-                            for (int q = r; q < d; q += g) atomicOr(&mine[q >> 5], 1u << (q & 31));
-                    }
-                }
-            }
-            __syncthreads();
-            if (k < kNeedWords && bt < pa.NB) pa.need[((size_t)l * pa.NB + bt) * kNeedWords + k] = mine[k];
+    for (int bt = (blockIdx.x - first_block) * 256 + threadIdx.x; bt < pa.NB; bt += n_blocks * 256) {
+        int best = 0;
+        for (int k = 0; k < kTileN; ++k) {
+            const int b = bt * kTileN + k;
+            if (b < pa.B) best = max(best, clamp_len(pa.lengths[b], pa.T) - pa.I - pa.H + 1);
         }
+        pa.pmax[bt] = best;
     }
 }
 
@@ -1217,27 +1183,16 @@ hipError_t allow_large_lds(const void *kernel, size_t lds)
 }
 }  // namespace
 
-hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode,
-                        hipStream_t st)
+hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, hipStream_t st)
 {
     SetupArgs a{};
     a.L = pl.L;
     a.pack = weights != nullptr;
-    a.prep.lengths = lengths;
-    a.prep.sc = reinterpret_cast<Scalars *>(ws + pl.scalars);
-    a.prep.pmax = reinterpret_cast<int32_t *>(ws + pl.pmax);
-    a.prep.NB = pl.NB;
-    a.prep.B = pl.B; a.prep.T = pl.T; a.prep.I = pl.I; a.prep.H = pl.H;
-    a.prep.cs_per_window = pl.h * pl.cfg.n_blocks;
-    a.prep.need = mode.need;
-    a.prep.L = pl.L;
-    for (int l = 0; l < pl.L; ++l) {
-        a.prep.dil[l] = pl.layer[l].dil;
-        a.prep.gcd_above[l] = l + 1 < pl.L ? std::gcd(pl.layer[l].dil, pl.layer[l + 1].dil) : 0;
-    }
+    a.prep = PrepArgs{lengths, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
+                      pl.B, pl.T, pl.I, pl.H, pl.h * pl.cfg.n_blocks};
     if (!a.pack) {
         // block 0 counts the loss normalisers, the others find the position bound of every tile
-        setup_kernel<<<dim3(1 + std::min((pl.NB + 15) / 16, 63), 1, 1), 256, 0, st>>>(a);
+        setup_kernel<<<dim3(1 + std::min((pl.NB + 255) / 256, 63), 1, 1), 256, 0, st>>>(a);
         return hipGetLastError();
     }
     int max_total = 256;
@@ -1356,13 +1311,49 @@ hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *len
 // series and never reach the forecast), and the network is causal in the window
 // position, so its output there is the out-of-sample output.
 // ---------------------------------------------------------------------------
+//
+// The same kernel finds what those outputs depend on: per 16-series tile and layer, the residue classes of the dilation
+// that the forward kernels have to walk (ForwardMode::need).  Top layer: the classes of the last windows.  Below: a layer is
+// read at the positions of the classes above it, which fall into every class congruent to one of those modulo the common
+// divisor g of the two dilations.  One thread per series, sixteen of a tile next to each other.
+struct ClassArgs {
+    unsigned *need;      // [L][NB][kNeedWords]; null: not wanted
+    int L, NB;
+    int dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: of the dilations of layers l and l + 1
+};
 __global__ void __launch_bounds__(256) extend_lengths_kernel(const int32_t *__restrict__ lengths, int32_t *__restrict__ ext,
-                                                              int B, int T, int I, int H)
+                                                              int B, int T, int I, int H, ClassArgs a)
 {
+    __shared__ unsigned s_masks[2][16][kNeedWords];    // [this layer, the one above][tile][word]
     const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= B) return;
-    const int len = lengths[b];
-    ext[b] = (len >= I && len <= T - H) ? len + H : 0;   // 0: the series takes no part
+    const int len = b < B ? lengths[b] : 0;
+    const bool takes_part = len >= I && len <= T - H;   // (a series that does not gets length 0)
+    if (b < B) ext[b] = takes_part ? len + H : 0;
+    if (!a.need) return;
+    const int grp = threadIdx.x >> 4, k = threadIdx.x & 15, bt = b >> 4;
+    for (int l = a.L - 1; l >= 0; --l) {
+        const int d = a.dil[l];
+        unsigned *mine = s_masks[l & 1][grp];
+        const unsigned *over = s_masks[(l + 1) & 1][grp];
+        __syncthreads();
+        if (k < kNeedWords) mine[k] = 0u;
+        __syncthreads();
+        if (d <= kNeedMost) {                           // (more classes than bits: the mask is not read)
+            if (l == a.L - 1) {
+                if (b < B && takes_part) atomicOr(&mine[(len - I) % d >> 5], 1u << ((len - I) % d & 31));
+            } else {
+                const int above = a.dil[l + 1], g = a.gcd_above[l];
+                for (int r = k; r < g; r += 16) {
+                    bool any = above > kNeedMost;
+                    for (int q = r; q < above && !any; q += g) any = (over[q >> 5] >> (q & 31)) & 1;
+                    if (any)
+                        for (int q = r; q < d; q += g) atomicOr(&mine[q >> 5], 1u << (q & 31));
+                }
+            }
+        }
+        __syncthreads();
+        if (k < kNeedWords && bt < a.NB) a.need[((size_t)l * a.NB + bt) * kNeedWords + k] = mine[k];
+    }
 }
 
 // forecast[b][h-1] = exp(output_h + ln l_t) * S1[t + ((h-1) mod m1) + 1] * S2[...], t = len-1: the last m
@@ -1413,10 +1404,18 @@ __global__ void __launch_bounds__(256) forecast_metrics_kernel(const float *__re
     mase[b] = (s_abs / (float)H) / (s_naive / (float)(len - m));
 }
 
-hipError_t launch_extend_lengths(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st)
+hipError_t launch_extend_lengths(const Plan &pl, const int32_t *lengths, float *ws, const ForwardMode &mode, hipStream_t st)
 {
-    extend_lengths_kernel<<<(pl.B + 255) / 256, 256, 0, st>>>(lengths, reinterpret_cast<int32_t *>(ws + pl.len_ext),
-                                                               pl.B, pl.T, pl.I, pl.H);
+    ClassArgs a{};
+    a.need = mode.need;
+    a.L = pl.L;
+    a.NB = pl.NB;
+    for (int l = 0; l < pl.L; ++l) {
+        a.dil[l] = pl.layer[l].dil;
+        a.gcd_above[l] = l + 1 < pl.L ? std::gcd(pl.layer[l].dil, pl.layer[l + 1].dil) : 0;
+    }
+    extend_lengths_kernel<<<(pl.B + 255) / 256, 256, 0, st>>>(lengths, reinterpret_cast<int32_t *>(ws + pl.len_ext), pl.B,
+                                                              pl.T, pl.I, pl.H, a);
     return hipGetLastError();
 }
 

@@ -181,7 +181,7 @@ esrnn_status esrnn_forward(esrnn_handle *h, const float *y, const int32_t *lengt
     hipStream_t st = static_cast<hipStream_t>(stream);
     h->forward_done = false;
     const ForwardMode mode{!h->forward_only, nullptr};
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, weights, ws, mode, st); }));
+    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, weights, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     for (int l = 0; l < pl.L; ++l)
@@ -280,8 +280,8 @@ esrnn_status esrnn_predict(esrnn_handle *h, const float *y, const int32_t *lengt
     // (8 words a layer and tile) lie where a reverse pass would leave the gradient of the windows.
     const bool room = (size_t)pl.L * 8 <= (size_t)pl.P * pl.IT * 64;
     const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.gX) : nullptr};
-    ESRNN_TRY(launch_extend_lengths(pl, lengths, ws, st));
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, ext, weights, ws, mode, st); }));
+    ESRNN_TRY(launch_extend_lengths(pl, lengths, ws, mode, st));
+    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, ext, weights, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, ext, es_params, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     for (int l = 0; l < pl.L; ++l)
@@ -329,7 +329,7 @@ esrnn_status esrnn_es_window_forward(esrnn_handle *h, const float *y, const int3
     const Plan &pl = h->plan;
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, nullptr, ws, ForwardMode{true, nullptr}, st); }));
+    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, nullptr, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     return ESRNN_OK;

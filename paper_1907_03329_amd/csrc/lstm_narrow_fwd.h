@@ -22,7 +22,6 @@ struct NarrowFwdArgs {
     const int32_t *lengths;
     float *cs_partial;    // [4*NB * gridDim.y] (cell-state penalty, CP instantiations only)
     int B, T, I, H;
-    const unsigned *need; // [NB][kNeedWords] residue classes to compute (null: all)
 };
 
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
@@ -51,8 +50,6 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
     // All four workgroups of a 16-series tile stop at the tile's longest series: what lies beyond is
     // neither computed here nor read by any later kernel.
     const int Pt = a.pmax[bt];
-    unsigned long long need = needed_classes(a.need, bt, blockIdx.y, gridDim.y, a.d);
-    if (need == 0) return;                                           // (before any barrier)
     const bool valid = blk < HT;
     const int unit = w * HT + min(blk, HT - 1);     // blocks past HT repeat the last unit
 
@@ -82,8 +79,7 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
     for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += kNT) (&xc[0][0][0])[e] = 0.0f;
     for (int e = threadIdx.x; e < 2 * HG * 64; e += kNT) (&hb[0][0])[e] = 0.0f;
 
-    for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y, need = need >> 1 | 1ull << 63) {
-        if (!(need & 1)) continue;
+    for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y) {
         const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
         float xs[CH], rs[CH];
         auto load_chunk = [&](int c) {
@@ -191,14 +187,13 @@ hipError_t run_nfwd(const NarrowFwdArgs &a, int chains, hipStream_t st)
 
 template <bool OUT>
 hipError_t launch_narrow_fwd(const Plan &pl, int layer, const int32_t *lengths, const float *weights, float *ws,
-                             const ForwardMode &mode, hipStream_t st)
+                             hipStream_t st)
 {
     const LayerPlan &lp = pl.layer[layer];
     const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
     NarrowFwdArgs a{ws + lp.wpack_fwd, weights + lp.b_off, ws + lp.xsrc, ws + lp.gates, ws + lp.c, ws + lp.hid,
                     lp.out ? ws + lp.resid : nullptr, lp.out ? ws + lp.out : nullptr, pl.P, pl.NB, lp.dil, pl.h,
-                    reinterpret_cast<const int32_t *>(ws + pl.pmax), lengths, cp ? ws + lp.cs_partial : nullptr, pl.B, pl.T, pl.I, pl.H,
-                    mode.need ? mode.need + (size_t)layer * pl.NB * kNeedWords : nullptr};
+                    reinterpret_cast<const int32_t *>(ws + pl.pmax), lengths, cp ? ws + lp.cs_partial : nullptr, pl.B, pl.T, pl.I, pl.H};
 #define X(HT_, KXT_) if (pl.HT == HT_ && lp.KXT == KXT_) return run_nfwd<HT_, KXT_, OUT>(a, lp.chains, st);
     ESRNN_LSTM_SHAPES(X)
 #undef X

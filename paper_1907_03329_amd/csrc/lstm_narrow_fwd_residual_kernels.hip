@@ -5,9 +5,9 @@
 namespace esrnn {
 
 hipError_t launch_lstm_forward_narrow_residual(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
-                                               float *ws, const ForwardMode &mode, hipStream_t st)
+                                               float *ws, hipStream_t st)
 {
-    return launch_narrow_fwd<true>(pl, layer, lengths, weights, ws, mode, st);
+    return launch_narrow_fwd<true>(pl, layer, lengths, weights, ws, st);
 }
 
 }  // namespace esrnn

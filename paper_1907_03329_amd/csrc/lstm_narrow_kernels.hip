@@ -4,10 +4,10 @@
 namespace esrnn {
 
 hipError_t launch_lstm_forward_narrow(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
-                                      float *ws, const ForwardMode &mode, hipStream_t st)
+                                      float *ws, hipStream_t st)
 {
-    if (pl.layer[layer].out) return launch_lstm_forward_narrow_residual(pl, layer, lengths, weights, ws, mode, st);
-    return launch_narrow_fwd<false>(pl, layer, lengths, weights, ws, mode, st);
+    if (pl.layer[layer].out) return launch_lstm_forward_narrow_residual(pl, layer, lengths, weights, ws, st);
+    return launch_narrow_fwd<false>(pl, layer, lengths, weights, ws, st);
 }
 
 }  // namespace esrnn
