@@ -34,15 +34,15 @@ MEASURED_TRAFFIC_BYTES = {
         "window_backward": 1.3e+05, "es_backward": 9e+04,
     },
     ('quarterly', 4096): {
-        "es_forward": 6.3e+06, "window_forward": 1.421e+07, "lstm_forward_l0": 2.442e+08, "lstm_forward_l1": 3.076e+08,
-        "lstm_forward_l2": 3.076e+08, "lstm_forward_l3": 3.076e+08, "head_forward_backward": 1.171e+08, "forecasts": 1.818e+07,
-        "lstm_backward_l3": 3.983e+08, "lstm_backward_l2": 3.983e+08, "lstm_backward_l1": 3.983e+08, "lstm_backward_l0": 2.957e+08,
+        "es_forward": 6.3e+06, "window_forward": 1.421e+07, "lstm_forward_l0": 2.446e+08, "lstm_forward_l1": 2.809e+08,
+        "lstm_forward_l2": 2.809e+08, "lstm_forward_l3": 3.693e+08, "head_forward_backward": 1.171e+08, "forecasts": 1.818e+07,
+        "lstm_backward_l3": 3.854e+08, "lstm_backward_l2": 3.854e+08, "lstm_backward_l1": 3.854e+08, "lstm_backward_l0": 2.972e+08,
         "window_backward": 1.56e+07, "es_backward": 6.15e+06,
     },
     ('monthly', 4096): {
-        "es_forward": 2.019e+07, "window_forward": 1.18e+08, "lstm_forward_l0": 1.121e+09, "lstm_forward_l1": 1.385e+09,
-        "lstm_forward_l2": 1.385e+09, "lstm_forward_l3": 1.385e+09, "head_forward_backward": 5.931e+08, "forecasts": 1.317e+08,
-        "lstm_backward_l3": 1.697e+09, "lstm_backward_l2": 1.697e+09, "lstm_backward_l1": 1.697e+09, "lstm_backward_l0": 1.355e+09,
+        "es_forward": 2.019e+07, "window_forward": 1.18e+08, "lstm_forward_l0": 1.121e+09, "lstm_forward_l1": 1.264e+09,
+        "lstm_forward_l2": 1.264e+09, "lstm_forward_l3": 1.639e+09, "head_forward_backward": 5.931e+08, "forecasts": 1.317e+08,
+        "lstm_backward_l3": 1.698e+09, "lstm_backward_l2": 1.698e+09, "lstm_backward_l1": 1.698e+09, "lstm_backward_l0": 1.356e+09,
         "window_backward": 2.069e+08, "es_backward": 2.005e+07,
     },
     ('yearly', 8192): {
