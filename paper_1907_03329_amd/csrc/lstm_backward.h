@@ -13,7 +13,9 @@
 //     the contraction, so that a wave multiplies what it has just computed in registers; the partial results meet in
 //     LDS and every wave sums those of its own units.  They also leave the three parts of da in LDS.
 //   factor waves (hidden sizes up to 40) read the stash and form whatever of A does not depend on the recurrent
-//     gradient, two positions ahead; a chain wave then has a dozen dependent instructions between the barrier and its
+//     gradient, two positions ahead: a chain wave takes the factors of the next position out of one half of their buffer
+//     while those of the one after it go to the other half. Before the loop a barrier of its own stands between the
+//     first taking and the first refilling of the same half. A chain wave then has a dozen dependent instructions between the barrier and its
 //     first product.  At 13 unit tiles the sixteen waves of a workgroup are taken: there seven chain waves of two tiles
 //     do it themselves, one position ahead.
 //   dx waves (one 16-row tile each) do B for the x rows, which nothing in the recurrence waits for, one position
@@ -191,7 +193,10 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
     auto consumer = [&](auto load, int nb, auto &&work) {
         constexpr bool LOAD = decltype(load)::value;
         if (n_steps == 0) return;
-        if constexpr (NF > 0) lds_barrier();               // (the first factors)
+        if constexpr (NF > 0) {                            // (the first factors complete; the first of them taken)
+            lds_barrier();
+            lds_barrier();
+        }
         ChainWalk now = start, ask = start;
         int at[3];                                         // LOAD: the next three positions, the last one ask's
         if constexpr (LOAD) {
@@ -322,6 +327,7 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                     lds_barrier();                         // factors of the first two positions complete
 #pragma unroll
                     for (int j = 0; j < NJ; ++j) { f[j][0] = factor_lds[0][tile_of(j)][0][lane]; f[j][1] = factor_lds[0][tile_of(j)][1][lane]; }
+                    lds_barrier();                         // taken: the factor waves' next position goes to the same half
                 }
             } else if (n_steps > 0) {
                 request_first_c(2 * s, np, ask);
@@ -553,7 +559,8 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
             leave(1, 1, p1);
             advance(1);
             at[2] = walk.p;
-            lds_barrier();
+            lds_barrier();                                 // both complete
+            lds_barrier();                                 // the first one taken by the chain waves
         }
         alternate(n_steps, [&](auto u) {
             constexpr int U = decltype(u)::value;
