@@ -1315,11 +1315,12 @@ hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *len
 // The same kernel finds what those outputs depend on: per 16-series tile and layer, the residue classes of the dilation
 // that the forward kernels have to walk (ForwardMode::need).  Top layer: the classes of the last windows.  Below: a layer is
 // read at the positions of the classes above it, which fall into every class congruent to one of those modulo the common
-// divisor g of the two dilations.  One thread per series, sixteen of a tile next to each other.
+// divisor g of the two dilations.  (Where every position is a class of its own, any multiple of the other dilation stands
+// for this one: g is that other dilation.)  One thread per series, sixteen of a tile next to each other.
 struct ClassArgs {
     unsigned *need;      // [L][NB][kNeedWords]; null: not wanted
     int L, NB;
-    int dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: of the dilations of layers l and l + 1
+    int dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: g of layers l and l + 1
 };
 __global__ void __launch_bounds__(256) extend_lengths_kernel(const int32_t *__restrict__ lengths, int32_t *__restrict__ ext,
                                                               int B, int T, int I, int H, ClassArgs a)
@@ -1411,8 +1412,8 @@ hipError_t launch_extend_lengths(const Plan &pl, const int32_t *lengths, float *
     a.L = pl.L;
     a.NB = pl.NB;
     for (int l = 0; l < pl.L; ++l) {
-        a.dil[l] = pl.layer[l].dil;
-        a.gcd_above[l] = l + 1 < pl.L ? std::gcd(pl.layer[l].dil, pl.layer[l + 1].dil) : 0;
+        const int d = a.dil[l] = pl.layer[l].dil, above = l + 1 < pl.L ? pl.layer[l + 1].dil : 0;
+        a.gcd_above[l] = above == pl.P ? d : d == pl.P ? above : std::gcd(d, above);
     }
     extend_lengths_kernel<<<(pl.B + 255) / 256, 256, 0, st>>>(lengths, reinterpret_cast<int32_t *>(ws + pl.len_ext), pl.B,
                                                               pl.T, pl.I, pl.H, a);

@@ -27,7 +27,8 @@ constexpr int kNarrowSeries = 4; // series per workgroup in the small-batch LSTM
 // A "unit tile" is 4 consecutive rows (64 floats = one float per lane).
 
 struct LayerPlan {
-    int dil, block, first_in_block, last_in_block;
+    int dil;             // dilation, at most P (then every position is a chain of its own)
+    int block, first_in_block, last_in_block;
     int in_dim;          // logical width of the layer input
     int KXT;             // unit tiles of the layer input (x part of the contraction)
     size_t w_off, b_off; // offsets into the caller's flat weight vector

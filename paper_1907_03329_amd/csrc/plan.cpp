@@ -156,8 +156,10 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         if (nl < 1 || nl > ESRNN_MAX_LAYERS_PER_BLOCK) return ESRNN_ERR_CONFIG;
         for (int j = 0; j < nl; ++j) {
             LayerPlan &lp = pl.layer[L];
-            lp.dil = cfg.dilation[k][j];
-            if (lp.dil < 1) return ESRNN_ERR_CONFIG;
+            if (cfg.dilation[k][j] < 1) return ESRNN_ERR_CONFIG;
+            // (a dilation past the last position leaves every position a chain of its own, like one of P; the kernels
+            // form positions a few dilations ahead in 32 bits)
+            lp.dil = std::min(cfg.dilation[k][j], pl.P);
             lp.block = k;
             lp.first_in_block = (j == 0);
             lp.last_in_block = (j == nl - 1);

@@ -56,3 +56,9 @@ def test_waves_of_a_workgroup_are_ordered(program, hidden, window):
     # 40 series: tiles of all positions, half of them, none; chains of several positions and of one
     assert run(program, 40, window + 3 + 6, window, 3, hidden, 0, "all", 1, 4) == (0, "ok")
     assert run(program, 40, window + 3 + 3, window, 3, hidden, 0.1, "all", 2, 1) == (0, "ok")
+
+
+@pytest.mark.parametrize("dilation", [30, 31, 715827883, 1 << 30, (1 << 31) - 1])
+def test_dilations_past_the_last_position_stay_in_the_workspace(program, dilation):
+    # 31 positions: from 31 on every position is a chain of its own
+    assert run(program, 20, 45, 12, 3, 40, 0, "all", dilation, 2, dilation) == (0, "ok")
