@@ -24,15 +24,19 @@ struct Bump {
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Layers whose 16-series grid has fewer workgroups than this run on the 4-series kernels, separately for the two
-// directions.  A workgroup of the forward kernel needs 0.60 us a position at hidden 40 and 16 series, 0.49 us at 4,
-// and with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each: 64
-// workgroups (1024 series of the quarterly shape, first layer) take 40 us against 35 us, 72 47 us against 51 us, 80 48 us
-// against 53 us, 128 (hourly shape, second layer) 131 us against 175 us.
-// In reverse the 16-series kernel needs 0.96 us a position at hidden 40 and one workgroup per compute unit, the
-// 4-series one 0.75 us with one workgroup per compute unit and 1.05 us with two: 64 groups (1024 series of the
-// quarterly shape, first layer) take 59 us against 53 us, 80 groups 58 us against 73 us, 128 (hourly shape, second
-// layer) 195 us against 288 us.
-constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65;
+// directions: with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each.
+// Measured on two layers of the same dilation, 61 positions (window 4) and 151 (window 12), in us (16-series kernel
+// against 4-series kernel, second layer, 61 positions unless stated; at 64 and less the 4-series kernels are the faster
+// ones or level, except at hidden 8 and 30: 9 / 11 and 14 / 16 at 64):
+//   hidden   groups 68 (dilation 2)                72 (dilation 1)                    128 (dilation 1)
+//      8     forward 14 / 21, reverse 18 / 23      21 / 37,  27 / 39                  22 / 39,  28 / 40
+//     30     21 / 35,  32 / 39                     37 / 62,  56 / 70                  38 / 67,  59 / 76
+//     40     29 / 40,  42 / 60                     52 / 71,  76 / 111                 54 / 75,  79 / 118
+//     50     40 / 45,  69 / 99                     73 / 81,  124 / 185                76 / 89,  130 / 200
+//     60     44 / 50,  201 / 118                   80 / 91,  388 / 219                82 / 102, 390 / 238
+// and with 151 positions alike (hidden 50, first layer, 72 groups: 138 / 142, 219 / 222).  Above hidden 52 the reverse
+// pass of 16 series is the fp32 kernel, which loses up to 148 groups (392 / 338 us) and at 160 with dilation 8 wins (59 / 66).
+constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwardBelowFp32 = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
 // 16384 tiles, streaming 0.053 / 0.079 / 0.25 ms; a wave of the streaming kernel is a chain of dependent memory
@@ -94,7 +98,8 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
 {
     std::memset(&pl, 0, sizeof(pl));
     // ESRNN_NARROW_BELOW overrides both thresholds (0: never, a large number: always), for measurements.
-    int narrow_fwd_below = kNarrowForwardBelow, narrow_bwd_below = kNarrowBackwardBelow;
+    int narrow_fwd_below = kNarrowForwardBelow;
+    int narrow_bwd_below = bwd_three_term(pick_ht(cfg.hidden)) ? kNarrowBackwardBelow : kNarrowBackwardBelowFp32;
     if (const char *env = std::getenv("ESRNN_NARROW_BELOW")) narrow_fwd_below = narrow_bwd_below = std::atoi(env);
     // The window adjoint streams tile by tile from this many series tiles on (one wave per tile needs enough
     // tiles to hide memory latency); ESRNN_WINDOW_STREAM_FROM overrides, for measurements.

@@ -82,3 +82,13 @@ def test_mid_size_batch_on_the_four_series_kernels():
     with forced(1 << 30):
         errs = gc.run_and_check(cfg, seed=81, ragged=True, stages=False)
     print(f"  worst {max(v for k, v in errs.items() if k != 'series_at_kink'):.2e}", flush=True)
+
+
+@pytest.mark.parametrize("hidden", [53, 60])
+def test_forward_and_reverse_pass_of_a_layer_on_different_kinds(hidden):
+    """70 and 140 workgroups of 16 series: above hidden 52 the forward pass runs on the 16-series kernel, the reverse
+    pass on the 4-series kernel."""
+    cfg = CONFIGS["quarterly"].with_(B=1113, T=26, hidden=hidden, blocks=((1, 2), (1,)))
+    with forced(None):
+        errs = gc.run_and_check(cfg, seed=82, ragged=True, stages=False)
+    print(f"  hidden {hidden}: worst {max(v for k, v in errs.items() if k != 'series_at_kink'):.2e}", flush=True)

@@ -62,3 +62,22 @@ def test_waves_of_a_workgroup_are_ordered(program, hidden, window):
 def test_dilations_past_the_last_position_stay_in_the_workspace(program, dilation):
     # 31 positions: from 31 on every position is a chain of its own
     assert run(program, 20, 45, 12, 3, 40, 0, "all", dilation, 2, dilation) == (0, "ok")
+
+
+def chosen(program, hidden, series, dilation):
+    """Per layer: 1 where the 4-series kernel was chosen, forward and reverse."""
+    env = {k: v for k, v in os.environ.items() if k != "ESRNN_NARROW_BELOW"}
+    out = subprocess.run([program, "plan", str(series), "60", "4", "3", str(hidden), "0", "all", str(dilation)], env=env,
+                         capture_output=True, text=True, check=True).stdout
+    return [tuple(int(v) for v in re.findall(r"narrow (\d) (\d)", line)[0]) for line in out.splitlines() if line.startswith("layer")]
+
+
+# workgroups of the 16-series grid: series / 16 times the dilation
+@pytest.mark.parametrize("series,dilation", [(16 * 64, 1), (16 * 65, 1), (16 * 32, 4), (16 * 159, 1), (16 * 160, 1), (16 * 40, 4)])
+def test_kernel_kind_follows_the_measured_limits(program, series, dilation):
+    groups = series // 16 * dilation
+    for hidden in (8, 30, 40, 52):
+        assert chosen(program, hidden, series, dilation) == [(int(groups < 65), int(groups < 65))]
+    # the fp32 reverse kernel of the largest hidden sizes is slower than the 4-series one up to 159 workgroups
+    for hidden in (53, 64):
+        assert chosen(program, hidden, series, dilation) == [(int(groups < 65), int(groups < 160))]
