@@ -277,9 +277,9 @@ esrnn_status esrnn_predict(esrnn_handle *h, const float *y, const int32_t *lengt
     h->forward_done = false;    // the workspace now holds the state of the extended problem, not of a training pass
     const int32_t *ext = reinterpret_cast<const int32_t *>(ws + pl.len_ext);
     // Only the outputs at the last windows are wanted: no stash, no residue class that they do not depend on.  The masks
-    // (8 words a layer and tile) lie where a reverse pass would leave the gradient of the windows.
-    const bool room = (size_t)pl.L * 8 <= (size_t)pl.P * pl.IT * 64;
-    const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.gX) : nullptr};
+    // (8 words a layer and tile) lie where the outputs come, which are written once the last layer has read them.
+    const bool room = (size_t)pl.L * 8 <= (size_t)pl.P * pl.OP * 16;
+    const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr};
     ESRNN_TRY(launch_extend_lengths(pl, lengths, ws, mode, st));
     ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, ext, weights, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, ext, es_params, ws, st); }));

@@ -123,3 +123,21 @@ def test_metrics_against_the_plain_definitions():
         np.testing.assert_allclose(sm.cpu().numpy(), oracle.smape(got, actual), rtol=2e-5)
         np.testing.assert_allclose(ms.cpu().numpy(), oracle.mase(got, actual, inp["y"], n, m), rtol=2e-5)
     step.close()
+
+
+@pytest.mark.parametrize("narrow", ["0", "100000"])
+def test_forecasts_leave_the_results_of_the_reverse_pass_alone(narrow, monkeypatch):
+    import torch
+    monkeypatch.setenv("ESRNN_NARROW_BELOW", narrow)
+    cfg = CONFIGS["tiny_quarterly"].with_(B=35)
+    inp = synth.make_inputs(cfg, seed=7)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in inp.items()}
+    step = binding.TrainingStep(cfg)
+    step.forward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+    step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+    names = ("grad_X", "grad_O", "grad_top", "grad_u", "grad_v")
+    before = [step.buffer(n) for n in names]
+    step.predict(dev["y"], torch.full_like(dev["lengths"], cfg.T - cfg.H), dev["es_params"], dev["weights"])
+    for n, t in zip(names, before):
+        assert torch.equal(step.buffer(n), t), n
+    step.close()
