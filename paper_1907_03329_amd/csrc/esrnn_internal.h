@@ -15,13 +15,11 @@ namespace esrnn {
 constexpr int kTileN = 16;       // series per tile (N of the 16x16x4 fp32 MFMA)
 constexpr int kMaxLayers = ESRNN_MAX_BLOCKS * ESRNN_MAX_LAYERS_PER_BLOCK;
 constexpr int kLstmWaves = 4;    // waves per workgroup in the LSTM kernels
-constexpr int kSinkLines = 256;  // 256-byte lines of the store sink
 constexpr int kReduceSplits = 16; // subsets of producers in the first stage of the weight-gradient reduction
 // Row stride of the LDS arrays [row][16 series] that are read transposed (lane = row n, column 4k + g).  With 18
 // the 32 lanes of a half wave (16 rows x 2 columns) hit 32 different banks: (18 n + g) mod 32 takes every value
 // once.  (17, the usual odd padding, leaves one two-way conflict in every such read.)
 constexpr int kLdsPad = 18;
-constexpr int kNarrowSeries = 4; // series per workgroup in the small-batch LSTM kernels
 
 // Tile layout TL(R): [P][NB][R][16]; element (p, b, r) at ((p*NB + b/16)*R + r)*16 + b%16.
 // A "unit tile" is 4 consecutive rows (64 floats = one float per lane).
@@ -76,7 +74,6 @@ struct Plan {
     size_t Wa_off, ba_off, Wo_off, bo_off, n_weights;
     // workspace map (offsets in floats)
     size_t scalars;      // float[16]: see Scalars
-    size_t sink;         // float[kSinkLines][64]: target of stores whose value nothing reads (a workgroup uses line id % kSinkLines)
     size_t len_ext;      // int32[B]: lengths extended by the horizon (out-of-sample forecasts)
     size_t pmax;         // int32[NB]: window positions the series of a 16-series tile need (max over the tile), by setup
     size_t opt_partial;  // float[512]: sums of squares of the gradients, per workgroup (parameter update)

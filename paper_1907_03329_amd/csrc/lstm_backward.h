@@ -60,7 +60,7 @@ struct LstmBwdArgs {
     float *gdst;          // TL(4*KXT)
     float *dw_partial;    // [NB*chains][HT*MB][4][64]
     float *db_partial;    // [NB*chains][HT][4][4]
-    int P, NB, d;
+    int NB, d;
     const int32_t *pmax;  // [NB] positions the longest series of a tile has: the tile's chains stop there
     // cell-state penalty (Section 8.4) of a block's first layer, kernels instantiated with CP only
     const int32_t *lengths;
@@ -660,7 +660,7 @@ inline LstmBwdArgs backward_args(const Plan &pl, int layer, const LstmBwdSources
     const LayerPlan &lp = pl.layer[layer];
     const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
     return LstmBwdArgs{reinterpret_cast<const u32x2 *>(ws + lp.wpack_bwd), ws + lp.xsrc, ws + lp.gates, ws + lp.c,
-                       ws + lp.hid, {src.g[0], src.g[1]}, src.n, ws + lp.gdst, ws + lp.dw_partial, ws + lp.db_partial, pl.P,
+                       ws + lp.hid, {src.g[0], src.g[1]}, src.n, ws + lp.gdst, ws + lp.dw_partial, ws + lp.db_partial,
                        pl.NB, lp.dil, reinterpret_cast<const int32_t *>(ws + pl.pmax), lengths,
                        cp ? reinterpret_cast<const Scalars *>(ws + pl.scalars) : nullptr, 2.0f * pl.cfg.lambda_cs, pl.B, pl.T,
                        pl.I, pl.H};

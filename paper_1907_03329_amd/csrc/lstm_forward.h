@@ -42,7 +42,7 @@ struct LstmFwdArgs {
     float *c, *hid;       // TL(HP)
     const float *resid;   // TL(HP)                  (layers that end a residual block)
     float *out;           // TL(HP): resid + hid
-    int P, NB, d;
+    int NB, d;
     const int32_t *pmax;  // [NB] positions the longest series of a tile has: the tile's chains stop there
     // cell-state penalty (Section 8.4) of a block's first layer
     const int32_t *lengths;
@@ -300,7 +300,7 @@ inline LstmFwdArgs forward_args(const Plan &pl, int layer, const int32_t *length
     const LayerPlan &lp = pl.layer[layer];
     const bool cp = lp.first_in_block && pl.cfg.lambda_cs != 0.0f;
     return LstmFwdArgs{reinterpret_cast<const u32x4 *>(ws + lp.wpack_fwd), ws + lp.bias_pack, ws + lp.xsrc, ws + lp.gates,
-                       ws + lp.c, ws + lp.hid, lp.out ? ws + lp.resid : nullptr, lp.out ? ws + lp.out : nullptr, pl.P, pl.NB,
+                       ws + lp.c, ws + lp.hid, lp.out ? ws + lp.resid : nullptr, lp.out ? ws + lp.out : nullptr, pl.NB,
                        lp.dil, reinterpret_cast<const int32_t *>(ws + pl.pmax), lengths, cp ? ws + lp.cs_partial : nullptr,
                        pl.B, pl.T, pl.I, pl.H, mode.stash ? 1 : 0,
                        mode.need ? mode.need + (size_t)layer * pl.NB * kNeedWords : nullptr};

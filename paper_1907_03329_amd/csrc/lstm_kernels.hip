@@ -48,10 +48,9 @@ struct LstmBwdArgs {
     const float *gsrc[2]; // TL(HP): the gradient arriving at the hidden output is the sum of these
     int n_gsrc;           // 1 or 2; gsrc[1] repeats gsrc[0] when there is one
     float *gdst;          // TL(4*KXT)
-    float *sink;          // [kSinkLines][64] floats that nothing reads: target of the stores a wave has no input tile for
     float *dw_partial;    // [NB*chains][HT*MB][4][64]
     float *db_partial;    // [NB*chains][HT][4][4]
-    int P, NB, d;
+    int NB, d;
     const int32_t *pmax;  // [NB] positions the longest series of a tile has: the tile's chains stop there
     // cell-state penalty (Section 8.4) of a block's first layer, kernels instantiated with CP only
     const int32_t *lengths;
@@ -65,16 +64,17 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
 {
     constexpr int W = kLstmWaves;
     constexpr int KT = KXT + HT;
-    constexpr int MB = (KT + 3) / 4;                 // 16-row tiles of [x ; h]
-    constexpr int MTW = (HT + W - 1) / W;            // unit tiles per wave
-    constexpr int QXW = (KXT + W - 1) / W;           // input unit tiles finalised per wave
+    constexpr int MB = KT / 4;                       // 16-row tiles of [x ; h]
+    static_assert(HT % W == 0 && KXT % W == 0 && KT % 4 == 0, "every wave owns as many tiles as the others, none is padding");
+    constexpr int MTW = HT / W;                      // unit tiles per wave
+    constexpr int QXW = KXT / W;                     // input unit tiles finalised per wave
     constexpr int NT = 64 * W;                       // threads of the chain waves
-    constexpr int DA_ROWS = 16 * W * MTW;            // includes dummy rows for tiles past HT
-    constexpr int XH_PER_THREAD = (KT * 64 + NT - 1) / NT;
-    constexpr int XH_ROWS = (16 * MB > 16 * XH_PER_THREAD) ? 16 * MB : 16 * XH_PER_THREAD;
+    constexpr int DA_ROWS = 16 * HT;
+    constexpr int XH_PER_THREAD = KT / W;
+    constexpr int XH_ROWS = 16 * MB;
 
     __shared__ float da_lds[2][DA_ROWS * kLdsPad];   // [mt][4*gate + unit][series]
-    __shared__ float xh_lds[2][XH_ROWS * kLdsPad];   // [row of x ; h][series]; rows past 4*KT are scratch
+    __shared__ float xh_lds[2][XH_ROWS * kLdsPad];   // [row of x ; h][series]
     __shared__ float part_lds[2][W][MB * 4][64];     // partial d[x ; h] of every chain wave
     static_assert(2 * (DA_ROWS * kLdsPad + XH_ROWS * kLdsPad + W * MB * 4 * 64) * 4 <= 128 * 1024,
                   "LDS budget of the reverse kernel");
@@ -91,7 +91,6 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
 
     if (!chain) {
         // ---- dW waves: rows (W-1-s) + W*j of the weight gradient, in accumulators for the whole launch
-        const bool last_row_valid = (W - 1 - s) + W * (MTW - 1) < HT;
         f32x4 dw[MTW][MB];
 #pragma unroll
         for (int j = 0; j < MTW; ++j)
@@ -111,12 +110,10 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
                     ar[j][ks] = da_lds[buf][(((W - 1 - s) + W * j) * 16 + n) * kLdsPad + 4 * ks + g];
 #pragma unroll
             for (int j = 0; j < MTW; ++j)
-                if (j < MTW - 1 || last_row_valid) {
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
+                for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-                        for (int nbk = 0; nbk < MB; ++nbk) dw[j][nbk] = mfma16(ar[j][ks], xb[nbk][ks], dw[j][nbk]);
-                }
+                    for (int nbk = 0; nbk < MB; ++nbk) dw[j][nbk] = mfma16(ar[j][ks], xb[nbk][ks], dw[j][nbk]);
         };
         for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
             const int p_last = r0 + ((Pt - 1 - r0) / a.d) * a.d;
@@ -131,22 +128,17 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
 #pragma unroll
         for (int j = 0; j < MTW; ++j) {
             const int row = (W - 1 - s) + W * j;
-            if (row < HT) {
 #pragma unroll
-                for (int nbk = 0; nbk < MB; ++nbk) {
-                    float *dst = a.dw_partial + (part * (HT * MB) + row * MB + nbk) * 256 + lane;
+            for (int nbk = 0; nbk < MB; ++nbk) {
+                float *dst = a.dw_partial + (part * (HT * MB) + row * MB + nbk) * 256 + lane;
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) dst[rr * 64] = dw[j][nbk][rr];
-                }
+                for (int rr = 0; rr < 4; ++rr) dst[rr * 64] = dw[j][nbk][rr];
             }
         }
         return;
     }
 
     // ---- chain waves: steps A and B
-    const bool last_own_valid = s + W * (MTW - 1) < HT;           // unit tile s + 4(MTW-1)
-    const bool last_qx_valid = s + W * (QXW - 1) < KXT;
-    float *sink_line = a.sink + ((bt + blockIdx.y * 61) % kSinkLines) * 64;
     // W^T operands of the k-steps this wave owns: k-step 4*mt + gate, mt = s + 4j
     float wreg[MB][4 * MTW];
 #pragma unroll
@@ -155,18 +147,14 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
         for (int j = 0; j < MTW; ++j) {
             const int mt = s + W * j;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float w = a.wpack[((size_t)mb * 4 * HT + 4 * min(mt, HT - 1) + r) * 64 + lane];
-                wreg[mb][4 * j + r] = mt < HT ? w : 0.0f;
-            }
+            for (int r = 0; r < 4; ++r) wreg[mb][4 * j + r] = a.wpack[((size_t)mb * 4 * HT + 4 * mt + r) * 64 + lane];
         }
     f32x4 dbacc[MTW];
 #pragma unroll
     for (int j = 0; j < MTW; ++j) dbacc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const size_t xtile = (size_t)KXT * 64, htile = (size_t)HT * 64;
 
-    // operands of one position, requested one position ahead.  Branch-free: tiles past HT alias the last tile, a
-    // missing predecessor aliases p itself, elements past the end of [x ; h] alias its last element.
+    // operands of one position, requested one position ahead.  Branch-free: a missing predecessor aliases p itself.
     float4 pf_gt[MTW];
     float pf_c[MTW], pf_cp[MTW], pf_g[MTW], pf_g2[MTW], pf_xh[XH_PER_THREAD];
     // The requests of a position go out piece by piece, each as soon as the registers it fills are free:
@@ -176,8 +164,7 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
         const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
 #pragma unroll
         for (int i = 0; i < XH_PER_THREAD; ++i) {
-            // unit tile s + W*i of [x ; h]; tiles past the end alias the last one
-            const int q = min(s + W * i, KT - 1);
+            const int q = s + W * i;                       // unit tile of [x ; h]
             const float *src = q < KXT ? a.xsrc + pb * xtile + q * 64 : a.hid + pbd * htile + (q - KXT) * 64;
             pf_xh[i] = src[lane];
         }
@@ -186,7 +173,7 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
         const size_t pb = (size_t)p * a.NB + bt;
         const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
         // wave-uniform tile bases plus the lane index: scalar address arithmetic
-        const int mt = min(s + W * j, HT - 1);
+        const int mt = s + W * j;
         const size_t tile = (pb * HT + mt) * 64;
         pf_gt[j] = (reinterpret_cast<const float4 *>(a.gates) + tile)[lane];
         pf_c[j] = first ? (a.c + tile)[lane] : pf_cp[j];
@@ -225,7 +212,7 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
         da[j][2] = dc_i * (1.0f - gt.z * gt.z);
         da[j][3] = dh_o * tc * (1.0f - gt.w);
         dcreg[j] = dc_f;
-        float *dst = da_lds[buf] + ((s + W * j) * 16 + g) * kLdsPad + n;   // dummy rows for tiles past HT
+        float *dst = da_lds[buf] + ((s + W * j) * 16 + g) * kLdsPad + n;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             dst[r * 4 * kLdsPad] = da[j][r];
@@ -244,18 +231,11 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < MTW - 1; ++j)
+        for (int j = 0; j < MTW; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) acc[mb] = mfma16(wreg[mb][4 * j + r], da[j][r], acc[mb]);
-        if (last_own_valid) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[mb] = mfma16(wreg[mb][4 * (MTW - 1) + r], da[MTW - 1][r], acc[mb]);
-        }
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -267,25 +247,19 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
         const float (*pt)[MB * 4][64] = part_lds[buf];
 #pragma unroll
         for (int j = 0; j < MTW; ++j) {
-            const int q = min(KXT + s + W * j, KT - 1);   // row of part_lds = unit tile of [x ; h]
+            const int q = KXT + s + W * j;   // row of part_lds = unit tile of [x ; h]
             dhreg[j] = (pt[0][q][lane] + pt[1][q][lane]) + (pt[2][q][lane] + pt[3][q][lane]);
         }
 #pragma unroll
         for (int j = 0; j < QXW; ++j) {
-            const int q = min(s + W * j, KXT - 1);
+            const int q = s + W * j;
             dxv[j] = (pt[0][q][lane] + pt[1][q][lane]) + (pt[2][q][lane] + pt[3][q][lane]);
         }
     };
-    // Every wave issues the same number of stores (one without an input tile for its last store writes to a sink):
-    // memory operations complete in order, and the compiler's wait for the operands requested one position ahead
-    // counts the stores issued since with the smallest number any wave issues.
     auto store_dx = [&](int p) {
         const size_t pb = (size_t)p * a.NB + bt;
 #pragma unroll
-        for (int j = 0; j < QXW; ++j) {
-            float *dst = (j < QXW - 1 || last_qx_valid) ? a.gdst + pb * xtile + (s + W * j) * 64 : sink_line;
-            dst[lane] = dxv[j];
-        }
+        for (int j = 0; j < QXW; ++j) (a.gdst + pb * xtile + (s + W * j) * 64)[lane] = dxv[j];
     };
 
     for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
@@ -324,7 +298,7 @@ __global__ void __launch_bounds__(128 * kLstmWaves, 1) lstm_backward_split_kerne
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
             const float tot = group16_sum(dbacc[j][rr]);
-            if (n == 0 && mt < HT) a.db_partial[(part * HT + mt) * 16 + g * 4 + rr] = tot;
+            if (n == 0) a.db_partial[(part * HT + mt) * 16 + g * 4 + rr] = tot;
         }
     }
 }
@@ -384,8 +358,7 @@ hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *length
     a.gsrc[0] = src.g[0];
     a.gsrc[1] = src.g[1];
     a.gdst = ws + lp.gdst; a.dw_partial = ws + lp.dw_partial; a.db_partial = ws + lp.db_partial;
-    a.sink = ws + pl.sink;
-    a.P = pl.P; a.NB = pl.NB; a.d = lp.dil;
+    a.NB = pl.NB; a.d = lp.dil;
     a.pmax = reinterpret_cast<const int32_t *>(ws + pl.pmax);
 #define X(HT_, KXT_) if constexpr (!bwd_three_term(HT_)) if (pl.HT == HT_ && lp.KXT == KXT_) return run_bwd<HT_, KXT_>(a, lp.chains_bwd, st);
     ESRNN_LSTM_SHAPES(X)

@@ -33,9 +33,9 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 //     30     21 / 35,  32 / 39                     37 / 62,  56 / 70                  38 / 67,  59 / 76
 //     40     29 / 40,  42 / 60                     52 / 71,  76 / 111                 54 / 75,  79 / 118
 //     50     40 / 45,  69 / 99                     73 / 81,  124 / 185                76 / 89,  130 / 200
-//     60     44 / 50,  201 / 118                   80 / 91,  388 / 219                82 / 102, 390 / 238
+//     60     44 / 52,  189 / 119                   79 / 91,  364 / 220                82 / 100, 370 / 235
 // and with 151 positions alike (hidden 50, first layer, 72 groups: 138 / 142, 219 / 222).  Above hidden 52 the reverse
-// pass of 16 series is the fp32 kernel, which loses up to 148 groups (392 / 338 us) and at 160 with dilation 8 wins (59 / 66).
+// pass of 16 series is the fp32 kernel, which loses up to 148 groups (372 / 337 us) and at 160 with dilation 8 wins (57 / 66).
 constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwardBelowFp32 = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
@@ -195,7 +195,6 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     pl.es_blocks = pl.Bt / 64;
     // first everything the smoothing and window stages touch (their own entry points need only this prefix)
     pl.scalars = ws.take(64);
-    pl.sink = ws.take(64 * kSinkLines);
     pl.len_ext = ws.take((size_t)pl.B);
     pl.pmax = ws.take((size_t)pl.NB);
     pl.opt_partial = ws.take(512);
