@@ -52,7 +52,7 @@ struct LayerPlan {
                          // weight-gradient partials are indexed by 4*NB*chains_bwd workgroups
     size_t dw_partial;   // [NB*chains][HT*MB][4][64] per-workgroup weight-gradient tiles
     size_t db_partial;   // [NB*chains][HT][4][4]
-    size_t dw_reduced, db_reduced;   // [kReduceSplits][...] first reduction stage
+    size_t dw_reduced, db_reduced;   // [kReduceSplits][...] first reduction stage (dw_reduced: in wpack_fwd's place)
     size_t cs_partial;   // [NB*chains] sums of squared cell states (first layer of a block, penalty on)
 };
 

@@ -227,13 +227,12 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         // on waves of its own: the faster kind where the grid has no more than that.
         lp.chains_bwd = lp.narrow_bwd ? chains_for(groups, 512) : wide_reverse_chains(groups, most_chains);
         lp.split_bwd = lp.narrow_bwd && groups * lp.chains_bwd <= 256 ? 1 : 0;
-        if (lp.narrow_fwd) {
-            lp.wpack_fwd = ws.take((size_t)4 * 4 * KT * 64);
-            lp.bias_pack = lp.wpack_fwd;                       // unused: the kernels read the caller's bias
-        } else {
-            lp.wpack_fwd = ws.take((size_t)pl.HT * (tt_a_quads((lp.KXT + 1) / 2) + tt_a_quads((pl.HT + 1) / 2)) * 256);
-            lp.bias_pack = ws.take((size_t)pl.HT * 16);
-        }
+        // The forward operands lie where the first reduction stage of the weight gradient comes at the end of the reverse
+        // pass, which does not need them any more and packs none for the next forward pass.
+        const size_t fwd_pack = lp.narrow_fwd ? (size_t)4 * 4 * KT * 64
+                                              : (size_t)pl.HT * (tt_a_quads((lp.KXT + 1) / 2) + tt_a_quads((pl.HT + 1) / 2)) * 256;
+        lp.wpack_fwd = lp.dw_reduced = ws.take(std::max((size_t)kReduceSplits * pl.HT * MB * 256, fwd_pack));
+        lp.bias_pack = lp.narrow_fwd ? lp.wpack_fwd : ws.take((size_t)pl.HT * 16);   // (unused by the 4-series kernel)
         lp.wpack_bwd = lp.narrow_bwd ? ws.take((size_t)4 * ceil_div(4 * KT, 64) * 4 * pl.HT * 64)
                        : bwd_three_term(pl.HT) ? ws.take((size_t)bwd_pack_dwords(pl.HT, lp.KXT))
                                                : ws.take((size_t)MB * 4 * pl.HT * 64);
@@ -242,7 +241,6 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.hid = ws.take(PN * tileH);
         lp.dw_partial = ws.take((size_t)groups * lp.chains_bwd * pl.HT * MB * 256);
         lp.db_partial = ws.take((size_t)groups * lp.chains_bwd * pl.HT * 16);
-        lp.dw_reduced = ws.take((size_t)kReduceSplits * pl.HT * MB * 256);
         lp.db_reduced = ws.take((size_t)kReduceSplits * pl.HT * 16);
         pl.dx[l] = l > 0 ? ws.take(PN * tileH) : pl.gX;
     }

@@ -92,3 +92,24 @@ def test_forward_and_reverse_pass_of_a_layer_on_different_kinds(hidden):
     with forced(None):
         errs = gc.run_and_check(cfg, seed=82, ragged=True, stages=False)
     print(f"  hidden {hidden}: worst {max(v for k, v in errs.items() if k != 'series_at_kink'):.2e}", flush=True)
+
+
+@pytest.mark.parametrize("kind", ["wide", "narrow"])
+def test_reverse_pass_can_be_repeated(kind):
+    """The weight-gradient reduction reuses the place of operands that only the forward pass reads."""
+    import torch
+    from paper_1907_03329_amd import binding, synth
+    cfg = CONFIGS["quarterly"].with_(B=70)
+    dev = gc.to_device(synth.make_inputs(cfg, seed=83, ragged=True))
+    args = [dev[k] for k in ("y", "lengths", "es_params", "weights")]
+    with forced(0 if kind == "wide" else 1 << 30):
+        step = binding.TrainingStep(cfg)
+    results = []
+    for passes in ("fbb", "fb"):
+        for p in passes:
+            step.forward(*args) if p == "f" else step.backward(*args)
+            if p == "b":
+                results.append((step.loss.clone(), step.forecasts.clone(), step.grad_es_params.clone(), step.grad_weights.clone()))
+    for other in results[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(results[0], other))
+    step.close()

@@ -145,3 +145,15 @@ def test_binding_refuses_host_tensors(lib):
     with pytest.raises(ValueError):
         binding.esrnn_forward(h, t, t, t, t, t, t)
     binding.esrnn_destroy(h)
+
+
+# Batches whose workspace just fits the array inside the library, and did with fp32 operands of the layers' products.
+@pytest.mark.parametrize("B,T,I,H,hidden,blocks", [
+    (55, 95, 12, 8, 33, ((55, 8),)), (287, 41, 10, 11, 52, ((14,),)), (151, 39, 11, 12, 33, ((57,), (1, 40))),
+    (291, 30, 12, 9, 40, ((1, 17, 1),)), (38, 77, 9, 12, 40, ((2, 55, 89),)),
+])
+def test_workspaces_at_the_size_of_the_built_in_one(lib, monkeypatch, B, T, I, H, hidden, blocks):
+    monkeypatch.delenv("ESRNN_NARROW_BELOW", raising=False)
+    h = binding.esrnn_create(bad(B=B, T=T, I=I, H=H, hidden=hidden, blocks=blocks))
+    assert binding.esrnn_workspace_bytes(h) <= 32 << 20
+    binding.esrnn_destroy(h)
