@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
         auto store_x = [&](int buf, const float (&v)[XTW]) {
             static_for<0, NX>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
-                TileHome<NPX, SX + j>::store(x_lds[buf], x_at[j], v[j]);
+                TileHome<NPX, SX + j>::store(x_lds[buf], x_at[j], splittable(v[j]));
             });
         };
         auto load_res = [&](int p, float (&v)[MTW]) {

@@ -124,6 +124,15 @@ __device__ __forceinline__ Parts split_pair(float a, float b)
     return p;
 }
 
+// An infinite input (the logarithm of a zero observation) as a number that still saturates what it is multiplied into: the
+// parts of an infinity would be inf, NaN, NaN.  NaN stays NaN.  Inputs are logarithms, states and flags, none of which
+// comes near the limit otherwise.
+__device__ __forceinline__ float splittable(float x)
+{
+    constexpr float limit = 0x1p100f;
+    return __builtin_fabsf(x) > limit ? __builtin_copysignf(limit, x) : x;
+}
+
 __device__ __forceinline__ unsigned part_of(const Parts &p, int part)
 {
     return part == 0 ? p.hi : part == 1 ? p.mid : part == 2 ? p.lo : 0u;

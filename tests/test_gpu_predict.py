@@ -141,3 +141,24 @@ def test_forecasts_leave_the_results_of_the_reverse_pass_alone(narrow, monkeypat
     for n, t in zip(names, before):
         assert torch.equal(step.buffer(n), t), n
     step.close()
+
+
+# One zero observation: the windows that hold it have an input of minus infinity, which saturates gates and goes no
+# further (the recursion itself only takes the value in).  The 16-series kernels take it at every hidden size, the 4-series
+# ones where no unit is padding.
+@pytest.mark.parametrize("narrow,hidden", [("0", 8), ("0", 40), ("0", 45), ("0", 60), ("100000", 8), ("100000", 40), ("100000", 64)])
+def test_a_zero_observation_saturates_and_does_not_spread(narrow, hidden, monkeypatch):
+    import torch
+    monkeypatch.setenv("ESRNN_NARROW_BELOW", narrow)
+    cfg = CONFIGS["tiny_quarterly"].with_(B=21, hidden=hidden)
+    inp = synth.make_inputs(cfg, seed=9)
+    n = np.full(cfg.B, cfg.T - cfg.H, dtype=np.int32)
+    inp["y"][n[0] - 2 - np.arange(cfg.B) % 12, np.arange(cfg.B)] = 0.0
+    want = oracle.predict(cfg, inp["y"], n, inp["es_params"], inp["weights"])
+    assert np.all(np.isfinite(want))
+    step = binding.TrainingStep(cfg, want_forecasts=False)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in dict(inp, lengths=n).items()}
+    got = step.predict(dev["y"], dev["lengths"], dev["es_params"], dev["weights"]).cpu().numpy()
+    step.close()
+    assert np.all(np.isfinite(got))
+    assert (np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)).max() <= 10 * TOL
