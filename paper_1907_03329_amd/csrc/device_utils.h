@@ -95,10 +95,13 @@ __device__ __forceinline__ float sigmoid_f(float x)
 
 // tanh(x) = 1 - 2 / (1 + exp(2x)); saturates correctly at both ends.  exp(2x) = 2^(x * 2 log2(e)): one
 // multiplication, with the same result as doubling x first (doubling is exact).
-__device__ __forceinline__ float tanh_f(float x)
+constexpr float kTanhExponent = 2.8853900817779268f, kSigmoidExponent = -1.4426950408889634f;
+__device__ __forceinline__ float tanh_of_exponent(float e)
 {
-    return 1.0f - 2.0f * fast_rcp(1.0f + __builtin_amdgcn_exp2f(x * 2.8853900817779268f));
+    return 1.0f - 2.0f * fast_rcp(1.0f + __builtin_amdgcn_exp2f(e));
 }
+__device__ __forceinline__ float sigmoid_of_exponent(float e) { return fast_rcp(1.0f + __builtin_amdgcn_exp2f(e)); }
+__device__ __forceinline__ float tanh_f(float x) { return tanh_of_exponent(x * kTanhExponent); }
 
 __device__ __forceinline__ float wave_sum(float v)
 {

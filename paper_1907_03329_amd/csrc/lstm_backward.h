@@ -394,11 +394,13 @@ __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) +
                         for (int mb = 0; mb < RH; ++mb) acc[mb] = mfma_bf16(w3[mb][k == 0], bb, acc[mb]);
                     }
                 };
-                third(0);                                  // smallest terms first: fewer roundings of the large sum
-                third(1);
-                pairs(std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
-                third(2);
+                // Largest terms first: an accumulator smaller than the sum it receives loses its low bits downwards
+                // (three_term.h), and a bias of dh adds up over positions and series.
                 pairs(std::integral_constant<int, 5>{}, std::integral_constant<int, 6>{});
+                third(2);
+                pairs(std::integral_constant<int, 0>{}, std::integral_constant<int, 5>{});
+                third(1);
+                third(0);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) {
 #pragma unroll

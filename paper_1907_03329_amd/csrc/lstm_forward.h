@@ -14,6 +14,13 @@
 // cross-lane traffic.  Of W waves, wave s owns the unit tiles s and s + W and brings the input tiles W - 1 - s and
 // 2 W - 1 - s (the waves with a unit tile fewer bring an input tile more).
 //
+// The bias is added last, by the multiply-add that scales a pre-activation for its exponential; only what the rounding of
+// the scaled bias leaves out goes in with the products.  Products added to the bias would all be rounded at its size, and
+// not at random: inputs and states vary little, so the sum of their leading parts takes few values, and what rounding
+// cuts off the bias is the same at every position.  Against float64, mean error of a unit's pre-activations over 2624
+// positions, biases around 1.5, hidden 32 to 64: 8 - 11e-8 (bias first 10 - 17e-8, fp32 matrix instruction 8 - 11e-8), rms
+// 36 - 51e-8 (44 - 65e-8, 46 - 68e-8).  No vector instruction more than with the bias first (forecasts 1 % faster).
+//
 // Order of a position: the recurrent half, on top of the input half formed one position earlier; the cell update,
 // whose hidden state goes to LDS; then the input half of the next position, which does not depend on the recurrence
 // and fills the matrix pipe while the waves run apart; the input of the position after that goes from registers to
@@ -99,6 +106,7 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
     static_assert(W == 8 || (MTW == 1 && XTW == 1), "tile s + W j lies in segment j, or there is one tile");
     __shared__ __align__(16) char h_lds[2][BH * 1024];               // parts of h_{p-d}, by position parity
     __shared__ __align__(16) char x_lds[2][BX * 1024];               // parts of x_p
+    __shared__ f32x4 rest_lds[HT][4];                                // what the rounding of that left out of the bias
 
     const int lane = threadIdx.x & 63, bt = blockIdx.x;
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, known to be uniform
@@ -111,7 +119,7 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
     }
 
     u32x4 wx[MTW][AX], wh[MTW][AH];
-    f32x4 bias[MTW];
+    f32x4 scaled[MTW];                                               // the bias as the exponentials take it
 #pragma unroll
     for (int j = 0; j < MTW; ++j) {
         const int mt = min(s + W * j, HT - 1);                       // (a tile past HT is never computed)
@@ -121,7 +129,15 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
 #pragma unroll
         for (int q = 0; q < AH; ++q) wh[j][q] = w[(AX + q) * 64];
         const float4 bv = *reinterpret_cast<const float4 *>(a.bpack + (mt * 4 + (lane >> 4)) * 4);
-        bias[j] = f32x4{bv.x, bv.y, bv.z, bv.w};
+        const float b[4] = {bv.x, bv.y, bv.z, bv.w};
+        f32x4 rest;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float k = r == 2 ? kTanhExponent : kSigmoidExponent;
+            scaled[j][r] = b[r] * k;
+            rest[r] = __builtin_fmaf(b[r], k, -scaled[j][r]) * (1.0f / k);
+        }
+        if ((lane & 15) == 0) rest_lds[mt][lane >> 4] = rest;
     }
     // halves of pairs that no tile fills stay zero
     for (int i = threadIdx.x; i < 2 * BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(h_lds)[i] = 0u;
@@ -173,13 +189,13 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
             return v;
         };
         f32x4 acc[MTW];
-        // acc = bias + Wx x, from the parts in x_lds[buf]
+        // acc = Wx x (+ the rest of the bias), from the parts in x_lds[buf]
         auto input_part = [&](int buf) {
             u32x4 b[BX];
 #pragma unroll
             for (int q = 0; q < BX; ++q) b[q] = read_quad(x_lds[buf], q);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[j] = bias[j];
+            for (int j = 0; j < NJ; ++j) acc[j] = rest_lds[min(s + W * j, HT - 1)][lane >> 4];
             static_for<0, tt_mfmas(NPX)>([&](auto ic) {
                 constexpr TtPair t = tt_mfma(NPX, decltype(ic)::value);
 #pragma unroll
@@ -231,10 +247,10 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
                 static_for<0, NJ>([&](auto jc) {
                     constexpr int j = decltype(jc)::value;
                     const int mt = s + W * j;
-                    const float gi = sigmoid_f(acc[j][0]);
-                    const float gf = sigmoid_f(acc[j][1]);
-                    const float gg = tanh_f(acc[j][2]);
-                    const float go = sigmoid_f(acc[j][3]);
+                    const float gi = sigmoid_of_exponent(acc[j][0] * kSigmoidExponent + scaled[j][0]);
+                    const float gf = sigmoid_of_exponent(acc[j][1] * kSigmoidExponent + scaled[j][1]);
+                    const float gg = tanh_of_exponent(acc[j][2] * kTanhExponent + scaled[j][2]);
+                    const float go = sigmoid_of_exponent(acc[j][3] * kSigmoidExponent + scaled[j][3]);
                     const float cn = gf * creg[j] + gi * gg;
                     const float hn = go * tanh_f(cn);
                     creg[j] = cn;

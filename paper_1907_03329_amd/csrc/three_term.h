@@ -3,10 +3,17 @@
 // A float is the exact sum of three bf16 numbers: hi = x rounded to bf16, mid = the rest rounded to bf16, lo = what
 // is left (24 significant bits = 8 + 8 + 8; each difference is exact).  A product x y is then the sum of nine
 // products of bf16 numbers, each exact in fp32.  The six largest are formed: hi hi, hi mid, mid hi, mid mid, hi lo,
-// lo hi.  The three left out (mid lo, lo mid, lo lo) are below 2^-26 of |x y| together, a quarter of the rounding
-// of one fp32 product; sums are kept in fp32 accumulators.  Measured over 10^5 dot products of length 96 against
-// float64: relative rms error 1.70e-7 with six terms, 1.70e-7 with all nine, 1.77e-7 with
-// v_mfma_f32_16x16x4_f32; largest error over the sum of |x y| 2.66e-7, 2.66e-7, 2.79e-7.
+// lo hi.  (The method is published: G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019.)  The three left out (mid lo, lo mid, lo lo)
+// reach 2^-24 of |x y| together (x = y = 1.0038986: 0.99 2^-24), as much as the rounding of one fp32 product at its
+// worst; their rms over all pairs of significands is 0.09 2^-24.  Sums are kept in fp32 accumulators.  Measured over
+// 10^5 dot products of length 96 against float64: relative rms error 1.70e-7 with six terms, 1.70e-7 with all nine,
+// 1.77e-7 with v_mfma_f32_16x16x4_f32; largest error over the sum of |x y| 2.66e-7, 2.66e-7, 2.79e-7.
+//
+// How the instruction rounds matters for sums over many positions and series (measured, 10^5 sums of 32 products): an
+// accumulator smaller than the sum of products it receives loses its low bits downwards, 0.07 to 0.10 of a unit in the
+// last place of the result on average for any accumulator up to a quarter of that sum; 0.02 to 0.04 at equal size, none
+// from four times the sum on and none from zero.  v_mfma_f32_16x16x4_f32 has no such bias.
 //
 // Why: v_mfma_f32_16x16x32_bf16 does 8192 multiply-adds in 16 cycles, the fp32 instruction 1024 in 32; six of the
 // one for eight of the other is 96 cycles against 256, and the bf16 instruction leaves the vector ALU of its SIMD
@@ -89,7 +96,7 @@ constexpr int bwd_pack_dwords(int HT, int KXT)
     return (bwd_x_row_tiles(HT, KXT) + bwd_h_row_tiles(HT)) * bwd_even_tiles(HT) * 3 * 128;
 }
 
-// quads of instruction i of one full group, smallest terms first: fewer roundings of the large sum
+// quads of instruction i of one full group, smallest terms first
 constexpr TtPair tt_group_rising(int i)
 {
     const int a[6] = {0, 2, 1, 0, 1, 0}, b[6] = {2, 0, 1, 1, 0, 0};
