@@ -32,3 +32,13 @@ def test_penalty_changes_the_gradient_and_the_loss():
     assert not torch.equal(a.grad_weights, b.grad_weights)
     assert torch.equal(a.forecasts, b.forecasts)
     a.close(); b.close()
+
+
+# Both kinds of LSTM kernels; the 16-series reverse kernels form the penalty's factor in waves of their own (up to 40), in
+# the waves that carry the recurrence (50), or in the fp32 kernel (64).
+@pytest.mark.parametrize("hidden", [8, 30, 40, 50, 64])
+@pytest.mark.parametrize("narrow", ["0", "100000"])
+def test_penalty_on_each_kernel_kind(hidden, narrow, monkeypatch):
+    monkeypatch.setenv("ESRNN_NARROW_BELOW", narrow)
+    cfg = CONFIGS["tiny_quarterly"].with_(B=39, T=70, blocks=((1, 3), (7,), (2, 5)), hidden=hidden, lambda_c=5.0)
+    gc.run_and_check(cfg, seed=64, ragged=True)

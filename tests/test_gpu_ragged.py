@@ -90,3 +90,31 @@ def test_out_of_sample_forecasts_on_a_poisoned_workspace():
     rel = np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1)
     assert rel.max() <= 1e-4, rel.max()
     step.close()
+
+
+# Forecasts leave out what they do not depend on: it is NaN here and must not be read where it counts.  Six tiles: with
+# a threshold of 20 workgroups the layers of dilation 1 to 3 run on the 4-series kernels, which compute every class, the
+# others on the 16-series kernels, which skip classes; a layer with the penalty computes every class on either.
+@pytest.mark.parametrize("narrow", ["0", "20", "100000"])
+@pytest.mark.parametrize("blocks", [((1, 2), (4, 8)), ((8, 4), (2, 1)), ((3, 6), (9,), (2,)), ((12,), (1, 10), (5,))])
+@pytest.mark.parametrize("penalty", [0.0, 1.0])
+def test_forecasts_skip_classes_on_a_poisoned_workspace(narrow, blocks, penalty, monkeypatch):
+    import torch
+    monkeypatch.setenv("ESRNN_NARROW_BELOW", narrow)
+    cfg = CONFIGS["quarterly"].with_(B=90, T=60, blocks=blocks, lambda_c=penalty)
+    for order in ("unsorted", "short_tile", "alike"):
+        inp = with_lengths(cfg, 93, order)
+        inp["lengths"] = np.minimum(inp["lengths"], cfg.T - cfg.H).astype(np.int32)
+        if order == "alike":
+            inp["lengths"][:] = 41 - np.arange(cfg.B) // 16         # one class of most dilations in every tile
+            inp["lengths"][5] = cfg.I - 1                           # a series that takes no part
+        step = binding.TrainingStep(cfg, want_forecasts=False)
+        step.workspace.fill_(float("nan"))
+        dev = gc.to_device(inp)
+        got = step.predict(dev["y"], dev["lengths"], dev["es_params"], dev["weights"]).cpu().numpy()
+        ok = inp["lengths"] >= cfg.I
+        want = oracle.predict(cfg, inp["y"], np.where(ok, inp["lengths"], cfg.T - cfg.H).astype(np.int32), inp["es_params"], inp["weights"])
+        assert np.all(got[~ok] == 0.0)
+        rel = (np.abs(got - want).max(axis=1) / np.abs(want).max(axis=1))[ok]
+        assert rel.max() <= 1e-4, (order, rel.max())
+        step.close()
