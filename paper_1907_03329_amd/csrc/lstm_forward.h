@@ -27,11 +27,11 @@
 // LDS and the one after it is requested.  One barrier per position.
 //
 // What bounds it: the activation stash.  A position writes 6 h floats per series (activated gates, cell, hidden) and
-// reads its input; at 4096 series and hidden 40 that is 308 MB a layer, 52 us at the rates a plain stream of stores
-// or loads reaches here (5.3 - 6.3 TB/s and 6.4 - 6.8 TB/s).  Measured: 50 us (60 us for a layer that also reads and
-// writes the block's residual); with the fp32 matrix instruction 72 us, bound by the issue of matrix and vector
-// instructions.  Monthly shape (240 steps, hidden 50, 1.39 GB a layer): 319 - 340 us, from 356 us; first layers
-// 63 us from 79 us and 255 us from 338 us.
+// reads its input; at 4096 series and hidden 40 that is 281 MB a layer (361 MB with the block's residual read and
+// written), 50 us at the rates a plain stream of stores or loads reaches here (5.3 - 6.3 TB/s and 6.4 - 6.8 TB/s).
+// Measured: 52 - 55 us (64 - 70 us with the residual); with the fp32 matrix instruction 72 us, bound by the issue of
+// matrix and vector instructions.  Monthly shape (240 steps, hidden 50, 1.26 GB a layer, 1.64 GB with the residual):
+// 350 - 355 us (380 - 390 us).  First layers 61 us from 79 us and 240 - 255 us from 338 us.
 #pragma once
 
 #include "esrnn_internal.h"
@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
             scaled[j][r] = b[r] * k;
             rest[r] = __builtin_fmaf(b[r], k, -scaled[j][r]) * (1.0f / k);
         }
-        if ((lane & 15) == 0) rest_lds[mt][lane >> 4] = rest;
+        if ((lane & 15) == 0 && s + W * j < HT) rest_lds[mt][lane >> 4] = rest;
     }
     // halves of pairs that no tile fills stay zero
     for (int i = threadIdx.x; i < 2 * BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(h_lds)[i] = 0u;

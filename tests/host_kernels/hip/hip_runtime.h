@@ -24,3 +24,33 @@ inline hipError_t hipGetLastError() { return hipSuccess; }
 extern dim3 threadIdx, blockIdx, gridDim;
 using std::max;
 using std::min;
+
+// ---- device builtins: addresses and barriers are those of the device, arithmetic across lanes is not formed ----
+void host_barrier();                            // host_kernels.cpp
+void host_global(const void *at, int bytes);    // stops the program if it lies outside the workspace
+template <class V>
+inline V &host_buffer(const char *r, unsigned bytes)
+{
+    host_global(r + bytes, sizeof(V));
+    return *reinterpret_cast<V *>(const_cast<char *>(r + bytes));
+}
+typedef unsigned host_b128 __attribute__((ext_vector_type(4)));
+typedef const char *__amdgpu_buffer_rsrc_t;
+#define __builtin_amdgcn_make_buffer_rsrc(base, stride, range, flags) static_cast<const char *>(base)
+#define __builtin_amdgcn_raw_buffer_load_b32(r, lane, tile, aux) host_buffer<unsigned>(r, (lane) + (tile))
+#define __builtin_amdgcn_raw_buffer_load_b128(r, lane, tile, aux) host_buffer<host_b128>(r, (lane) + (tile))
+#define __builtin_amdgcn_raw_buffer_store_b32(v, r, lane, tile, aux) (host_buffer<unsigned>(r, (lane) + (tile)) = (v))
+#define __builtin_amdgcn_raw_buffer_store_b128(v, r, lane, tile, aux) (host_buffer<host_b128>(r, (lane) + (tile)) = (v))
+#define __syncthreads() host_barrier()
+#define __ballot(x) ((void)(x), ~0ull)
+#define __shfl_xor(v, off, width) (v)
+#define __expf(x) (x)
+#define __builtin_amdgcn_rcpf(x) (x)
+#define __builtin_amdgcn_logf(x) (x)
+#define __builtin_amdgcn_exp2f(x) (x)
+#define __builtin_amdgcn_readfirstlane(x) (x)
+#define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_canonicalizef(x) (x)
+#define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
+#define __builtin_amdgcn_ds_read_tr16_b64_v4i16(at) (*(at))
