@@ -224,8 +224,9 @@ esrnn_status esrnn_adam_update_indexed(esrnn_handle *h, const esrnn_adam_config 
  *              rows are read; their values do not reach the forecasts.
  *
  * Inputs and workspace as for esrnn_forward.  The workspace afterwards holds the
- * state of the extended problem: esrnn_backward must not follow (it returns
- * ESRNN_ERR_ORDER).
+ * state of the extended problem, the network's only as far as the forecasts
+ * depend on it: esrnn_backward must not follow (it returns ESRNN_ERR_ORDER).
+ * What an earlier esrnn_backward left in the workspace stays.
  */
 esrnn_status esrnn_predict(esrnn_handle *h, const float *y, const int32_t *lengths, const float *es_params,
                            const float *weights, void *workspace, float *forecasts, void *stream);
@@ -287,6 +288,9 @@ esrnn_status esrnn_es_window_backward(esrnn_handle *h, const float *y, const int
  *   ESRNN_LAYOUT_GATE_TILE   as TILE with a trailing [4] (activated input,
  *                            forget, candidate, output gate of hidden unit r)
  * dims = {T or P, Bt or Bp, R (padded rows), logical rows}.
+ * The network's tiles are complete (up to the last window of the longest series of 16) after an esrnn_forward that
+ * esrnn_backward may follow.  After one on a forward-only handle gates and cell states may be those of an earlier
+ * pass; after esrnn_predict hidden states, block outputs and outputs too, wherever no forecast depends on them.
  */
 typedef enum {
     ESRNN_BUF_LEVEL = 0, ESRNN_BUF_S1, ESRNN_BUF_S2, ESRNN_BUF_U, ESRNN_BUF_V,   /* time-major */

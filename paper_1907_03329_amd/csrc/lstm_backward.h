@@ -27,10 +27,10 @@
 // dW waves do not suffice.
 //
 // What bounds it. Hidden 40, 4096 series, 61 positions: 90 - 94 us a layer (fp32 kernel: 128 - 131 us), first layer 70
-// - 73 us (103 us), i.e. 1.45 us a position; 385 MB of traffic at 4.2 TB/s, where a large copy reaches 5.2. Without
+// - 73 us (103 us), i.e. 1.45 us a position; 370 - 414 MB of traffic at 4.1 TB/s, where a large copy reaches 5.2. Without
 // the dW waves' part it is 69 us, without dx and dW 61 us; without the dW products alone 82 us: the reads of
-// transposed operands from LDS (80 of 195 KB a position) weigh more than the products (matrix pipe busy 33 %). Hidden
-// 50, 240 steps, 1.70 GB: 440 - 480 us (780 - 810 us), first layer 340 - 360 us (517 us). Tried without gain: chain
+// transposed operands from LDS (80 of 195 KB a position) weigh more than the products (matrix pipe busy 36 %). Hidden
+// 50, 240 steps, 1.64 - 1.82 GB: 440 - 485 us (780 - 810 us), first layer 340 - 375 us (517 us). Tried without gain: chain
 // waves that form their own factors (12 waves: 90 us, first layer 74 us; alone on the chip 1.03 us a position against
 // 0.92), five chain waves of two tiles (two of them share a SIMD), raised priority of the chain waves (+2 %), all
 // operands of a consumer read at once (+3 %), dW waves that own 32 columns and read them from memory with 32x32
