@@ -135,7 +135,8 @@ __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(Lst
         for (int r = 0; r < 4; ++r) {
             const float k = r == 2 ? kTanhExponent : kSigmoidExponent;
             scaled[j][r] = b[r] * k;
-            rest[r] = __builtin_fmaf(b[r], k, -scaled[j][r]) * (1.0f / k);
+            // (nothing is left out of an infinite one, and inf - inf would be NaN)
+            rest[r] = __builtin_isinf(scaled[j][r]) ? 0.0f : __builtin_fmaf(b[r], k, -scaled[j][r]) * (1.0f / k);
         }
         if ((lane & 15) == 0 && s + W * j < HT) rest_lds[mt][lane >> 4] = rest;
     }

@@ -113,3 +113,21 @@ def test_reverse_pass_can_be_repeated(kind):
     for other in results[1:]:
         assert all(torch.equal(a, b) for a, b in zip(results[0], other))
     step.close()
+
+
+@pytest.mark.parametrize("hidden", [8, 40, 52])
+@pytest.mark.parametrize("kind", ["wide", "narrow"])
+def test_infinite_biases_hold_gates_open_and_shut(kind, hidden):
+    import numpy as np
+    from paper_1907_03329_amd import synth
+    cfg = small("infinite_bias", hidden=hidden)
+
+    def mutate(inp):
+        for name, off, shape in synth.weight_layout(cfg):
+            if name in ("b1", "b2"):
+                b = inp["weights"][off:off + 4 * hidden].reshape(4, hidden)
+                b[0, 1] = b[1, 3] = b[2, 5] = np.inf
+                b[0, 2] = b[3, 4] = -np.inf
+
+    with forced(0 if kind == "wide" else 1 << 30):
+        gc.run_and_check(cfg, seed=84, ragged=True, mutate=mutate)
