@@ -142,7 +142,7 @@ __device__ void pack_forward(const PackLstmArgs &a)
         const int i = lane & 15, k = lane >> 4, unit = 4 * mt + (i >> 2), gate = i & 3;
         const bool in_x = q < qx;
         const TtDword w = tt_a_dword(in_x ? npx : nph, in_x ? q : q - qx, d);
-        const Parts p = split_pair(a.at(gate, unit, in_x, 8 * w.pair + k), a.at(gate, unit, in_x, 8 * w.pair + 4 + k));
+        const Parts p = split_pair(splittable(a.at(gate, unit, in_x, 8 * w.pair + k)), splittable(a.at(gate, unit, in_x, 8 * w.pair + 4 + k)));
         reinterpret_cast<unsigned *>(a.fwd)[idx] = part_of(p, w.part);
     }
     for (int j = blockIdx.x * 256 + threadIdx.x; j < a.HT * 16; j += gridDim.x * 256) {

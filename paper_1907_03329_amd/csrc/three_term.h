@@ -131,9 +131,9 @@ __device__ __forceinline__ Parts split_pair(float a, float b)
     return p;
 }
 
-// An infinite input (the logarithm of a zero observation) as a number that still saturates what it is multiplied into: the
-// parts of an infinity would be inf, NaN, NaN.  NaN stays NaN.  Inputs are logarithms, states and flags, none of which
-// comes near the limit otherwise.
+// An infinite input (the logarithm of a zero observation) or weight as a number that still saturates what it is multiplied
+// into: the parts of an infinity would be inf, NaN, NaN.  NaN stays NaN.  Inputs are logarithms, states and flags; neither
+// they nor weights come near the limit otherwise.
 __device__ __forceinline__ float splittable(float x)
 {
     constexpr float limit = 0x1p100f;

@@ -131,3 +131,24 @@ def test_infinite_biases_hold_gates_open_and_shut(kind, hidden):
 
     with forced(0 if kind == "wide" else 1 << 30):
         gc.run_and_check(cfg, seed=84, ragged=True, mutate=mutate)
+
+
+@pytest.mark.parametrize("hidden", [8, 40, 52])
+@pytest.mark.parametrize("kind", ["wide", "narrow"])
+def test_infinite_input_weights_saturate_gates(kind, hidden):
+    """Forward pass: an infinite weight of a layer's input makes its gate follow the input's sign."""
+    import numpy as np
+    from oracle import oracle
+    from paper_1907_03329_amd import synth
+    cfg = small("infinite_weight", hidden=hidden)
+    inp = synth.make_inputs(cfg, seed=85, ragged=True)
+    for name, off, shape in synth.weight_layout(cfg):
+        if name == "W2":
+            w = inp["weights"][off:off + int(np.prod(shape))].reshape(shape)
+            w[1, 0], w[hidden + 2, 3], w[3 * hidden + 4, 5] = np.inf, -np.inf, np.inf
+    f = oracle.forward(cfg, inp["y"], inp["lengths"], inp["es_params"], inp["weights"])
+    assert np.all(np.isfinite(f.forecasts))
+    with forced(0 if kind == "wide" else 1 << 30):
+        step = gc.run_gpu(cfg, inp, backward=False)
+    gc.check_forward(cfg, inp, step, f)
+    step.close()
