@@ -16,40 +16,65 @@ namespace {
 
 __device__ __forceinline__ int clamp_len(int len, int T) { return len < 0 ? 0 : (len > T ? T : len); }
 
+// What the caller's lengths mean to a call.  Training: the observations there are.  Out-of-sample forecasts (extend = H):
+// every series runs H steps further, so that the window that ends at its last observation counts as complete; a series too
+// short for one window, or too long for H more rows, takes no part.
+struct Lengths {
+    const int32_t *of;
+    int T, I, extend;
+    __device__ int run(int len) const
+    {
+        if (extend == 0) return clamp_len(len, T);
+        return len >= I && len <= T - extend ? len + extend : 0;
+    }
+    __device__ int at(int b) const { return run(of[b]); }
+};
+
 // ---------------------------------------------------------------------------
 // Loss normalisers (Section 3.5: padded outputs are masked out of the loss).
 // ---------------------------------------------------------------------------
 struct PrepArgs {
-    const int32_t *lengths;
+    Lengths lengths;
     Scalars *sc;
     int32_t *pmax;       // [NB] window positions needed by the longest series of every 16-series tile
     int NB;
-    int B, T, I, H;
+    int B, H;
     int cs_per_window;   // cell-state values per valid window in the cell-state penalty: hidden * blocks
 };
 
-__device__ void prep_body(const PrepArgs &pa)
+// One workgroup reads all lengths, eight requests in flight per thread, of four lengths each where the caller's array is
+// aligned for that (65 536 series: 26 us a length at a time as a launch of its own; now beside the recursions, which take
+// 18 us).  The counts are whole numbers: any order of adding them up gives the same sums.
+__device__ void prep_body(const PrepArgs &pa, float *scratch)
 {
-    const int32_t *__restrict__ lengths = pa.lengths;
-    Scalars *__restrict__ sc = pa.sc;
-    const int B = pa.B, T = pa.T, I = pa.I, H = pa.H;
-    __shared__ double s_pin[256], s_lv[256];
-    double np_ = 0.0, nl = 0.0;
-    // eight independent loads in flight per thread: one workgroup has to read all lengths
-    for (int b0 = threadIdx.x; b0 < B; b0 += 8 * 256) {
+    const Lengths L = pa.lengths;
+    unsigned long long *s_pin = reinterpret_cast<unsigned long long *>(scratch), *s_lv = s_pin + 256;
+    unsigned long long np_ = 0, nl = 0;
+    auto count = [&](int raw) {
+        const int l = L.run(raw), windows = l - L.I - pa.H + 1;
+        if (windows > 0) np_ += (unsigned)windows;
+        if (l > 2) nl += (unsigned)(l - 2);
+    };
+    const bool aligned = (reinterpret_cast<size_t>(L.of) & 15) == 0;
+    const int quads = aligned ? pa.B / 4 : 0;
+    for (int q0 = threadIdx.x; q0 < quads; q0 += 8 * 256) {
+        int4 len[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int q = q0 + k * 256;
+            len[k] = reinterpret_cast<const int4 *>(L.of)[q < quads ? q : quads - 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (q0 + k * 256 < quads) { count(len[k].x); count(len[k].y); count(len[k].z); count(len[k].w); }
+    }
+    for (int b0 = 4 * quads + threadIdx.x; b0 < pa.B; b0 += 8 * 256) {
         int len[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int b = b0 + k * 256;
-            len[k] = b < B ? lengths[b] : 0;
-        }
+        for (int k = 0; k < 8; ++k) len[k] = L.of[min(b0 + k * 256, pa.B - 1)];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int l = clamp_len(len[k], T);
-            const int Pb = l - I - H + 1;
-            if (Pb > 0) np_ += (double)Pb * H;
-            if (l > 2) nl += (double)(l - 2);
-        }
+        for (int k = 0; k < 8; ++k)
+            if (b0 + k * 256 < pa.B) count(len[k]);
     }
     s_pin[threadIdx.x] = np_;
     s_lv[threadIdx.x] = nl;
@@ -62,22 +87,23 @@ __device__ void prep_body(const PrepArgs &pa)
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        sc->inv_n_pin = s_pin[0] > 0.0 ? (float)(1.0 / s_pin[0]) : 0.0f;
-        sc->inv_n_lv = s_lv[0] > 0.0 ? (float)(1.0 / s_lv[0]) : 0.0f;
-        const double n_cs = s_pin[0] / (double)H * (double)pa.cs_per_window;   // valid windows x hidden x blocks
-        sc->inv_n_cs = n_cs > 0.0 ? (float)(1.0 / n_cs) : 0.0f;
+        const double windows = (double)s_pin[0], n_pin = windows * pa.H, n_lv = (double)s_lv[0];
+        pa.sc->inv_n_pin = n_pin > 0.0 ? (float)(1.0 / n_pin) : 0.0f;
+        pa.sc->inv_n_lv = n_lv > 0.0 ? (float)(1.0 / n_lv) : 0.0f;
+        const double n_cs = windows * (double)pa.cs_per_window;   // valid windows x hidden x blocks
+        pa.sc->inv_n_cs = n_cs > 0.0 ? (float)(1.0 / n_cs) : 0.0f;
     }
 }
 
 // Ragged batches (Section 8.1: padding multiplies the iterations of the recursions): every later kernel
 // stops a 16-series tile at the number of window positions its longest series has.  One thread per tile.
-__device__ void pmax_body(const PrepArgs &pa, int first_block, int n_blocks)
+__device__ void pmax_body(const PrepArgs &pa, int block, int n_blocks)
 {
-    for (int bt = (blockIdx.x - first_block) * 256 + threadIdx.x; bt < pa.NB; bt += n_blocks * 256) {
+    for (int bt = block * 256 + threadIdx.x; bt < pa.NB; bt += n_blocks * 256) {
         int best = 0;
         for (int k = 0; k < kTileN; ++k) {
             const int b = bt * kTileN + k;
-            if (b < pa.B) best = max(best, clamp_len(pa.lengths[b], pa.T) - pa.I - pa.H + 1);
+            if (b < pa.B) best = max(best, pa.lengths.at(b) - pa.lengths.I - pa.H + 1);
         }
         pa.pmax[bt] = best;
     }
@@ -113,18 +139,18 @@ struct PackLstmArgs {
 //   forward  [wave][column k of x ; h][lane]: gate l%4 of unit wave*HT + min(l/4, HT-1) (the blocks past HT
 //            repeat the last unit, so that all lanes do the same work on the same addresses)
 //   reverse  [wave][group g][k-step 4*u + gate][lane]: W[gate, unit wave*HT + u][column 64*g + l]
-__device__ void pack_forward_narrow(const PackLstmArgs &a)
+__device__ void pack_forward_narrow(const PackLstmArgs &a, int block, int n_blocks)
 {
     const int KT4 = 4 * (a.KXT + a.HT), n = 4 * KT4 * 64;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int lane = idx & 63, k = (idx >> 6) % KT4, w = (idx >> 6) / KT4;
         a.fwd[idx] = a.at_row(lane & 3, w * a.HT + min(lane >> 2, a.HT - 1), k);
     }
 }
-__device__ void pack_backward_narrow(const PackLstmArgs &a)
+__device__ void pack_backward_narrow(const PackLstmArgs &a, int block, int n_blocks)
 {
     const int NG = (4 * (a.KXT + a.HT) + 63) / 64, n = 4 * NG * 4 * a.HT * 64;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int lane = idx & 63, ks = (idx >> 6) % (4 * a.HT), g = ((idx >> 6) / (4 * a.HT)) % NG, w = (idx >> 6) / (4 * a.HT * NG);
         a.bwd[idx] = a.at_row(ks & 3, w * a.HT + (ks >> 2), 64 * g + lane);
     }
@@ -133,11 +159,11 @@ __device__ void pack_backward_narrow(const PackLstmArgs &a)
 // Operands of the 16-series forward kernel: three bf16 parts of W (three_term.h) as [unit tile][quads of x, then of
 // h][lane][dword], and the bias as [unit tile][unit][gate].  Row 4g+r of unit tile mt is gate r of unit 4mt+g; lane
 // group k of a pair of input tiles stands for unit k of each.
-__device__ void pack_forward(const PackLstmArgs &a)
+__device__ void pack_forward(const PackLstmArgs &a, int block, int n_blocks)
 {
     const int npx = (a.KXT + 1) / 2, nph = (a.HT + 1) / 2, qx = tt_a_quads(npx), quads = qx + tt_a_quads(nph);
     const int n = a.HT * quads * 256;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, mt = (idx >> 8) / quads;
         const int i = lane & 15, k = lane >> 4, unit = 4 * mt + (i >> 2), gate = i & 3;
         const bool in_x = q < qx;
@@ -145,7 +171,7 @@ __device__ void pack_forward(const PackLstmArgs &a)
         const Parts p = split_pair(splittable(a.at(gate, unit, in_x, 8 * w.pair + k)), splittable(a.at(gate, unit, in_x, 8 * w.pair + 4 + k)));
         reinterpret_cast<unsigned *>(a.fwd)[idx] = part_of(p, w.part);
     }
-    for (int j = blockIdx.x * 256 + threadIdx.x; j < a.HT * 16; j += gridDim.x * 256) {
+    for (int j = block * 256 + threadIdx.x; j < a.HT * 16; j += n_blocks * 256) {
         const int gate = j & 3, unit = j >> 2;   // (mt*4+g)*4 + r  ->  unit = 4mt+g
         a.bias[j] = unit < a.h ? a.b[gate * a.h + unit] : 0.0f;
     }
@@ -155,11 +181,11 @@ __device__ void pack_forward(const PackLstmArgs &a)
 // group k of unit tile t is unit 4t+k, its dwords are the gate pairs (0, 1) and (2, 3); row 4g+r of a row tile is unit
 // g of its unit tile r.  The row tiles of x come first; the unit tiles of the others are those of h and then the
 // merged ones of x (three_term.h).
-__device__ void pack_backward(const PackLstmArgs &a)
+__device__ void pack_backward(const PackLstmArgs &a, int block, int n_blocks)
 {
     const int rx = bwd_x_row_tiles(a.HT, a.KXT), ml = bwd_merged_tiles(a.HT, a.KXT), tiles = bwd_even_tiles(a.HT);
     const int n = bwd_pack_dwords(a.HT, a.KXT);
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int d = idx & 1, lane = (idx >> 1) & 63, part = (idx >> 7) % 3, t = (idx / 384) % tiles, rt = idx / (384 * tiles);
         const int i = lane & 15, unit = 4 * t + (lane >> 4);
         const int slot = 4 * (rt < rx ? rt : rt - rx) + (i & 3);
@@ -173,23 +199,23 @@ __device__ void pack_backward(const PackLstmArgs &a)
 
 // The same for the fp32 kernel (hidden sizes above 52).  Transposed contraction: k-step 4mt+gate, lane group = unit within
 // tile; output row 4g+r of tile mb is row g of input unit tile 4mb+r.
-__device__ void pack_backward_fp32(const PackLstmArgs &a)
+__device__ void pack_backward_fp32(const PackLstmArgs &a, int block, int n_blocks)
 {
     const int MB = (a.KXT + a.HT + 3) / 4, n = MB * 4 * a.HT * 64;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < n; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int lane = idx & 63, ks = (idx >> 6) % (4 * a.HT), mb = (idx >> 6) / (4 * a.HT);
         const int i = lane & 15;
         a.bwd[idx] = a.at_row(ks & 3, 4 * (ks >> 2) + (lane >> 4), 4 * (4 * mb + (i & 3)) + (i >> 2));
     }
 }
 
-__device__ void pack_lstm_body(const PackLstmArgs &a)
+__device__ void pack_lstm_body(const PackLstmArgs &a, int block, int n_blocks)
 {
-    if (a.narrow_fwd) pack_forward_narrow(a);
-    else pack_forward(a);
-    if (a.narrow_bwd) pack_backward_narrow(a);
-    else if (bwd_three_term(a.HT)) pack_backward(a);
-    else pack_backward_fp32(a);
+    if (a.narrow_fwd) pack_forward_narrow(a, block, n_blocks);
+    else pack_forward(a, block, n_blocks);
+    if (a.narrow_bwd) pack_backward_narrow(a, block, n_blocks);
+    else if (bwd_three_term(a.HT)) pack_backward(a, block, n_blocks);
+    else pack_backward_fp32(a, block, n_blocks);
 }
 
 struct PackHeadArgs {
@@ -198,12 +224,12 @@ struct PackHeadArgs {
     int h, H, HT, MA, MO, OT;
 };
 
-__device__ void pack_head_body(const PackHeadArgs &a)
+__device__ void pack_head_body(const PackHeadArgs &a, int block, int n_blocks)
 {
     const int nWaF = a.MA * a.HT * 64, nbaF = a.MA * 16, nWoF = a.MO * a.HT * 64, nboF = a.MO * 16;
     const int nWoT = a.MA * a.OT * 64, nWaT = a.MA * a.HT * 64;
     const int total = nWaF + nbaF + nWoF + nboF + nWoT + nWaT;
-    for (int idx = blockIdx.x * 256 + threadIdx.x; idx < total; idx += gridDim.x * 256) {
+    for (int idx = block * 256 + threadIdx.x; idx < total; idx += n_blocks * 256) {
         int j = idx;
         if (j < nWaF) {
             const int lane = j & 63, q = (j >> 6) % a.HT, ma = (j >> 6) / a.HT;
@@ -252,22 +278,78 @@ __device__ void pack_head_body(const PackHeadArgs &a)
     }
 }
 
-// One launch for everything that only depends on the weights and the lengths:
-// blockIdx.z selects an LSTM layer, the output stage, or the loss normalisers.
+// Out-of-sample forecasts, Section 3.4 with Eq. (4) and (5): the forward pass is run with every length extended by H (the
+// rows past a series never reach its forecast: the network is causal in the window position).  The later kernels read the
+// extended lengths from `ext`.
+//
+// The same workgroups find what those outputs depend on: per 16-series tile and layer, the residue classes of the dilation
+// that the forward kernels have to walk (ForwardMode::need).  Top layer: the classes of the last windows.  Below: a layer is
+// read at the positions of the classes above it, which fall into every class congruent to one of those modulo the common
+// divisor g of the two dilations.  (Where every position is a class of its own, any multiple of the other dilation stands
+// for this one: g is that other dilation.)  One thread per series, sixteen of a tile next to each other.
+struct ClassArgs {
+    Lengths lengths;
+    int32_t *ext;        // [B]
+    unsigned *need;      // [L][NB][kNeedWords]; null: not wanted
+    int L, NB, B;
+    int dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: g of layers l and l + 1
+};
+__device__ void extend_body(const ClassArgs &a, int block, unsigned *masks)
+{
+    // masks: [this layer, the one above][tile][word]
+    const int b = block * 256 + threadIdx.x;
+    const int len = b < a.B ? a.lengths.at(b) : 0;      // (a series that takes no part has length 0)
+    if (b < a.B) a.ext[b] = len;
+    if (!a.need) return;
+    const int last = len - a.lengths.extend - a.lengths.I;      // its last window
+    const int grp = threadIdx.x >> 4, k = threadIdx.x & 15, bt = b >> 4;
+    for (int l = a.L - 1; l >= 0; --l) {
+        const int d = a.dil[l];
+        unsigned *mine = masks + ((l & 1) * 16 + grp) * kNeedWords;
+        const unsigned *over = masks + (((l + 1) & 1) * 16 + grp) * kNeedWords;
+        __syncthreads();
+        if (k < kNeedWords) mine[k] = 0u;
+        __syncthreads();
+        if (d <= kNeedMost) {                           // (more classes than bits: the mask is not read)
+            if (l == a.L - 1) {
+                if (len > 0) atomicOr(&mine[last % d >> 5], 1u << (last % d & 31));
+            } else {
+                const int above = a.dil[l + 1], g = a.gcd_above[l];
+                for (int r = k; r < g; r += 16) {
+                    bool any = above > kNeedMost;
+                    for (int q = r; q < above && !any; q += g) any = (over[q >> 5] >> (q & 31)) & 1;
+                    if (any)
+                        for (int q = r; q < d; q += g) atomicOr(&mine[q >> 5], 1u << (q & 31));
+                }
+            }
+        }
+        __syncthreads();
+        if (k < kNeedWords && bt < a.NB) a.need[((size_t)l * a.NB + bt) * kNeedWords + k] = mine[k];
+    }
+}
+
+// Everything that only depends on the weights and the lengths, by workgroup: the loss normalisers, the position bounds,
+// the extended lengths, the operands of every layer and of the output stage.  `scratch`: kSetupScratch floats of LDS.
+constexpr int kSetupScratch = 1024;
 struct SetupArgs {
     PackLstmArgs lstm[kMaxLayers];
     PackHeadArgs head;
     PrepArgs prep;
-    int L, pack;     // pack = 0: only the loss normalisers
+    ClassArgs classes;
+    int L, pmax_blocks, extend_blocks, pack_blocks;     // pack_blocks: per layer (0: nothing is packed)
+    int blocks() const { return 1 + pmax_blocks + extend_blocks + (pack_blocks ? (L + 1) * pack_blocks : 0); }
 };
-
-__global__ void __launch_bounds__(256) setup_kernel(SetupArgs a)
+__device__ void setup_body(const SetupArgs &a, int block, float *scratch)
 {
-    const int z = blockIdx.z;
-    if (a.pack && z < a.L) pack_lstm_body(a.lstm[z]);
-    else if (a.pack && z == a.L) pack_head_body(a.head);
-    else if (blockIdx.x == 0) prep_body(a.prep);
-    else pmax_body(a.prep, 1, gridDim.x - 1);
+    if (block == 0) { prep_body(a.prep, scratch); return; }
+    block -= 1;
+    if (block < a.pmax_blocks) { pmax_body(a.prep, block, a.pmax_blocks); return; }
+    block -= a.pmax_blocks;
+    if (block < a.extend_blocks) { extend_body(a.classes, block, reinterpret_cast<unsigned *>(scratch)); return; }
+    block -= a.extend_blocks;
+    const int z = block / a.pack_blocks, k = block % a.pack_blocks;
+    if (z < a.L) pack_lstm_body(a.lstm[z], k, a.pack_blocks);
+    else pack_head_body(a.head, k, a.pack_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -280,10 +362,11 @@ __global__ void __launch_bounds__(256) setup_kernel(SetupArgs a)
 // ---------------------------------------------------------------------------
 struct EsArgs {
     const float *y;           // [T][B]
-    const int32_t *lengths;
+    Lengths lengths;
     const float *es;          // [K][B]
     float *lvl, *S1, *S2, *u, *v;   // [T][Bp], one column per lane of every wave
-    float *lv_partial;        // [gridDim.x]
+    float *lv_partial;        // [blocks]
+    int blocks;               // workgroups of the recursions; the launch's others do the set-up
     int B, Bp, T, n_seas, m1, m2, logit;   // Bp: row stride of the time-major arrays (batch padded to 64)
     int row_gamma1, row_gamma2, row_s1, row_s2;
 };
@@ -306,17 +389,25 @@ constexpr int kEsAhead = 4;                 // chunks between the request of a r
 // staged per step: level, de-seasonalised value, and one factor per seasonality
 constexpr int es_stage_floats(int n_seas) { return 2 * kEsChunk * (2 + n_seas) * 64; }
 
+//
+// The set-up work needs nothing of the recursions and they nothing of it, and neither fills the chip: one launch has both
+// (as two launches: 11 + 6.5 us at 4096 quarterly series, 9.9 + 4.8 us at 16; a forecast had a third one for the lengths).
 template <int NS, int CS>
-__global__ void __launch_bounds__(NS == 0 ? 192 : 256) es_forward_kernel(EsArgs a)
+__global__ void __launch_bounds__(256) es_forward_kernel(EsArgs a, SetupArgs setup)
 {
-    extern __shared__ float ring[];   // [m1 + m2][64] rings, then [2][kEsChunk][2 + NS][64] staging
+    extern __shared__ __align__(16) float ring[];   // [m1 + m2][64] rings, then [2][kEsChunk][2 + NS][64] staging
+    if ((int)blockIdx.x >= a.blocks) {
+        setup_body(setup, blockIdx.x - a.blocks, ring);
+        return;
+    }
     constexpr int CH = kEsChunk, NF = 2 + NS;
     static_assert(CH % CS == 0, "groups tile a chunk");
     const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (NS == 0 && role == 3) return;       // (no seasonal factors to store)
     const int lane = threadIdx.x & 63;
     const int b = blockIdx.x * 64 + lane;
     const bool in_batch = b < a.B;
-    const int len = in_batch ? clamp_len(a.lengths[b], a.T) : 0;
+    const int len = in_batch ? a.lengths.at(b) : 0;
     float *ring1 = ring, *ring2 = ring + (size_t)a.m1 * 64;
     float *stage = ring + (size_t)(a.m1 + a.m2) * 64;       // [buffer][step][lt, q, s1, s2][lane]
     // Ragged batches (Section 8.1): the sweep ends at the longest series of the wave.  Rows between a
@@ -815,7 +906,7 @@ constexpr int es_bwd_stage_floats(int n_seas) { return 2 * kEsBwdChunk * es_bwd_
 template <int NS>
 __global__ void __launch_bounds__(64 * (1 + kEsBwdHelpers)) es_backward_kernel(EsBwdArgs a)
 {
-    extern __shared__ float ring[];           // [m1 + m2][64] rings, then [2][kEsBwdChunk][4 + 4 NS][64] staging
+    extern __shared__ __align__(16) float ring[];   // [m1 + m2][64] rings, then [2][kEsBwdChunk][4 + 4 NS][64] staging
     constexpr int CH = kEsBwdChunk, NC = es_bwd_coefs(NS);
     const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -1183,18 +1274,27 @@ hipError_t allow_large_lds(const void *kernel, size_t lds)
 }
 }  // namespace
 
-hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, hipStream_t st)
+namespace {
+SetupArgs setup_args(const Plan &pl, const Lengths &len, const float *weights, unsigned *need, float *ws)
 {
     SetupArgs a{};
     a.L = pl.L;
-    a.pack = weights != nullptr;
-    a.prep = PrepArgs{lengths, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
-                      pl.B, pl.T, pl.I, pl.H, pl.h * pl.cfg.n_blocks};
-    if (!a.pack) {
-        // block 0 counts the loss normalisers, the others find the position bound of every tile
-        setup_kernel<<<dim3(1 + std::min((pl.NB + 255) / 256, 63), 1, 1), 256, 0, st>>>(a);
-        return hipGetLastError();
+    a.prep = PrepArgs{len, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
+                      pl.B, pl.H, pl.h * pl.cfg.n_blocks};
+    a.pmax_blocks = std::min((pl.NB + 255) / 256, 63);
+    if (len.extend) {
+        ClassArgs &c = a.classes;
+        c.lengths = len;
+        c.ext = reinterpret_cast<int32_t *>(ws + pl.len_ext);
+        c.need = need;
+        c.L = pl.L; c.NB = pl.NB; c.B = pl.B;
+        for (int l = 0; l < pl.L; ++l) {
+            const int d = c.dil[l] = pl.layer[l].dil, above = l + 1 < pl.L ? pl.layer[l + 1].dil : 0;
+            c.gcd_above[l] = above == pl.P ? d : d == pl.P ? above : std::gcd(d, above);
+        }
+        a.extend_blocks = (pl.B + 255) / 256;
     }
+    if (!weights) return a;
     int max_total = 256;
     for (int l = 0; l < pl.L; ++l) {
         const LayerPlan &lp = pl.layer[l];
@@ -1207,24 +1307,27 @@ hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *wei
     a.head = PackHeadArgs{weights + pl.Wa_off, weights + pl.ba_off, weights + pl.Wo_off, weights + pl.bo_off,
                           f + hp.WaF, f + hp.baF, f + hp.WoF, f + hp.boF, b + hp.WoT, b + hp.WaT,
                           pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
-    const int blocks = std::max(2, std::min((max_total + 255) / 256, 64));   // the bodies loop over their elements
-    setup_kernel<<<dim3(blocks, 1, pl.L + 2), 256, 0, st>>>(a);
-    return hipGetLastError();
+    a.pack_blocks = std::min((max_total + 255) / 256, 64);      // (the bodies loop over their elements)
+    return a;
 }
+}  // namespace
 
-hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *lengths, const float *es, float *ws,
-                             hipStream_t st)
+hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *lengths, const float *es, const float *weights,
+                             float *ws, const ForwardMode &mode, hipStream_t st)
 {
     const esrnn_config &c = pl.cfg;
-    EsArgs a{y, lengths, es, ws + pl.lvl, ws + pl.S1, ws + pl.S2, ws + pl.u, ws + pl.v,
-             ws + pl.loss_partial + (pl.n_loss_partial - pl.es_blocks),
+    const Lengths len{lengths, pl.T, pl.I, mode.out_of_sample ? pl.H : 0};
+    const SetupArgs setup = setup_args(pl, len, weights, mode.need, ws);
+    EsArgs a{y, len, es, ws + pl.lvl, ws + pl.S1, ws + pl.S2, ws + pl.u, ws + pl.v,
+             ws + pl.loss_partial + (pl.n_loss_partial - pl.es_blocks), pl.es_blocks,
              pl.B, pl.Bt, pl.T, c.n_seas, c.n_seas >= 1 ? c.m1 : 0, c.n_seas >= 2 ? c.m2 : 0,
              c.param_space == ESRNN_PARAMS_LOGIT, pl.row_gamma1, pl.row_gamma2, pl.row_s1, pl.row_s2};
+    static_assert(es_stage_floats(0) >= kSetupScratch, "the set-up works in the same LDS");
     const size_t lds = ((size_t)(a.m1 + a.m2) * 64 + es_stage_floats(c.n_seas)) * sizeof(float);
     auto run = [&](auto kernel) {
         hipError_t e = allow_large_lds(reinterpret_cast<const void *>(kernel), lds);
         if (e != hipSuccess) return e;
-        kernel<<<pl.es_blocks, c.n_seas == 0 ? 192 : 256, lds, st>>>(a);
+        kernel<<<pl.es_blocks + setup.blocks(), 256, lds, st>>>(a, setup);
         return hipGetLastError();
     };
     // steps per group: the largest divisor of 8 that no period is shorter than
@@ -1305,58 +1408,8 @@ hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *len
 }
 
 // ---------------------------------------------------------------------------
-// Out-of-sample forecasts, Section 3.4 with Eq. (4) and (5).  The forward pass is
-// run with every length extended by H: the window that ends at a series' last
-// observation then counts as a complete window (its "targets" are rows past the
-// series and never reach the forecast), and the network is causal in the window
-// position, so its output there is the out-of-sample output.
+// Out-of-sample forecasts (extend_body above) at the end of every series.
 // ---------------------------------------------------------------------------
-//
-// The same kernel finds what those outputs depend on: per 16-series tile and layer, the residue classes of the dilation
-// that the forward kernels have to walk (ForwardMode::need).  Top layer: the classes of the last windows.  Below: a layer is
-// read at the positions of the classes above it, which fall into every class congruent to one of those modulo the common
-// divisor g of the two dilations.  (Where every position is a class of its own, any multiple of the other dilation stands
-// for this one: g is that other dilation.)  One thread per series, sixteen of a tile next to each other.
-struct ClassArgs {
-    unsigned *need;      // [L][NB][kNeedWords]; null: not wanted
-    int L, NB;
-    int dil[kMaxLayers], gcd_above[kMaxLayers];   // gcd_above[l]: g of layers l and l + 1
-};
-__global__ void __launch_bounds__(256) extend_lengths_kernel(const int32_t *__restrict__ lengths, int32_t *__restrict__ ext,
-                                                              int B, int T, int I, int H, ClassArgs a)
-{
-    __shared__ unsigned s_masks[2][16][kNeedWords];    // [this layer, the one above][tile][word]
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    const int len = b < B ? lengths[b] : 0;
-    const bool takes_part = len >= I && len <= T - H;   // (a series that does not gets length 0)
-    if (b < B) ext[b] = takes_part ? len + H : 0;
-    if (!a.need) return;
-    const int grp = threadIdx.x >> 4, k = threadIdx.x & 15, bt = b >> 4;
-    for (int l = a.L - 1; l >= 0; --l) {
-        const int d = a.dil[l];
-        unsigned *mine = s_masks[l & 1][grp];
-        const unsigned *over = s_masks[(l + 1) & 1][grp];
-        __syncthreads();
-        if (k < kNeedWords) mine[k] = 0u;
-        __syncthreads();
-        if (d <= kNeedMost) {                           // (more classes than bits: the mask is not read)
-            if (l == a.L - 1) {
-                if (b < B && takes_part) atomicOr(&mine[(len - I) % d >> 5], 1u << ((len - I) % d & 31));
-            } else {
-                const int above = a.dil[l + 1], g = a.gcd_above[l];
-                for (int r = k; r < g; r += 16) {
-                    bool any = above > kNeedMost;
-                    for (int q = r; q < above && !any; q += g) any = (over[q >> 5] >> (q & 31)) & 1;
-                    if (any)
-                        for (int q = r; q < d; q += g) atomicOr(&mine[q >> 5], 1u << (q & 31));
-                }
-            }
-        }
-        __syncthreads();
-        if (k < kNeedWords && bt < a.NB) a.need[((size_t)l * a.NB + bt) * kNeedWords + k] = mine[k];
-    }
-}
-
 // forecast[b][h-1] = exp(output_h + ln l_t) * S1[t + ((h-1) mod m1) + 1] * S2[...], t = len-1: the last m
 // factors the recursion produced, repeated with their period (Eq. (4)).
 __global__ void __launch_bounds__(256) forecast_tail_kernel(const float *__restrict__ O, const float *__restrict__ u,
@@ -1403,21 +1456,6 @@ __global__ void __launch_bounds__(256) forecast_metrics_kernel(const float *__re
     for (int t = m; t < len; ++t) s_naive += fabsf(y[(size_t)t * B + b] - y[(size_t)(t - m) * B + b]);
     smape[b] = s_sym / (float)H;
     mase[b] = (s_abs / (float)H) / (s_naive / (float)(len - m));
-}
-
-hipError_t launch_extend_lengths(const Plan &pl, const int32_t *lengths, float *ws, const ForwardMode &mode, hipStream_t st)
-{
-    ClassArgs a{};
-    a.need = mode.need;
-    a.L = pl.L;
-    a.NB = pl.NB;
-    for (int l = 0; l < pl.L; ++l) {
-        const int d = a.dil[l] = pl.layer[l].dil, above = l + 1 < pl.L ? pl.layer[l + 1].dil : 0;
-        a.gcd_above[l] = above == pl.P ? d : d == pl.P ? above : std::gcd(d, above);
-    }
-    extend_lengths_kernel<<<(pl.B + 255) / 256, 256, 0, st>>>(lengths, reinterpret_cast<int32_t *>(ws + pl.len_ext), pl.B,
-                                                              pl.T, pl.I, pl.H, a);
-    return hipGetLastError();
 }
 
 hipError_t launch_forecast_tail(const Plan &pl, const int32_t *lengths, float *ws, float *out, hipStream_t st)

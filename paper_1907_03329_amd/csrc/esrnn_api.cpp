@@ -25,7 +25,7 @@ struct esrnn_handle {
     int n_stages;
     Stage stage[kMaxStages];
     // stage indices
-    int st_setup, st_es_fwd, st_win_fwd, st_lstm_fwd[kMaxLayers], st_head, st_fc, st_loss;
+    int st_es_fwd, st_win_fwd, st_lstm_fwd[kMaxLayers], st_head, st_fc, st_loss;
     int st_lstm_bwd[kMaxLayers], st_win_bwd, st_es_bwd, st_reduce, st_tail;
     const int32_t *categories;   // device array of the caller, or null
     bool forward_only;           // esrnn_forward skips the reverse pass of the output stage; esrnn_backward is refused
@@ -84,7 +84,6 @@ esrnn_status esrnn_create(const esrnn_config *cfg, esrnn_handle **out)
     h->forward_only = false;
     h->n_stages = 0;
     const Plan &pl = h->plan;
-    h->st_setup = add_stage(h, "setup", 0);
     h->st_es_fwd = add_stage(h, "es_forward", 0);
     h->st_win_fwd = add_stage(h, "window_forward", 0);
     for (int l = 0; l < pl.L; ++l) h->st_lstm_fwd[l] = add_stage(h, "lstm_forward_l%d", l);
@@ -180,9 +179,8 @@ esrnn_status esrnn_forward(esrnn_handle *h, const float *y, const int32_t *lengt
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
     h->forward_done = false;
-    const ForwardMode mode{!h->forward_only, nullptr};
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, weights, ws, st); }));
-    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, ws, st); }));
+    const ForwardMode mode{!h->forward_only, nullptr, false};
+    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, weights, ws, mode, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     for (int l = 0; l < pl.L; ++l)
         ESRNN_TRY(run_stage(h, h->st_lstm_fwd[l], st, [&] { return launch_lstm_forward(pl, l, lengths, weights, ws, mode, st); }));
@@ -279,10 +277,8 @@ esrnn_status esrnn_predict(esrnn_handle *h, const float *y, const int32_t *lengt
     // Only the outputs at the last windows are wanted: no stash, no residue class that they do not depend on.  The masks
     // (8 words a layer and tile) lie where the outputs come, which are written once the last layer has read them.
     const bool room = (size_t)pl.L * 8 <= (size_t)pl.P * pl.OP * 16;
-    const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr};
-    ESRNN_TRY(launch_extend_lengths(pl, lengths, ws, mode, st));
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, ext, weights, ws, st); }));
-    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, ext, es_params, ws, st); }));
+    const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr, true};
+    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, weights, ws, mode, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     for (int l = 0; l < pl.L; ++l)
         ESRNN_TRY(run_stage(h, h->st_lstm_fwd[l], st, [&] { return launch_lstm_forward(pl, l, ext, weights, ws, mode, st); }));
@@ -329,8 +325,8 @@ esrnn_status esrnn_es_window_forward(esrnn_handle *h, const float *y, const int3
     const Plan &pl = h->plan;
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    ESRNN_TRY(run_stage(h, h->st_setup, st, [&] { return launch_setup(pl, lengths, nullptr, ws, st); }));
-    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, ws, st); }));
+    const ForwardMode mode{false, nullptr, false};
+    ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, nullptr, ws, mode, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
     return ESRNN_OK;
 }

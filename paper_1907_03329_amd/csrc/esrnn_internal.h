@@ -120,16 +120,19 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl);
 // ---- kernel launchers (each returns hipGetLastError()) -----------------------------------
 // What a forward pass is for.  `stash`: a reverse pass may follow, so gates and cell states are written.  `need` (null:
 // everything): only the outputs at the last window of every series are wanted; [L][NB][8] bit masks of the residue classes
-// of every layer and series tile that those outputs depend on, by launch_extend_lengths.  For the 16-series kernels: a
+// of every layer and series tile that those outputs depend on, by launch_es_forward.  For the 16-series kernels: a
 // layer on the 4-series kernels runs its classes side by side, writes the stash and computes every class (what it reads at
 // positions that a layer below has left out reaches no class that is wanted).
+// `out_of_sample`: the lengths given are to be extended by the horizon (launch_es_forward leaves the extended ones in
+// Plan::len_ext for the later stages).
 struct ForwardMode {
     bool stash;
     unsigned *need;
+    bool out_of_sample;
 };
-hipError_t launch_setup(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, hipStream_t st);
-hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *lengths, const float *es,
-                             float *ws, hipStream_t st);
+// smoothing recursions and, in the same launch, the set-up: loss normalisers, position bounds, operands (none if weights is null)
+hipError_t launch_es_forward(const Plan &pl, const float *y, const int32_t *lengths, const float *es, const float *weights,
+                             float *ws, const ForwardMode &mode, hipStream_t st);
 hipError_t launch_window_forward(const Plan &pl, const int32_t *categories, float *ws, hipStream_t st);
 hipError_t launch_lstm_forward(const Plan &pl, int layer, const int32_t *lengths, const float *weights, float *ws,
                                const ForwardMode &mode, hipStream_t st);
@@ -173,7 +176,6 @@ hipError_t launch_adam_update_indexed(const Plan &pl, const esrnn_adam_config &o
                                       const float *grad_weights, float *m_w, float *v_w, float *es_store,
                                       const float *grad_es, float *m_es, float *v_es, int32_t *counts,
                                       const int32_t *index, int N, float *ws, hipStream_t st);
-hipError_t launch_extend_lengths(const Plan &pl, const int32_t *lengths, float *ws, const ForwardMode &mode, hipStream_t st);
 hipError_t launch_forecast_tail(const Plan &pl, const int32_t *lengths, float *ws, float *out, hipStream_t st);
 hipError_t launch_forecast_metrics(const Plan &pl, const float *forecasts, const float *actuals, const float *y,
                                    const int32_t *lengths, int m, float *smape, float *mase, hipStream_t st);
