@@ -702,6 +702,163 @@ __device__ __forceinline__ float level_penalty_grad(const float *__restrict__ u,
 }
 
 // ---------------------------------------------------------------------------
+// Weight-gradient reduction: sums the per-workgroup (LSTM) and per-wave (head)
+// partial tiles in a fixed order and writes the caller's packing.
+// ---------------------------------------------------------------------------
+// Stage 1: every job (one block of partial results per producer workgroup or
+// wave) is cut into `splits` interleaved subsets of the producers; a thread sums
+// one element over one subset.  Stage 2 (the kernels below) sums the subsets and
+// writes the caller's packing.  Both orders are fixed.
+//
+// Neither stage has anything to do with the smoothing part of the reverse pass: the first is in the launch of the window
+// adjoint, the second in that of the recursions' adjoint, whose few workgroups are one long chain (as launches of their
+// own: 19 + 5 us at 4096 quarterly series, 5 + 4.6 us at 16).
+struct ReduceJob {
+    const float *src;
+    float *dst;          // [splits][n_elems]
+    unsigned stride;     // floats between consecutive partial blocks
+    int n_part, n_elems, splits;
+    int end;             // workgroups of this job and those before it
+};
+constexpr int kMaxReduceJobs = 2 * kMaxLayers + 1;
+struct ReduceJobs {
+    ReduceJob job[kMaxReduceJobs];
+    int blocks;          // 0: nothing to reduce
+};
+
+__device__ void reduce_stage1_body(const ReduceJobs &jobs, int block)
+{
+    int i = 0;
+    while (block >= jobs.job[i].end) ++i;
+    const ReduceJob &j = jobs.job[i];
+    if (i > 0) block -= jobs.job[i - 1].end;
+    const int chunks = (j.n_elems + 255) / 256;
+    const int e = block % chunks * 256 + threadIdx.x, sp = block / chunks;
+    if (e >= j.n_elems) return;
+    const float *src = j.src + e;
+    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+    int w = sp;
+    for (; w + 3 * j.splits < j.n_part; w += 4 * j.splits) {
+        a0 += src[(size_t)w * j.stride];
+        a1 += src[(size_t)(w + j.splits) * j.stride];
+        a2 += src[(size_t)(w + 2 * j.splits) * j.stride];
+        a3 += src[(size_t)(w + 3 * j.splits) * j.stride];
+    }
+    for (; w < j.n_part; w += j.splits) a0 += src[(size_t)w * j.stride];
+    j.dst[(size_t)sp * j.n_elems + e] = (a0 + a1) + (a2 + a3);
+}
+
+struct ReduceLstmArgs {
+    const float *dw_partial, *db_partial;
+    float *gW, *gb;
+    int NB, h, in_dim, HT, KXT;
+};
+
+// Sums `n_part` partial blocks for 64 consecutive elements per workgroup: the
+// four waves take interleaved quarters of the partials (each load instruction
+// reads 256 contiguous bytes of one partial), then combine in a fixed order.
+__device__ __forceinline__ float reduce_partials(const float *__restrict__ base, size_t stride, int n_part, int elem,
+                                                 bool active, float (*s_red)[64])
+{
+    const int e = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    float acc = 0.0f;
+    if (active) {
+        const float *src = base + elem;
+        int w = sl;
+        for (; w + 12 < n_part; w += 16) {
+            const float a0 = src[(size_t)w * stride], a1 = src[(size_t)(w + 4) * stride];
+            const float a2 = src[(size_t)(w + 8) * stride], a3 = src[(size_t)(w + 12) * stride];
+            acc += (a0 + a1) + (a2 + a3);
+        }
+        for (; w < n_part; w += 4) acc += src[(size_t)w * stride];
+    }
+    s_red[sl][e] = acc;
+    __syncthreads();
+    return (s_red[0][e] + s_red[1][e]) + (s_red[2][e] + s_red[3][e]);
+}
+
+__device__ void reduce_lstm_body(const ReduceLstmArgs &a, int block, float (*s_red)[64])
+{
+    const int KT = a.KXT + a.HT, MB = (KT + 3) / 4, ld = a.in_dim + a.h;
+    const int n_dw = a.HT * MB * 256, n_db = a.HT * 16;
+    const int n_dw_blocks = (n_dw + 63) / 64;
+    const int e = threadIdx.x & 63;
+    if (block < n_dw_blocks) {
+        const int idx = block * 64 + e;                  // element of the tile block: [tile][component][lane]
+        const float tot = reduce_partials(a.dw_partial, (size_t)n_dw, a.NB, idx, idx < n_dw, s_red);
+        if (threadIdx.x < 64 && idx < n_dw) {
+            const int lane = idx & 63, comp = (idx >> 6) & 3, tix = idx >> 8;
+            const int mt = tix / MB, nbk = tix % MB;
+            // tile row 4*gate + unit-in-tile sits in lane group `gate`, component `unit-in-tile`
+            const int gate = lane >> 4, unit = 4 * mt + comp;
+            const int xr = 16 * nbk + (lane & 15);
+            int col = -1;
+            if (xr < 4 * a.KXT) { if (xr < a.in_dim) col = xr; }
+            else if (xr - 4 * a.KXT < a.h) col = a.in_dim + xr - 4 * a.KXT;
+            if (unit < a.h && col >= 0) a.gW[(size_t)(gate * a.h + unit) * ld + col] = tot;
+        }
+    } else {
+        const int idx = (block - n_dw_blocks) * 64 + e;   // [unit tile][unit][gate]
+        const float tot = reduce_partials(a.db_partial, (size_t)n_db, a.NB, idx, idx < n_db, s_red);
+        if (threadIdx.x < 64 && idx < n_db) {
+            const int gate = idx & 3, unit = idx >> 2;
+            if (unit < a.h) a.gb[gate * a.h + unit] = tot;
+        }
+    }
+}
+
+struct ReduceHeadArgs {
+    const float *partial;
+    float *gWa, *gba, *gWo, *gbo;
+    int n_part, stride, h, H, HT, MA, MO, OT;
+};
+
+__device__ void reduce_head_body(const ReduceHeadArgs &a, int block, float (*s_red)[64])
+{
+    // partial block: dWo tiles [MO*MA][4][64], dWa tiles [MA*MA][4][64], dbo [4*OT], dba [4*HT]
+    const int offWa = a.MO * a.MA * 256, offbo = offWa + a.MA * a.MA * 256, offba = offbo + 4 * a.OT;
+    const int n = offba + 4 * a.HT;
+    const int idx = block * 64 + (threadIdx.x & 63);
+    const float tot = reduce_partials(a.partial, (size_t)a.stride, a.n_part, idx, idx < n, s_red);
+    if (threadIdx.x >= 64 || idx >= n) return;
+    if (idx < offbo) {
+        const bool isWa = idx >= offWa;
+        const int j = isWa ? idx - offWa : idx;
+        const int lane = j & 63, comp = (j >> 6) & 3, tix = j >> 8;
+        const int mt = tix / a.MA, nt = tix % a.MA;
+        const int row = 16 * mt + 4 * (lane >> 4) + comp, col = 16 * nt + (lane & 15);
+        if (col < a.h) {
+            if (isWa) { if (row < a.h) a.gWa[row * a.h + col] = tot; }
+            else if (row < a.H) a.gWo[row * a.h + col] = tot;
+        }
+    } else if (idx < offba) {
+        const int j = idx - offbo;
+        if (j < a.H) a.gbo[j] = tot;
+    } else {
+        const int j = idx - offba;
+        if (j < a.h) a.gba[j] = tot;
+    }
+}
+
+struct ReduceStage2Args {
+    ReduceLstmArgs lstm[kMaxLayers];
+    ReduceHeadArgs head;
+    int end[kMaxLayers + 1];    // workgroups of this layer (the last one: of the output stage) and those before it
+    int L;
+    int blocks() const { return end[kMaxLayers]; }      // 0: nothing to reduce
+};
+
+__device__ void reduce_stage2_body(const ReduceStage2Args &a, int block, float *scratch)
+{
+    float (*s_red)[64] = reinterpret_cast<float (*)[64]>(scratch);
+    int z = 0;
+    while (z < a.L && block >= a.end[z]) ++z;
+    if (z > 0) block -= a.end[z - 1];
+    if (z < a.L) reduce_lstm_body(a.lstm[z], block, s_red);
+    else reduce_head_body(a.head, block, s_red);
+}
+
+// ---------------------------------------------------------------------------
 // Window adjoint in gather form (no atomics): every x and z is v[.] - u[t], so
 //   gv[k] = sum_i gX[k-i][i] + sum_j gZ[k-(I-1)-j][j],  gu[t] = -(sum of row p = t-I+1),
 // with gZ = -gO, plus the gradient of the level penalty (Section 8.4).
@@ -712,28 +869,41 @@ __device__ __forceinline__ float level_penalty_grad(const float *__restrict__ u,
 // series therefore all run on the same XCD (workgroups go to the XCDs in turn), one after the other in
 // time order: the line is then fetched from memory once and found in that XCD's L2 afterwards.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) window_backward_kernel(const float *__restrict__ gX, const float *__restrict__ gO,
-                                                               const float *__restrict__ u, const int32_t *__restrict__ lengths,
-                                                               const Scalars *__restrict__ sc, float lambda,
-                                                               float *__restrict__ gu, float *__restrict__ gv,
-                                                               int P_all, int NB, int B, int Bp, int T, int I, int H, int xrows, int zrows,
-                                                               const int32_t *__restrict__ pmax, int t_chunks)
+struct WindowBwdArgs {
+    const float *gX, *gO, *u;
+    const int32_t *lengths;
+    const Scalars *sc;
+    float lambda;
+    float *gu, *gv;
+    int P, NB, B, Bp, T, I, H, xrows, zrows;    // Bp: row stride of the time-major arrays (the batch padded to 64)
+    const int32_t *pmax;
+    int t_chunks;        // gather: groups of four time steps
+    int R;               // streaming: slots of the ring
+    int blocks;          // workgroups of the window adjoint; the launch's others reduce weight gradients
+};
+
+__global__ void __launch_bounds__(256) window_backward_kernel(WindowBwdArgs a, ReduceJobs jobs)
 {
-    // Bp: row stride of the time-major arrays (the batch padded to 64); columns past the 16 * NB series of
-    // the tiles have no windows
+    if ((int)blockIdx.x >= a.blocks) {
+        reduce_stage1_body(jobs, blockIdx.x - a.blocks);
+        return;
+    }
+    const float *__restrict__ gX = a.gX, *__restrict__ gO = a.gO;
+    const int NB = a.NB, Bp = a.Bp, T = a.T, I = a.I, H = a.H, xrows = a.xrows, zrows = a.zrows;
+    // (columns past the 16 * NB series of the tiles have no windows)
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int cg = (slot / t_chunks) * 8 + xcd;                 // group of 64 series
-    const int t = (slot % t_chunks) * 4 + (threadIdx.x >> 6);
+    const int cg = (slot / a.t_chunks) * 8 + xcd;               // group of 64 series
+    const int t = (slot % a.t_chunks) * 4 + (threadIdx.x >> 6);
     if (cg * 64 >= Bp || t >= T) return;
     const int col = cg * 64 + (threadIdx.x & 63);
     const size_t idx = (size_t)t * Bp + col;
     if (col >= 16 * NB) {
-        gu[idx] = 0.0f;
-        gv[idx] = 0.0f;
+        a.gu[idx] = 0.0f;
+        a.gv[idx] = 0.0f;
         return;
     }
     const int bt = col >> 4, n = col & 15;
-    const int P = min(P_all, pmax[bt]);      // window gradients past the tile's longest series do not exist
+    const int P = min(a.P, a.pmax[bt]);      // window gradients past the tile's longest series do not exist
     float sv = 0.0f, su = 0.0f;
     for (int i = 0; i < I; ++i) {
         const int p = t - i;
@@ -750,10 +920,10 @@ __global__ void __launch_bounds__(256) window_backward_kernel(const float *__res
             for (int j = 0; j < H; ++j) su += gO[((size_t)(p * NB + bt) * zrows + j) * 16 + n];
         }
     }
-    if (lambda != 0.0f)
-        su += level_penalty_grad(u, Bp, col, t, col < B ? clamp_len(lengths[col], T) : 0, lambda * 2.0f * sc->inv_n_lv);
-    gu[idx] = su;
-    gv[idx] = sv;
+    if (a.lambda != 0.0f)
+        su += level_penalty_grad(a.u, Bp, col, t, col < a.B ? clamp_len(a.lengths[col], T) : 0, a.lambda * 2.0f * a.sc->inv_n_lv);
+    a.gu[idx] = su;
+    a.gv[idx] = sv;
 }
 
 // ---------------------------------------------------------------------------
@@ -767,13 +937,15 @@ __global__ void __launch_bounds__(256) window_backward_kernel(const float *__res
 // position.  The gather kernel above reads every element twice in 64-byte pieces; this one is the faster
 // of the two once there are enough tiles for the waves to hide each other's memory latency.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) window_backward_stream_kernel(const float *__restrict__ gX, const float *__restrict__ gO,
-                                                                      const float *__restrict__ u, const int32_t *__restrict__ lengths,
-                                                                      const Scalars *__restrict__ sc, float lambda,
-                                                                      float *__restrict__ gu, float *__restrict__ gv,
-                                                                      int P_all, int NB, int B, int Bp, int T, int I, int H, int xrows,
-                                                                      int zrows, const int32_t *__restrict__ pmax, int R)
+__global__ void __launch_bounds__(256) window_backward_stream_kernel(WindowBwdArgs a, ReduceJobs jobs)
 {
+    if ((int)blockIdx.x >= a.blocks) {
+        reduce_stage1_body(jobs, blockIdx.x - a.blocks);
+        return;
+    }
+    const float *__restrict__ gX = a.gX, *__restrict__ gO = a.gO;
+    const float lambda = a.lambda;
+    const int NB = a.NB, Bp = a.Bp, T = a.T, I = a.I, H = a.H, xrows = a.xrows, zrows = a.zrows, R = a.R;
     extern __shared__ float ring_all[];                     // [wave][R][16]
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, n = lane & 15;
@@ -782,10 +954,10 @@ __global__ void __launch_bounds__(256) window_backward_stream_kernel(const float
     float *ring = ring_all + wave * R * 16;
     for (int e = lane; e < R * 16; e += 64) ring[e] = 0.0f;
     const int mask = R - 1;
-    const int Pt = min(P_all, pmax[bt]);
+    const int Pt = min(a.P, a.pmax[bt]);
     const int col = bt * 16 + n;
-    const int len = col < B ? clamp_len(lengths[col], T) : 0;
-    const float pen = lambda * 2.0f * sc->inv_n_lv;
+    const int len = col < a.B ? clamp_len(a.lengths[col], T) : 0;
+    const float pen = lambda * 2.0f * a.sc->inv_n_lv;
     const int QX = (I + 3) >> 2, Q = QX + ((H + 3) >> 2);   // row groups that hold window elements
     // columns between the last tile and the padded batch: the wave of the last tile clears them
     const int pad_col = 16 * NB + lane;
@@ -796,7 +968,7 @@ __global__ void __launch_bounds__(256) window_backward_stream_kernel(const float
         // the penalty term of this lane's gu row, requested ahead of the gradient tiles: its five loads then
         // travel together with theirs instead of being a second round trip at the end of the block
         const int t_pen = s0 + g + I - 1;
-        const float pen_grad = (lambda != 0.0f && t_pen >= 0 && t_pen < T) ? level_penalty_grad(u, Bp, col, t_pen, len, pen) : 0.0f;
+        const float pen_grad = (lambda != 0.0f && t_pen >= 0 && t_pen < T) ? level_penalty_grad(a.u, Bp, col, t_pen, len, pen) : 0.0f;
         if (s0 + 3 >= 0 && s0 < Pt) {
             for (int e0 = 0; e0 < Q; e0 += 4) {
                 float w[4][4];
@@ -856,17 +1028,17 @@ __global__ void __launch_bounds__(256) window_backward_stream_kernel(const float
         const int s = s0 + g;
         if (s >= 0 && s < T) {
             float *slot = &ring[(s & mask) * 16 + n];
-            gv[(size_t)s * Bp + col] = *slot;
+            a.gv[(size_t)s * Bp + col] = *slot;
             *slot = 0.0f;
         }
         const int t = s + I - 1;
         if (t >= 0 && t < T) {
-            gu[(size_t)t * Bp + col] = mine + pen_grad;
+            a.gu[(size_t)t * Bp + col] = mine + pen_grad;
         }
         if (pads && pad_col < Bp) {
             for (int k = 0; k < 4; ++k) {
-                if (s0 + k >= 0 && s0 + k < T) gv[(size_t)(s0 + k) * Bp + pad_col] = 0.0f;
-                if (s0 + k + I - 1 >= 0 && s0 + k + I - 1 < T) gu[(size_t)(s0 + k + I - 1) * Bp + pad_col] = 0.0f;
+                if (s0 + k >= 0 && s0 + k < T) a.gv[(size_t)(s0 + k) * Bp + pad_col] = 0.0f;
+                if (s0 + k + I - 1 >= 0 && s0 + k + I - 1 < T) a.gu[(size_t)(s0 + k + I - 1) * Bp + pad_col] = 0.0f;
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -885,6 +1057,7 @@ struct EsBwdArgs {
     const float *es;
     const float *lvl, *S1, *S2, *gu, *gv;   // [T][Bp]
     float *grad_es;                          // [K][B]
+    int blocks;                              // workgroups of the recursions; the launch's others reduce weight gradients
     int B, Bp, T, n_seas, m1, m2, logit;
     int row_gamma1, row_gamma2, row_s1, row_s2;
 };
@@ -904,9 +1077,14 @@ constexpr int es_bwd_coefs(int n_seas) { return 4 + 4 * n_seas; }
 constexpr int es_bwd_stage_floats(int n_seas) { return 2 * kEsBwdChunk * es_bwd_coefs(n_seas) * 64; }
 
 template <int NS>
-__global__ void __launch_bounds__(64 * (1 + kEsBwdHelpers)) es_backward_kernel(EsBwdArgs a)
+__global__ void __launch_bounds__(64 * (1 + kEsBwdHelpers)) es_backward_kernel(EsBwdArgs a, ReduceStage2Args reduce)
 {
     extern __shared__ __align__(16) float ring[];   // [m1 + m2][64] rings, then [2][kEsBwdChunk][4 + 4 NS][64] staging
+    static_assert(kEsBwdHelpers == 3 && es_bwd_stage_floats(0) >= 256, "the reduction has 256 threads and works in the same LDS");
+    if ((int)blockIdx.x >= a.blocks) {
+        reduce_stage2_body(reduce, blockIdx.x - a.blocks, ring);
+        return;
+    }
     constexpr int CH = kEsBwdChunk, NC = es_bwd_coefs(NS);
     const int role = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -1102,149 +1280,6 @@ __global__ void __launch_bounds__(64 * (1 + kEsBwdHelpers)) es_backward_kernel(E
     }
 }
 
-// ---------------------------------------------------------------------------
-// Weight-gradient reduction: sums the per-workgroup (LSTM) and per-wave (head)
-// partial tiles in a fixed order and writes the caller's packing.
-// ---------------------------------------------------------------------------
-// Stage 1: every job (one block of partial results per producer workgroup or
-// wave) is cut into `splits` interleaved subsets of the producers; a thread sums
-// one element over one subset.  Stage 2 (the kernels below) sums the subsets and
-// writes the caller's packing.  Both orders are fixed.
-struct ReduceJob {
-    const float *src;
-    float *dst;          // [splits][n_elems]
-    unsigned stride;     // floats between consecutive partial blocks
-    int n_part, n_elems, splits;
-};
-constexpr int kMaxReduceJobs = 2 * kMaxLayers + 1;
-struct ReduceJobs {
-    ReduceJob job[kMaxReduceJobs];
-};
-
-__global__ void __launch_bounds__(256) reduce_stage1_kernel(ReduceJobs jobs)
-{
-    const ReduceJob &j = jobs.job[blockIdx.z];
-    const int e = blockIdx.x * 256 + threadIdx.x, sp = blockIdx.y;
-    if (sp >= j.splits || e >= j.n_elems) return;
-    const float *src = j.src + e;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-    int w = sp;
-    for (; w + 3 * j.splits < j.n_part; w += 4 * j.splits) {
-        a0 += src[(size_t)w * j.stride];
-        a1 += src[(size_t)(w + j.splits) * j.stride];
-        a2 += src[(size_t)(w + 2 * j.splits) * j.stride];
-        a3 += src[(size_t)(w + 3 * j.splits) * j.stride];
-    }
-    for (; w < j.n_part; w += j.splits) a0 += src[(size_t)w * j.stride];
-    j.dst[(size_t)sp * j.n_elems + e] = (a0 + a1) + (a2 + a3);
-}
-
-struct ReduceLstmArgs {
-    const float *dw_partial, *db_partial;
-    float *gW, *gb;
-    int NB, h, in_dim, HT, KXT;
-};
-
-// Sums `n_part` partial blocks for 64 consecutive elements per workgroup: the
-// four waves take interleaved quarters of the partials (each load instruction
-// reads 256 contiguous bytes of one partial), then combine in a fixed order.
-__device__ __forceinline__ float reduce_partials(const float *__restrict__ base, size_t stride, int n_part, int elem,
-                                                 bool active, float (*s_red)[64])
-{
-    const int e = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    float acc = 0.0f;
-    if (active) {
-        const float *src = base + elem;
-        int w = sl;
-        for (; w + 12 < n_part; w += 16) {
-            const float a0 = src[(size_t)w * stride], a1 = src[(size_t)(w + 4) * stride];
-            const float a2 = src[(size_t)(w + 8) * stride], a3 = src[(size_t)(w + 12) * stride];
-            acc += (a0 + a1) + (a2 + a3);
-        }
-        for (; w < n_part; w += 4) acc += src[(size_t)w * stride];
-    }
-    s_red[sl][e] = acc;
-    __syncthreads();
-    return (s_red[0][e] + s_red[1][e]) + (s_red[2][e] + s_red[3][e]);
-}
-
-__device__ void reduce_lstm_body(const ReduceLstmArgs &a, float (*s_red)[64])
-{
-    const int KT = a.KXT + a.HT, MB = (KT + 3) / 4, ld = a.in_dim + a.h;
-    const int n_dw = a.HT * MB * 256, n_db = a.HT * 16;
-    const int n_dw_blocks = (n_dw + 63) / 64;
-    const int e = threadIdx.x & 63;
-    if ((int)blockIdx.x < n_dw_blocks) {
-        const int idx = blockIdx.x * 64 + e;                  // element of the tile block: [tile][component][lane]
-        const float tot = reduce_partials(a.dw_partial, (size_t)n_dw, a.NB, idx, idx < n_dw, s_red);
-        if (threadIdx.x < 64 && idx < n_dw) {
-            const int lane = idx & 63, comp = (idx >> 6) & 3, tix = idx >> 8;
-            const int mt = tix / MB, nbk = tix % MB;
-            // tile row 4*gate + unit-in-tile sits in lane group `gate`, component `unit-in-tile`
-            const int gate = lane >> 4, unit = 4 * mt + comp;
-            const int xr = 16 * nbk + (lane & 15);
-            int col = -1;
-            if (xr < 4 * a.KXT) { if (xr < a.in_dim) col = xr; }
-            else if (xr - 4 * a.KXT < a.h) col = a.in_dim + xr - 4 * a.KXT;
-            if (unit < a.h && col >= 0) a.gW[(size_t)(gate * a.h + unit) * ld + col] = tot;
-        }
-    } else {
-        const int idx = (blockIdx.x - n_dw_blocks) * 64 + e;   // [unit tile][unit][gate]
-        const float tot = reduce_partials(a.db_partial, (size_t)n_db, a.NB, idx, idx < n_db, s_red);
-        if (threadIdx.x < 64 && idx < n_db) {
-            const int gate = idx & 3, unit = idx >> 2;
-            if (unit < a.h) a.gb[gate * a.h + unit] = tot;
-        }
-    }
-}
-
-struct ReduceHeadArgs {
-    const float *partial;
-    float *gWa, *gba, *gWo, *gbo;
-    int n_part, stride, h, H, HT, MA, MO, OT;
-};
-
-__device__ void reduce_head_body(const ReduceHeadArgs &a, float (*s_red)[64])
-{
-    // partial block: dWo tiles [MO*MA][4][64], dWa tiles [MA*MA][4][64], dbo [4*OT], dba [4*HT]
-    const int offWa = a.MO * a.MA * 256, offbo = offWa + a.MA * a.MA * 256, offba = offbo + 4 * a.OT;
-    const int n = offba + 4 * a.HT;
-    const int idx = blockIdx.x * 64 + (threadIdx.x & 63);
-    const float tot = reduce_partials(a.partial, (size_t)a.stride, a.n_part, idx, idx < n, s_red);
-    if (threadIdx.x >= 64 || idx >= n) return;
-    if (idx < offbo) {
-        const bool isWa = idx >= offWa;
-        const int j = isWa ? idx - offWa : idx;
-        const int lane = j & 63, comp = (j >> 6) & 3, tix = j >> 8;
-        const int mt = tix / a.MA, nt = tix % a.MA;
-        const int row = 16 * mt + 4 * (lane >> 4) + comp, col = 16 * nt + (lane & 15);
-        if (col < a.h) {
-            if (isWa) { if (row < a.h) a.gWa[row * a.h + col] = tot; }
-            else if (row < a.H) a.gWo[row * a.h + col] = tot;
-        }
-    } else if (idx < offba) {
-        const int j = idx - offbo;
-        if (j < a.H) a.gbo[j] = tot;
-    } else {
-        const int j = idx - offba;
-        if (j < a.h) a.gba[j] = tot;
-    }
-}
-
-struct ReduceStage2Args {
-    ReduceLstmArgs lstm[kMaxLayers];
-    ReduceHeadArgs head;
-    int L;
-};
-
-__global__ void __launch_bounds__(256) reduce_stage2_kernel(ReduceStage2Args a)
-{
-    __shared__ float s_red[4][64];
-    const int z = blockIdx.z;
-    if (z < a.L) reduce_lstm_body(a.lstm[z], s_red);
-    else reduce_head_body(a.head, s_red);
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1368,38 +1403,84 @@ hipError_t launch_loss_finalize(const Plan &pl, float *ws, float *loss, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st)
+namespace {
+int reduce_splits(int n_part) { return std::min(n_part, kReduceSplits); }
+
+ReduceJobs reduce_jobs(const Plan &pl, float *ws)
 {
-    const Scalars *sc = reinterpret_cast<const Scalars *>(ws + pl.scalars);
-    const int32_t *pmax = reinterpret_cast<const int32_t *>(ws + pl.pmax);
+    ReduceJobs jobs{};
+    int nj = 0;
+    auto add = [&](size_t src, size_t dst, size_t stride, int n_part, int n_elems) {
+        const int splits = reduce_splits(n_part);
+        jobs.blocks += (n_elems + 255) / 256 * splits;
+        jobs.job[nj++] = ReduceJob{ws + src, ws + dst, (unsigned)stride, n_part, n_elems, splits, jobs.blocks};
+    };
+    for (int l = 0; l < pl.L; ++l) {
+        const LayerPlan &lp = pl.layer[l];
+        const int MB = (lp.KXT + pl.HT + 3) / 4;
+        const int n_dw = pl.HT * MB * 256, n_db = pl.HT * 16;
+        add(lp.dw_partial, lp.dw_reduced, n_dw, pl.partial_groups(lp), n_dw);
+        add(lp.db_partial, lp.db_reduced, n_db, pl.partial_groups(lp), n_db);
+    }
+    const int n_head = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
+    add(pl.head_dw_partial, pl.head_dw_reduced, pl.head_dw_stride, pl.n_head_waves, n_head);
+    return jobs;
+}
+
+ReduceStage2Args reduce_stage2_args(const Plan &pl, float *ws, float *grad_weights)
+{
+    ReduceStage2Args r{};
+    r.L = pl.L;
+    int blocks = 0;
+    for (int l = 0; l < pl.L; ++l) {
+        const LayerPlan &lp = pl.layer[l];
+        r.lstm[l] = ReduceLstmArgs{ws + lp.dw_reduced, ws + lp.db_reduced, grad_weights + lp.w_off,
+                                   grad_weights + lp.b_off, reduce_splits(pl.partial_groups(lp)), pl.h, lp.in_dim, pl.HT, lp.KXT};
+        const int MB = (lp.KXT + pl.HT + 3) / 4;
+        r.end[l] = blocks += (pl.HT * MB * 256 + 63) / 64 + (pl.HT * 16 + 63) / 64;
+    }
+    const int n_head = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
+    r.head = ReduceHeadArgs{ws + pl.head_dw_reduced, grad_weights + pl.Wa_off, grad_weights + pl.ba_off,
+                            grad_weights + pl.Wo_off, grad_weights + pl.bo_off,
+                            reduce_splits(pl.n_head_waves), n_head, pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
+    r.end[kMaxLayers] = blocks + (n_head + 63) / 64;
+    return r;
+}
+}  // namespace
+
+hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float *ws, bool reduce, hipStream_t st)
+{
+    const ReduceJobs jobs = reduce ? reduce_jobs(pl, ws) : ReduceJobs{};
+    WindowBwdArgs a{ws + pl.gX, ws + pl.gO, ws + pl.u, lengths, reinterpret_cast<const Scalars *>(ws + pl.scalars),
+                    pl.cfg.lambda_lv, ws + pl.gu, ws + pl.gv, pl.P, pl.NB, pl.B, pl.Bt, pl.T, pl.I, pl.H, 4 * pl.IT, pl.OP,
+                    reinterpret_cast<const int32_t *>(ws + pl.pmax), 0, 0, 0};
     if (pl.window_stream) {
-        int R = 16;
-        while (R < pl.I + pl.H + 4) R *= 2;                 // ring of anti-diagonal sums, a power of two
-        window_backward_stream_kernel<<<(unsigned)((pl.NB + 3) / 4), 256, (size_t)4 * R * 16 * sizeof(float), st>>>(
-            ws + pl.gX, ws + pl.gO, ws + pl.u, lengths, sc, pl.cfg.lambda_lv, ws + pl.gu, ws + pl.gv, pl.P, pl.NB, pl.B,
-            pl.Bt, pl.T, pl.I, pl.H, 4 * pl.IT, pl.OP, pmax, R);
+        a.R = 16;
+        while (a.R < pl.I + pl.H + 4) a.R *= 2;             // ring of anti-diagonal sums, a power of two
+        a.blocks = (pl.NB + 3) / 4;
+        window_backward_stream_kernel<<<(unsigned)(a.blocks + jobs.blocks), 256, (size_t)4 * a.R * 16 * sizeof(float), st>>>(a, jobs);
         return hipGetLastError();
     }
-    const int t_chunks = (pl.T + 3) / 4;                    // four time steps per workgroup
+    a.t_chunks = (pl.T + 3) / 4;                            // four time steps per workgroup
     const int col_slots = (pl.Bt / 64 + 7) / 8;             // groups of 64 series per XCD
-    window_backward_kernel<<<(unsigned)(8 * col_slots * t_chunks), 256, 0, st>>>(
-        ws + pl.gX, ws + pl.gO, ws + pl.u, lengths, sc, pl.cfg.lambda_lv, ws + pl.gu, ws + pl.gv, pl.P, pl.NB, pl.B, pl.Bt,
-        pl.T, pl.I, pl.H, 4 * pl.IT, pl.OP, pmax, t_chunks);
+    a.blocks = 8 * col_slots * a.t_chunks;
+    window_backward_kernel<<<(unsigned)(a.blocks + jobs.blocks), 256, 0, st>>>(a, jobs);
     return hipGetLastError();
 }
 
 hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *lengths, const float *es, float *ws,
-                              float *grad_es, hipStream_t st)
+                              float *grad_es, float *grad_weights, hipStream_t st)
 {
     const esrnn_config &c = pl.cfg;
-    EsBwdArgs a{y, lengths, es, ws + pl.lvl, ws + pl.S1, ws + pl.S2, ws + pl.gu, ws + pl.gv, grad_es,
+    const ReduceStage2Args reduce = grad_weights ? reduce_stage2_args(pl, ws, grad_weights) : ReduceStage2Args{};
+    EsBwdArgs a{y, lengths, es, ws + pl.lvl, ws + pl.S1, ws + pl.S2, ws + pl.gu, ws + pl.gv, grad_es, (pl.B + 63) / 64,
                 pl.B, pl.Bt, pl.T, c.n_seas, c.n_seas >= 1 ? c.m1 : 0, c.n_seas >= 2 ? c.m2 : 0,
                 c.param_space == ESRNN_PARAMS_LOGIT, pl.row_gamma1, pl.row_gamma2, pl.row_s1, pl.row_s2};
     const size_t lds = ((size_t)(a.m1 + a.m2) * 64 + es_bwd_stage_floats(c.n_seas)) * sizeof(float);
     auto run = [&](auto kernel) {
         hipError_t e = allow_large_lds(reinterpret_cast<const void *>(kernel), lds);
         if (e != hipSuccess) return e;
-        kernel<<<(pl.B + 63) / 64, 64 * (1 + kEsBwdHelpers), lds, st>>>(a);
+        kernel<<<(unsigned)(a.blocks + reduce.blocks()), 64 * (1 + kEsBwdHelpers), lds, st>>>(a, reduce);
         return hipGetLastError();
     };
     if (c.n_seas == 0) return run(es_backward_kernel<0>);
@@ -1473,46 +1554,6 @@ hipError_t launch_forecast_metrics(const Plan &pl, const float *forecasts, const
 {
     forecast_metrics_kernel<<<(pl.B + 255) / 256, 256, 0, st>>>(forecasts, actuals, y, lengths, smape, mase,
                                                                  pl.B, pl.T, pl.H, m);
-    return hipGetLastError();
-}
-
-hipError_t launch_reduce_weight_grads(const Plan &pl, float *ws, float *grad_weights, hipStream_t st)
-{
-    ReduceJobs jobs{};
-    int nj = 0, max_elems = 0, max_splits = 1;
-    auto add = [&](size_t src, size_t dst, size_t stride, int n_part, int n_elems) {
-        const int splits = n_part < kReduceSplits ? n_part : kReduceSplits;
-        jobs.job[nj++] = ReduceJob{ws + src, ws + dst, (unsigned)stride, n_part, n_elems, splits};
-        if (n_elems > max_elems) max_elems = n_elems;
-        if (splits > max_splits) max_splits = splits;
-        return splits;
-    };
-    int lstm_splits[kMaxLayers];
-    for (int l = 0; l < pl.L; ++l) {
-        const LayerPlan &lp = pl.layer[l];
-        const int MB = (lp.KXT + pl.HT + 3) / 4;
-        const int n_dw = pl.HT * MB * 256, n_db = pl.HT * 16;
-        lstm_splits[l] = add(lp.dw_partial, lp.dw_reduced, n_dw, pl.partial_groups(lp), n_dw);
-        add(lp.db_partial, lp.db_reduced, n_db, pl.partial_groups(lp), n_db);
-    }
-    const int n_head = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
-    const int head_splits = add(pl.head_dw_partial, pl.head_dw_reduced, pl.head_dw_stride, pl.n_head_waves, n_head);
-    reduce_stage1_kernel<<<dim3((max_elems + 255) / 256, max_splits, nj), 256, 0, st>>>(jobs);
-
-    ReduceStage2Args r{};
-    r.L = pl.L;
-    int max_blocks = (n_head + 63) / 64;
-    for (int l = 0; l < pl.L; ++l) {
-        const LayerPlan &lp = pl.layer[l];
-        r.lstm[l] = ReduceLstmArgs{ws + lp.dw_reduced, ws + lp.db_reduced, grad_weights + lp.w_off,
-                                   grad_weights + lp.b_off, lstm_splits[l], pl.h, lp.in_dim, pl.HT, lp.KXT};
-        const int MB = (lp.KXT + pl.HT + 3) / 4;
-        max_blocks = std::max(max_blocks, (pl.HT * MB * 256 + 63) / 64 + (pl.HT * 16 + 63) / 64);
-    }
-    r.head = ReduceHeadArgs{ws + pl.head_dw_reduced, grad_weights + pl.Wa_off, grad_weights + pl.ba_off,
-                            grad_weights + pl.Wo_off, grad_weights + pl.bo_off,
-                            head_splits, n_head, pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
-    reduce_stage2_kernel<<<dim3(max_blocks, 1, pl.L + 1), 256, 0, st>>>(r);
     return hipGetLastError();
 }
 

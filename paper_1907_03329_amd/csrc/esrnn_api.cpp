@@ -26,7 +26,7 @@ struct esrnn_handle {
     Stage stage[kMaxStages];
     // stage indices
     int st_es_fwd, st_win_fwd, st_lstm_fwd[kMaxLayers], st_head, st_fc, st_loss;
-    int st_lstm_bwd[kMaxLayers], st_win_bwd, st_es_bwd, st_reduce, st_tail;
+    int st_lstm_bwd[kMaxLayers], st_win_bwd, st_es_bwd, st_tail;
     const int32_t *categories;   // device array of the caller, or null
     bool forward_only;           // esrnn_forward skips the reverse pass of the output stage; esrnn_backward is refused
 };
@@ -93,7 +93,6 @@ esrnn_status esrnn_create(const esrnn_config *cfg, esrnn_handle **out)
     for (int l = pl.L - 1; l >= 0; --l) h->st_lstm_bwd[l] = add_stage(h, "lstm_backward_l%d", l);
     h->st_win_bwd = add_stage(h, "window_backward", 0);
     h->st_es_bwd = add_stage(h, "es_backward", 0);
-    h->st_reduce = add_stage(h, "reduce_weight_grads", 0);
     h->st_tail = add_stage(h, "forecast_tail", 0);
     *out = h;
     return ESRNN_OK;
@@ -206,10 +205,9 @@ esrnn_status esrnn_backward(esrnn_handle *h, const float *y, const int32_t *leng
     hipStream_t st = static_cast<hipStream_t>(stream);
     for (int l = pl.L - 1; l >= 0; --l)
         ESRNN_TRY(run_stage(h, h->st_lstm_bwd[l], st, [&] { return launch_lstm_backward(pl, l, lengths, ws, st); }));
-    ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, st); }));
+    ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, true, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_bwd, st,
-                        [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, st); }));
-    ESRNN_TRY(run_stage(h, h->st_reduce, st, [&] { return launch_reduce_weight_grads(pl, ws, grad_weights, st); }));
+                        [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, grad_weights, st); }));
     return ESRNN_OK;
 }
 
@@ -339,9 +337,9 @@ esrnn_status esrnn_es_window_backward(esrnn_handle *h, const float *y, const int
     const Plan &pl = h->plan;
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, st); }));
+    ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, false, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_bwd, st,
-                        [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, st); }));
+                        [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, nullptr, st); }));
     return ESRNN_OK;
 }
 

@@ -162,10 +162,11 @@ hipError_t launch_lstm_backward_three_term(const Plan &pl, int layer, const Lstm
                                            float *ws, hipStream_t st);
 hipError_t launch_lstm_backward_three_term_large(const Plan &pl, int layer, const LstmBwdSources &src,
                                                  const int32_t *lengths, float *ws, hipStream_t st);
-hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st);
+// window adjoint and, in the same launch, the first stage of the weight-gradient reduction (`reduce`); adjoint of the
+// recursions and the second stage (grad_weights: not null)
+hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float *ws, bool reduce, hipStream_t st);
 hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *lengths, const float *es,
-                              float *ws, float *grad_es, hipStream_t st);
-hipError_t launch_reduce_weight_grads(const Plan &pl, float *ws, float *grad_weights, hipStream_t st);
+                              float *ws, float *grad_es, float *grad_weights, hipStream_t st);
 
 hipError_t launch_adam_update(const Plan &pl, const esrnn_adam_config &opt, int step, float *weights,
                               const float *grad_weights, float *m_w, float *v_w, float *es_params,
