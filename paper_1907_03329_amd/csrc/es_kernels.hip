@@ -654,37 +654,6 @@ __global__ void __launch_bounds__(256) window_forward_kernel(const float *__rest
     }
 }
 
-// ---------------------------------------------------------------------------
-// Loss: sum of the per-workgroup partial sums in double, then
-// loss = pinball_sum / n_pin + lambda * level_sum / n_lv.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) loss_finalize_kernel(const float *__restrict__ partial, int n_pin_parts, int n_lv_parts,
-                                                             const float *__restrict__ cs_partial, int n_cs_parts,
-                                                             const Scalars *__restrict__ sc, float lambda, float lambda_cs,
-                                                             float *__restrict__ loss)
-{
-    __shared__ double s_a[256], s_b[256], s_c[256];
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int i = threadIdx.x; i < n_pin_parts; i += 256) a += (double)partial[i];
-    for (int i = threadIdx.x; i < n_lv_parts; i += 256) b += (double)partial[n_pin_parts + i];
-    for (int i = threadIdx.x; i < n_cs_parts; i += 256) c += (double)cs_partial[i];
-    s_a[threadIdx.x] = a;
-    s_b[threadIdx.x] = b;
-    s_c[threadIdx.x] = c;
-    __syncthreads();
-    for (int off = 128; off >= 1; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            s_a[threadIdx.x] += s_a[threadIdx.x + off];
-            s_b[threadIdx.x] += s_b[threadIdx.x + off];
-            s_c[threadIdx.x] += s_c[threadIdx.x + off];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        *loss = (float)(s_a[0] * (double)sc->inv_n_pin + (double)lambda * s_b[0] * (double)sc->inv_n_lv +
-                        (double)lambda_cs * s_c[0] * (double)sc->inv_n_cs);
-}
-
 // Gradient of the level penalty (Section 8.4) with respect to u[t] of one series, times `scale`:
 // e[k] = u[k] - 2u[k-1] + u[k-2] for 2 <= k < len; d/du[t] of sum e^2 = 2(e[t] - 2e[t+1] + e[t+2]).
 __device__ __forceinline__ float level_penalty_grad(const float *__restrict__ u, int Bp, int col, int t, int len, float scale)
@@ -1394,15 +1363,6 @@ hipError_t launch_window_forward(const Plan &pl, const int32_t *categories, floa
     return hipGetLastError();
 }
 
-hipError_t launch_loss_finalize(const Plan &pl, float *ws, float *loss, hipStream_t st)
-{
-    loss_finalize_kernel<<<1, 256, 0, st>>>(ws + pl.loss_partial, pl.n_loss_partial - pl.es_blocks, pl.es_blocks,
-                                            ws + pl.cs_partial, pl.n_cs_partial,
-                                            reinterpret_cast<const Scalars *>(ws + pl.scalars), pl.cfg.lambda_lv,
-                                            pl.cfg.lambda_cs, loss);
-    return hipGetLastError();
-}
-
 namespace {
 int reduce_splits(int n_part) { return std::min(n_part, kReduceSplits); }
 
@@ -1489,32 +1449,6 @@ hipError_t launch_es_backward(const Plan &pl, const float *y, const int32_t *len
 }
 
 // ---------------------------------------------------------------------------
-// Out-of-sample forecasts (extend_body above) at the end of every series.
-// ---------------------------------------------------------------------------
-// forecast[b][h-1] = exp(output_h + ln l_t) * S1[t + ((h-1) mod m1) + 1] * S2[...], t = len-1: the last m
-// factors the recursion produced, repeated with their period (Eq. (4)).
-__global__ void __launch_bounds__(256) forecast_tail_kernel(const float *__restrict__ O, const float *__restrict__ u,
-                                                             const float *__restrict__ S1, const float *__restrict__ S2,
-                                                             const int32_t *__restrict__ lengths, float *__restrict__ out,
-                                                             int B, int Bp, int NB, int T, int I, int H, int orows,
-                                                             int m1, int m2)
-{
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= B * H) return;
-    const int b = idx / H, j = idx % H;
-    const int len = lengths[b];
-    float f = 0.0f;
-    if (len >= I && len <= T - H) {
-        const int t = len - 1, p = len - I;
-        const float o = O[(((size_t)p * NB + (b >> 4)) * orows + j) * 16 + (b & 15)];
-        float sv = 1.0f;
-        if (m1 > 0) sv = S1[(size_t)(t + (j % m1) + 1) * Bp + b];
-        if (m2 > 0) sv *= S2[(size_t)(t + (j % m2) + 1) * Bp + b];
-        f = __expf(o + u[(size_t)t * Bp + b]) * sv;
-    }
-    out[idx] = f;
-}
-
 // Accuracy of forecasts against actual values, per series (Section 3.5 names the two metrics of the
 // M4 competition): sMAPE = mean_h 200 |a - f| / (|a| + |f|); MASE = mean_h |a - f| divided by the
 // in-sample mean of |y_t - y_{t-m}|, t = m .. len-1 (seasonal naive forecast of period m).
@@ -1537,16 +1471,6 @@ __global__ void __launch_bounds__(256) forecast_metrics_kernel(const float *__re
     for (int t = m; t < len; ++t) s_naive += fabsf(y[(size_t)t * B + b] - y[(size_t)(t - m) * B + b]);
     smape[b] = s_sym / (float)H;
     mase[b] = (s_abs / (float)H) / (s_naive / (float)(len - m));
-}
-
-hipError_t launch_forecast_tail(const Plan &pl, const int32_t *lengths, float *ws, float *out, hipStream_t st)
-{
-    const esrnn_config &c = pl.cfg;
-    const int n = pl.B * pl.H;
-    forecast_tail_kernel<<<(n + 255) / 256, 256, 0, st>>>(ws + pl.O, ws + pl.u, ws + pl.S1, ws + pl.S2, lengths, out,
-                                                          pl.B, pl.Bt, pl.NB, pl.T, pl.I, pl.H, pl.OP,
-                                                          c.n_seas >= 1 ? c.m1 : 0, c.n_seas >= 2 ? c.m2 : 0);
-    return hipGetLastError();
 }
 
 hipError_t launch_forecast_metrics(const Plan &pl, const float *forecasts, const float *actuals, const float *y,

@@ -145,12 +145,12 @@ hipError_t launch_lstm_forward_narrow_residual(const Plan &pl, int layer, const 
                                       float *ws, hipStream_t st);
 hipError_t launch_lstm_backward_narrow(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
 hipError_t launch_lstm_backward_narrow_split(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
-// output stage, forward and reverse in one launch (needs the loss normalisers of launch_setup)
+// output stage, forward and reverse in one launch (needs the loss normalisers of launch_es_forward)
 hipError_t launch_head(const Plan &pl, const int32_t *lengths, float *ws, bool reverse, hipStream_t st);
-// output stage at the last window of every series only, forward
-hipError_t launch_head_last(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st);
-hipError_t launch_forecasts(const Plan &pl, const int32_t *lengths, float *ws, float *forecasts, hipStream_t st);
-hipError_t launch_loss_finalize(const Plan &pl, float *ws, float *loss, hipStream_t st);
+// output stage at the last window of every series only, forward, and the forecasts that follow from it (extended lengths)
+hipError_t launch_head_last(const Plan &pl, const int32_t *lengths, float *ws, float *forecasts, hipStream_t st);
+// the loss, and the in-sample forecasts (none if null)
+hipError_t launch_loss_and_forecasts(const Plan &pl, const int32_t *lengths, float *ws, float *loss, float *forecasts, hipStream_t st);
 
 hipError_t launch_lstm_backward(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st);
 // the gradient arriving at a layer's hidden output is the sum of n (1 or 2) arrays; g[1] repeats g[0] when there is one
@@ -177,7 +177,6 @@ hipError_t launch_adam_update_indexed(const Plan &pl, const esrnn_adam_config &o
                                       const float *grad_weights, float *m_w, float *v_w, float *es_store,
                                       const float *grad_es, float *m_es, float *v_es, int32_t *counts,
                                       const int32_t *index, int N, float *ws, hipStream_t st);
-hipError_t launch_forecast_tail(const Plan &pl, const int32_t *lengths, float *ws, float *out, hipStream_t st);
 hipError_t launch_forecast_metrics(const Plan &pl, const float *forecasts, const float *actuals, const float *y,
                                    const int32_t *lengths, int m, float *smape, float *mase, hipStream_t st);
 

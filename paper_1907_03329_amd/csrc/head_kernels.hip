@@ -39,6 +39,10 @@ struct HeadArgs {
     int orows;              // rows of the Z, O and gO tiles: 4 * ceil(H / 4)
     float tau;
     int reverse;            // 0: forward only (outputs and loss); the reverse pass and its stores are skipped
+    // forecasts at the end of the series (head_last_kernel)
+    float *forecasts;       // [B][H]
+    const float *u, *S1, *S2;
+    int Bt, m1, m2;         // row stride of those; periods (0: no such seasonality)
 };
 
 template <int HT, int MO>
@@ -324,6 +328,9 @@ __global__ void __launch_bounds__(256) head_kernel(HeadArgs a)
 // The output stage, forward, at the LAST window of every series only (out-of-sample forecasts).  One wave per 16-series
 // tile: a column of the products is a series, so every lane reads the block output at its own series' position, and the
 // arithmetic per column is that of head_kernel.  Replaces a pass over all positions (4096 quarterly series: 32 -> 5 us).
+// The lane that has an output of step j turns it into the forecast (Eq. (4), (5); a launch of its own took 4 - 5 us):
+// exp(output + ln l_t) * S1[t + (j mod m1) + 1] * S2[...], t the last observation, j from 0: the last m factors the
+// recursion produced, repeated with their period.  Series that take no part (length 0) have zeros.
 // ---------------------------------------------------------------------------
 template <int HT, int MO>
 __global__ void __launch_bounds__(256) head_last_kernel(HeadArgs a)
@@ -339,6 +346,17 @@ __global__ void __launch_bounds__(256) head_last_kernel(HeadArgs a)
     float br[HT];
 #pragma unroll
     for (int q = 0; q < HT; ++q) br[q] = a.R[tile * HT * 64 + q * 64 + lane];
+    const int t = max(len - a.H - 1, 0), col = min(b, a.B - 1);
+    const float ut = a.u[(size_t)t * a.Bt + col];
+    float seas[OTMAX];
+#pragma unroll
+    for (int ks = 0; ks < OTMAX; ++ks) {
+        const int j = min(4 * ks + g, a.H - 1);
+        float s1 = 1.0f, s2 = 1.0f;
+        if (a.m1 > 0) s1 = a.S1[(size_t)min(t + j % a.m1 + 1, a.T - 1) * a.Bt + col];
+        if (a.m2 > 0) s2 = a.S2[(size_t)min(t + j % a.m2 + 1, a.T - 1) * a.Bt + col];
+        seas[ks] = s1 * s2;
+    }
     f32x4 acc[MA], oc[MO];
 #pragma unroll
     for (int ma = 0; ma < MA; ++ma) acc[ma] = *reinterpret_cast<const f32x4 *>(a.baF + (ma * 4 + g) * 4);
@@ -354,12 +372,51 @@ __global__ void __launch_bounds__(256) head_last_kernel(HeadArgs a)
 #pragma unroll
         for (int mo = 0; mo < MO; ++mo) oc[mo] = mfma16(a.WoF[(mo * HT + q) * 64 + lane], av, oc[mo]);
     }
-    if (windows < 1) return;
 #pragma unroll
     for (int ks = 0; ks < OTMAX; ++ks) {
         const int j = 4 * ks + g;
-        if (j < a.orows) a.O[tile * a.orows * 16 + j * 16 + n] = oc[ks >> 2][ks & 3];
+        const float o = oc[ks >> 2][ks & 3];
+        if (windows >= 1 && j < a.orows) a.O[tile * a.orows * 16 + j * 16 + n] = o;
+        if (b < a.B && j < a.H) a.forecasts[(size_t)b * a.H + j] = windows >= 1 ? __expf(o + ut) * seas[ks] : 0.0f;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Loss: sum of the per-workgroup partial sums in double, then
+// loss = pinball_sum / n_pin + lambda * level_sum / n_lv + lambda_cs * cell_state_sum / n_cs.
+// ---------------------------------------------------------------------------
+struct LossArgs {
+    const float *pin, *lv, *cs;
+    int n_pin, n_lv, n_cs;
+    const Scalars *sc;
+    float lambda, lambda_cs;
+    float *loss;
+};
+
+// sum over the workgroup of a value per thread, in a fixed order
+__device__ __forceinline__ double block_sum(double v, double *s_wave)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
+    __syncthreads();
+    return v;
+}
+
+__device__ void loss_body(const LossArgs &a, double *s_wave)
+{
+    double pin = 0.0, lv = 0.0, cs = 0.0;
+    for (int i = threadIdx.x; i < a.n_pin; i += 256) pin += (double)a.pin[i];
+    for (int i = threadIdx.x; i < a.n_lv; i += 256) lv += (double)a.lv[i];
+    for (int i = threadIdx.x; i < a.n_cs; i += 256) cs += (double)a.cs[i];
+    pin = block_sum(pin, s_wave);
+    lv = block_sum(lv, s_wave);
+    cs = block_sum(cs, s_wave);
+    if (threadIdx.x == 0)
+        *a.loss = (float)(pin * (double)a.sc->inv_n_pin + (double)a.lambda * lv * (double)a.sc->inv_n_lv +
+                          (double)a.lambda_cs * cs * (double)a.sc->inv_n_cs);
 }
 
 // ---------------------------------------------------------------------------
@@ -369,17 +426,24 @@ __global__ void __launch_bounds__(256) head_last_kernel(HeadArgs a)
 // seasonal factors are read in their storage order.  The tile's 16 * H forecasts are contiguous in the
 // [P][B][H] array but ordered [series][step]: they are turned through the wave's corner of LDS and written
 // out in storage order as well.
+//
+// The first workgroup adds up the loss instead (a launch of its own took 4 - 5 us; done by the output-stage workgroup that
+// finishes last, 256 counts of one counter and the cache write-backs that order them cost the same 4 us).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) forecast_kernel(const float *__restrict__ O, const float *__restrict__ u,
                                                         const float *__restrict__ S1, const float *__restrict__ S2,
                                                         const int32_t *__restrict__ lengths, const int32_t *__restrict__ pmax,
                                                         float *__restrict__ forecasts, int P, int NB, int B, int Bp, int T,
-                                                        int I, int H, int orows, int n_seas)
+                                                        int I, int H, int orows, int n_seas, LossArgs loss)
 {
-    __shared__ float s_f[4][16 * ESRNN_MAX_WINDOW];
+    __shared__ __align__(16) float s_f[4][16 * ESRNN_MAX_WINDOW];
     const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
     float *fl = s_f[threadIdx.x >> 6];
-    const long long tile = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blockIdx.x == 0) {
+        loss_body(loss, reinterpret_cast<double *>(&s_f[0][0]));
+        return;
+    }
+    const long long tile = (long long)(blockIdx.x - 1) * 4 + (threadIdx.x >> 6);
     if (tile >= (long long)P * NB) return;              // (no workgroup barrier below)
     const int p = (int)(tile / NB), bt = (int)(tile % NB);
     const int t = p + I - 1;
@@ -410,33 +474,38 @@ __global__ void __launch_bounds__(256) forecast_kernel(const float *__restrict__
 
 }  // namespace
 
-hipError_t launch_forecasts(const Plan &pl, const int32_t *lengths, float *ws, float *forecasts, hipStream_t st)
+hipError_t launch_loss_and_forecasts(const Plan &pl, const int32_t *lengths, float *ws, float *loss, float *forecasts, hipStream_t st)
 {
-    const long long tiles = (long long)pl.P * pl.NB;
-    forecast_kernel<<<(unsigned)((tiles + 3) / 4), 256, 0, st>>>(
+    const esrnn_config &c = pl.cfg;
+    const LossArgs la{ws + pl.loss_partial, ws + pl.loss_partial + pl.head_blocks, ws + pl.cs_partial, pl.head_blocks, pl.es_blocks,
+                      pl.n_cs_partial, reinterpret_cast<const Scalars *>(ws + pl.scalars), c.lambda_lv, c.lambda_cs, loss};
+    const long long tiles = forecasts ? (long long)pl.P * pl.NB : 0;
+    forecast_kernel<<<(unsigned)(1 + (tiles + 3) / 4), 256, 0, st>>>(
         ws + pl.O, ws + pl.u, ws + pl.S1, ws + pl.S2, lengths, reinterpret_cast<const int32_t *>(ws + pl.pmax), forecasts,
-        pl.P, pl.NB, pl.B, pl.Bt, pl.T, pl.I, pl.H, pl.OP, pl.cfg.n_seas);
+        pl.P, pl.NB, pl.B, pl.Bt, pl.T, pl.I, pl.H, pl.OP, pl.cfg.n_seas, la);
     return hipGetLastError();
 }
 
 namespace {
-HeadArgs head_args(const Plan &pl, const int32_t *lengths, float *ws, bool reverse)
+HeadArgs head_args(const Plan &pl, const int32_t *lengths, float *ws, bool reverse, float *forecasts)
 {
+    const esrnn_config &c = pl.cfg;
     const HeadPack hp = head_pack_layout(pl);
     const float *f = ws + pl.head_fwd_pack, *bk = ws + pl.head_bwd_pack;
     return HeadArgs{f + hp.WaF, f + hp.baF, f + hp.WoF, f + hp.boF, bk + hp.WoT, bk + hp.WaT,
                     ws + pl.blk_out[pl.cfg.n_blocks - 1], ws + pl.Z, lengths,
                     reinterpret_cast<const int32_t *>(ws + pl.pmax), reinterpret_cast<const Scalars *>(ws + pl.scalars), ws + pl.O, ws + pl.loss_partial,
                     ws + pl.gO, ws + pl.gTop, ws + pl.head_dw_partial,
-                    pl.P, pl.NB, pl.B, pl.T, pl.I, pl.H, pl.head_dw_stride, pl.OP, pl.cfg.tau,
-                    reverse ? 1 : 0};
+                    pl.P, pl.NB, pl.B, pl.T, pl.I, pl.H, pl.head_dw_stride, pl.OP, c.tau,
+                    reverse ? 1 : 0, forecasts, ws + pl.u, ws + pl.S1, ws + pl.S2, pl.Bt,
+                    c.n_seas >= 1 ? c.m1 : 0, c.n_seas >= 2 ? c.m2 : 0};
 }
 }  // namespace
 
 hipError_t launch_head(const Plan &pl, const int32_t *lengths, float *ws, bool reverse, hipStream_t st)
 {
-    const int blocks = pl.n_head_waves / 4;
-    const HeadArgs a = head_args(pl, lengths, ws, reverse);
+    const int blocks = pl.head_blocks;
+    const HeadArgs a = head_args(pl, lengths, ws, reverse, nullptr);
 #define X(HT_, MO_)                                              \
     if (pl.HT == HT_ && pl.MO == MO_) {                          \
         head_kernel<HT_, MO_><<<blocks, 256, 0, st>>>(a);        \
@@ -447,9 +516,9 @@ hipError_t launch_head(const Plan &pl, const int32_t *lengths, float *ws, bool r
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_head_last(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st)
+hipError_t launch_head_last(const Plan &pl, const int32_t *lengths, float *ws, float *forecasts, hipStream_t st)
 {
-    const HeadArgs a = head_args(pl, lengths, ws, false);
+    const HeadArgs a = head_args(pl, lengths, ws, false, forecasts);
 #define X(HT_, MO_)                                                              \
     if (pl.HT == HT_ && pl.MO == MO_) {                                          \
         head_last_kernel<HT_, MO_><<<(pl.NB + 3) / 4, 256, 0, st>>>(a);          \
