@@ -221,60 +221,35 @@ __device__ void pack_lstm_body(const PackLstmArgs &a, int block, int n_blocks)
 struct PackHeadArgs {
     const float *Wa, *ba, *Wo, *bo;
     float *WaF, *baF, *WoF, *boF, *WoT, *WaT;
-    int h, H, HT, MA, MO, OT;
+    int h, H, HT, MA, MO;
 };
 
+// Operands of the output stage (head_kernels.hip): three bf16 parts as [tile][quad][lane][dword], rows in unit-tile order:
+// row 4g+r of tile m is row 4(4m+r)+g of the product.
 __device__ void pack_head_body(const PackHeadArgs &a, int block, int n_blocks)
 {
-    const int nWaF = a.MA * a.HT * 64, nbaF = a.MA * 16, nWoF = a.MO * a.HT * 64, nboF = a.MO * 16;
-    const int nWoT = a.MA * a.OT * 64, nWaT = a.MA * a.HT * 64;
-    const int total = nWaF + nbaF + nWoF + nboF + nWoT + nWaT;
-    for (int idx = block * 256 + threadIdx.x; idx < total; idx += n_blocks * 256) {
-        int j = idx;
-        if (j < nWaF) {
-            const int lane = j & 63, q = (j >> 6) % a.HT, ma = (j >> 6) / a.HT;
-            const int i = lane & 15, kk = lane >> 4;
-            const int out = 4 * (4 * ma + (i & 3)) + (i >> 2), in = 4 * q + kk;
-            a.WaF[j] = (out < a.h && in < a.h) ? a.Wa[out * a.h + in] : 0.0f;
-            continue;
+    const int np_h = (a.HT + 1) / 2, np_o = 2 * a.MO, qh = tt_a_quads(np_h), qo = tt_a_quads(np_o);
+    auto pack = [&](float *dst, int tiles, int quads, int np, auto &&at) {      // at(row, column), zero outside
+        for (int idx = block * 256 + threadIdx.x; idx < tiles * quads * 256; idx += n_blocks * 256) {
+            const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, m = (idx >> 8) / quads;
+            const int i = lane & 15, k = lane >> 4, row = 4 * (4 * m + (i & 3)) + (i >> 2);
+            const TtDword w = tt_a_dword(np, q, d);
+            const Parts p = split_pair(splittable(at(row, 8 * w.pair + k)), splittable(at(row, 8 * w.pair + 4 + k)));
+            reinterpret_cast<unsigned *>(dst)[idx] = part_of(p, w.part);
         }
-        j -= nWaF;
-        if (j < nbaF) {
-            const int r = j & 3, g = (j >> 2) & 3, ma = j >> 4;
-            const int unit = 4 * (4 * ma + r) + g;
-            a.baF[j] = unit < a.h ? a.ba[unit] : 0.0f;
-            continue;
-        }
-        j -= nbaF;
-        if (j < nWoF) {
-            const int lane = j & 63, q = (j >> 6) % a.HT, mo = (j >> 6) / a.HT;
-            const int i = lane & 15;
-            const int row = 4 * (4 * mo + (i & 3)) + (i >> 2), in = 4 * q + (lane >> 4);
-            a.WoF[j] = (row < a.H && in < a.h) ? a.Wo[row * a.h + in] : 0.0f;
-            continue;
-        }
-        j -= nWoF;
-        if (j < nboF) {
-            const int r = j & 3, g = (j >> 2) & 3, mo = j >> 4;
-            const int row = 4 * (4 * mo + r) + g;
-            a.boF[j] = row < a.H ? a.bo[row] : 0.0f;
-            continue;
-        }
-        j -= nboF;
-        if (j < nWoT) {
-            const int lane = j & 63, ks = (j >> 6) % a.OT, ma = (j >> 6) / a.OT;
-            const int i = lane & 15, kk = lane >> 4;
-            const int unit = 4 * (4 * ma + (i & 3)) + (i >> 2), row = 4 * ks + kk;
-            a.WoT[j] = (unit < a.h && row < a.H) ? a.Wo[row * a.h + unit] : 0.0f;
-            continue;
-        }
-        j -= nWoT;
-        {
-            const int lane = j & 63, q = (j >> 6) % a.HT, ma = (j >> 6) / a.HT;
-            const int i = lane & 15, kk = lane >> 4;
-            const int unit = 4 * (4 * ma + (i & 3)) + (i >> 2), row = 4 * q + kk;
-            a.WaT[j] = (unit < a.h && row < a.h) ? a.Wa[row * a.h + unit] : 0.0f;
-        }
+    };
+    auto wa = [&](int out, int in) { return out < a.h && in < a.h ? a.Wa[out * a.h + in] : 0.0f; };
+    auto wo = [&](int out, int in) { return out < a.H && in < a.h ? a.Wo[out * a.h + in] : 0.0f; };
+    pack(a.WaF, a.MA, qh, np_h, wa);
+    pack(a.WoF, a.MO, qh, np_h, wo);
+    pack(a.WoT, a.MA, qo, np_o, [&](int unit, int out) { return wo(out, unit); });
+    pack(a.WaT, a.MA, qh, np_h, [&](int unit, int out) { return wa(out, unit); });
+    for (int j = block * 256 + threadIdx.x; j < 16 * (a.MA + a.MO); j += n_blocks * 256) {
+        const bool second = j >= 16 * a.MA;
+        const int e = second ? j - 16 * a.MA : j;
+        const int row = 4 * (4 * (e >> 4) + (e & 3)) + ((e >> 2) & 3);
+        if (second) a.boF[e] = row < a.H ? a.bo[row] : 0.0f;
+        else a.baF[e] = row < a.h ? a.ba[row] : 0.0f;
     }
 }
 
@@ -671,11 +646,10 @@ __device__ __forceinline__ float level_penalty_grad(const float *__restrict__ u,
 }
 
 // ---------------------------------------------------------------------------
-// Weight-gradient reduction: sums the per-workgroup (LSTM) and per-wave (head)
-// partial tiles in a fixed order and writes the caller's packing.
+// Weight-gradient reduction: sums the per-workgroup partial tiles in a fixed order and writes the caller's packing.
 // ---------------------------------------------------------------------------
-// Stage 1: every job (one block of partial results per producer workgroup or
-// wave) is cut into `splits` interleaved subsets of the producers; a thread sums
+// Stage 1: every job (one block of partial results per producer
+// workgroup) is cut into `splits` interleaved subsets of the producers; a thread sums
 // one element over one subset.  Stage 2 (the kernels below) sums the subsets and
 // writes the caller's packing.  Both orders are fixed.
 //
@@ -795,7 +769,8 @@ __device__ void reduce_head_body(const ReduceHeadArgs &a, int block, float (*s_r
         const int j = isWa ? idx - offWa : idx;
         const int lane = j & 63, comp = (j >> 6) & 3, tix = j >> 8;
         const int mt = tix / a.MA, nt = tix % a.MA;
-        const int row = 16 * mt + 4 * (lane >> 4) + comp, col = 16 * nt + (lane & 15);
+        // (rows and columns of a tile in unit-tile order)
+        const int row = 4 * (4 * mt + comp) + (lane >> 4), col = 4 * (4 * nt + (lane & 3)) + ((lane & 15) >> 2);
         if (col < a.h) {
             if (isWa) { if (row < a.h) a.gWa[row * a.h + col] = tot; }
             else if (row < a.H) a.gWo[row * a.h + col] = tot;
@@ -1310,7 +1285,7 @@ SetupArgs setup_args(const Plan &pl, const Lengths &len, const float *weights, u
     float *f = ws + pl.head_fwd_pack, *b = ws + pl.head_bwd_pack;
     a.head = PackHeadArgs{weights + pl.Wa_off, weights + pl.ba_off, weights + pl.Wo_off, weights + pl.bo_off,
                           f + hp.WaF, f + hp.baF, f + hp.WoF, f + hp.boF, b + hp.WoT, b + hp.WaT,
-                          pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
+                          pl.h, pl.H, pl.HT, pl.MA, pl.MO};
     a.pack_blocks = std::min((max_total + 255) / 256, 64);      // (the bodies loop over their elements)
     return a;
 }
@@ -1383,7 +1358,7 @@ ReduceJobs reduce_jobs(const Plan &pl, float *ws)
         add(lp.db_partial, lp.db_reduced, n_db, pl.partial_groups(lp), n_db);
     }
     const int n_head = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
-    add(pl.head_dw_partial, pl.head_dw_reduced, pl.head_dw_stride, pl.n_head_waves, n_head);
+    add(pl.head_dw_partial, pl.head_dw_reduced, pl.head_dw_stride, pl.head_blocks, n_head);
     return jobs;
 }
 
@@ -1402,7 +1377,7 @@ ReduceStage2Args reduce_stage2_args(const Plan &pl, float *ws, float *grad_weigh
     const int n_head = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
     r.head = ReduceHeadArgs{ws + pl.head_dw_reduced, grad_weights + pl.Wa_off, grad_weights + pl.ba_off,
                             grad_weights + pl.Wo_off, grad_weights + pl.bo_off,
-                            reduce_splits(pl.n_head_waves), n_head, pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
+                            reduce_splits(pl.head_blocks), n_head, pl.h, pl.H, pl.HT, pl.MA, pl.MO, pl.OT};
     r.end[kMaxLayers] = blocks + (n_head + 63) / 64;
     return r;
 }

@@ -87,7 +87,7 @@ struct Plan {
     size_t loss_partial; int n_loss_partial;   // [head_blocks] pinball sums, then [es_blocks] level-penalty sums
     size_t cs_partial; int n_cs_partial;       // sums of squared cell states of all penalised layers, contiguous
     int head_blocks;                           // workgroups of the output-stage kernel
-    size_t head_dw_partial; int n_head_waves;  // [n_head_waves][head_dw_stride]; 4 waves per workgroup
+    size_t head_dw_partial;                    // [head_blocks][head_dw_stride]
     int head_dw_stride;
     size_t head_dw_reduced;
     int es_blocks;
@@ -106,10 +106,10 @@ struct Scalars {
 
 // offsets inside the packed head operand blocks (floats), filled by plan.cpp
 struct HeadPack {
-    // forward: Wa as A operand in unit-tile order [MA][HT][64], ba [MA][4][4],
-    //          Wo as A operand in unit-tile order [MO][HT][64], bo [MO][4][4]
+    // forward: Wa as A operand in unit-tile order [MA][quads][64][4], split in three (three_term.h), ba [MA][4][4],
+    //          Wo likewise [MO][quads][64][4], bo [MO][4][4]
     size_t WaF, baF, WoF, boF, fwd_total;
-    // backward: Wo^T [MA][OT][64], Wa^T [MA][HT][64]
+    // backward: Wo^T and Wa^T, likewise
     size_t WoT, WaT, bwd_total;
 };
 HeadPack head_pack_layout(const Plan &pl);

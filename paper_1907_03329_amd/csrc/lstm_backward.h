@@ -120,15 +120,6 @@ __device__ __forceinline__ void arrived(u32x4 &v) { asm volatile("" : "+v"(v)); 
 // (inline assembly does not).
 __device__ __forceinline__ float own_register(float v) { return __builtin_canonicalizef(v); }
 
-constexpr int kPartBytes = 64 * 8 + 32;                    // LDS home of one part of 16 rows x 16 series
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ u32x2 lds_read_transposed(const char *at)
-{
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at)));
-}
-
 // Workgroups are alone on their compute unit (for their registers), so the waves of one fill it: four per SIMD.
 template <int HT, int KXT, bool CP>
 __global__ void __launch_bounds__(64 * bwd_waves(HT, KXT), (bwd_waves(HT, KXT) + 3) / 4) lstm_backward_kernel(LstmBwdArgs a)

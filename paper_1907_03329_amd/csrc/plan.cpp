@@ -82,14 +82,15 @@ HeadPack head_pack_layout(const Plan &pl)
 {
     HeadPack hp{};
     Bump b;
-    hp.WaF = b.take((size_t)pl.MA * pl.HT * 64);
+    const size_t qh = (size_t)tt_a_quads((pl.HT + 1) / 2) * 256, qo = (size_t)tt_a_quads(2 * pl.MO) * 256;
+    hp.WaF = b.take(pl.MA * qh);
     hp.baF = b.take((size_t)pl.MA * 16);
-    hp.WoF = b.take((size_t)pl.MO * pl.HT * 64);
+    hp.WoF = b.take(pl.MO * qh);
     hp.boF = b.take((size_t)pl.MO * 16);
     hp.fwd_total = b.at;
     Bump c;
-    hp.WoT = c.take((size_t)pl.MA * pl.OT * 64);
-    hp.WaT = c.take((size_t)pl.MA * pl.HT * 64);
+    hp.WoT = c.take(pl.MA * qo);
+    hp.WaT = c.take(pl.MA * qh);
     hp.bwd_total = c.at;
     return hp;
 }
@@ -187,11 +188,10 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     const size_t TB = (size_t)pl.T * pl.Bt;
     const size_t PN = (size_t)pl.P * pl.NB;
     const size_t tileH = (size_t)pl.HT * 64;         // floats of one (p, series-tile) block with HP rows
-    // output stage: every wave leaves a block of weight-gradient partials, so no more waves than fill the chip
-    const size_t n_tiles = PN;
-    const int head_blocks = (int)std::min<size_t>((n_tiles + 3) / 4, 256);
+    // output stage: a tile per wave, no more workgroups than compute units
+    const int head_w = head_waves(pl.HT, pl.MO);
+    const int head_blocks = (int)std::min<size_t>((PN + head_w - 1) / head_w, 256);
     pl.head_blocks = head_blocks;
-    pl.n_head_waves = 4 * head_blocks;
     pl.es_blocks = pl.Bt / 64;
     // first everything the smoothing and window stages touch (their own entry points need only this prefix)
     pl.scalars = ws.take(64);
@@ -289,8 +289,8 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     pl.head_bwd_pack = ws.take(hp.bwd_total);
     pl.head_dw_stride = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
     pl.head_dw_stride = (pl.head_dw_stride + 63) & ~63;
-    pl.head_dw_partial = ws.take((size_t)pl.n_head_waves * pl.head_dw_stride);
-    pl.head_dw_reduced = ws.take((size_t)kReduceSplits * pl.head_dw_stride);
+    pl.head_dw_partial = ws.take((size_t)pl.head_blocks * pl.head_dw_stride);
+    pl.head_dw_reduced = ws.take((size_t)std::min(kReduceSplits, head_blocks) * pl.head_dw_stride);
     pl.total_floats = ws.at;
     return ESRNN_OK;
 }

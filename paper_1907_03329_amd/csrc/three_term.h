@@ -31,6 +31,10 @@
 
 namespace esrnn {
 
+// ---- output stage (head_kernels.hip): waves of a workgroup.  Eight (two per SIMD) where their corners of LDS and the
+// operands kept there fit into 128 KB and a lane's sums into 256 registers.
+constexpr int head_waves(int HT, int MO) { return (HT <= 10 && MO == 1) || (HT <= 8 && MO == 2) ? 8 : 4; }
+
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -143,6 +147,17 @@ __device__ __forceinline__ float splittable(float x)
 __device__ __forceinline__ unsigned part_of(const Parts &p, int part)
 {
     return part == 0 ? p.hi : part == 1 ? p.mid : part == 2 ? p.lo : 0u;
+}
+
+// LDS home of 16 rows x 16 series in one part, for operands that are read turned (lstm_backward.h): the four rows of a lane
+// group as one 8-byte chunk per lane, [chunk][series], the second half shifted by 32 bytes.
+constexpr int kPartBytes = 64 * 8 + 32;
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 lds_read_transposed(const char *at)
+{
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(at)));
 }
 
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c)
