@@ -579,16 +579,28 @@ __global__ void __launch_bounds__(256) forecast_kernel(const float *__restrict__
     const bool valid = p < pmax[bt] && p < len - I - H + 1;     // past pmax the tile of outputs holds nothing
     const float ut = valid ? u[(size_t)t * Bp + b] : 0.0f;
     const float *ot = O + (size_t)tile * orows * 16;
-    for (int j = g; j < H; j += 4) {
-        float f = 0.0f;
-        if (valid) {
-            float seas = 1.0f;
-            if (n_seas >= 1) seas = S1[(size_t)(t + 1 + j) * Bp + b];
-            if (n_seas >= 2) seas *= S2[(size_t)(t + 1 + j) * Bp + b];
-            f = __expf(ot[j * 16 + n] + ut) * seas;
+    // Several steps' operands at a time, in range by choice of address (behind a condition each, a lane waited for every one
+    // of them: 50 us at 512 hourly series, 44 us at 4096 monthly ones; now 34 and 41 us, 128 and 124 MB).
+    const int col = min(b, Bp - 1);
+    auto steps = [&](auto kc) {
+        constexpr int K = decltype(kc)::value;
+        for (int j0 = g; j0 < H; j0 += 4 * K) {
+            float o[K], s1[K], s2[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int j = min(j0 + 4 * k, H - 1);
+                const size_t at = (size_t)min(t + 1 + j, T - 1) * Bp + col;
+                o[k] = ot[j * 16 + n];
+                s1[k] = n_seas >= 1 ? S1[at] : 1.0f;
+                s2[k] = n_seas >= 2 ? S2[at] : 1.0f;
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (j0 + 4 * k < H) fl[n * H + j0 + 4 * k] = valid ? __expf(o[k] + ut) * (s1[k] * s2[k]) : 0.0f;
         }
-        fl[n * H + j] = f;
-    }
+    };
+    if (H <= 8) steps(std::integral_constant<int, 2>{});
+    else steps(std::integral_constant<int, 4>{});
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // same wave: LDS serves its instructions in order
     float *ft = forecasts + ((size_t)p * B + bt * 16) * H;
     for (int e = lane; e < cols * H; e += 64) ft[e] = fl[e];
