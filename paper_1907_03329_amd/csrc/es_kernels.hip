@@ -1105,20 +1105,28 @@ __global__ void __launch_bounds__(256) window_backward_kernel(WindowBwdArgs a, R
     const int bt = col >> 4, n = col & 15;
     const int P = min(a.P, a.pmax[bt]);      // window gradients past the tile's longest series do not exist
     float sv = 0.0f, su = 0.0f;
-    for (int i = 0; i < I; ++i) {
-        const int p = t - i;
-        if (p >= 0 && p < P) sv += gX[((size_t)(p * NB + bt) * xrows + i) * 16 + n];
-    }
-    for (int j = 1; j <= H; ++j) {
-        const int p = t - (I - 1) - j;
-        if (p >= 0 && p < P) sv -= gO[((size_t)(p * NB + bt) * zrows + (j - 1)) * 16 + n];
-    }
-    {
-        const int p = t - I + 1;
-        if (p >= 0 && p < P) {
-            for (int i = 0; i < I; ++i) su -= gX[((size_t)(p * NB + bt) * xrows + i) * 16 + n];
-            for (int j = 0; j < H; ++j) su += gO[((size_t)(p * NB + bt) * zrows + j) * 16 + n];
+    // Eight independent requests at a time, in range by choice of address, not behind a condition each.  (One after the
+    // other, a thread was a chain of 2 (I + H) round trips.)
+    auto sum8 = [&](int rows, auto &&at, auto &&counts) {
+        float total = 0.0f;
+        for (int r0 = 0; r0 < rows; r0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[k] = at(min(r0 + k, rows - 1));
+#pragma unroll
+            for (int k = 0; k < 8; ++k) total += r0 + k < rows && counts(r0 + k) ? v[k] : 0.0f;
         }
+        return total;
+    };
+    if (P > 0) {
+        const int last = P - 1, p_u = t - I + 1, p_row = min(max(p_u, 0), last);
+        sv = sum8(I, [&](int i) { return gX[((size_t)(min(max(t - i, 0), last) * NB + bt) * xrows + i) * 16 + n]; },
+                  [&](int i) { return t - i >= 0 && t - i <= last; }) -
+             sum8(H, [&](int j) { return gO[((size_t)(min(max(t - I - j, 0), last) * NB + bt) * zrows + j) * 16 + n]; },
+                  [&](int j) { return t - I - j >= 0 && t - I - j <= last; });
+        if (p_u >= 0 && p_u <= last)
+            su = sum8(H, [&](int j) { return gO[((size_t)(p_row * NB + bt) * zrows + j) * 16 + n]; }, [](int) { return true; }) -
+                 sum8(I, [&](int i) { return gX[((size_t)(p_row * NB + bt) * xrows + i) * 16 + n]; }, [](int) { return true; });
     }
     if (a.lambda != 0.0f)
         su += level_penalty_grad(a.u, Bp, col, t, col < a.B ? clamp_len(a.lengths[col], T) : 0, a.lambda * 2.0f * a.sc->inv_n_lv);

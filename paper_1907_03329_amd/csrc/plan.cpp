@@ -38,9 +38,10 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // pass of 16 series is the fp32 kernel, which loses up to 148 groups (372 / 337 us) and at 160 with dilation 8 wins (57 / 66).
 constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwardBelowFp32 = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
-// time step and series).  Measured on the quarterly shape: gather 0.026 / 0.118 / 0.476 ms at 1024 / 4096 /
-// 16384 tiles, streaming 0.053 / 0.079 / 0.25 ms; a wave of the streaming kernel is a chain of dependent memory
-// round trips and needs about sixteen waves per SIMD to hide them.
+// time step and series).  Gather against streaming in us: quarterly shape at 1024 / 2048 / 4096 / 8192 tiles 21 / 35 / 77 / 157
+// and 52 / 58 / 77 / 155, yearly 14 / 22 / 37 / 81 and 28 / 33 / 40 / 85, monthly 131 / 257 / 497 / 979 and 274 / 324 / 440 / 949;
+// a wave of the streaming kernel is a chain of dependent memory round trips and needs about sixteen waves per SIMD to
+// hide them.
 constexpr int kWindowStreamFromDefault = 4096;
 
 // Chains of the 16-series reverse kernels, which have one workgroup per compute unit: the fewest that take the least
