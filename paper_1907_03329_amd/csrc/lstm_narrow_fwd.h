@@ -24,10 +24,18 @@ struct NarrowFwdArgs {
     int B, T, I, H;
 };
 
+// Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the next
+// position's pre-activations (with the bias), which does not depend on it: the chain then has 4 HT instead of
+// 4 (KXT + HT) matrix instructions a position, and no request of its own.  Both kinds meet the same barriers.
+// 512 hourly series, first layer (24 + 40 columns, 649 positions): 348 -> 331 us (333 -> 317 us for 333); 501 monthly ones
+// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  What
+// bounds it is the issue of one wave: 147 instructions a position, five cycles each, and an LDS round trip.  (Three
+// accumulators, which need no wait states between the matrix instructions: 340 us.)
+//
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
 // block input, writes the block output).
 template <int HT, int KXT, bool CP, bool OUT>
-__global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs a)
+__global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdArgs a)
 {
     constexpr int KX = 4 * KXT, HP = 4 * HT;
     constexpr int CH = 8;                       // positions per chunk of staged inputs
@@ -35,11 +43,12 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
     // inputs x_p of a chunk of positions [column][series], by chunk parity (+ 64 floats that take the writes of
     // the threads with no input row, so that staging is the same instruction stream in every thread)
     __shared__ float xc[2][CH][XG * 64 + 64];
-    __shared__ float rc[CH][kNT];               // residual input of this thread's (unit, series)
+    __shared__ float rc[OUT ? 2 : 1][OUT ? CH : 1][kNT];      // residual input of a thread's (unit, series), likewise
     __shared__ float hb[2][HG * 64];            // h_{p-d} [unit][series], by position parity
+    __shared__ f32x4 half[2][kNW][64];          // input half, by position parity
 
-    const int lane = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, tid = threadIdx.x & (kNT - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & (kNW - 1);
     const int blk = lane >> 2, j = lane & 3;
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
@@ -50,24 +59,91 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
     // All four workgroups of a 16-series tile stop at the tile's longest series: what lies beyond is
     // neither computed here nor read by any later kernel.
     const int Pt = a.pmax[bt];
-    const bool valid = blk < HT;
     const int unit = w * HT + min(blk, HT - 1);     // blocks past HT repeat the last unit
-
-    float wx[KX], wh[HP];
-#pragma unroll
-    for (int k = 0; k < KX; ++k) wx[k] = a.wpack[((size_t)w * (KX + HP) + k) * 64 + lane];
-#pragma unroll
-    for (int k = 0; k < HP; ++k) wh[k] = a.wpack[((size_t)w * (KX + HP) + KX + k) * 64 + lane];
-    // before the transpose a lane holds gate j of its unit for the four series
-    const float bias = unit < a.h ? a.bias[j * a.h + unit] : 0.0f;
-
     // element of this lane inside the TL(HP) block of one (position, series tile)
     const int lane_off = unit * 16 + 4 * q + j;
-    // cooperative input load: thread t < 4*KX brings row t/4 of series t%4 (the others repeat row 0)
-    const bool x_thread = (int)threadIdx.x < 4 * KX;
-    const int x_off = (x_thread ? (int)threadIdx.x >> 2 : 0) * 16 + 4 * q + (threadIdx.x & 3);
-    const int x_slot = x_thread ? (int)threadIdx.x : XG * 64 + lane;
+    // columns past KX / HP in the last group of 16 are never written: zero once (their weights do not exist)
+    for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += 2 * kNT) (&xc[0][0][0])[e] = 0.0f;
+    for (int e = threadIdx.x; e < 2 * HG * 64; e += 2 * kNT) (&hb[0][0])[e] = 0.0f;
 
+    if (wave >= kNW) {
+        // =========================== input waves ===========================
+        float wx[KX];
+#pragma unroll
+        for (int k = 0; k < KX; ++k) wx[k] = a.wpack[((size_t)w * (KX + HP) + k) * 64 + lane];
+        // before the transpose a lane holds gate j of its unit for the four series
+        const float bias = unit < a.h ? a.bias[j * a.h + unit] : 0.0f;
+        // cooperative input load: thread t < 4*KX brings row t/4 of series t%4 (the others repeat row 0)
+        const bool x_thread = tid < 4 * KX;
+        const int x_off = (x_thread ? tid >> 2 : 0) * 16 + 4 * q + (tid & 3);
+        const int x_slot = x_thread ? tid : XG * 64 + lane;
+        for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y) {
+            const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
+            float xs[CH], rs[CH];
+            auto load_chunk = [&](int c) {
+#pragma unroll
+                for (int ii = 0; ii < CH; ++ii) {
+                    const size_t tile = (size_t)(r + min(c * CH + ii, n - 1) * a.d) * a.NB + bt;
+                    xs[ii] = (a.xsrc + tile * (KX * 16))[x_off];
+                    rs[ii] = OUT ? (a.resid + tile * (HP * 16))[lane_off] : 0.0f;
+                }
+            };
+            auto flush_chunk = [&](int c) {
+#pragma unroll
+                for (int ii = 0; ii < CH; ++ii) {
+                    xc[c & 1][ii][x_slot] = xs[ii];
+                    if constexpr (OUT) rc[c & 1][ii][tid] = rs[ii];
+                }
+            };
+            // input half of the position in slot ii of the chunk of parity cpar, left for the position of parity par
+            auto input_half = [&](int cpar, int ii, int par) {
+                float vx[XG];
+#pragma unroll
+                for (int m = 0; m < XG; ++m) vx[m] = xc[cpar][ii][64 * m + lane];
+                f32x4 acc0 = f32x4{bias, bias, bias, bias}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+                static_for<0, KX / 2>([&](auto ic) {
+                    constexpr int k = 2 * decltype(ic)::value;
+                    acc0 = mfma4_bcast<k % 16>(vx[k / 16], wx[k], acc0);
+                    acc1 = mfma4_bcast<(k + 1) % 16>(vx[k / 16], wx[k + 1], acc1);
+                });
+                half[par][w][lane] = acc0 + acc1;
+            };
+            load_chunk(0);
+            __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
+            flush_chunk(0);
+            lds_barrier();
+            input_half(0, 0, 0);
+            lds_barrier();
+            // Whole chunks: the body of a chunk is one straight run of instructions, and requests are staged in the run that
+            // issued them, two positions before its end: the first position of the next chunk is formed in the last one.
+            int c = 0;
+            for (; (c + 1) * CH <= n; ++c) {
+                load_chunk(c + 1);              // (row indices stop at the chain's last position)
+                static_for<0, CH>([&](auto iic) {
+                    constexpr int ii = decltype(iic)::value;
+                    if constexpr (ii == CH - 2) flush_chunk(c + 1);
+                    if constexpr (ii == CH - 1) input_half((c + 1) & 1, 0, 0);
+                    else input_half(c & 1, ii + 1, (ii + 1) & 1);
+                    lds_barrier();
+                });
+            }
+            // the last, partial chunk
+            for (int i = c * CH; i < n; ++i) {
+                input_half(c & 1, min(i + 1 - c * CH, CH - 1), (i + 1) & 1);
+                lds_barrier();
+            }
+        }
+        if constexpr (CP) __syncthreads();
+        return;
+    }
+
+    // =========================== chain waves ===========================
+    // (ahead of the input wave of the same SIMD: what that one does has a whole position's time)
+    __builtin_amdgcn_s_setprio(3);
+    const bool valid = blk < HT;
+    float wh[HP];
+#pragma unroll
+    for (int k = 0; k < HP; ++k) wh[k] = a.wpack[((size_t)w * (KX + HP) + KX + k) * 64 + lane];
     int n_valid = 0;
     float csq = 0.0f;
     if constexpr (CP) {
@@ -75,48 +151,38 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
         const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
         n_valid = len - a.I - a.H + 1;
     }
-    // columns past KX / HP in the last group of 16 are never written: zero once (their weights do not exist)
-    for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += kNT) (&xc[0][0][0])[e] = 0.0f;
-    for (int e = threadIdx.x; e < 2 * HG * 64; e += kNT) (&hb[0][0])[e] = 0.0f;
-
     for (int r = blockIdx.y; r < a.d && r < Pt; r += gridDim.y) {
-        const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
-        float xs[CH], rs[CH];
-        auto load_chunk = [&](int c) {
-#pragma unroll
-            for (int ii = 0; ii < CH; ++ii) {
-                const size_t tile = (size_t)(r + min(c * CH + ii, n - 1) * a.d) * a.NB + bt;
-                xs[ii] = (a.xsrc + tile * (KX * 16))[x_off];
-                rs[ii] = OUT ? (a.resid + tile * (HP * 16))[lane_off] : 0.0f;
-            }
-        };
-        auto flush_chunk = [&](int c) {
-#pragma unroll
-            for (int ii = 0; ii < CH; ++ii) {
-                xc[c & 1][ii][x_slot] = xs[ii];
-                if (OUT) rc[ii][threadIdx.x] = rs[ii];
-            }
-        };
+        const int n = (Pt - r + a.d - 1) / a.d;
         float creg = 0.0f;
-        // One position.  `staged` runs after the recurrent state is published and before the position's
-        // stores are issued (the staging of the next chunk goes there).
-        auto position = [&](int i, int ii, int cpar, auto staged) {
+        __syncthreads();
+        for (int e = tid; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;    // start of a chain: zero state
+        lds_barrier();
+        lds_barrier();
+        // What a position leaves in memory is stored while the next one waits for its first operands from LDS.
+        f32x4 gates;
+        float cell, hidden, output;
+        auto store = [&](int p) {
+            // wave-uniform tile base plus the lane's element: scalar address arithmetic
+            const size_t tile = ((size_t)p * a.NB + bt) * (HP * 16);
+            __builtin_nontemporal_store(gates, reinterpret_cast<f32x4 *>(a.gates) + tile + lane_off);
+            (a.c + tile)[lane_off] = cell;     // (a plain store: the four quarter-row writes of a tile then merge in L2)
+            (a.hid + tile)[lane_off] = hidden;
+            if (OUT) (a.out + tile)[lane_off] = output;
+        };
+        auto position = [&](int i, auto parc, auto firstc) {
+            constexpr int par = decltype(parc)::value;
             const int p = r + i * a.d;
-            // [x_p ; h_{p-d}] of the four series: lane (b, s) of register m holds column 16m + b of series s
-            float vh[HG], vx[XG];
+            // h_{p-d} of the four series: lane (b, s) of register m holds unit 16m + b of series s
+            float vh[HG];
 #pragma unroll
-            for (int m = 0; m < HG; ++m) vh[m] = hb[i & 1][64 * m + lane];
-#pragma unroll
-            for (int m = 0; m < XG; ++m) vx[m] = xc[cpar][ii][64 * m + lane];
-            const float res = OUT ? rc[ii][threadIdx.x] : 0.0f;
-            // two accumulators: consecutive instructions never depend on each other (measured: one is
-            // slower, four are slower too)
-            f32x4 acc0 = f32x4{bias, bias, bias, bias}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-            static_for<0, KX / 2>([&](auto ic) {
-                constexpr int k = 2 * decltype(ic)::value;
-                acc0 = mfma4_bcast<k % 16>(vx[k / 16], wx[k], acc0);
-                acc1 = mfma4_bcast<(k + 1) % 16>(vx[k / 16], wx[k + 1], acc1);
-            });
+            for (int m = 0; m < HG; ++m) vh[m] = hb[par][64 * m + lane];
+            // two accumulators: consecutive instructions never depend on each other (measured: one, three and four are
+            // slower)
+            f32x4 acc0 = half[par][w][lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float res = OUT ? rc[OUT ? (i / CH) & 1 : 0][OUT ? i % CH : 0][tid] : 0.0f;
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!decltype(firstc)::value) store(p - a.d);
+            __builtin_amdgcn_sched_barrier(0);
             static_for<0, HP / 2>([&](auto ic) {
                 constexpr int k = 2 * decltype(ic)::value;
                 acc0 = mfma4_bcast<k % 16>(vh[k / 16], wh[k], acc0);
@@ -132,39 +198,22 @@ __global__ void __launch_bounds__(kNT) lstm_forward_narrow_kernel(NarrowFwdArgs 
             const float hn = go * tanh_f(cn);
             creg = cn;
             if constexpr (CP) csq += (valid && p < n_valid) ? cn * cn : 0.0f;
-            hb[(i + 1) & 1][4 * unit + j] = hn;
-            staged();
-            // wave-uniform tile base plus the lane's element: scalar address arithmetic
-            const size_t tile = ((size_t)p * a.NB + bt) * (HP * 16);
-            __builtin_nontemporal_store(f32x4{gi, gf, gg, go}, reinterpret_cast<f32x4 *>(a.gates) + tile + lane_off);
-            (a.c + tile)[lane_off] = cn;     // (a plain store: the four quarter-row writes of a tile then merge in L2)
-            (a.hid + tile)[lane_off] = hn;
-            if (OUT) (a.out + tile)[lane_off] = res + hn;
+            hb[par ^ 1][4 * unit + j] = hn;
+            gates = f32x4{gi, gf, gg, go};
+            cell = cn;
+            hidden = hn;
+            output = res + hn;
             lds_barrier();
         };
-        // start of a chain: zero state, inputs of the first chunk staged
-        load_chunk(0);
-        __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
-        for (int e = threadIdx.x; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;
-        flush_chunk(0);
-        lds_barrier();
-
-        // Whole chunks: the body of a chunk is one straight run of instructions.  The inputs of the next chunk
-        // are requested at its start and staged at its end, before the stores of its last position: memory
-        // operations complete in order, and with request and use in the same run the wait for a request is a
-        // count of the stores issued since (those of seven positions), never a wait for the newest stores.
-        int c = 0;
-        for (; (c + 1) * CH <= n; ++c) {
-            load_chunk(c + 1);              // (row indices stop at the chain's last position)
-            static_for<0, CH>([&](auto iic) {
-                constexpr int ii = decltype(iic)::value;
-                position(c * CH + ii, ii, c & 1, [&] {
-                    if constexpr (ii == CH - 1) flush_chunk(c + 1);
-                });
-            });
+        using std::integral_constant;
+        position(0, integral_constant<int, 0>{}, std::true_type{});
+        int i = 1;
+        for (; i + 1 < n; i += 2) {
+            position(i, integral_constant<int, 1>{}, std::false_type{});
+            position(i + 1, integral_constant<int, 0>{}, std::false_type{});
         }
-        // the last, partial chunk (staged by the run before it, or by the start of the chain)
-        for (int i = c * CH; i < n; ++i) position(i, i - c * CH, c & 1, [] {});
+        if (i < n) position(i, integral_constant<int, 1>{}, std::false_type{});
+        store(r + (n - 1) * a.d);
     }
     if constexpr (CP) {
         __shared__ float s_cs[kNW];
@@ -180,8 +229,8 @@ template <int HT, int KXT, bool OUT>
 hipError_t run_nfwd(const NarrowFwdArgs &a, int chains, hipStream_t st)
 {
     const dim3 grid(narrow_grid_x(a.NB), chains);
-    if (a.cs_partial) lstm_forward_narrow_kernel<HT, KXT, true, OUT><<<grid, 64 * kNW, 0, st>>>(a);
-    else lstm_forward_narrow_kernel<HT, KXT, false, OUT><<<grid, 64 * kNW, 0, st>>>(a);
+    if (a.cs_partial) lstm_forward_narrow_kernel<HT, KXT, true, OUT><<<grid, 2 * kNT, 0, st>>>(a);
+    else lstm_forward_narrow_kernel<HT, KXT, false, OUT><<<grid, 2 * kNT, 0, st>>>(a);
     return hipGetLastError();
 }
 
