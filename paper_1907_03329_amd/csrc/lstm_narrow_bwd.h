@@ -47,11 +47,12 @@ struct NarrowBwdArgs {
 
 // (up to hidden 40 the kernel is held to 256 registers: two workgroups per compute unit, which the chains of a
 // dilated layer need to run side by side)
-// SPLIT: eight waves.  Waves 0-3 carry the recurrence (steps A and B and the sums); waves 4-7 do step C, the
-// weight gradient, which only consumes what step A leaves in LDS, one barrier behind them.  Both kinds take the
-// same barriers (one per position).  For grids of at most one workgroup per compute unit: the chain waves then
-// have half the matrix work per position, and the SIMDs have the weight-gradient waves' work while a chain wave
-// waits.
+// SPLIT: eight waves.  Waves 0-3 carry the recurrence: steps A and B and the sums of the recurrent gradient, nothing else.
+// Waves 4-7 request and stage all operands, and one barrier behind the recurrence do step C, the weight gradient, and sum
+// and store the input gradient.  Both kinds take the same barriers (one per position).  For grids of at most one workgroup
+// per compute unit: a chain wave is bound by the instructions it issues, and the SIMDs have the other waves' work while it
+// waits.  (With requests, staging and input gradient on the chain waves the first layer of 512 hourly series took 491 us,
+// now 440; that of 501 monthly ones 247 us, now 221; that of 16 quarterly ones 43.6 us, now 39.7.)
 template <int HT, int KXT, bool CP, bool SPLIT>
 __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 2 : 1) lstm_backward_narrow_kernel(NarrowBwdArgs a)
 {
@@ -63,7 +64,8 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     constexpr int XH_PER = (4 * KT4 + kNT - 1) / kNT;
     __shared__ __align__(16) float da_all[2][HP * 16];           // [unit][series][gate]
     __shared__ __align__(16) float part[2][kNW][NG * 64 * 4];    // partial W^T da of every wave [column][series]
-    __shared__ __align__(16) f32x4 lc[CH][2][kNT];               // per thread: activated gates; c, c_{p-d}, two gradient sources
+    constexpr int SLOTS = SPLIT ? 2 * CH : CH;   // positions of staged per-thread operands (one wave writes, another reads: two chunks)
+    __shared__ __align__(16) f32x4 lc[SLOTS][2][kNT];            // per thread: activated gates; c, c_{p-d}, two gradient sources
     __shared__ float xhc[2][CH][CT * 64];                        // [column of x_p ; h_{p-d}][series]
 
     const int lane = threadIdx.x & 63;
@@ -84,16 +86,12 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     const int unit = w * HT + min(blk, HT - 1);     // blocks past HT repeat the last unit
     const int lane_off = unit * 16 + 4 * q + j;
     // input gradient: thread t sums and stores element t mod 4*KX (threads past 4*KX repeat earlier ones)
-    const int dx_el = (int)threadIdx.x % (4 * KX);
+    const int tid = (int)threadIdx.x & (kNT - 1);
+    const int dx_el = tid % (4 * KX);
     // operands of the weight-gradient tiles inside 64 consecutive floats of da_all / xhc
     const int ar_off = 16 * (lane & 3) + 4 * (lane >> 4) + ((lane & 15) >> 2);   // unit l%4, series l/16, gate (l%16)/4
     const int xb_off = 4 * (lane & 15) + (lane >> 4);                            // column l%16, series l/16
 
-    float wreg[NG][4 * HT];
-#pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int k = 0; k < 4 * HT; ++k) wreg[g][k] = a.wpack[(((size_t)w * NG + g) * (4 * HT) + k) * 64 + lane];
     f32x4 dw[MTW][CT];
 #pragma unroll
     for (int t = 0; t < MTW; ++t)
@@ -117,39 +115,105 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
             }
         }
     };
+    // ---- requests and staging of a chunk: the c * CH + ii-th positions from the end of a chain that ends at p_last and has
+    // n positions (requests past the chain repeat the last)
+    f32x4 s_gt[CH], s_o[CH];     // (native vectors: arrays of the HIP float4 class do not stay in registers)
+    float s_xh[CH][XH_PER];
+    auto load_chunk = [&](int c, int n, int p_last) {
+#pragma unroll
+        for (int ii = 0; ii < CH; ++ii) {
+            const int p = p_last - min(c * CH + ii, n - 1) * a.d;
+            const size_t pb = (size_t)p * a.NB + bt;
+            const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
+            const size_t e = pb * (HP * 16) + lane_off;
+            s_gt[ii] = reinterpret_cast<const f32x4 *>(a.gates)[e];
+            s_o[ii] = f32x4{a.c[e], a.c[pbd * (HP * 16) + lane_off], a.gsrc[0][e], a.gsrc[1][e]};
+#pragma unroll
+            for (int k = 0; k < XH_PER; ++k) {
+                const int el = min(tid + k * kNT, 4 * KT4 - 1);
+                const int col = el >> 2, jj = el & 3;
+                // one base pointer and a per-lane offset (a per-lane choice between two pointers would be
+                // fetched from the argument block in memory, with a wait, before every request)
+                const ptrdiff_t off = col < KX ? (ptrdiff_t)((pb * KX + col) * 16)
+                                               : a.hid_minus_xsrc + (ptrdiff_t)((pbd * HP + (col - KX)) * 16);
+                s_xh[ii][k] = a.xsrc[off + 4 * q + jj];
+            }
+        }
+    };
+    auto flush_chunk = [&](int c, int n, int p_last) {
+#pragma unroll
+        for (int ii = 0; ii < CH; ++ii) {
+            const bool has_prev = p_last - min(c * CH + ii, n - 1) * a.d >= a.d;
+            const int slot = SPLIT ? (c & 1) * CH + ii : ii;
+            lc[slot][0][tid] = s_gt[ii];
+            lc[slot][1][tid] = s_o[ii];
+#pragma unroll
+            for (int k = 0; k < XH_PER; ++k) {
+                const int el = tid + k * kNT;
+                if (el < 4 * KT4) xhc[c & 1][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
+            }
+        }
+    };
+    // ---- sum and store of one position's input gradient
+    auto input_gradient = [&](int p, int par) {
+        const float dxv = (part[par][0][dx_el] + part[par][1][dx_el]) + (part[par][2][dx_el] + part[par][3][dx_el]);
+        (a.gdst + ((size_t)p * a.NB + bt) * (KX * 16))[(dx_el >> 2) * 16 + 4 * q + (dx_el & 3)] = dxv;
+    };
+    // ---- C: weight gradient of one position, k = the four series; da in da_all[par], [x ; h] in xhc[cpar][ii]
+    auto step_c = [&](int par, int cpar, int ii) {
+        float xb[CT];
+#pragma unroll
+        for (int nb = 0; nb < CT; ++nb) xb[nb] = xhc[cpar][ii][64 * nb + xb_off];
+#pragma unroll
+        for (int t = 0; t < MTW; ++t) {
+            const int mt = w + kNW * t;
+            if (mt < HT) {
+                // row 4*gate + u of the tile is gate `gate` of unit 4*mt + u
+                const float ar = da_all[par][64 * mt + ar_off];
+#pragma unroll
+                for (int nb = 0; nb < CT; ++nb) dw[t][nb] = mfma16(ar, xb[nb], dw[t][nb]);
+            }
+        }
+    };
     if constexpr (SPLIT) {
         if (dw_wave) {
-            // ---- C: weight gradient of one position, k = the four series; da in da_all[par], [x ; h] in xhc[cpar][ii]
-            auto step_c = [&](int par, int cpar, int ii) {
-                float xb[CT];
-#pragma unroll
-                for (int nb = 0; nb < CT; ++nb) xb[nb] = xhc[cpar][ii][64 * nb + xb_off];
-#pragma unroll
-                for (int t = 0; t < MTW; ++t) {
-                    const int mt = w + kNW * t;
-                    if (mt < HT) {
-                        // row 4*gate + u of the tile is gate `gate` of unit 4*mt + u
-                        const float ar = da_all[par][64 * mt + ar_off];
-#pragma unroll
-                        for (int nb = 0; nb < CT; ++nb) dw[t][nb] = mfma16(ar, xb[nb], dw[t][nb]);
-                    }
-                }
-            };
             // the same barriers as the chain waves below: start of a chain, first staging, one per position
             for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
-                const int n = (Pt - r0 + a.d - 1) / a.d;
+                const int n = (Pt - r0 + a.d - 1) / a.d, p_last = r0 + (n - 1) * a.d;
+                load_chunk(0, n, p_last);
                 __syncthreads();
+                flush_chunk(0, n, p_last);
                 lds_barrier();
-                for (int i = 0; i < n; ++i) {
+                int c = 0;
+                for (; (c + 1) * CH <= n; ++c) {
+                    load_chunk(c + 1, n, p_last);
+                    static_for<0, CH>([&](auto iic) {
+                        constexpr int ii = decltype(iic)::value;
+                        // (the chain reads a position's operands in the interval before it)
+                        if constexpr (ii == CH - 2) flush_chunk(c + 1, n, p_last);
+                        lds_barrier();
+                        const int i = c * CH + ii;
+                        step_c(i & 1, c & 1, ii);
+                        input_gradient(p_last - i * a.d, i & 1);
+                    });
+                }
+                for (int i = c * CH; i < n; ++i) {
                     lds_barrier();
-                    step_c(i & 1, (i / CH) & 1, i % CH);
+                    step_c(i & 1, c & 1, i - c * CH);
+                    input_gradient(p_last - i * a.d, i & 1);
                 }
             }
             store_dw();
             return;
         }
+        __builtin_amdgcn_s_setprio(3);      // (ahead of the other wave of the SIMD)
     }
 
+    float wreg[NG][4 * HT];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int k = 0; k < 4 * HT; ++k) wreg[g][k] = a.wpack[(((size_t)w * NG + g) * (4 * HT) + k) * 64 + lane];
     const float g2_scale = a.n_gsrc >= 2 ? 1.0f : 0.0f;
     int n_valid = 0;
     float pen = 0.0f;
@@ -163,53 +227,16 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
         const int n = (Pt - r0 + a.d - 1) / a.d;
         const int p_last = r0 + (n - 1) * a.d;
-        // operands of the i-th position from the end of the chain (requests past the chain repeat the last)
-        f32x4 s_gt[CH], s_o[CH];     // (native vectors: arrays of the HIP float4 class do not stay in registers)
-        float s_xh[CH][XH_PER];
-        auto load_chunk = [&](int c) {
-#pragma unroll
-            for (int ii = 0; ii < CH; ++ii) {
-                const int p = p_last - min(c * CH + ii, n - 1) * a.d;
-                const size_t pb = (size_t)p * a.NB + bt;
-                const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
-                const size_t e = pb * (HP * 16) + lane_off;
-                s_gt[ii] = reinterpret_cast<const f32x4 *>(a.gates)[e];
-                s_o[ii] = f32x4{a.c[e], a.c[pbd * (HP * 16) + lane_off], a.gsrc[0][e], a.gsrc[1][e]};
-#pragma unroll
-                for (int k = 0; k < XH_PER; ++k) {
-                    const int el = min((int)threadIdx.x + k * kNT, 4 * KT4 - 1);
-                    const int col = el >> 2, jj = el & 3;
-                    // one base pointer and a per-lane offset (a per-lane choice between two pointers would be
-                    // fetched from the argument block in memory, with a wait, before every request)
-                    const ptrdiff_t off = col < KX ? (ptrdiff_t)((pb * KX + col) * 16)
-                                                   : a.hid_minus_xsrc + (ptrdiff_t)((pbd * HP + (col - KX)) * 16);
-                    s_xh[ii][k] = a.xsrc[off + 4 * q + jj];
-                }
-            }
-        };
-        auto flush_chunk = [&](int c) {
-#pragma unroll
-            for (int ii = 0; ii < CH; ++ii) {
-                const bool has_prev = p_last - min(c * CH + ii, n - 1) * a.d >= a.d;
-                lc[ii][0][threadIdx.x] = s_gt[ii];
-                lc[ii][1][threadIdx.x] = s_o[ii];
-#pragma unroll
-                for (int k = 0; k < XH_PER; ++k) {
-                    const int el = (int)threadIdx.x + k * kNT;
-                    if (el < 4 * KT4) xhc[c & 1][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
-                }
-            }
-        };
-        load_chunk(0);
+        if constexpr (!SPLIT) load_chunk(0, n, p_last);
         float dcreg = 0.0f, dhreg = 0.0f;
         __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
-        flush_chunk(0);
+        if constexpr (!SPLIT) flush_chunk(0, n, p_last);
         lds_barrier();
 
         // per-thread operands of the first position; those of position i+1 are read before the barrier
         // that ends position i
-        f32x4 gt = lc[0][0][threadIdx.x];      // activated input, forget, candidate, output gate
-        f32x4 o = lc[0][1][threadIdx.x];       // c, c_{p-d}, gradient sources
+        f32x4 gt = lc[0][0][tid];      // activated input, forget, candidate, output gate
+        f32x4 o = lc[0][1][tid];       // c, c_{p-d}, gradient sources
         // One position: the i-th from the end of the chain, staged in slot ii of the chunk buffers of parity
         // cpar; the per-thread operands of the next position are in slot `next`.  `staged` runs after they
         // have been read and before the barrier (the staging of the next chunk goes there).
@@ -260,8 +287,8 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
                 *reinterpret_cast<f32x4 *>(&part[par][w][(64 * g + lane) * 4]) =
                     kBwdAcc == 4 ? (acc[g][0] + acc[g][1]) + (acc[g][2] + acc[g][3]) : kBwdAcc == 2 ? acc[g][0] + acc[g][1] : acc[g][0];
             // per-thread operands of the next position (staged at least one barrier ago)
-            gt = lc[next][0][threadIdx.x];
-            o = lc[next][1][threadIdx.x];
+            gt = lc[next][0][tid];
+            o = lc[next][1][tid];
             staged();
             lds_barrier();
             // ---- sums of the four partials: recurrent dh of this lane; input gradient
@@ -269,36 +296,32 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
                 const int e = 4 * (KX + unit) + j;
                 dhreg = (part[par][0][e] + part[par][1][e]) + (part[par][2][e] + part[par][3][e]);
             }
-            const float dxv = (part[par][0][dx_el] + part[par][1][dx_el]) + (part[par][2][dx_el] + part[par][3][dx_el]);
-            (a.gdst + ((size_t)p * a.NB + bt) * (KX * 16))[(dx_el >> 2) * 16 + 4 * q + (dx_el & 3)] = dxv;
-            // ---- C: weight gradient, k = the four series (on the waves of its own where there are some)
-            if constexpr (!SPLIT) {
-                float xb[CT];
-#pragma unroll
-                for (int nb = 0; nb < CT; ++nb) xb[nb] = xhc[cpar][ii][64 * nb + xb_off];
-#pragma unroll
-                for (int t = 0; t < MTW; ++t) {
-                    const int mt = w + kNW * t;
-                    if (mt < HT) {
-                        // row 4*gate + u of the tile is gate `gate` of unit 4*mt + u
-                        const float ar = da_all[par][64 * mt + ar_off];
-#pragma unroll
-                        for (int nb = 0; nb < CT; ++nb) dw[t][nb] = mfma16(ar, xb[nb], dw[t][nb]);
-                    }
-                }
+            if constexpr (!SPLIT) {         // (the other waves' work where there are some)
+                input_gradient(p, par);
+                step_c(par, cpar, ii);
             }
         };
+        if constexpr (SPLIT) {
+            // (slots by position modulo two chunks)
+            int i = 0;
+            for (; i + 1 < n; i += 2) {
+                position(i, 0, 0, (i + 1) & (SLOTS - 1), [] {});
+                position(i + 1, 0, 0, (i + 2) & (SLOTS - 1), [] {});
+            }
+            if (i < n) position(i, 0, 0, 0, [] {});
+            continue;
+        }
         // Whole chunks: one straight run of instructions each.  The operands of the next chunk are requested
         // at its start and staged one position before its end (after this thread has read its operands of the
         // chunk's last position): request and use in the same run, so the wait for a request counts the
         // memory operations issued since instead of waiting for all of them.
         int c = 0;
         for (; (c + 1) * CH <= n; ++c) {
-            load_chunk(c + 1);              // (requests past the chain repeat its last position)
+            load_chunk(c + 1, n, p_last);   // (requests past the chain repeat its last position)
             static_for<0, CH>([&](auto iic) {
                 constexpr int ii = decltype(iic)::value;
                 position(c * CH + ii, ii, c & 1, (ii + 1) % CH, [&] {
-                    if constexpr (ii == CH - 2) flush_chunk(c + 1);
+                    if constexpr (ii == CH - 2) flush_chunk(c + 1, n, p_last);
                 });
             });
         }
