@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace esrnn {
 
@@ -19,6 +20,20 @@ __device__ __forceinline__ void static_for(F &&f)
         f(std::integral_constant<int, I>{});
         static_for<I + 1, N>(f);
     }
+}
+
+// f(std::integral_constant<int, k % N>, k) for k = 0, 1, ... while it returns true: a loop unrolled N times that is left
+// from any of its parts.  (With parts that are skipped instead, the compiler sees ways around the requests in them, and waits
+// for everything that is under way wherever one of them is used.)
+template <int N, class F, int... I>
+__device__ __forceinline__ bool round_of(F &&f, int first, std::integer_sequence<int, I...>)
+{
+    return (f(std::integral_constant<int, I>{}, first + I) && ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void rotate_while(F &&f)
+{
+    for (int first = 0; round_of<N>(f, first, std::make_integer_sequence<int, N>{}); first += N) {}
 }
 
 // D = A(16x4) * B(4x16) + C(16x16), fp32.  Lane l supplies A[l%16][l/16] and

@@ -492,25 +492,22 @@ __global__ void __launch_bounds__(256) es_forward_kernel(EsArgs a, SetupArgs set
             }
         };
         static_for<0, kEsAhead>([&](auto d) { load_chunk(decltype(d)::value, ybuf[decltype(d)::value]); });
-        for (int c0 = 0; c0 < n_chunks; c0 += kEsAhead) {
-            static_for<0, kEsAhead>([&](auto dd) {
-                constexpr int d = decltype(dd)::value;
-                const int c = c0 + d;
-                if (c < n_chunks) {                         // (wave-uniform)
-                    float *out = stage + (c & 1) * (CH * NF * 64);
+        rotate_while<kEsAhead>([&](auto dd, int c) {
+            constexpr int d = decltype(dd)::value;
+            if (c >= n_chunks) return false;                // (wave-uniform)
+            float *out = stage + (c & 1) * (CH * NF * 64);
 #pragma unroll
-                    for (int k = 0; k < CH; k += CS) {
-                        const bool wraps = (NS >= 1 && i1 + CS > a.m1) || (NS >= 2 && i2 + CS > a.m2);   // (wave-uniform)
-                        if (wraps) steps(std::true_type{}, c * CH + k, ybuf[d] + k, out + k * NF * 64);
-                        else steps(std::false_type{}, c * CH + k, ybuf[d] + k, out + k * NF * 64);
-                    }
-                    load_chunk(c + kEsAhead, ybuf[d]);
-                    // chunk c is staged; the other waves have finished with chunk c - 1, whose buffer chunk
-                    // c + 1 reuses
-                    lds_barrier();
-                }
-            });
-        }
+            for (int k = 0; k < CH; k += CS) {
+                const bool wraps = (NS >= 1 && i1 + CS > a.m1) || (NS >= 2 && i2 + CS > a.m2);   // (wave-uniform)
+                if (wraps) steps(std::true_type{}, c * CH + k, ybuf[d] + k, out + k * NF * 64);
+                else steps(std::false_type{}, c * CH + k, ybuf[d] + k, out + k * NF * 64);
+            }
+            load_chunk(c + kEsAhead, ybuf[d]);
+            // chunk c is staged; the other waves have finished with chunk c - 1, whose buffer chunk
+            // c + 1 reuses
+            lds_barrier();
+            return true;
+        });
         return;
     }
 
@@ -1350,45 +1347,42 @@ __global__ void __launch_bounds__(64 * (1 + kEsBwdHelpers)) es_backward_kernel(E
         // rows are requested kEsAhead chunks ahead (register sets rotating through an unrolled loop, as in the
         // forward recursion)
         static_for<0, kEsAhead>([&](auto d) { load_chunk(decltype(d)::value, raw[decltype(d)::value]); });
-        for (int j0 = 0; j0 <= n_chunks; j0 += kEsAhead) {
-            static_for<0, kEsAhead>([&](auto dd) {
-                constexpr int d = decltype(dd)::value;
-                const int j = j0 + d;
-                if (j > n_chunks) return;                   // (wave-uniform)
-                if (j < n_chunks) {
-                    float *out = stage + (j & 1) * (CH * NC * 64) + lane;
+        // (the last interval stages a chunk that nobody takes: one way through the loop)
+        rotate_while<kEsAhead>([&](auto dd, int j) {
+            constexpr int d = decltype(dd)::value;
+            if (j > n_chunks) return false;                 // (wave-uniform)
+            float *out = stage + (j & 1) * (CH * NC * 64) + lane;
 #pragma unroll
-                    for (int i = 0; i < NK; ++i) {
-                        const int k = (role - 1) + i * kEsBwdHelpers;
-                        const Raw &r = raw[d][i];
-                        const float ilp = fast_rcp(r.lp);
-                        const float is1 = NS >= 1 ? fast_rcp(r.s1) : 1.0f, is2 = NS >= 2 ? fast_rcp(r.s2) : 1.0f;
-                        const float ry = r.y * ilp;
-                        const float r1 = ry * is2, r2 = ry * is1;
-                        const float q = r.y * (is1 * is2);
-                        float *o = out + k * NC * 64;
-                        o[0 * 64] = r.gu * fast_rcp(r.lt);
-                        o[1 * 64] = ilp;
-                        o[2 * 64] = alpha * q;
-                        o[3 * 64] = q - r.lp;
-                        if (NS >= 1) {
-                            o[4 * 64] = -r.gv * is1;
-                            o[5 * 64] = is1;
-                            o[6 * 64] = g1 * r1;
-                            o[7 * 64] = r1 - r.s1;
-                        }
-                        if (NS >= 2) {
-                            o[8 * 64] = -r.gv * is2;
-                            o[9 * 64] = is2;
-                            o[10 * 64] = g2 * r2;
-                            o[11 * 64] = r2 - r.s2;
-                        }
-                    }
-                    load_chunk(j + kEsAhead, raw[d]);
+            for (int i = 0; i < NK; ++i) {
+                const int k = (role - 1) + i * kEsBwdHelpers;
+                const Raw &r = raw[d][i];
+                const float ilp = fast_rcp(r.lp);
+                const float is1 = NS >= 1 ? fast_rcp(r.s1) : 1.0f, is2 = NS >= 2 ? fast_rcp(r.s2) : 1.0f;
+                const float ry = r.y * ilp;
+                const float r1 = ry * is2, r2 = ry * is1;
+                const float q = r.y * (is1 * is2);
+                float *o = out + k * NC * 64;
+                o[0 * 64] = r.gu * fast_rcp(r.lt);
+                o[1 * 64] = ilp;
+                o[2 * 64] = alpha * q;
+                o[3 * 64] = q - r.lp;
+                if (NS >= 1) {
+                    o[4 * 64] = -r.gv * is1;
+                    o[5 * 64] = is1;
+                    o[6 * 64] = g1 * r1;
+                    o[7 * 64] = r1 - r.s1;
                 }
-                lds_barrier();
-            });
-        }
+                if (NS >= 2) {
+                    o[8 * 64] = -r.gv * is2;
+                    o[9 * 64] = is2;
+                    o[10 * 64] = g2 * r2;
+                    o[11 * 64] = r2 - r.s2;
+                }
+            }
+            load_chunk(j + kEsAhead, raw[d]);
+            lds_barrier();
+            return true;
+        });
         return;
     }
 
