@@ -355,8 +355,8 @@ struct EsArgs {
 // Division of labour.  A workgroup serves 64 series with three or four waves.  Wave 0 runs the recursion and
 // nothing else: it reads observations (several chunks ahead), keeps the rings, and leaves level,
 // de-seasonalised value and factors of every step in an LDS staging buffer; it issues no global store and
-// computes no logarithm.  Of the previous chunk, wave 1 turns the staged level into lvl, u = ln(level) and
-// the level penalty, wave 2 the staged value into v, and wave 3 (seasonal shapes) stores the factors.  A lone
+// computes no logarithm.  Of the previous chunk, wave 1 forms the level penalty, wave 2 turns the staged level into
+// lvl and u = ln(level) and the staged value into v, and wave 3 (seasonal shapes) stores the factors.  A lone
 // wave issues one instruction every few cycles whatever the instruction is; with the chain, five stores and two
 // logarithms per step on the same wave a step took about three times as long as the chain alone.
 constexpr int kEsChunk = 8;                 // steps per staging buffer
@@ -364,7 +364,32 @@ constexpr int kEsAhead = 4;                 // chunks between the request of a r
 // staged per step: level, de-seasonalised value, and one factor per seasonality
 constexpr int es_stage_floats(int n_seas) { return 2 * kEsChunk * (2 + n_seas) * 64; }
 
-//
+
+// Storing of staged rows, four steps and four series a lane: a quarter of the stores (a wave has at most 63 under way) and of
+// the instructions around them.  501 monthly series 24.0 -> 23.4 us, 65 536 quarterly ones 27.4 -> 26.7 us, 16 9.7 -> 9.3 us;
+// with long periods, below, 0.55 -> 0.47 us a chunk.
+struct ChunkRows {
+    int row, col, t_end, lens[4];       // this lane's step of four, its first series, and the lengths of its series
+    size_t base, Bp;
+    __device__ ChunkRows(int Bp_, int t_end_, int len) : row((threadIdx.x & 63) >> 4), col(4 * (threadIdx.x & 15)), t_end(t_end_), Bp(Bp_)
+    {
+        base = (size_t)blockIdx.x * 64 + col;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lens[e] = __shfl(len, col + e, 64);
+    }
+    // of a row of 64 series staged every `stride` floats from `at` on
+    __device__ f32x4 quad(const float *at, int stride) const { return *reinterpret_cast<const f32x4 *>(at + row * stride + col); }
+    __device__ f32x4 logs(const f32x4 &v) const { return f32x4{fast_log(v[0]), fast_log(v[1]), fast_log(v[2]), fast_log(v[3])}; }
+    // row t (if the wave's series go that far), the padding value past a series' end
+    __device__ void put(float *to, int t, const f32x4 &v, float pad) const
+    {
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = t < lens[e] ? v[e] : pad;
+        if (t < t_end) *reinterpret_cast<f32x4 *>(to + (size_t)t * Bp + base) = r;
+    }
+};
+
 // The set-up work needs nothing of the recursions and they nothing of it, and neither fills the chip: one launch has both
 // (as two launches: 11 + 6.5 us at 4096 quarterly series, 9.9 + 4.8 us at 16; a forecast had a third one for the lengths).
 template <int NS, int CS>
@@ -511,79 +536,44 @@ __global__ void __launch_bounds__(256) es_forward_kernel(EsArgs a, SetupArgs set
         return;
     }
 
-    // ---- the storing waves: chunk c after the barrier that publishes it.  One loop per role, the staged
-    // values of a whole chunk read together, no branch inside a full chunk.
-    const int full_chunks = t_end / CH;            // chunks that lie entirely below the bound
-    if (role == 1) {
+    // ---- the other waves: chunk c after the barrier that publishes it, the staged values of a whole chunk read together
+    if (role == 1) {                            // Section 8.4: squared second difference of the log level
         float u1 = 0.0f, u2 = 0.0f, lv_sum = 0.0f;
-        auto chunk = [&](int c, int n_steps) {
+        for (int c = 0; c < n_chunks; ++c) {
+            lds_barrier();
             const float *in = stage + (c & 1) * (CH * NF * 64) + lane;
             float lt[CH];
 #pragma unroll
             for (int k = 0; k < CH; ++k) lt[k] = in[k * NF * 64];
 #pragma unroll
             for (int k = 0; k < CH; ++k) {
-                if (k >= n_steps) break;
                 const int t = c * CH + k;
-                const bool live = t < len;
-                const float l = live ? lt[k] : 1.0f;
-                const float ut = live ? fast_log(l) : 0.0f;
-                const unsigned at = (unsigned)t * (unsigned)a.Bp + ub;     // (B * T is at most 2^30)
-                a.lvl[at] = l;
-                a.u[at] = ut;
-                // Section 8.4: squared second difference of the log level
-                const float e = ut - 2.0f * u1 + u2;
-                lv_sum += (live && t >= 2) ? e * e : 0.0f;
+                const float ut = fast_log(lt[k]), e = ut - 2.0f * u1 + u2;
+                lv_sum += t < len && t >= 2 ? e * e : 0.0f;
                 u2 = u1; u1 = ut;
             }
-        };
-        for (int c = 0; c < n_chunks; ++c) {
-            lds_barrier();
-            if (c < full_chunks) chunk(c, CH);
-            else chunk(c, t_end - c * CH);
         }
         const float tot = wave_sum(lv_sum);
         if (lane == 0) a.lv_partial[blockIdx.x] = tot;
-    } else if (role == 2) {
-        auto chunk = [&](int c, int n_steps) {
-            const float *in = stage + (c & 1) * (CH * NF * 64) + 64 + lane;
-            float q[CH];
+        return;
+    }
+    const ChunkRows rows(a.Bp, t_end, len);
+    for (int c = 0; c < n_chunks; ++c) {
+        lds_barrier();
+        const float *in = stage + (c & 1) * (CH * NF * 64);
 #pragma unroll
-            for (int k = 0; k < CH; ++k) q[k] = in[k * NF * 64];
-#pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                if (k >= n_steps) break;
-                const int t = c * CH + k;
-                a.v[(unsigned)t * (unsigned)a.Bp + ub] = t < len ? fast_log(q[k]) : 0.0f;      // ln y - ln(S1 S2)
+        for (int k0 = 0; k0 < CH; k0 += 4) {
+            const int t = c * CH + k0 + rows.row;
+            auto staged = [&](int f) { return rows.quad(in + (k0 * NF + f) * 64, NF * 64); };
+            if (role == 2) {
+                const f32x4 l = staged(0);
+                rows.put(a.lvl, t, l, 1.0f);
+                rows.put(a.u, t, rows.logs(l), 0.0f);
+                rows.put(a.v, t, rows.logs(staged(1)), 0.0f);              // ln y - ln(S1 S2)
+            } else {
+                if constexpr (NS >= 1) rows.put(a.S1, t, staged(2), 1.0f);
+                if constexpr (NS >= 2) rows.put(a.S2, t, staged(3), 1.0f);
             }
-        };
-        for (int c = 0; c < n_chunks; ++c) {
-            lds_barrier();
-            if (c < full_chunks) chunk(c, CH);
-            else chunk(c, t_end - c * CH);
-        }
-    } else {
-        auto chunk = [&](int c, int n_steps) {
-            const float *in = stage + (c & 1) * (CH * NF * 64) + 128 + lane;
-            float s1[CH], s2[CH];
-#pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                s1[k] = NS >= 1 ? in[k * NF * 64] : 1.0f;
-                s2[k] = NS >= 2 ? in[k * NF * 64 + 64] : 1.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                if (k >= n_steps) break;
-                const int t = c * CH + k;
-                const unsigned at = (unsigned)t * (unsigned)a.Bp + ub;
-                if (NS >= 1) a.S1[at] = t < len ? s1[k] : 1.0f;
-                if (NS >= 2) a.S2[at] = t < len ? s2[k] : 1.0f;
-            }
-        };
-        for (int c = 0; c < n_chunks; ++c) {
-            lds_barrier();
-            if (c < full_chunks) chunk(c, CH);
-            else chunk(c, t_end - c * CH);
         }
     }
 }
@@ -800,42 +790,22 @@ __global__ void __launch_bounds__(64 * kEsLongWaves) es_forward_long_kernel(EsAr
         const float tot = wave_sum(lv_sum);
         if (lane == 0) a.lv_partial[blockIdx.x] = tot;
     } else {                                        // ---- stores
-        // Four steps and four series a lane: a wave has at most 63 stores under way, and with one row each (256 bytes) that
-        // limit was the kernel's (0.55 us a chunk).
-        const int row = lane >> 4, col = 4 * (lane & 15);
-        int lens[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) lens[e] = __shfl(len, col + e, 64);
-        const float *stage4 = stage - lane + col;
-        auto quad = [&](int c, int k, int f) {
-            return *reinterpret_cast<const f32x4 *>(stage4 + (((c & (kEsLongSlots - 1)) * CH + k) * NF + f) * 64);
-        };
-        const size_t base = (size_t)blockIdx.x * 64 + col;
-        auto put = [&](float *to, int t, const f32x4 &v) {
-            if (t < t_end) *reinterpret_cast<f32x4 *>(to + (size_t)t * a.Bp + base) = v;
-        };
-        // padding values past a series' end
-        auto pick = [&](int t, const f32x4 &v, float pad) {
-            f32x4 r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = t < lens[e] ? v[e] : pad;
-            return r;
-        };
-        auto logs = [&](const f32x4 &v) { return f32x4{fast_log(v[0]), fast_log(v[1]), fast_log(v[2]), fast_log(v[3])}; };
+        const ChunkRows rows(a.Bp, t_end, len);
         for (int j = 0; j < intervals; ++j) {
             const int c = j - 2;
             if (c >= 0 && c < n) {
 #pragma unroll
                 for (int k0 = 0; k0 < CH; k0 += 4) {
-                    const int k = k0 + row, t = c * CH + k;
+                    const int t = c * CH + k0 + rows.row;
+                    auto staged = [&](int f) { return rows.quad(&field(c, k0, f) - lane, NF * 64); };
                     if (role == 2 * SHARES + 2) {
-                        const f32x4 l = quad(c, k, kLevel);
-                        put(a.lvl, t, pick(t, l, 1.0f));
-                        put(a.u, t, pick(t, logs(l), 0.0f));
+                        const f32x4 l = staged(kLevel);
+                        rows.put(a.lvl, t, l, 1.0f);
+                        rows.put(a.u, t, rows.logs(l), 0.0f);
                     } else {
-                        put(a.v, t, pick(t, logs(quad(c, k, kQ)), 0.0f));               // ln y - ln(S1 S2)
-                        put(a.S1, t, pick(t, quad(c, k, kS1), 1.0f));
-                        if constexpr (NS >= 2) put(a.S2, t, pick(t, quad(c, k, kS2), 1.0f));
+                        rows.put(a.v, t, rows.logs(staged(kQ)), 0.0f);              // ln y - ln(S1 S2)
+                        rows.put(a.S1, t, staged(kS1), 1.0f);
+                        if constexpr (NS >= 2) rows.put(a.S2, t, staged(kS2), 1.0f);
                     }
                 }
             }
