@@ -30,34 +30,34 @@ PEAK_HBM_GBS = 8000.0           # MI355X HBM3E peak
 # (FETCH x 2.0, WRITE x 1.0): profiles/hbm_traffic_<workload>_B<batch>.txt.  Valid for that workload and batch only.
 MEASURED_TRAFFIC_BYTES = {
     ('tiny_quarterly', 16): {
-        "es_forward": 1.136e+05, "window_forward": 1.53e+05, "lstm_forward_l0": 1.083e+06, "lstm_forward_l1": 1.25e+06,
-        "lstm_forward_l2": 1.247e+06, "lstm_forward_l3": 1.56e+06, "head_forward_backward": 1.565e+06, "forecasts": 1.405e+05,
-        "lstm_backward_l3": 3.176e+06, "lstm_backward_l2": 2.356e+06, "lstm_backward_l1": 2.103e+06, "lstm_backward_l0": 1.329e+06,
-        "window_backward": 1.33e+05, "es_backward": 9.528e+04,
+        "es_forward": 2.324e+06, "window_forward": 1.53e+05, "lstm_forward_l0": 1.037e+06, "lstm_forward_l1": 1.244e+06,
+        "lstm_forward_l2": 1.24e+06, "lstm_forward_l3": 1.554e+06, "head_forward_backward": 1.05e+06, "forecasts": 1.559e+05,
+        "lstm_backward_l3": 3.175e+06, "lstm_backward_l2": 2.355e+06, "lstm_backward_l1": 2.101e+06, "lstm_backward_l0": 1.338e+06,
+        "window_backward": 5.584e+06, "es_backward": 2.709e+06,
     },
     ('quarterly', 4096): {
-        "es_forward": 6.297e+06, "window_forward": 1.421e+07, "lstm_forward_l0": 2.446e+08, "lstm_forward_l1": 2.808e+08,
-        "lstm_forward_l2": 2.809e+08, "lstm_forward_l3": 3.626e+08, "head_forward_backward": 1.171e+08, "forecasts": 1.818e+07,
+        "es_forward": 8.522e+06, "window_forward": 1.421e+07, "lstm_forward_l0": 2.446e+08, "lstm_forward_l1": 2.808e+08,
+        "lstm_forward_l2": 2.809e+08, "lstm_forward_l3": 3.625e+08, "head_forward_backward": 1.077e+08, "forecasts": 1.819e+07,
         "lstm_backward_l3": 3.696e+08, "lstm_backward_l2": 3.723e+08, "lstm_backward_l1": 4.136e+08, "lstm_backward_l0": 2.969e+08,
-        "window_backward": 1.56e+07, "es_backward": 6.163e+06,
+        "window_backward": 6.992e+07, "es_backward": 9.663e+06,
     },
     ('monthly', 4096): {
-        "es_forward": 2.019e+07, "window_forward": 1.181e+08, "lstm_forward_l0": 1.121e+09, "lstm_forward_l1": 1.263e+09,
-        "lstm_forward_l2": 1.265e+09, "lstm_forward_l3": 1.639e+09, "head_forward_backward": 5.931e+08, "forecasts": 1.317e+08,
+        "es_forward": 2.389e+07, "window_forward": 1.181e+08, "lstm_forward_l0": 1.121e+09, "lstm_forward_l1": 1.263e+09,
+        "lstm_forward_l2": 1.265e+09, "lstm_forward_l3": 1.639e+09, "head_forward_backward": 5.743e+08, "forecasts": 1.317e+08,
         "lstm_backward_l3": 1.636e+09, "lstm_backward_l2": 1.641e+09, "lstm_backward_l1": 1.823e+09, "lstm_backward_l0": 1.356e+09,
-        "window_backward": 2.073e+08, "es_backward": 2.006e+07,
+        "window_backward": 2.733e+08, "es_backward": 2.649e+07,
     },
     ('yearly', 8192): {
-        "es_forward": 5.5e+06, "window_forward": 1.751e+07, "lstm_forward_l0": 1.905e+08, "lstm_forward_l1": 2.136e+08,
-        "lstm_forward_l2": 2.136e+08, "lstm_forward_l3": 2.75e+08, "head_forward_backward": 9.038e+07, "forecasts": 1.245e+07,
+        "es_forward": 6.891e+06, "window_forward": 1.751e+07, "lstm_forward_l0": 1.905e+08, "lstm_forward_l1": 2.134e+08,
+        "lstm_forward_l2": 2.136e+08, "lstm_forward_l3": 2.748e+08, "head_forward_backward": 8.561e+07, "forecasts": 1.247e+07,
         "lstm_backward_l3": 2.855e+08, "lstm_backward_l2": 2.897e+08, "lstm_backward_l1": 3.201e+08, "lstm_backward_l0": 2.407e+08,
-        "window_backward": 1.543e+07, "es_backward": 4.033e+06,
+        "window_backward": 8.38e+07, "es_backward": 6.392e+06,
     },
     ('hourly', 512): {
-        "es_forward": 9.568e+06, "window_forward": 9.854e+07, "lstm_forward_l0": 4.244e+08, "lstm_forward_l1": 3.731e+08,
-        "lstm_forward_l2": 3.732e+08, "lstm_forward_l3": 4.8e+08, "head_forward_backward": 3.176e+08, "forecasts": 1.318e+08,
-        "lstm_backward_l3": 4.798e+08, "lstm_backward_l2": 4.916e+08, "lstm_backward_l1": 5.394e+08, "lstm_backward_l0": 4.417e+08,
-        "window_backward": 1.949e+08, "es_backward": 9.431e+06,
+        "window_forward": 9.854e+07, "lstm_forward_l0": 4.218e+08, "lstm_forward_l1": 3.731e+08, "lstm_forward_l2": 3.732e+08,
+        "lstm_forward_l3": 4.801e+08, "head_forward_backward": 3.033e+08, "forecasts": 1.318e+08, "lstm_backward_l3": 4.798e+08,
+        "lstm_backward_l2": 4.916e+08, "lstm_backward_l1": 5.394e+08, "lstm_backward_l0": 4.417e+08, "window_backward": 2.425e+08,
+        "es_backward": 1.327e+07,
     },
 }
 

@@ -17,8 +17,8 @@
 // the weights: block u, lane g of a wave holds gate g of hidden unit u.  One
 // instruction advances 16 units x 4 gates x 4 series by one input column, and no
 // operand has to be replicated over the blocks: a wave reads [x_p ; h_{p-d}] of
-// the four series from LDS with one 4-byte load per 16 columns.  A workgroup has
-// four waves; wave w owns the units w*HT .. w*HT+HT-1 (HT <= 16; the padded
+// the four series from LDS with one 4-byte load per 16 columns.  Four waves
+// share the units; wave w owns w*HT .. w*HT+HT-1 (HT <= 16; the padded
 // hidden size is 4*HT).  A lane ends up with one gate of one unit for the four
 // series; a 4x4 transpose inside each quad of lanes (DPP) turns that into the
 // four gates of one unit for ONE series, and the cell update is lane-local as
@@ -34,6 +34,11 @@
 // are double-buffered by position parity, which leaves one barrier per
 // position.  Every LDS array is laid out [row][4 series], so that each access
 // of a wave covers consecutive addresses.
+//
+// Waves that carry the recurrence are bound by the instructions they issue, so
+// whatever it does not need is done by four more waves: the inputs and their half
+// of the pre-activations (forward), and in the reverse kernel, where the grid leaves
+// the room, all requests, the weight gradient and the input gradient.
 //
 // Global operands.  A position takes a fraction of a microsecond here, less
 // than the latency of HBM, so operands are requested a whole chunk of positions
@@ -63,8 +68,8 @@ namespace esrnn {
 
 namespace {
 
-constexpr int kNW = 4;          // waves per workgroup
-constexpr int kNT = 64 * kNW;   // threads per workgroup
+constexpr int kNW = 4;          // waves that share the units (twice as many run where there are two kinds of waves)
+constexpr int kNT = 64 * kNW;
 
 // D_blk[i][j] += A_ABID[i] * B_blk[j] for all 16 blocks: the A values of block ABID serve every block.
 template <int ABID>
