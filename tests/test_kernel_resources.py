@@ -1,0 +1,46 @@
+"""What the compiler made of kernels that rely on their registers, read from the metadata of the built library."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_1907_03329_amd import binding, build
+
+READELF = os.environ.get("LLVM_READELF", "/opt/rocm/llvm/bin/llvm-readelf")
+BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+@pytest.fixture(scope="module")
+def scratch(tmp_path_factory):
+    """{kernel: bytes of scratch per lane}"""
+    if not os.path.exists(binding.LIB_PATH):
+        build.build()
+    data = open(binding.LIB_PATH, "rb").read()
+    d, out, at = tmp_path_factory.mktemp("code_objects"), {}, data.find(BUNDLE)
+    while at >= 0:      # one bundle per translation unit: entries of offset, size, length of the triple, triple
+        n, pos = struct.unpack_from("<Q", data, at + len(BUNDLE))[0], at + len(BUNDLE) + 8
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<3Q", data, pos)
+            triple = data[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if b"gfx950" not in triple or not size:
+                continue
+            path = d / "code"
+            path.write_bytes(data[at + offset:at + offset + size])
+            notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+            names = re.findall(r"^\s+\.name:\s+(_Z\S+)\s*$", notes, re.M)
+            sizes = re.findall(r"^\s+\.private_segment_fixed_size:\s+(\d+)\s*$", notes, re.M)
+            assert len(names) == len(sizes)
+            out.update(zip(names, map(int, sizes)))
+        at = data.find(BUNDLE, at + 1)
+    return out
+
+
+def test_rows_requested_ahead_stay_in_registers(scratch):
+    """Smoothing recursions: a wave's requests for observations, chunks of steps ahead, have constant places.  In scratch
+    (as when their steps are calls and not inlined) every one of them is waited for: 43 -> 82 us for 240 steps at period 1."""
+    kernels = {k: v for k, v in scratch.items() if re.search(r"es_(forward|forward_long|backward)_kernel", k)}
+    assert len(kernels) == 14       # forward: 9 of seasonalities and steps per group, 2 for long periods; reverse: 3
+    assert not {k: v for k, v in kernels.items() if v}
