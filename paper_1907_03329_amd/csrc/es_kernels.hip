@@ -221,29 +221,58 @@ __device__ __forceinline__ void pack_lstm_body(const PackLstmArgs &a, int block,
 struct PackHeadArgs {
     const float *Wa, *ba, *Wo, *bo;
     float *WaF, *baF, *WoF, *boF, *WoT, *WaT;
+    Scalars *sc;
     int h, H, HT, MA, MO;
 };
 
+// An infinity has no parts: inf, NaN, NaN.  Forward, the largest number that has three parts stands for it: in the tanh
+// layer it saturates a unit, and the linear layer finds the rows that are to be infinite in Scalars::infinite_rows.
+// Transposed, where an infinite weight meets a gradient that is zero (of a saturated unit, of a masked output) and others
+// that are not, NaN does.  (A run that has diverged is to see it in its loss and its gradients, as with fp32 products.)
+__device__ __forceinline__ float finite_parts(float x)
+{
+    return __builtin_fabsf(x) >= 0x1.ffp127f ? __builtin_copysignf(0x1.fep127f, x) : x;      // (halfway to 2^128)
+}
+__device__ __forceinline__ float nan_parts(float x) { return __builtin_isinf(x) ? __builtin_nanf("") : finite_parts(x); }
+
+// One workgroup; `found`: 4 words of LDS
+__device__ __forceinline__ void infinite_rows_body(const PackHeadArgs &a, unsigned long long *found)
+{
+    constexpr int per = ESRNN_MAX_WINDOW / 4;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float w[per];
+#pragma unroll
+    for (int k = 0; k < per; ++k) w[k] = a.Wo[min(4 * k + wave, a.H - 1) * a.h + min(lane, a.h - 1)];
+    unsigned long long rows = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k)
+        if (__ballot(__builtin_isinf(w[k])) != 0 && 4 * k + wave < a.H) rows |= 1ull << (4 * k + wave);
+    if (lane == 0) found[wave] = rows;
+    __syncthreads();
+    if (threadIdx.x == 0) a.sc->infinite_rows = found[0] | found[1] | found[2] | found[3];
+}
+
 // Operands of the output stage (head_kernels.hip): three bf16 parts as [tile][quad][lane][dword], rows in unit-tile order:
 // row 4g+r of tile m is row 4(4m+r)+g of the product.
-__device__ __forceinline__ void pack_head_body(const PackHeadArgs &a, int block, int n_blocks)
+__device__ __forceinline__ void pack_head_body(const PackHeadArgs &a, int block, int n_blocks, float *scratch)
 {
+    if (block == n_blocks - 1) infinite_rows_body(a, reinterpret_cast<unsigned long long *>(scratch));   // (has the least to pack)
     const int np_h = (a.HT + 1) / 2, np_o = 2 * a.MO, qh = tt_a_quads(np_h), qo = tt_a_quads(np_o);
     auto pack = [&](float *dst, int tiles, int quads, int np, auto &&at) {      // at(row, column), zero outside
         for (int idx = block * 256 + threadIdx.x; idx < tiles * quads * 256; idx += n_blocks * 256) {
             const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, m = (idx >> 8) / quads;
             const int i = lane & 15, k = lane >> 4, row = 4 * (4 * m + (i & 3)) + (i >> 2);
             const TtDword w = tt_a_dword(np, q, d);
-            const Parts p = split_pair(splittable(at(row, 8 * w.pair + k)), splittable(at(row, 8 * w.pair + 4 + k)));
+            const Parts p = split_pair(at(row, 8 * w.pair + k), at(row, 8 * w.pair + 4 + k));
             reinterpret_cast<unsigned *>(dst)[idx] = part_of(p, w.part);
         }
     };
     auto wa = [&](int out, int in) { return out < a.h && in < a.h ? a.Wa[out * a.h + in] : 0.0f; };
     auto wo = [&](int out, int in) { return out < a.H && in < a.h ? a.Wo[out * a.h + in] : 0.0f; };
-    pack(a.WaF, a.MA, qh, np_h, wa);
-    pack(a.WoF, a.MO, qh, np_h, wo);
-    pack(a.WoT, a.MA, qo, np_o, [&](int unit, int out) { return wo(out, unit); });
-    pack(a.WaT, a.MA, qh, np_h, [&](int unit, int out) { return wa(out, unit); });
+    pack(a.WaF, a.MA, qh, np_h, [&](int unit, int in) { return finite_parts(wa(unit, in)); });
+    pack(a.WoF, a.MO, qh, np_h, [&](int out, int in) { return finite_parts(wo(out, in)); });
+    pack(a.WoT, a.MA, qo, np_o, [&](int unit, int out) { return nan_parts(wo(out, unit)); });
+    pack(a.WaT, a.MA, qh, np_h, [&](int unit, int out) { return nan_parts(wa(out, unit)); });
     for (int j = block * 256 + threadIdx.x; j < 16 * (a.MA + a.MO); j += n_blocks * 256) {
         const bool second = j >= 16 * a.MA;
         const int e = second ? j - 16 * a.MA : j;
@@ -324,7 +353,7 @@ __device__ __forceinline__ void setup_body(const SetupArgs &a, int block, float 
     block -= a.extend_blocks;
     const int z = block / a.pack_blocks, k = block % a.pack_blocks;
     if (z < a.L) pack_lstm_body(a.lstm[z], k, a.pack_blocks);
-    else pack_head_body(a.head, k, a.pack_blocks);
+    else pack_head_body(a.head, k, a.pack_blocks, scratch);
 }
 
 // ---------------------------------------------------------------------------
@@ -1520,7 +1549,7 @@ SetupArgs setup_args(const Plan &pl, const Lengths &len, const float *weights, u
     const HeadPack hp = head_pack_layout(pl);
     float *f = ws + pl.head_fwd_pack, *b = ws + pl.head_bwd_pack;
     a.head = PackHeadArgs{weights + pl.Wa_off, weights + pl.ba_off, weights + pl.Wo_off, weights + pl.bo_off,
-                          f + hp.WaF, f + hp.baF, f + hp.WoF, f + hp.boF, b + hp.WoT, b + hp.WaT,
+                          f + hp.WaF, f + hp.baF, f + hp.WoF, f + hp.boF, b + hp.WoT, b + hp.WaT, a.prep.sc,
                           pl.h, pl.H, pl.HT, pl.MA, pl.MO};
     a.pack_blocks = std::min((max_total + 255) / 256, 64);      // (the bodies loop over their elements)
     return a;

@@ -97,11 +97,12 @@ struct Plan {
     size_t total_floats;
 };
 
-// device-side scalars computed from lengths
+// device-side scalars computed from lengths, and from weights
 struct Scalars {
     float inv_n_pin;   // 1 / number of unmasked head outputs
     float inv_n_lv;    // 1 / number of second differences of the log level (0 if none)
     float inv_n_cs;    // 1 / number of cell-state values in the cell-state penalty (0 if none)
+    unsigned long long infinite_rows;   // steps of the horizon whose weights in the linear layer are not all finite
 };
 
 // offsets inside the packed head operand blocks (floats), filled by plan.cpp

@@ -136,6 +136,12 @@ struct Contraction {
     }
 };
 
+// What a sum of the linear layer is multiplied by: infinite where a weight of its row is (whose operand is a finite number).
+__device__ __forceinline__ float row_scale(unsigned long long infinite_rows, int row)
+{
+    return (infinite_rows >> row) & 1 ? __builtin_inff() : 1.0f;
+}
+
 template <int HT, int MO>
 struct HeadShape {
     static constexpr int MA = (HT + 3) / 4;             // 16-row tiles of the hidden units
@@ -168,7 +174,8 @@ __global__ void __launch_bounds__(64 * head_waves(HT, MO)) head_kernel(HeadArgs 
     constexpr int MA = S::MA, OTMAX = S::OTMAX, NPH = S::NPH, NPO = S::NPO, QH = S::QH, QO = S::QO, W = S::W;
     __shared__ __align__(16) char lds[S::kBytes];
     __shared__ float s_part[W];
-    __shared__ __align__(16) float s_bias[16 * (MA + MO)];      // [tile][lane group][component]
+    __shared__ __align__(16) float s_ba[16 * MA];               // [tile][lane group][component]
+    __shared__ __align__(16) float s_out[16 * MO][2];           // likewise: scale of a sum, bias
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, known to be uniform
@@ -229,8 +236,12 @@ __global__ void __launch_bounds__(64 * head_waves(HT, MO)) head_kernel(HeadArgs 
             if (k * 64 * W + (int)threadIdx.x < kAll) s_WoT[k * 64 * W + threadIdx.x] = v[k];
     }
     __builtin_amdgcn_sched_barrier(0);
-    if ((int)threadIdx.x < 16 * (MA + MO))
-        s_bias[threadIdx.x] = (int)threadIdx.x < 16 * MA ? a.baF[threadIdx.x] : a.boF[threadIdx.x - 16 * MA];
+    if ((int)threadIdx.x < 16 * MA) {
+        s_ba[threadIdx.x] = a.baF[threadIdx.x];
+    } else if (const int e = (int)threadIdx.x - 16 * MA; e < 16 * MO) {
+        s_out[e][0] = row_scale(a.sc->infinite_rows, 4 * (4 * (e >> 4) + (e & 3)) + ((e >> 2) & 3));
+        s_out[e][1] = a.boF[e];
+    }
     u32x4 wa[MA][QH], wo[S::kWoLds ? 1 : MO][S::kWoLds ? 1 : QH];
 #pragma unroll
     for (int m = 0; m < MA; ++m)
@@ -330,7 +341,7 @@ __global__ void __launch_bounds__(64 * head_waves(HT, MO)) head_kernel(HeadArgs 
             linear_layer.request(wo_op);
 #pragma unroll
             for (int m = 0; m < MA; ++m) {
-                const f32x4 ba = *reinterpret_cast<const f32x4 *>(s_bias + (m * 4 + g) * 4);
+                const f32x4 ba = *reinterpret_cast<const f32x4 *>(s_ba + (m * 4 + g) * 4);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) av[4 * m + r] = (4 * m + r < HT) ? tanh_f(acc[m][r] + ba[r]) : 0.0f;
             }
@@ -347,7 +358,8 @@ __global__ void __launch_bounds__(64 * head_waves(HT, MO)) head_kernel(HeadArgs 
             go[ks] = 0.0f;
             if (4 * ks >= a.orows) continue;        // (uniform; the rows of a tile are whole unit tiles)
             const int j = 4 * ks + g;               // 0-based step of the horizon
-            const float o = oc[ks >> 2][ks & 3] + s_bias[((MA + (ks >> 2)) * 4 + g) * 4 + (ks & 3)];
+            const float *of = s_out[((ks >> 2) * 4 + g) * 4 + (ks & 3)];
+            const float o = fmaf(oc[ks >> 2][ks & 3], of[0], of[1]);
             const float d = z[ks] - o;
             const bool counted = valid && j < a.H;
             if (counted) loss += d >= 0.0f ? a.tau * d : (a.tau - 1.0f) * d;
@@ -501,7 +513,7 @@ __global__ void __launch_bounds__(256) head_last_kernel(HeadArgs a)
 #pragma unroll
     for (int ks = 0; ks < OTMAX; ++ks) {
         const int j = 4 * ks + g;
-        const float o = oc[ks >> 2][ks & 3] + bo[ks >> 2][ks & 3];
+        const float o = fmaf(oc[ks >> 2][ks & 3], row_scale(a.sc->infinite_rows, j), bo[ks >> 2][ks & 3]);
         if (windows >= 1 && j < a.orows) a.O[tile * a.orows * 16 + j * 16 + n] = o;
         if (b < a.B && j < a.H) a.forecasts[(size_t)b * a.H + j] = windows >= 1 ? __expf(o + ut) * seas[ks] : 0.0f;
     }
