@@ -49,7 +49,8 @@ def relative(got, want):
 # The 4-series kernels form fp32 products: the 16-series ones have to be as close to float64 on the same inputs, tensor by
 # tensor.  A sum of products that lacks one of the small terms is off by 2.4e-6 to 3.5e-6 of its size (random factors,
 # lengths 16 and 160); the errors here are 2e-7 to 6e-7 (4e-7 to 1.6e-6 for the first layer with long windows, most of it
-# from its inputs), so half as much again and 3e-7 tell the two apart.
+# from its inputs), so half as much again and 3e-7 tell the two apart.  (The output stage is the same on both sides; what its
+# products are held to is in test_output_stage_accuracy.py.)
 @pytest.mark.parametrize("hidden,window", SHAPES)
 def test_gradients_are_as_accurate_as_with_fp32_products(hidden, window, monkeypatch):
     cfg = Config("three_term", B=17, T=window + 3 + 40, n_seas=1, m1=4, m2=0, I=window, H=3, hidden=hidden,
