@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
 #pragma unroll
         for (int nb = 0; nb < CT; ++nb) dw[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 dbacc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int e = threadIdx.x; e < 2 * CH * CT * 64; e += kNT) (&xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
+    for (int e = threadIdx.x; e < 2 * CH * CT * 64; e += SPLIT ? 2 * kNT : kNT) (&xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
 
     auto store_dw = [&]() {
         const size_t partix = (size_t)(4 * bt + q) * gridDim.y + blockIdx.y;

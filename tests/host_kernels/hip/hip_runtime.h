@@ -14,16 +14,29 @@
 #define __shared__ static __attribute__((section("lds")))
 
 struct float4 { float x, y, z, w; };
+struct int4 { int x, y, z, w; };
 struct dim3 {
     unsigned x, y, z;
     dim3(unsigned x_ = 1, unsigned y_ = 1, unsigned z_ = 1) : x(x_), y(y_), z(z_) {}
 };
 enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1 };
 typedef void *hipStream_t;
+enum { hipFuncAttributeMaxDynamicSharedMemorySize };
 inline hipError_t hipGetLastError() { return hipSuccess; }
+inline hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+inline hipError_t hipFuncSetAttribute(const void *, int, int) { return hipSuccess; }
 extern dim3 threadIdx, blockIdx, gridDim;
 using std::max;
 using std::min;
+
+// ---- launches (host_kernels.cpp): thread(context) for every thread of the grid ----
+extern float host_dynamic_lds[];
+void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *), void *context);
+template <class F>
+void host_launch(dim3 grid, int threads, size_t dynamic_lds, F &&f)
+{
+    host_run(grid, threads, dynamic_lds, [](void *c) { (*static_cast<std::remove_reference_t<F> *>(c))(); }, &f);
+}
 
 // ---- device builtins: addresses and barriers are those of the device, arithmetic across lanes is not formed ----
 void host_barrier();                            // host_kernels.cpp
@@ -44,13 +57,24 @@ typedef const char *__amdgpu_buffer_rsrc_t;
 #define __syncthreads() host_barrier()
 #define __ballot(x) ((void)(x), ~0ull)
 #define __shfl_xor(v, off, width) (v)
+#define __shfl(v, lane, width) (v)
 #define __expf(x) (x)
 #define __builtin_amdgcn_rcpf(x) (x)
 #define __builtin_amdgcn_logf(x) (x)
 #define __builtin_amdgcn_exp2f(x) (x)
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_s_setprio(x) ((void)0)
+#define __builtin_amdgcn_fence(order, scope) ((void)0)
+#define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) (v)
 #define __builtin_canonicalizef(x) (x)
-#define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)
-#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
+// (the operands count as used, so that the loads that bring them stay)
+template <class V>
+inline void host_use(const V &v) { __asm__ volatile("" : : "m"(v)); }
+#define HOST_MFMA(a, b, c) (host_use(a), host_use(b), (c))
+#define __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, x, y, z) HOST_MFMA(a, b, c)
+#define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) HOST_MFMA(a, b, c)
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) HOST_MFMA(a, b, c)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(at) (*(at))
+// (the other waves' bits count for the same wave here)
+inline unsigned atomicOr(unsigned *at, unsigned v) { return *at |= v; }

@@ -1,12 +1,14 @@
-// Runs the 16-series LSTM kernels on the CPU, thread by thread, and checks what does not depend on values:
-//   every global access lies in the workspace;
-//   every wave of a workgroup meets the same barriers;
-//   between two barriers no wave touches LDS that another one writes.
+// Runs the kernels on the CPU, thread by thread, and checks what does not depend on values:
+//   every access lies in the workspace, in an input or output at its size, in the launch's LDS, or in the program itself;
+//   every wave of a workgroup meets the same barriers (or none: it has ended before the first one);
+//   between two barriers no wave touches LDS that another one writes (what is never read may be written by all).
 // The interval between two barriers that an access falls into, and its address, depend on the wave, the lane and the
 // shape alone, so the threads need not run side by side.
 //
 // usage: host_kernels B T I H hidden lambda_cs fwd|bwd|all  dilation [dilation ...]   (blocks of one layer)
 //        host_kernels plan ... the same: what the plan chose per layer, nothing is run
+//        host_kernels step B T I H hidden m1 m2 lambda_cs lengths dilation [dilation ...]: all kernels of a training step and of
+//        a forecast; lengths: of every 64 series (a wave's bounds are those of its own lane here), separated by commas
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -19,7 +21,10 @@
 dim3 threadIdx, blockIdx, gridDim;
 
 namespace {
-const char *g_ws, *g_ws_end;
+struct Range { const char *begin, *end; };
+std::vector<Range> g_memory;        // what the kernels may touch beside LDS, the stack and the program's own data
+const char *g_stack;
+size_t g_dynamic_lds;
 int g_wave, g_interval;
 char g_what[96];
 struct Use { unsigned short readers, writers; };
@@ -30,13 +35,38 @@ std::unordered_map<size_t, std::vector<Use>> g_lds;      // by address / 2, then
     printf("FAIL %s: %s (block %u %u, wave %d, after barrier %d)\n", g_what, why, blockIdx.x, blockIdx.y, g_wave, g_interval);
     exit(1);
 }
+
+// zeros, where the kernels may read and write
+template <class T>
+T *memory(size_t n)
+{
+    const size_t bytes = (n * sizeof(T) + 255) / 256 * 256;
+    char *p = static_cast<char *>(aligned_alloc(256, bytes));
+    memset(p, 0, bytes);
+    g_memory.push_back({p, p + n * sizeof(T)});
+    return reinterpret_cast<T *>(p);
+}
+
+bool known(const char *p, int bytes)
+{
+    for (const Range &r : g_memory)
+        if (p >= r.begin && p + bytes <= r.end) return true;
+    return false;
+}
 }  // namespace
 
-extern "C" char __start_lds, __stop_lds;
+__attribute__((section("lds"), aligned(256))) float host_dynamic_lds[40960];     // the most a workgroup has
+extern "C" char __start_lds, __stop_lds, __executable_start, end;
 static void touch(const void *at, int bytes, bool write)
 {
     const char *p = static_cast<const char *>(at);
-    if (p < &__start_lds || p >= &__stop_lds) return;
+    if (p < &__start_lds || p >= &__stop_lds) {
+        const bool own = (p >= &__executable_start && p < &end) || (p >= static_cast<char *>(__builtin_frame_address(0)) && p < g_stack);
+        if (!own && !known(p, bytes)) fail("access outside the workspace, the inputs and the outputs");
+        return;
+    }
+    const char *dynamic = reinterpret_cast<const char *>(host_dynamic_lds);
+    if (p >= dynamic && p < dynamic + sizeof host_dynamic_lds && p + bytes > dynamic + g_dynamic_lds) fail("access past the LDS of the launch");
     for (int i = 0; i < std::max(bytes / 2, 1); ++i) {
         std::vector<Use> &u = g_lds[reinterpret_cast<size_t>(p) / 2 + i];
         if (u.size() <= (size_t)g_interval) u.resize(g_interval + 1, Use{0, 0});
@@ -52,27 +82,29 @@ X(1, uint8_t) X(2, uint16_t) X(4, uint32_t) X(8, uint64_t) X(16, __uint128_t)
 void host_barrier() { ++g_interval; }
 void host_global(const void *at, int bytes)
 {
-    const char *p = static_cast<const char *>(at);
-    if (p < g_ws || p + bytes > g_ws_end) fail("global access outside the workspace");
+    if (!known(static_cast<const char *>(at), bytes)) fail("access outside the workspace, the inputs and the outputs");
 }
 
-// one launch: kernel(args) for every thread of the grid
-void host_launch(void (*thread)(const void *), const void *args, dim3 grid, int threads)
+void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *), void *context)
 {
     gridDim = grid;
+    g_dynamic_lds = dynamic_lds;
     for (blockIdx.y = 0; blockIdx.y < grid.y; ++blockIdx.y)
         for (blockIdx.x = 0; blockIdx.x < grid.x; ++blockIdx.x) {
             g_lds.clear();
-            int barriers = -1;
+            int barriers = 0;
             for (int t = 0; t < threads; ++t) {
                 threadIdx.x = t;
                 g_wave = t / 64;
                 g_interval = 0;
-                thread(args);
-                if (barriers >= 0 && barriers != g_interval) fail("waves meet different numbers of barriers");
-                barriers = g_interval;
+                thread(context);
+                if (barriers > 0 && g_interval > 0 && barriers != g_interval) fail("waves meet different numbers of barriers");
+                barriers = std::max(barriers, g_interval);
             }
-            for (const auto &e : g_lds)
+            for (const auto &e : g_lds) {
+                unsigned readers = 0;
+                for (const Use &u : e.second) readers |= u.readers;
+                if (!readers) continue;
                 for (size_t i = 0; i < e.second.size(); ++i) {
                     const unsigned w = e.second[i].writers, all = w | e.second[i].readers;
                     if (w && (all & (all - 1))) {
@@ -81,28 +113,80 @@ void host_launch(void (*thread)(const void *), const void *args, dim3 grid, int 
                         fail("LDS written by this wave is touched by another one with no barrier in between");
                     }
                 }
+            }
         }
 }
 
-namespace esrnn {
-// (the 4-series kernels are not built here)
-hipError_t launch_lstm_forward_narrow(const Plan &, int, const int32_t *, const float *, float *, hipStream_t) { return hipErrorInvalidValue; }
-}  // namespace esrnn
+using namespace esrnn;
+
+// every kernel of a training step, with and without a reverse pass to come, and of a forecast
+static int step(const Plan &pl, const std::vector<int> &lens)
+{
+    float *ws = memory<float>(pl.total_floats);
+    const float *y = memory<float>((size_t)pl.T * pl.B), *es = memory<float>((size_t)pl.K * pl.B), *weights = memory<float>(pl.n_weights);
+    float *loss = memory<float>(1), *in_sample = memory<float>((size_t)pl.P * pl.B * pl.H), *ahead = memory<float>((size_t)pl.B * pl.H);
+    float *grad_es = memory<float>((size_t)pl.K * pl.B), *grad_weights = memory<float>(pl.n_weights);
+    int32_t *lengths = memory<int32_t>(pl.B), *shorter = memory<int32_t>(pl.B);
+    for (int b = 0; b < pl.B; ++b) {
+        lengths[b] = lens[b / 64 % lens.size()];
+        shorter[b] = lengths[b] - pl.H;
+    }
+    auto run = [&](const char *what, int layer, hipError_t e) {
+        if (e == hipSuccess) return;
+        printf("FAIL %s %d: not launched\n", what, layer);
+        exit(1);
+    };
+#define RUN(layer, call) (snprintf(g_what, sizeof g_what, "%s, layer %d", #call, layer), run(#call, layer, call))
+    for (int pass = 0; pass < 3; ++pass) {
+        const bool reverse = pass == 0, predict = pass == 2;
+        const ForwardMode mode{reverse, predict ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr, predict};
+        const int32_t *n = predict ? reinterpret_cast<const int32_t *>(ws + pl.len_ext) : lengths;
+        RUN(-1, launch_es_forward(pl, y, predict ? shorter : lengths, es, weights, ws, mode, nullptr));
+        RUN(-1, launch_window_forward(pl, nullptr, ws, nullptr));
+        for (int l = 0; l < pl.L; ++l) RUN(l, launch_lstm_forward(pl, l, n, weights, ws, mode, nullptr));
+        if (predict) {
+            RUN(-1, launch_head_last(pl, n, ws, ahead, nullptr));
+            continue;
+        }
+        RUN(-1, launch_head(pl, n, ws, reverse, nullptr));
+        RUN(-1, launch_loss_and_forecasts(pl, n, ws, loss, in_sample, nullptr));
+        if (!reverse) continue;
+        for (int l = pl.L - 1; l >= 0; --l) RUN(l, launch_lstm_backward(pl, l, n, ws, nullptr));
+        RUN(-1, launch_window_backward(pl, n, ws, true, nullptr));
+        RUN(-1, launch_es_backward(pl, y, n, es, ws, grad_es, grad_weights, nullptr));
+    }
+#undef RUN
+    printf("ok\n");
+    return 0;
+}
 
 int main(int argc, char **argv)
 {
-    using namespace esrnn;
+    g_stack = static_cast<const char *>(__builtin_frame_address(0)) + 4096;
     const bool plan_only = argc > 1 && !strcmp(argv[1], "plan");
     if (plan_only) { --argc; ++argv; }
     if (argc < 9) return 2;
     esrnn_config c{};
+    static Plan pl;
+    if (!strcmp(argv[1], "step")) {
+        c.B = atoi(argv[2]); c.T = atoi(argv[3]); c.I = atoi(argv[4]); c.H = atoi(argv[5]); c.hidden = atoi(argv[6]);
+        c.m1 = atoi(argv[7]); c.m2 = atoi(argv[8]); c.lambda_cs = (float)atof(argv[9]);
+        c.n_seas = (c.m1 > 0) + (c.m2 > 0);
+        c.lambda_lv = 1.0f;
+        c.tau = 0.5f;
+        std::vector<int> lens;
+        for (char *at = argv[10]; at; at = strchr(at, ',') ? strchr(at, ',') + 1 : nullptr) lens.push_back(atoi(at));
+        c.n_blocks = argc - 11;
+        for (int i = 0; i < c.n_blocks; ++i) { c.layers_in_block[i] = 1; c.dilation[i][0] = atoi(argv[11 + i]); }
+        if (c.B % 64 || build_plan(c, pl) != ESRNN_OK) { printf("refused\n"); return 1; }
+        return step(pl, lens);
+    }
     c.B = atoi(argv[1]); c.T = atoi(argv[2]); c.I = atoi(argv[3]); c.H = atoi(argv[4]); c.hidden = atoi(argv[5]);
     c.lambda_cs = (float)atof(argv[6]);
     c.tau = 0.5f;
     const bool fwd = strcmp(argv[7], "bwd"), bwd = strcmp(argv[7], "fwd");
     c.n_blocks = argc - 8;
     for (int i = 0; i < c.n_blocks; ++i) { c.layers_in_block[i] = 1; c.dilation[i][0] = atoi(argv[8 + i]); }
-    static Plan pl;
     if (build_plan(c, pl) != ESRNN_OK) { printf("refused\n"); return 1; }
     if (plan_only) {
         printf("total %zu\n", pl.total_floats);
@@ -111,23 +195,21 @@ int main(int argc, char **argv)
                    pl.layer[l].narrow_bwd, pl.layer[l].chains, pl.layer[l].chains_bwd);
         return 0;
     }
-    float *ws = static_cast<float *>(aligned_alloc(256, pl.total_floats * 4));
-    memset(ws, 0, pl.total_floats * 4);
-    g_ws = reinterpret_cast<const char *>(ws);
-    g_ws_end = g_ws + pl.total_floats * 4;
+    float *ws = memory<float>(pl.total_floats);
     // tiles of different lengths, one without any position
     for (int t = 0; t < pl.NB; ++t) reinterpret_cast<int32_t *>(ws + pl.pmax)[t] = t == 0 ? pl.P : t == 1 ? (pl.P + 1) / 2 : 0;
-    std::vector<int32_t> lengths(c.B, c.T);
+    int32_t *lengths = memory<int32_t>(c.B);
+    std::fill(lengths, lengths + c.B, c.T);
     for (int l = 0; l < pl.L; ++l) {
         const LayerPlan &lp = pl.layer[l];
         for (int stash = 0; fwd && stash < 2; ++stash) {
             snprintf(g_what, sizeof g_what, "forward, layer %d (%d, %d unit tiles)", l, pl.HT, lp.KXT);
-            if (launch_lstm_forward(pl, l, lengths.data(), nullptr, ws, ForwardMode{stash != 0, nullptr}, nullptr) != hipSuccess) return 3;
+            if (launch_lstm_forward(pl, l, lengths, nullptr, ws, ForwardMode{stash != 0, nullptr}, nullptr) != hipSuccess) return 3;
         }
         if (bwd && bwd_three_term(pl.HT)) {
             snprintf(g_what, sizeof g_what, "reverse, layer %d (%d, %d unit tiles)", l, pl.HT, lp.KXT);
             const LstmBwdSources src{{ws + lp.gsrc[0], ws + lp.gsrc[lp.n_gsrc >= 2]}, std::min(lp.n_gsrc, 2)};
-            if (launch_lstm_backward_three_term(pl, l, src, lengths.data(), ws, nullptr) != hipSuccess) return 3;
+            if (launch_lstm_backward_three_term(pl, l, src, lengths, ws, nullptr) != hipSuccess) return 3;
         }
     }
     printf("ok\n");

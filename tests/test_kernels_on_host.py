@@ -1,6 +1,6 @@
-"""What the 16-series LSTM kernels' correctness needs beside their arithmetic, checked without a GPU: the kernel sources
-are built for the CPU and run thread by thread (tests/host_kernels/host_kernels.cpp).  Every global access has to lie in
-the workspace, every wave has to meet the same barriers, and between two barriers no wave may touch LDS that another one
+"""What the kernels' correctness needs beside their arithmetic, checked without a GPU: the kernel sources are built for the
+CPU and run thread by thread (tests/host_kernels/host_kernels.cpp).  Every access has to lie in the workspace or an array
+of the call, every wave has to meet the same barriers, and between two barriers no wave may touch LDS that another one
 writes."""
 import os
 import re
@@ -15,27 +15,58 @@ CSRC = os.path.join(ROOT, "paper_1907_03329_amd", "csrc")
 CLANG = os.environ.get("HOST_CLANG", "/opt/rocm/llvm/bin/clang++")
 
 
+def without_launches(text):
+    """kernel<<<grid, threads, lds, st>>>(arguments) -> a call per thread (host_launch)"""
+    def closing(at, opening, ending):
+        depth = 0
+        while True:
+            depth += (text[at] in opening) - (text[at] in ending)
+            if depth == 0:
+                return at
+            at += 1
+    at = text.find("<<<")
+    while at >= 0:
+        start = re.search(r"\w+(<[^<>;]*>)?$", text[:at]).start()
+        stop = text.index(">>>", at)
+        depth, parts = 0, [""]
+        for c in text[at + 3:stop]:
+            depth += (c in "(") - (c in ")")
+            if c == "," and depth == 0:
+                parts.append("")
+            else:
+                parts[-1] += c
+        end = closing(stop + 3, "(", ")")
+        call = f"host_launch({parts[0]}, {parts[1]}, {parts[2]}, [&] {{ {text[start:at]}{text[stop + 3:end + 1]}; }})"
+        text = text[:start] + call + text[end + 1:]
+        at = text.find("<<<", start + len(call))
+    return text
+
+
+PARTS = ["lstm_backward_kernels", "lstm_backward_large_kernels", "lstm_forward_kernels", "lstm_forward_residual_kernels",
+         "lstm_narrow_kernels", "lstm_narrow_fwd_residual_kernels", "lstm_narrow_bwd_kernels", "lstm_narrow_bwd_split_kernels",
+         "lstm_kernels", "es_kernels", "head_kernels"]
+
+
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
-    """The kernel sources with what has no meaning on a CPU replaced: launches, the barrier in inline assembly, empty asm
-    statements that hold the device compiler back, and the address space of an LDS pointer."""
+    """The kernel sources with what has no meaning on a CPU replaced: launches, LDS whose size the launch gives, the barrier in
+    inline assembly, empty asm statements that hold the device compiler back, and the address space of an LDS pointer."""
     d = str(tmp_path_factory.mktemp("host_kernels"))
     shutil.copytree(HERE, d, dirs_exist_ok=True)
     for name in os.listdir(CSRC):
-        if not name.startswith(("lstm_backward", "lstm_forward", "three_term", "esrnn_internal", "device_utils", "plan")):
+        if not name.startswith(("lstm_", "es_kernels", "head_kernels", "three_term", "esrnn_internal", "device_utils", "plan")):
             continue
-        text = open(os.path.join(CSRC, name)).read()
-        text = re.sub(r"(\w+<[^<>;]*>)<<<(.*?), 0, st>>>\(a\)",
-                      r"host_launch([](const void *p) { \1(*static_cast<const std::decay_t<decltype(a)> *>(p)); }, &a, \2)", text)
+        text = without_launches(open(os.path.join(CSRC, name)).read())
+        text = re.sub(r"extern __shared__ (__align__\(16\) )?float (\w+)\[\];", r"float *\2 = host_dynamic_lds;", text)
         text = re.sub(r'asm volatile\("s_waitcnt lgkmcnt\(0\)\\n\\ts_barrier"[^;]*;', "host_barrier();", text)
         text = re.sub(r'asm( volatile)?\(""[^;]*;', ";", text)
-        assert "asm" not in re.sub(r"//.*", "", text), name
+        assert "asm" not in re.sub(r"//.*", "", text) and "extern __shared__" not in text, name
         text = text.replace("__attribute__((address_space(3)))", "")
         open(os.path.join(d, name), "w").write(text)
     common = [CLANG, "-std=c++17", "-O1", "-w", "-I", d, "-I", os.path.join(ROOT, "include")]
     trace = ["-fsanitize-coverage=edge,trace-loads,trace-stores"]
-    parts = [("reverse.o", "kernels.cpp", trace + ["-DREVERSE"]), ("forward.o", "kernels.cpp", trace), ("plan.o", "plan.cpp", []),
-             ("main.o", "host_kernels.cpp", [])]
+    parts = [(f"{part}.o", "kernels.cpp", trace + [f'-DPART="{part}.hip"']) for part in PARTS]
+    parts += [("plan.o", "plan.cpp", []), ("main.o", "host_kernels.cpp", [])]
     jobs = [subprocess.Popen(common + extra + ["-c", os.path.join(d, src), "-o", os.path.join(d, obj)]) for obj, src, extra in parts]
     assert not any([j.wait() for j in jobs])
     out = os.path.join(d, "host_kernels")
@@ -83,3 +114,50 @@ def test_kernel_kind_follows_the_measured_limits(program, series, dilation):
     # the fp32 reverse kernel of the largest hidden sizes is slower than the 4-series one up to 159 workgroups
     for hidden in (53, 64):
         assert chosen(program, hidden, series, dilation) == [(int(groups < 65), int(groups < 160))]
+
+
+def run_step(program, narrow, *args):
+    r = subprocess.run([program, "step"] + [str(a) for a in args], env=dict(os.environ, ESRNN_NARROW_BELOW=str(narrow)),
+                       capture_output=True, text=True)
+    return r.returncode, r.stdout.strip()
+
+
+# 4-series kernels: chains around a chunk (forward 8 positions, reverse 4) and two, several chains a workgroup, tiles of half the
+# positions and of none, and the output stage and everything else of a step beside them
+@pytest.mark.parametrize("hidden,window", SHAPES)
+def test_waves_of_the_4_series_kernels_are_ordered(program, hidden, window):
+    for positions, lambda_cs, dilations in ((8, 0, (1, 1, 4)), (17, 0.1, (1,))):
+        T = window + 3 + positions - 1
+        assert run_step(program, 100000, 128, T, window, 3, hidden, min(T, 4), 0, lambda_cs, f"{T},{window + 3}", *dilations) == (0, "ok")
+
+
+@pytest.mark.parametrize("positions", [1, 2, 3, 4, 5, 7, 9, 16])
+def test_chains_of_every_length(program, positions):
+    T = 4 + 3 + positions - 1
+    assert run_step(program, 100000, 64, T, 4, 3, 32, 4, 0, 0, T, 1, 2) == (0, "ok")
+
+
+# 64 groups of four series have eight chains for twelve classes; past 256 workgroups the reverse kernel has four waves
+@pytest.mark.parametrize("hidden,series,positions,dilations", [(8, 256, 14, (12, 3)), (40, 128, 34, (16,)), (64, 128, 20, (16,))])
+def test_several_chains_a_workgroup(program, hidden, series, positions, dilations):
+    window = 64 if hidden == 64 else 4
+    T = window + 3 + positions - 1
+    assert run_step(program, 100000, series, T, window, 3, hidden, 4, 0, 0, f"{T},{window + 9}", *dilations) == (0, "ok")
+
+
+@pytest.mark.parametrize("hidden,H", [(8, 1), (8, 64), (32, 17), (40, 8), (40, 48), (50, 18), (50, 40), (64, 33), (64, 64)])
+def test_waves_of_the_output_stage_are_ordered(program, hidden, H):
+    T = 20 + H + 9 if hidden > 8 else 8 + H + 9
+    assert run_step(program, 0, 64, T, T - H - 9, H, hidden, 4, 0, 0, T, 1) == (0, "ok")
+
+
+# recursions: one, two, four and eight steps a group, and the kernel for long periods at its limit; lengths of one step, of
+# no multiple of a chunk, and of none that a window fits into
+@pytest.mark.parametrize("m1,m2", [(0, 0), (1, 0), (1, 1), (2, 3), (4, 7), (9, 12), (23, 0), (24, 0), (25, 24), (24, 37), (60, 0), (24, 23)])
+def test_waves_of_the_recursions_are_ordered(program, m1, m2):
+    for lengths in ("61,1", "60,48", "7,25"):
+        assert run_step(program, 0, 128, 61, 4, 3, 8, m1, m2, 0, lengths, 1) == (0, "ok")
+
+
+def test_waves_of_the_recursions_with_the_largest_rings(program):
+    assert run_step(program, 0, 64, 305, 4, 3, 8, 300, 148, 0, "303", 1) == (0, "ok")
