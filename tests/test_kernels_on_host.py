@@ -122,13 +122,14 @@ def run_step(program, narrow, *args):
     return r.returncode, r.stdout.strip()
 
 
-# 4-series kernels: chains around a chunk (forward 8 positions, reverse 4) and two, several chains a workgroup, tiles of half the
-# positions and of none, and the output stage and everything else of a step beside them
+# 4-series kernels: chains around a chunk (forward 8 positions, reverse 4) and two, tiles of few positions, and the output stage and
+# everything else of a step beside them
 @pytest.mark.parametrize("hidden,window", SHAPES)
 def test_waves_of_the_4_series_kernels_are_ordered(program, hidden, window):
-    for positions, lambda_cs, dilations in ((8, 0, (1, 1, 4)), (17, 0.1, (1,))):
-        T = window + 3 + positions - 1
-        assert run_step(program, 100000, 128, T, window, 3, hidden, min(T, 4), 0, lambda_cs, f"{T},{window + 3}", *dilations) == (0, "ok")
+    T = window + 3 + 7
+    assert run_step(program, 100000, 64, T, window, 3, hidden, min(T, 4), 0, 0, T, 1, 4) == (0, "ok")
+    T = window + 3 + 16
+    assert run_step(program, 100000, 128, T, window, 3, hidden, min(T, 4), 0, 0.1, f"{T},{window + 4}", 1) == (0, "ok")
 
 
 @pytest.mark.parametrize("positions", [1, 2, 3, 4, 5, 7, 9, 16])
