@@ -54,7 +54,7 @@ MEASURED_TRAFFIC_BYTES = {
         "window_backward": 8.38e+07, "es_backward": 6.392e+06,
     },
     ('hourly', 512): {
-        "window_forward": 9.854e+07, "lstm_forward_l0": 4.218e+08, "lstm_forward_l1": 3.731e+08, "lstm_forward_l2": 3.732e+08,
+        "es_forward": 1.212e+07, "window_forward": 9.854e+07, "lstm_forward_l0": 4.218e+08, "lstm_forward_l1": 3.731e+08, "lstm_forward_l2": 3.732e+08,
         "lstm_forward_l3": 4.801e+08, "head_forward_backward": 3.033e+08, "forecasts": 1.318e+08, "lstm_backward_l3": 4.798e+08,
         "lstm_backward_l2": 4.916e+08, "lstm_backward_l1": 5.394e+08, "lstm_backward_l0": 4.417e+08, "window_backward": 2.425e+08,
         "es_backward": 1.327e+07,
@@ -62,11 +62,39 @@ MEASURED_TRAFFIC_BYTES = {
 }
 
 
-def stage_model(cfg, name):
+def reverse_workgroups(cfg, dilation):
+    """Workgroups of the reverse pass of a layer, each of which leaves a block of weight-gradient partials: the rule by which
+    the library's plan (csrc/plan.cpp) chooses them."""
+    tiles, classes = -(-cfg.B // 16), min(dilation, cfg.P)
+
+    def chains(groups):
+        return min(classes, max(1, -(-512 // groups)))
+    if tiles * chains(tiles) < (65 if cfg.hidden <= 52 else 160):       # four series a workgroup
+        return 4 * tiles * chains(4 * tiles)
+    fitting = [c for c in range(1, classes + 1) if c == 1 or tiles * c <= 256]
+    return tiles * min(fitting, key=lambda c: (-(-tiles * c // 256) * -(-classes // c), c))
+
+
+def weight_partials(cfg):
+    """(floats of a block of partial sums, number of such blocks) of every layer and of the output stage."""
+    h, H = cfg.hidden, cfg.H
+    parts = [(4 * h * ((cfg.I + cfg.n_cat if l == 0 else h) + h + 1), reverse_workgroups(cfg, d)) for l, d in enumerate(cfg.dilations)]
+    waves = 8 if (h <= 40 and H <= 16) or (h <= 32 and H <= 32) else 4      # of a workgroup of the output stage
+    return parts + [(h * h + h + H * h + H, min(256, -(-cfg.P * -(-cfg.B // 16) // waves)))]
+
+
+REDUCE_SPLITS = 16      # partial sums that the first stage of the weight-gradient reduction leaves
+
+
+def stage_model(cfg, name, network=True):
     """Algorithmic work of one launch of a stage: (bound, amount, unit).
 
     Contractions are priced in flops (2 per multiply-add, logical sizes, no
-    padding); streaming stages in the bytes the method has to move (fp32)."""
+    padding); streaming stages in the bytes the method has to move (fp32).
+    In a step of the whole network the launches of the smoothing and window stages
+    have other work beside them, and are priced with it: the packing of the weights
+    (read once, written in three bf16 parts for either direction) and the two stages
+    of the weight-gradient reduction."""
     B, T, I, H, h = cfg.B, cfg.T, cfg.I, cfg.H, cfg.hidden
     P = T - I - H + 1
     n_seas = cfg.n_seas
@@ -85,13 +113,16 @@ def stage_model(cfg, name):
         # read outputs, log level and seasonal factors of the target times; write forecasts
         return "hbm", 4.0 * B * P * 2 * H + 4.0 * B * T * (1 + n_seas), "byte"
     if name == "es_forward":
-        return "hbm", 4.0 * B * T * (1 + 3 + n_seas) + 4.0 * B * cfg.K, "byte"       # read y; write level, u, v, factors
+        packing = (4.0 + 2 * 6.0) * cfg.weight_count if network else 0.0
+        return "hbm", 4.0 * B * T * (1 + 3 + n_seas) + 4.0 * B * cfg.K + packing, "byte"     # read y; write level, u, v, factors
     if name == "es_backward":
-        return "hbm", 4.0 * B * T * (4 + n_seas) + 4.0 * B * cfg.K, "byte"           # read y, level, gu, gv, factors
+        second = sum(4.0 * n * min(blocks, REDUCE_SPLITS) for n, blocks in weight_partials(cfg)) + 4.0 * cfg.weight_count if network else 0.0
+        return "hbm", 4.0 * B * T * (4 + n_seas) + 4.0 * B * cfg.K + second, "byte"  # read y, level, gu, gv, factors
     if name == "window_forward":
         return "hbm", 4.0 * B * P * (I + H) + 8.0 * B * T, "byte"                     # write X, Z; read u, v
     if name == "window_backward":
-        return "hbm", 4.0 * B * P * (I + H) + 8.0 * B * T, "byte"                     # read gX, gO; write gu, gv
+        first = sum(4.0 * n * (blocks + min(blocks, REDUCE_SPLITS)) for n, blocks in weight_partials(cfg)) if network else 0.0
+        return "hbm", 4.0 * B * P * (I + H) + 8.0 * B * T + first, "byte"             # read gX, gO; write gu, gv
     return None, 0.0, ""
 
 
@@ -334,7 +365,7 @@ def es_window_sweep(args, torch, binding, synth):
         binding.esrnn_profile_enable(h, False)
         out = {"workload": cfg.name, "B": B, "T": cfg.T, "workspace_MB": round(nbytes / 1e6, 1), "stages": {}}
         for name, ms in stages.items():
-            bound, amt, _ = stage_model(cfg, name)
+            bound, amt, _ = stage_model(cfg, name, network=False)
             e = {"ms": round(ms, 4)}
             if bound == "hbm":
                 e["gbs"] = round(amt / (ms * 1e-3) / 1e9, 1)
