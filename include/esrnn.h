@@ -87,7 +87,7 @@ typedef struct {
 typedef struct esrnn_handle esrnn_handle;
 
 /* Validates the configuration (I + H <= T, periods <= T and m1 + m2 <= 448 (the seasonal rings of 64 series
- * and a 48 KB staging buffer must fit into the 160 KB of LDS), dilations >= 1, sizes within the ESRNN_MAX_* limits, 0 < tau < 1) and
+ * and a staging buffer of up to 36 KB must fit into the 160 KB of LDS), dilations >= 1, sizes within the ESRNN_MAX_* limits, 0 < tau < 1) and
  * builds the launch plan.
  * The plan picks, from the batch size, between two kernels each for the LSTM layers (4-series tiles at small
  * batches, 16-series tiles otherwise) and for the window adjoint (gather, or streaming at very many series);
@@ -317,9 +317,11 @@ esrnn_status esrnn_workspace_buffer(const esrnn_handle *h, int32_t which, int32_
 
 /*
  * Per-stage timing for benchmarks.  While enabled, esrnn_forward and
- * esrnn_backward bracket every stage (one kernel launch, except the packing
- * and gradient-reduction stages, which launch one small kernel per layer) with
- * HIP events on the caller's stream.  esrnn_profile_collect waits for the
+ * esrnn_backward bracket every stage (one kernel launch; a reverse layer behind
+ * three or more residual blocks has a second one that sums its gradients) with
+ * HIP events on the caller's stream.  The set-up (normalisers, operand packing)
+ * is part of the first stage's launch, the weight-gradient reduction of the last
+ * two stages', the loss of that of the forecasts.  esrnn_profile_collect waits for the
  * events of the last forward/backward pair (the only call here that blocks the
  * host) and adds their elapsed times to per-stage totals; call it once after
  * each pair.  esrnn_profile_read copies the totals in milliseconds and the

@@ -163,9 +163,10 @@ struct HeadShape {
 };
 
 // What bounds it: issue and dependency stalls of the one or two waves a SIMD has room for.  Hidden 40, horizon 8, 4096 series,
-// 61 positions: 47 - 50 us (fp32 products 64 - 67 us; 117 MB, 23 us at the rate of a large copy); matrix pipe 21 % busy,
-// instructions issued 34 % of the time.  Hidden 50, horizon 18, 211 positions: 246 - 262 us (369 us); matrix pipe 33 %,
-// issue 53 %.  Hidden 30: 33 us (42 us); hidden 40, horizon 48, 512 series: 95 - 99 us (131 - 135 us).
+// 61 positions: 44 - 47 us (fp32 products 64 - 67 us; 108 MB, 21 us at the rate of a large copy); matrix pipe 21 % busy,
+// instructions issued 34 % of the time.  Hidden 50, horizon 18, 211 positions: 254 - 256 us (369 us); matrix pipe 33 %,
+// issue 53 %.  Hidden 30: 32 us (42 us); hidden 40, horizon 48, 512 series: 98 us (131 - 135 us).  Hidden 50, 40 positions: horizon
+// 40 74 us (100), 64 216 us (245), where registers spill.
 // REVERSE: a reverse pass follows; without it outputs and loss are all.
 template <int HT, int MO, bool REVERSE>
 __global__ void __launch_bounds__(64 * head_waves(HT, MO)) head_kernel(HeadArgs a)

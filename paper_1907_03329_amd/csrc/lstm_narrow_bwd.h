@@ -24,7 +24,8 @@ namespace {
 // da_all and part alternate between two copies by position parity: what a
 // position writes was last read two positions earlier, one barrier ago.  The
 // staged operands of a chunk of positions: per-thread values (gates, cell
-// states, arriving gradient) in a buffer every thread reads only where it wrote;
+// states, arriving gradient) in a buffer that the same thread reads, or with
+// eight waves that of the chain wave with the same number, in two by chunk parity;
 // [x ; h] rows, which the whole workgroup reads, in two buffers by chunk parity.
 // ---------------------------------------------------------------------------
 struct NarrowBwdArgs {
@@ -265,9 +266,9 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
             // column groups, or with one group two accumulators (more would cost the second resident
             // workgroup its registers at hidden 40).
             constexpr int kBwdAcc = NG == 1 ? 2 : 1;
-            f32x4 acc[NG][4];
+            f32x4 acc[NG][kBwdAcc];
 #pragma unroll
-            for (int g = 0; g < NG; ++g) acc[g][0] = acc[g][1] = acc[g][2] = acc[g][3] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int g = 0; g < NG; ++g) acc[g][0] = acc[g][kBwdAcc - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
             static_for<0, HT>([&](auto ic) {
                 constexpr int ul = decltype(ic)::value;
 #pragma unroll
@@ -285,7 +286,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
 #pragma unroll
             for (int g = 0; g < NG; ++g)
                 *reinterpret_cast<f32x4 *>(&part[par][w][(64 * g + lane) * 4]) =
-                    kBwdAcc == 4 ? (acc[g][0] + acc[g][1]) + (acc[g][2] + acc[g][3]) : kBwdAcc == 2 ? acc[g][0] + acc[g][1] : acc[g][0];
+                    kBwdAcc == 2 ? acc[g][0] + acc[g][1] : acc[g][0];
             // per-thread operands of the next position (staged at least one barrier ago)
             gt = lc[next][0][tid];
             o = lc[next][1][tid];

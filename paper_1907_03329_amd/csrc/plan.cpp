@@ -27,15 +27,16 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // directions: with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each.
 // Measured on two layers of the same dilation, 61 positions (window 4) and 151 (window 12), in us (16-series kernel
 // against 4-series kernel, second layer, 61 positions unless stated; at 64 and less the 4-series kernels are the faster
-// ones or level, except at hidden 8 and 30: 9 / 11 and 14 / 16 at 64):
+// ones or level, except at hidden 8: 21 / 24 and 26 / 27 at 64):
 //   hidden   groups 68 (dilation 2)                72 (dilation 1)                    128 (dilation 1)
-//      8     forward 14 / 21, reverse 18 / 23      21 / 37,  27 / 39                  22 / 39,  28 / 40
-//     30     21 / 35,  32 / 39                     37 / 62,  56 / 70                  38 / 67,  59 / 76
-//     40     29 / 40,  42 / 60                     52 / 71,  76 / 111                 54 / 75,  79 / 118
-//     50     40 / 45,  69 / 99                     73 / 81,  124 / 185                76 / 89,  130 / 200
-//     60     44 / 52,  189 / 119                   79 / 91,  364 / 220                82 / 100, 370 / 235
-// and with 151 positions alike (hidden 50, first layer, 72 groups: 138 / 142, 219 / 222).  Above hidden 52 the reverse
-// pass of 16 series is the fp32 kernel, which loses up to 148 groups (372 / 337 us) and at 160 with dilation 8 wins (57 / 66).
+//      8     forward 13 / 19, reverse 16 / 22      21 / 32,  26 / 38                  22 / 34,  28 / 39
+//     30     22 / 32,  32 / 38                     38 / 56,  55 / 68                  39 / 58,  56 / 70
+//     40     30 / 36,  42 / 58                     54 / 64,  74 / 105                 55 / 66,  75 / 107
+//     50     39 / 43,  66 / 98                     71 / 77,  121 / 179                72 / 79,  123 / 184
+//     60     42 / 48,  189 / 115                   77 / 87,  363 / 212                79 / 91,  366 / 218
+// and with 151 positions alike; first layers with few inputs are nearest to the line (151 positions, 72 groups: hidden 30
+// 105 / 106, hidden 50 129 / 132, 222 / 216).  Above hidden 52 the reverse pass of 16 series is the fp32 kernel, which loses up
+// to 148 groups (369 / 323 us); at 160 it depends on the dilation (one 371 / 324, eight 57 / 64).
 constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwardBelowFp32 = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Gather against streaming in us: quarterly shape at 1024 / 2048 / 4096 / 8192 tiles 21 / 35 / 77 / 157
@@ -114,7 +115,7 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     if (cfg.n_seas >= 1 && (cfg.m1 < 1 || cfg.m1 > cfg.T)) return ESRNN_ERR_CONFIG;
     if (cfg.n_seas >= 2 && (cfg.m2 < 1 || cfg.m2 > cfg.T)) return ESRNN_ERR_CONFIG;
     // the smoothing kernels keep the seasonal rings of 64 series in LDS: (m1 + m2) * 64 floats, which with the
-    // 48 KB staging buffer of the reverse recursion must fit into 160 KB
+    // 36 KB staging buffer of the reverse recursion must fit into 160 KB
     if ((long long)(cfg.n_seas >= 1 ? cfg.m1 : 0) + (cfg.n_seas >= 2 ? cfg.m2 : 0) > 448) return ESRNN_ERR_CONFIG;
     if ((long long)cfg.I + cfg.H > cfg.T) return ESRNN_ERR_CONFIG;
     if (cfg.n_blocks < 1 || cfg.n_blocks > ESRNN_MAX_BLOCKS) return ESRNN_ERR_CONFIG;
