@@ -136,7 +136,7 @@ struct PackLstmArgs {
 };
 
 // Operands of the 4-series kernels.  v_mfma_f32_4x4x1: lane l supplies A[l%4] of block l/4.
-//   forward  [wave][column k of x ; h][lane]: gate l%4 of unit wave*HT + min(l/4, HT-1) (the blocks past HT
+//   forward  [wave][column k of x ; h][lane]: gate l/16 of unit wave*HT + min(l%16, HT-1) (the lanes past HT
 //            repeat the last unit, so that all lanes do the same work on the same addresses)
 //   reverse  [wave][group g][k-step 4*u + gate][lane]: W[gate, unit wave*HT + u][column 64*g + l]
 __device__ __forceinline__ void pack_forward_narrow(const PackLstmArgs &a, int block, int n_blocks)
@@ -144,7 +144,7 @@ __device__ __forceinline__ void pack_forward_narrow(const PackLstmArgs &a, int b
     const int KT4 = 4 * (a.KXT + a.HT), n = 4 * KT4 * 64;
     for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
         const int lane = idx & 63, k = (idx >> 6) % KT4, w = (idx >> 6) / KT4;
-        a.fwd[idx] = a.at_row(lane & 3, w * a.HT + min(lane >> 2, a.HT - 1), k);
+        a.fwd[idx] = a.at_row(lane >> 4, w * a.HT + min(lane & 15, a.HT - 1), k);
     }
 }
 __device__ __forceinline__ void pack_backward_narrow(const PackLstmArgs &a, int block, int n_blocks)

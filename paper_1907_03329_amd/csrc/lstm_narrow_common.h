@@ -14,15 +14,15 @@
 // broadcast control (cbsz = 4, abid = b) all sixteen blocks take the A values
 // of block b.  Here A carries the ACTIVATIONS of the four series for one input
 // column, broadcast from the block whose four lanes hold them, and B carries
-// the weights: block u, lane g of a wave holds gate g of hidden unit u.  One
+// the weights: lane 16 g + u of a wave holds gate g of hidden unit u.  One
 // instruction advances 16 units x 4 gates x 4 series by one input column, and no
 // operand has to be replicated over the blocks: a wave reads [x_p ; h_{p-d}] of
 // the four series from LDS with one 4-byte load per 16 columns.  Four waves
 // share the units; wave w owns w*HT .. w*HT+HT-1 (HT <= 16; the padded
 // hidden size is 4*HT).  A lane ends up with one gate of one unit for the four
-// series; a 4x4 transpose inside each quad of lanes (DPP) turns that into the
-// four gates of one unit for ONE series, and the cell update is lane-local as
-// in the 16-series kernels.
+// series; a transpose between components and rows of sixteen lanes (four
+// instructions) turns that into the four gates of one unit for ONE series, and
+// the cell update is lane-local as in the 16-series kernels.
 //
 // The reverse kernel follows the 16-series one step by step (gate gradients,
 // transposed contraction split over the waves along the contraction, weight
@@ -50,7 +50,7 @@
 // stores issued since instead of waiting for all of them.  (With the request in
 // one loop iteration and the use in another, every chunk waited for its newest
 // stores; a ring of registers with one request per position was slower still.)
-// Blocks past HT repeat the last unit of the wave, operands and addresses alike,
+// Lanes past HT repeat the last unit of the wave, operands and addresses alike,
 // and threads without an input row stage into a spare LDS column, so no memory
 // operation sits behind a divergent branch.
 //
@@ -85,20 +85,28 @@ __device__ __forceinline__ float quad_perm(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
 }
 
-// 4x4 transpose inside each quad of lanes: lane j, component c  <->  lane c, component j
-__device__ __forceinline__ void quad_transpose(f32x4 &v, int j)
+// 4x4 transpose between the components and the rows of sixteen lanes: row s, component c  <->  row c, component s.
+__device__ __forceinline__ void row_transpose(f32x4 &v)
 {
-    const bool lo = j & 1, hi = j & 2;
-    {   // lanes j ^ 1, component pairs (0,1) and (2,3)
-        const float r01 = quad_perm<0xB1>(lo ? v[0] : v[1]);
-        const float r23 = quad_perm<0xB1>(lo ? v[2] : v[3]);
-        if (lo) { v[0] = r01; v[2] = r23; } else { v[1] = r01; v[3] = r23; }
-    }
-    {   // lanes j ^ 2, component pairs (0,2) and (1,3)
-        const float r02 = quad_perm<0x4E>(hi ? v[0] : v[2]);
-        const float r13 = quad_perm<0x4E>(hi ? v[1] : v[3]);
-        if (hi) { v[0] = r02; v[1] = r13; } else { v[2] = r02; v[3] = r13; }
-    }
+    // (the pair's elements are copied first: a bit cast of the second element itself takes the first one)
+    auto swap16 = [](float &x, float &y) {          // row bit 0 against the choice of x or y
+        const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+        const unsigned r0 = r[0], r1 = r[1];
+        x = __builtin_bit_cast(float, r0);
+        y = __builtin_bit_cast(float, r1);
+    };
+    auto swap32 = [](float &x, float &y) {          // row bit 1
+        const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+        const unsigned r0 = r[0], r1 = r[1];
+        x = __builtin_bit_cast(float, r0);
+        y = __builtin_bit_cast(float, r1);
+    };
+    float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+    swap16(v0, v1);
+    swap16(v2, v3);
+    swap32(v0, v2);
+    swap32(v1, v3);
+    v = f32x4{v0, v1, v2, v3};
 }
 
 // workgroups along x: groups of 32 = 8 tiles x 4 quarters

@@ -10,7 +10,7 @@ namespace esrnn {
 namespace {
 
 struct NarrowFwdArgs {
-    const float *wpack;   // [4][KT4][64]  weight operands: wave, input column, lane (gate l%4 of unit l/4 of the wave)
+    const float *wpack;   // [4][KT4][64]  weight operands: wave, input column, lane (gate l/16 of unit l%16 of the wave)
     const float *bias;    // caller's bias vector [4h]
     const float *xsrc;    // TL(4*KXT)
     float *gates;         // TL(HP) x [4]
@@ -28,9 +28,12 @@ struct NarrowFwdArgs {
 // position's pre-activations (with the bias), which does not depend on it: the chain then has 4 HT instead of
 // 4 (KXT + HT) matrix instructions a position, and no request of its own.  Both kinds meet the same barriers.
 // 512 hourly series, first layer (24 + 40 columns, 649 positions): 348 -> 331 us (333 -> 317 us for 333); 501 monthly ones
-// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  What
-// bounds it is the issue of one wave: 147 instructions a position, five cycles each, and an LDS round trip.  (Three
-// accumulators, which need no wait states between the matrix instructions: 340 us.)
+// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  (Three
+// accumulators, which need no wait states between the matrix instructions: 340 us.)  What bounds it is the issue of one
+// wave and what the input wave of its SIMD takes from it: without the input half 264 of 327 us.  Gates in the rows of sixteen
+// lanes, which four instructions transpose (26 between the lanes of a quad), and stores through pointers that move on
+// (13 scalar instructions a position instead of some 20 scalar and vector ones for addresses): 327 -> 290 us for 512 hourly
+// series, 114 -> 108 us for 501 monthly ones, 27.7 -> 25.7 us for 16 quarterly ones.
 //
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
 // block input, writes the block output).
@@ -49,7 +52,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
 
     const int lane = threadIdx.x & 63, tid = threadIdx.x & (kNT - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = wave & (kNW - 1);
-    const int blk = lane >> 2, j = lane & 3;
+    const int blk = lane & 15, j = lane >> 4;   // unit of the wave; gate of the products, series of the cell update
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
     // quarters of ONE tile, so they land on the same XCD at about the same time and a row is fetched from
@@ -59,7 +62,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
     // All four workgroups of a 16-series tile stop at the tile's longest series: what lies beyond is
     // neither computed here nor read by any later kernel.
     const int Pt = a.pmax[bt];
-    const int unit = w * HT + min(blk, HT - 1);     // blocks past HT repeat the last unit
+    const int unit = w * HT + min(blk, HT - 1);     // lanes past HT repeat the last unit
     // element of this lane inside the TL(HP) block of one (position, series tile)
     const int lane_off = unit * 16 + 4 * q + j;
     // columns past KX / HP in the last group of 16 are never written: zero once (their weights do not exist)
@@ -158,16 +161,21 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
         for (int e = tid; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;    // start of a chain: zero state
         lds_barrier();
         lds_barrier();
-        // What a position leaves in memory is stored while the next one waits for its first operands from LDS.
+        // What a position leaves in memory is stored while the next one waits for its first operands from LDS, through
+        // scalar pointers that move on by a position.
         f32x4 gates;
         float cell, hidden, output;
-        auto store = [&](int p) {
-            // wave-uniform tile base plus the lane's element: scalar address arithmetic
-            const size_t tile = ((size_t)p * a.NB + bt) * (HP * 16);
-            __builtin_nontemporal_store(gates, reinterpret_cast<f32x4 *>(a.gates) + tile + lane_off);
-            (a.c + tile)[lane_off] = cell;     // (a plain store: the four quarter-row writes of a tile then merge in L2)
-            (a.hid + tile)[lane_off] = hidden;
-            if (OUT) (a.out + tile)[lane_off] = output;
+        const size_t first = ((size_t)r * a.NB + bt) * (HP * 16), step = (size_t)a.d * a.NB * (HP * 16);
+        float *at_gates = a.gates + 4 * first, *at_c = a.c + first, *at_hid = a.hid + first, *at_out = OUT ? a.out + first : nullptr;
+        auto store = [&]() {
+            buf_store4<true>(make_rsrc(at_gates), 16 * lane_off, gates);
+            buf_store(make_rsrc(at_c), 4 * lane_off, 0, cell);     // (plain: the four quarter-row writes of a tile then merge in L2)
+            buf_store(make_rsrc(at_hid), 4 * lane_off, 0, hidden);
+            if (OUT) buf_store(make_rsrc(at_out), 4 * lane_off, 0, output);
+            at_gates += 4 * step;
+            at_c += step;
+            at_hid += step;
+            if (OUT) at_out += step;
         };
         auto position = [&](int i, auto parc, auto firstc) {
             constexpr int par = decltype(parc)::value;
@@ -181,7 +189,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
             f32x4 acc0 = half[par][w][lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
             const float res = OUT ? rc[OUT ? (i / CH) & 1 : 0][OUT ? i % CH : 0][tid] : 0.0f;
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (!decltype(firstc)::value) store(p - a.d);
+            if constexpr (!decltype(firstc)::value) store();
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, HP / 2>([&](auto ic) {
                 constexpr int k = 2 * decltype(ic)::value;
@@ -189,7 +197,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
                 acc1 = mfma4_bcast<(k + 1) % 16>(vh[k / 16], wh[k + 1], acc1);
             });
             f32x4 pre = acc0 + acc1;        // gate j of the unit, series 0..3
-            quad_transpose(pre, j);         // gates 0..3 of the unit, series j
+            row_transpose(pre);             // gates 0..3 of the unit, series j
             const float gi = sigmoid_f(pre[0]);
             const float gf = sigmoid_f(pre[1]);
             const float gg = tanh_f(pre[2]);
@@ -213,7 +221,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
             position(i + 1, integral_constant<int, 0>{}, std::false_type{});
         }
         if (i < n) position(i, integral_constant<int, 1>{}, std::false_type{});
-        store(r + (n - 1) * a.d);
+        store();
     }
     if constexpr (CP) {
         __shared__ float s_cs[kNW];

@@ -67,6 +67,9 @@ typedef const char *__amdgpu_buffer_rsrc_t;
 #define __builtin_amdgcn_s_setprio(x) ((void)0)
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) (v)
+struct host_pair { unsigned v[2]; unsigned operator[](int i) const { return v[i]; } };
+#define __builtin_amdgcn_permlane16_swap(a, b, fi, bc) host_pair{{(a), (b)}}
+#define __builtin_amdgcn_permlane32_swap(a, b, fi, bc) host_pair{{(a), (b)}}
 #define __builtin_canonicalizef(x) (x)
 // (the operands count as used, so that the loads that bring them stay)
 template <class V>
