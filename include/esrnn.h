@@ -326,7 +326,8 @@ esrnn_status esrnn_workspace_buffer(const esrnn_handle *h, int32_t which, int32_
  * host) and adds their elapsed times to per-stage totals; call it once after
  * each pair.  esrnn_profile_read copies the totals in milliseconds and the
  * number of collected launches into host arrays of esrnn_profile_stage_count
- * entries.  Enabling resets the totals.
+ * entries.  Enabling resets the totals.  While enabled, every layer has a launch of its own (small batches run several
+ * in one otherwise).
  */
 esrnn_status esrnn_profile_enable(esrnn_handle *h, int32_t on);
 esrnn_status esrnn_profile_stage_count(const esrnn_handle *h, int32_t *n);

@@ -49,9 +49,9 @@ __device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c)
 // vector ALU, whose cycles the fp32 MFMAs need.  A resource spans 4 GiB from its base (raw buffer, no stride, no
 // range limit): callers rebase it per window position and keep the offsets inside one position.
 typedef __amdgpu_buffer_rsrc_t buf_rsrc;
-__device__ __forceinline__ buf_rsrc make_rsrc(const void *base)
+__device__ __forceinline__ buf_rsrc make_rsrc(const void *base, int bytes = -1)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
 }
 __device__ __forceinline__ float buf_load(buf_rsrc r, unsigned lane_bytes, unsigned tile_bytes)
 {
@@ -77,6 +77,18 @@ template <bool kStream = false>
 __device__ __forceinline__ void buf_store4(buf_rsrc r, unsigned lane_bytes, f32x4 v)
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, lane_bytes, 0, kStream ? 2 : 0);
+}
+
+// The same for data that another workgroup of the launch writes or reads, at any place of the chip (every XCD has an L2 of
+// its own): written through to memory, read past the caches.
+constexpr int kBufShared = 16;
+__device__ __forceinline__ float buf_load_shared(buf_rsrc r, unsigned lane_bytes, unsigned tile_bytes)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, lane_bytes, tile_bytes, kBufShared));
+}
+__device__ __forceinline__ void buf_store_shared(buf_rsrc r, unsigned lane_bytes, unsigned tile_bytes, float v)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane_bytes, tile_bytes, kBufShared);
 }
 
 // Which of the residue classes r, r + step, ... below d a forward pass has to compute for a series tile: bit i for class

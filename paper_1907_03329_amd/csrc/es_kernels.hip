@@ -40,6 +40,8 @@ struct PrepArgs {
     int NB;
     int B, H;
     int cs_per_window;   // cell-state values per valid window in the cell-state penalty: hidden * blocks
+    unsigned *words;     // by which layers of one launch follow each other, and how many
+    int n_words;
 };
 
 // One workgroup reads all lengths, eight requests in flight per thread, of four lengths each where the caller's array is
@@ -48,6 +50,7 @@ struct PrepArgs {
 __device__ __forceinline__ void prep_body(const PrepArgs &pa, float *scratch)
 {
     const Lengths L = pa.lengths;
+    for (int i = threadIdx.x; i < pa.n_words; i += 256) pa.words[i * kWordStride] = 0u;
     unsigned long long *s_pin = reinterpret_cast<unsigned long long *>(scratch), *s_lv = s_pin + 256;
     unsigned long long np_ = 0, nl = 0;
     auto count = [&](int raw) {
@@ -1524,7 +1527,7 @@ SetupArgs setup_args(const Plan &pl, const Lengths &len, const float *weights, u
     SetupArgs a{};
     a.L = pl.L;
     a.prep = PrepArgs{len, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
-                      pl.B, pl.H, pl.h * pl.cfg.n_blocks};
+                      pl.B, pl.H, pl.h * pl.cfg.n_blocks, reinterpret_cast<unsigned *>(ws + pl.together_words), weights && pl.together_fwd ? 1 + pl.together_groups : 0};
     a.pmax_blocks = std::min((pl.NB + 255) / 256, 63);
     if (len.extend) {
         ClassArgs &c = a.classes;

@@ -57,6 +57,23 @@ hipError_t run_stage(esrnn_handle *h, int idx, hipStream_t st, F &&launch)
     s.recorded = true;
     return e;
 }
+
+// All layers of the forward pass.  (Stages are timed one by one, so with profiling on every layer has a launch of its own.)
+hipError_t lstm_layers(esrnn_handle *h, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode, hipStream_t st)
+{
+    const Plan &pl = h->plan;
+    int l = 0;
+    if (pl.together_fwd && !h->profiling) {
+        const hipError_t e = launch_lstm_forward_together(pl, lengths, weights, ws, mode, st);
+        if (e != hipSuccess) return e;
+        l = pl.together_fwd;
+    }
+    for (; l < pl.L; ++l) {
+        const hipError_t e = run_stage(h, h->st_lstm_fwd[l], st, [&] { return launch_lstm_forward(pl, l, lengths, weights, ws, mode, st); });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 }  // namespace
 
 #define ESRNN_TRY(expr)                              \
@@ -179,8 +196,7 @@ esrnn_status esrnn_forward(esrnn_handle *h, const float *y, const int32_t *lengt
     const ForwardMode mode{!h->forward_only, nullptr, false};
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, weights, ws, mode, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
-    for (int l = 0; l < pl.L; ++l)
-        ESRNN_TRY(run_stage(h, h->st_lstm_fwd[l], st, [&] { return launch_lstm_forward(pl, l, lengths, weights, ws, mode, st); }));
+    ESRNN_TRY(lstm_layers(h, lengths, weights, ws, mode, st));
     // the output stage runs its reverse pass in the same launch: the loss gradient needs nothing beyond it
     ESRNN_TRY(run_stage(h, h->st_head, st, [&] { return launch_head(pl, lengths, ws, !h->forward_only, st); }));
     ESRNN_TRY(run_stage(h, h->st_fc, st, [&] { return launch_loss_and_forecasts(pl, lengths, ws, loss, forecasts, st); }));
@@ -274,8 +290,7 @@ esrnn_status esrnn_predict(esrnn_handle *h, const float *y, const int32_t *lengt
     const ForwardMode mode{false, room ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr, true};
     ESRNN_TRY(run_stage(h, h->st_es_fwd, st, [&] { return launch_es_forward(pl, y, lengths, es_params, weights, ws, mode, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_fwd, st, [&] { return launch_window_forward(pl, h->categories, ws, st); }));
-    for (int l = 0; l < pl.L; ++l)
-        ESRNN_TRY(run_stage(h, h->st_lstm_fwd[l], st, [&] { return launch_lstm_forward(pl, l, ext, weights, ws, mode, st); }));
+    ESRNN_TRY(lstm_layers(h, ext, weights, ws, mode, st));
     ESRNN_TRY(run_stage(h, h->st_head, st, [&] { return launch_head_last(pl, ext, ws, forecasts, st); }));
     return ESRNN_OK;
 }

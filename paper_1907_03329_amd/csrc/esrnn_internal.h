@@ -14,6 +14,9 @@ namespace esrnn {
 
 constexpr int kTileN = 16;       // series per tile (N of the 16x16x4 fp32 MFMA)
 constexpr int kMaxLayers = ESRNN_MAX_BLOCKS * ESRNN_MAX_LAYERS_PER_BLOCK;
+// Layers that follow each other in one launch (lstm_together.h): at most so many, of so many workgroups in all
+constexpr int kTogetherMost = 8, kTogetherGroups = 256;
+constexpr int kWordStride = 32;     // floats between the words by which they do so: a cache line each
 constexpr int kLstmWaves = 4;    // waves per workgroup in the LSTM kernels
 constexpr int kReduceSplits = 16; // subsets of producers in the first stage of the weight-gradient reduction
 // Row stride of the LDS arrays [row][16 series] that are read transposed (lane = row n, column 4k + g).  With 18
@@ -77,6 +80,10 @@ struct Plan {
     size_t len_ext;      // int32[B]: lengths extended by the horizon (out-of-sample forecasts)
     size_t pmax;         // int32[NB]: window positions the series of a 16-series tile need (max over the tile), by setup
     size_t opt_partial;  // float[512]: sums of squares of the gradients, per workgroup (parameter update)
+    size_t together_words;   // the words by which the layers of one launch follow each other (lstm_together.h), cleared by the
+                         // set-up: in the place of the outputs O, which come when those layers are done
+    int together_groups; // workgroups of that launch
+    int together_fwd;    // so many first layers of the forward pass run in one launch (0: every layer in one of its own)
     size_t lvl, S1, S2, u, v, gu, gv;   // [T][Bt]
     size_t X, Z;         // TL(4*IT), TL(OP)
     size_t blk_out[ESRNN_MAX_BLOCKS];
@@ -139,6 +146,13 @@ hipError_t launch_lstm_forward(const Plan &pl, int layer, const int32_t *lengths
                                const ForwardMode &mode, hipStream_t st);
 hipError_t launch_lstm_forward_residual(const Plan &pl, int layer, const int32_t *lengths, float *ws, const ForwardMode &mode,
                                         hipStream_t st);
+// the first Plan::together_fwd layers
+hipError_t launch_lstm_forward_together(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode,
+                                        hipStream_t st);
+hipError_t launch_lstm_forward_together_wide(const Plan &pl, const int32_t *lengths, const float *weights, float *ws,
+                                             const ForwardMode &mode, hipStream_t st);
+hipError_t launch_lstm_forward_together_forecast(const Plan &pl, const int32_t *lengths, const float *weights, float *ws,
+                                                 const ForwardMode &mode, hipStream_t st);
 // 4-series kernels for layers with few workgroups (called by the two launchers above and below)
 hipError_t launch_lstm_forward_narrow(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
                                       float *ws, hipStream_t st);

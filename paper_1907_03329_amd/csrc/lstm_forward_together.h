@@ -1,0 +1,88 @@
+// First layers of the network in one launch, each behind the one below (see lstm_together.h): 4-series layers, the last one
+// possibly a 16-series one.  The kernel template and its launcher, included by one translation unit per kind of last layer.
+//
+// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 65 us and three gaps between launches -> 42 us;
+// the first two layers of 512 hourly series 433 -> 365 us (of 333, for forecasts, 396 -> 293 us), of 501 monthly ones 187 -> 137 us.
+// Whole calls: 7 quarterly series 80 -> 58 us, step of 16 211 -> 188 us, forecasts of 333 hourly ones 540 -> 431 us, step of 512
+// 1770 -> 1740 us.  What bounds it is the first layer's chain; at the end every layer adds what a store, a look and a load past
+// the caches take and a few positions of its own, some 5 us.
+#pragma once
+
+#include "lstm_forward.h"
+#include "lstm_narrow_fwd.h"
+
+namespace esrnn {
+
+namespace {
+
+struct FwdTogetherArgs {
+    NarrowFwdArgs narrow[kTogetherMost];
+    LstmFwdArgs wide;                   // of the last layer, if that is a 16-series one
+    Places places;
+};
+
+// kind of the last layer
+enum { kAllNarrow, kWideStash, kWideNoStash };
+
+template <int HT, int KXT, bool CP, int KIND>
+__global__ void __launch_bounds__(2 * kNT) lstm_forward_together_kernel(FwdTogetherArgs t)
+{
+    using Narrow = NarrowFwdLds<HT, KXT, false, kFirst>;
+    using Later = NarrowFwdLds<HT, HT, true, kLater>;
+    using Wide = FwdLds<HT, HT, 8>;
+    constexpr size_t bytes = std::max({sizeof(Narrow), sizeof(Later), sizeof(NarrowFwdLds<HT, HT, false, kLater>),
+                                       KIND == kAllNarrow ? size_t(0) : sizeof(Wide)});
+    __shared__ __align__(16) char lds[bytes];
+    __shared__ unsigned ticket;
+    const Place at = draw_place(t.places, &ticket);
+    const int l = at.layer, d = t.places.d[l], bt = at.bt, q = at.q, chain = at.chain;
+    const bool wide = KIND != kAllNarrow && l == t.places.layers - 1;
+    const Progress progress = progress_of(t.places, at, l - 1);
+    auto as = [&](auto *type) -> decltype(*type) { return reinterpret_cast<decltype(*type)>(lds); };
+    if (l == 0) {
+        lstm_forward_narrow_body<HT, KXT, CP, false, kFirst>(t.narrow[0], as((Narrow *)nullptr), bt, q, chain, d, progress);
+    } else if (wide) {
+        if constexpr (KIND != kAllNarrow) {
+            constexpr bool stash = KIND == kWideStash;
+            if (t.wide.out) lstm_forward_body<HT, HT, 8, CP, true, stash, true>(t.wide, as((Wide *)nullptr), bt, chain, d, progress);
+            else lstm_forward_body<HT, HT, 8, CP, false, stash, true>(t.wide, as((Wide *)nullptr), bt, chain, d, progress);
+        }
+    } else if (t.narrow[l].out) {
+        lstm_forward_narrow_body<HT, HT, CP, true, kLater>(t.narrow[l], as((Later *)nullptr), bt, q, chain, d, progress);
+    } else {
+        lstm_forward_narrow_body<HT, HT, CP, false, kLater>(t.narrow[l], as((NarrowFwdLds<HT, HT, false, kLater> *)nullptr), bt, q, chain, d, progress);
+    }
+}
+
+template <int KIND>
+hipError_t launch_together(const Plan &pl, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode, hipStream_t st)
+{
+    FwdTogetherArgs t{};
+    Places &places = t.places;
+    places.layers = pl.together_fwd;
+    places.NB = pl.NB;
+    places.words = reinterpret_cast<unsigned *>(ws + pl.together_words);
+    for (int l = 0; l < places.layers; ++l) {
+        const LayerPlan &lp = pl.layer[l];
+        places.d[l] = lp.dil;
+        places.quarters[l] = lp.narrow_fwd ? 4 : 1;
+        places.first[l + 1] = places.first[l] + pl.forward_groups(lp);
+        if (lp.narrow_fwd) t.narrow[l] = narrow_forward_args(pl, l, lengths, weights, ws);
+        else t.wide = forward_args(pl, l, lengths, ws, mode);
+    }
+    const bool cp = pl.cfg.lambda_cs != 0.0f;
+    const int blocks = places.first[places.layers];
+#define X(HT_, KXT_)                                                                                                            \
+    if (pl.HT == HT_ && pl.layer[0].KXT == KXT_) {                                                                              \
+        if (cp && KIND != kWideNoStash) lstm_forward_together_kernel<HT_, KXT_, KIND != kWideNoStash, KIND><<<blocks, 2 * kNT, 0, st>>>(t);        \
+        else lstm_forward_together_kernel<HT_, KXT_, false, KIND><<<blocks, 2 * kNT, 0, st>>>(t);                               \
+        return hipGetLastError();                                                                                               \
+    }
+    ESRNN_LSTM_SHAPES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+}  // namespace esrnn

@@ -108,6 +108,10 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     // tiles to hide memory latency); ESRNN_WINDOW_STREAM_FROM overrides, for measurements.
     int window_stream_from = kWindowStreamFromDefault;
     if (const char *env = std::getenv("ESRNN_WINDOW_STREAM_FROM")) window_stream_from = std::atoi(env);
+    // At most so many workgroups in a launch of several layers; ESRNN_TOGETHER overrides (0: every layer in a launch of its own),
+    // for measurements.
+    int together_groups = kTogetherGroups;
+    if (const char *env = std::getenv("ESRNN_TOGETHER")) together_groups = std::min(std::atoi(env), kTogetherGroups);
     pl.cfg = cfg;
     if (cfg.B < 1 || cfg.T < 1 || cfg.I < 1 || cfg.H < 1 || cfg.hidden < 1) return ESRNN_ERR_CONFIG;
     if (cfg.hidden > ESRNN_MAX_HIDDEN || cfg.I > ESRNN_MAX_WINDOW || cfg.H > ESRNN_MAX_WINDOW) return ESRNN_ERR_CONFIG;
@@ -245,6 +249,24 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.db_partial = ws.take((size_t)groups * lp.chains_bwd * pl.HT * 16);
         lp.db_reduced = ws.take((size_t)kReduceSplits * pl.HT * 16);
         pl.dx[l] = l > 0 ? ws.take(PN * tileH) : pl.gX;
+    }
+    // First layers in one launch: every workgroup has one class, so that positions rise in all of them, there is a compute unit for
+    // each, and a lane for every word that a workgroup looks at.  16-series layers count no positions: one can only be the last.
+    {
+        int n = 0, total = 0;
+        for (; n < std::min(L, kTogetherMost); ++n) {
+            const LayerPlan &lp = pl.layer[n];
+            const int here = pl.forward_groups(lp);
+            if (lp.chains < std::min(lp.dil, pl.P) || total + here > together_groups) break;
+            if (n == 0 && !lp.narrow_fwd) break;
+            if (n > 0 && (!pl.layer[n - 1].narrow_fwd || pl.layer[n - 1].dil * (lp.narrow_fwd ? 1 : 4) > 64)) break;
+            // (in front of the words lie the masks of a forecast)
+            if ((size_t)L * pl.NB * 8 + (size_t)(1 + total + here) * kWordStride > PN * (size_t)pl.OP * 16) break;
+            total += here;
+        }
+        pl.together_fwd = n > 1 ? n : 0;
+        pl.together_groups = n > 1 ? total : 0;
+        pl.together_words = pl.O + (size_t)L * pl.NB * 8;
     }
     // cell-state penalty: one partial sum per forward workgroup of every block's first layer, contiguous
     pl.cs_partial = ws.at;

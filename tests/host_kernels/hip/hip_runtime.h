@@ -65,6 +65,8 @@ typedef const char *__amdgpu_buffer_rsrc_t;
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
 #define __builtin_amdgcn_s_setprio(x) ((void)0)
+#define __builtin_amdgcn_s_sleep(x) ((void)0)
+#define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) (v)
 struct host_pair { unsigned v[2]; unsigned operator[](int i) const { return v[i]; } };
@@ -80,4 +82,5 @@ inline void host_use(const V &v) { __asm__ volatile("" : : "m"(v)); }
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) HOST_MFMA(a, b, c)
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(at) (*(at))
 // (the other waves' bits count for the same wave here)
+inline unsigned atomicAdd(unsigned *at, unsigned v) { const unsigned was = *at; *at += v; return was; }
 inline unsigned atomicOr(unsigned *at, unsigned v) { return *at |= v; }

@@ -144,6 +144,7 @@ static int step(const Plan &pl, const std::vector<int> &lens)
         RUN(-1, launch_es_forward(pl, y, predict ? shorter : lengths, es, weights, ws, mode, nullptr));
         RUN(-1, launch_window_forward(pl, nullptr, ws, nullptr));
         for (int l = 0; l < pl.L; ++l) RUN(l, launch_lstm_forward(pl, l, n, weights, ws, mode, nullptr));
+        if (pl.together_fwd) RUN(pl.together_fwd, launch_lstm_forward_together(pl, n, weights, ws, mode, nullptr));
         if (predict) {
             RUN(-1, launch_head_last(pl, n, ws, ahead, nullptr));
             continue;
@@ -193,6 +194,7 @@ int main(int argc, char **argv)
         for (int l = 0; l < pl.L; ++l)
             printf("layer %d dilation %d narrow %d %d chains %d %d\n", l, pl.layer[l].dil, pl.layer[l].narrow_fwd,
                    pl.layer[l].narrow_bwd, pl.layer[l].chains, pl.layer[l].chains_bwd);
+        printf("together %d\n", pl.together_fwd);
         return 0;
     }
     float *ws = memory<float>(pl.total_floats);

@@ -1,0 +1,64 @@
+"""Layers that follow each other in one launch against the same layers in launches of their own: every result is the same, bit
+for bit, however the workgroups of the layers overtake each other."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1907_03329_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+# chains around a chunk of staged inputs, fewer positions than classes, tiles that end at different positions, hidden sizes of
+# every instantiation, rising and falling dilations, layers that end a block or not, last layers of either kind
+CASES = {
+    "serve": dict(B=7),
+    "eight_tiles_and_more": dict(B=145, blocks=((1,), (3,))),
+    "16_series_layer_last": dict(B=512, blocks=((1, 4), (2, 8))),
+    "16_series_layer_ends_a_block": dict(B=400, blocks=((1,), (5,), (2,)), hidden=50, I=12),
+    "several_narrow_layers_then_16_series": dict(B=160, blocks=((1, 2), (8,))),
+    "falling_dilations": dict(B=40, blocks=((4, 2), (1,))),
+    "one_position": dict(B=20, T=12, blocks=((1,), (1,))),
+    "few_positions": dict(B=33, T=16, blocks=((1, 2), (9, 3))),
+    "nine_positions": dict(B=33, T=20, blocks=((1, 1), (1, 2))),
+    "many_layers": dict(B=18, T=40, blocks=((1, 2, 1), (2, 1, 3), (1, 2, 1))),
+    "hidden_8": dict(B=50, hidden=8, blocks=((1, 2), (3,))),
+    "hidden_30": dict(B=100, hidden=30, I=6, blocks=((1, 2), (2, 6))),
+    "hidden_64": dict(B=36, hidden=64, I=40, T=90, blocks=((1, 2), (4,))),
+    "hidden_64_16_series": dict(B=300, hidden=64, I=40, T=90, blocks=((1, 4), (4,))),
+    "penalty": dict(B=70, hidden=50, I=12, blocks=((1, 3), (2, 6)), lambda_c=0.3, n_cat=6),
+    "penalty_16_series": dict(B=501, hidden=50, I=12, blocks=((1, 3), (2, 6)), lambda_c=0.3, n_cat=6),
+}
+
+
+def results(cfg, together, monkeypatch, repeat):
+    if together is None:
+        monkeypatch.delenv("ESRNN_TOGETHER", raising=False)
+    else:
+        monkeypatch.setenv("ESRNN_TOGETHER", together)
+    inp = synth.make_inputs(cfg, seed=3, ragged=True)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in inp.items()}
+    step = binding.TrainingStep(cfg)
+    if cfg.n_cat:
+        step.set_categories(dev["categories"])
+    out = []
+    for _ in range(repeat):
+        step.forward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        got = [step.loss, step.forecasts, step.grad_es_params, step.grad_weights]
+        got = [t.cpu().numpy().copy() for t in got]
+        ahead = torch.clamp(dev["lengths"] - cfg.H, min=cfg.I + max(cfg.m1, 2))
+        got.append(step.predict(dev["y"], ahead, dev["es_params"], dev["weights"]).cpu().numpy().copy())
+        out.append(got)
+    step.close()
+    return out
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_layers_of_one_launch_are_those_of_several(case, monkeypatch):
+    cfg = synth.CONFIGS["quarterly"].with_(**CASES[case])
+    want, = results(cfg, "0", monkeypatch, 1)
+    assert all(np.isfinite(w).all() for w in want)
+    for got in results(cfg, None, monkeypatch, 3):
+        for name, g, w in zip(("loss", "forecasts", "grad_es", "grad_weights", "ahead"), got, want):
+            assert np.array_equal(g, w), name
