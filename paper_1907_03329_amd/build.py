@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libesrnn_hip.so")
 SOURCES = ["esrnn_api.cpp", "plan.cpp", "es_kernels.hip", "lstm_kernels.hip", "lstm_backward_kernels.hip", "lstm_backward_large_kernels.hip",
            "lstm_forward_kernels.hip", "lstm_forward_residual_kernels.hip", "lstm_narrow_kernels.hip", "lstm_narrow_fwd_residual_kernels.hip", "lstm_narrow_bwd_kernels.hip", "lstm_narrow_bwd_split_kernels.hip", "lstm_together_kernels.hip",
-           "lstm_together_wide_kernels.hip", "lstm_together_forecast_kernels.hip", "head_kernels.hip", "opt_kernels.hip",
+           "lstm_together_wide_kernels.hip", "lstm_together_forecast_kernels.hip", "lstm_together_reverse_kernels.hip", "head_kernels.hip", "opt_kernels.hip",
            "static_scratch.hip", "probe_kernels.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-x", "hip",

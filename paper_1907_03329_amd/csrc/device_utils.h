@@ -102,6 +102,13 @@ __device__ __forceinline__ unsigned long long needed_classes(const unsigned *mas
     return __ballot(want);
 }
 
+// (by a workgroup of 256 threads)
+template <class Words>
+__device__ __forceinline__ void clear_words(const Words &w, int stride)
+{
+    for (int i = threadIdx.x; i < w.n; i += 256) w.at[i * stride] = 0u;
+}
+
 // Workgroup barrier that orders LDS traffic only: global loads and stores in
 // flight are not waited for.
 __device__ __forceinline__ void lds_barrier()

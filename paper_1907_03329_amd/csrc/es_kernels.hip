@@ -40,8 +40,7 @@ struct PrepArgs {
     int NB;
     int B, H;
     int cs_per_window;   // cell-state values per valid window in the cell-state penalty: hidden * blocks
-    unsigned *words;     // by which layers of one launch follow each other, and how many
-    int n_words;
+    TogetherWords words; // of the forward pass
 };
 
 // One workgroup reads all lengths, eight requests in flight per thread, of four lengths each where the caller's array is
@@ -50,7 +49,7 @@ struct PrepArgs {
 __device__ __forceinline__ void prep_body(const PrepArgs &pa, float *scratch)
 {
     const Lengths L = pa.lengths;
-    for (int i = threadIdx.x; i < pa.n_words; i += 256) pa.words[i * kWordStride] = 0u;
+    clear_words(pa.words, kWordStride);
     unsigned long long *s_pin = reinterpret_cast<unsigned long long *>(scratch), *s_lv = s_pin + 256;
     unsigned long long np_ = 0, nl = 0;
     auto count = [&](int raw) {
@@ -1046,12 +1045,14 @@ struct ReduceStage2Args {
     ReduceHeadArgs head;
     int end[kMaxLayers + 1];    // workgroups of this layer (the last one: of the output stage) and those before it
     int L;
+    TogetherWords words;        // of the reverse pass, for the next one
     int blocks() const { return end[kMaxLayers]; }      // 0: nothing to reduce
 };
 
 __device__ __forceinline__ void reduce_stage2_body(const ReduceStage2Args &a, int block, float *scratch)
 {
     float (*s_red)[64] = reinterpret_cast<float (*)[64]>(scratch);
+    if (block == 0) clear_words(a.words, kWordStride);
     int z = 0;
     while (z < a.L && block >= a.end[z]) ++z;
     if (z > 0) block -= a.end[z - 1];
@@ -1527,7 +1528,7 @@ SetupArgs setup_args(const Plan &pl, const Lengths &len, const float *weights, u
     SetupArgs a{};
     a.L = pl.L;
     a.prep = PrepArgs{len, reinterpret_cast<Scalars *>(ws + pl.scalars), reinterpret_cast<int32_t *>(ws + pl.pmax), pl.NB,
-                      pl.B, pl.H, pl.h * pl.cfg.n_blocks, reinterpret_cast<unsigned *>(ws + pl.together_words), weights && pl.together_fwd ? 1 + pl.together_groups : 0};
+                      pl.B, pl.H, pl.h * pl.cfg.n_blocks, TogetherWords{reinterpret_cast<unsigned *>(ws + pl.together_words), weights && pl.together_fwd ? 1 + pl.together_groups : 0}};
     a.pmax_blocks = std::min((pl.NB + 255) / 256, 63);
     if (len.extend) {
         ClassArgs &c = a.classes;
@@ -1643,6 +1644,7 @@ ReduceStage2Args reduce_stage2_args(const Plan &pl, float *ws, float *grad_weigh
 {
     ReduceStage2Args r{};
     r.L = pl.L;
+    r.words = TogetherWords{reinterpret_cast<unsigned *>(ws + pl.together_words_bwd), pl.together_bwd ? 1 + pl.together_groups_bwd : 0};
     int blocks = 0;
     for (int l = 0; l < pl.L; ++l) {
         const LayerPlan &lp = pl.layer[l];

@@ -215,8 +215,10 @@ esrnn_status esrnn_backward(esrnn_handle *h, const float *y, const int32_t *leng
     const Plan &pl = h->plan;
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    for (int l = pl.L - 1; l >= 0; --l)
+    const int together = h->profiling ? 0 : pl.together_bwd;
+    for (int l = pl.L - 1; l >= together; --l)
         ESRNN_TRY(run_stage(h, h->st_lstm_bwd[l], st, [&] { return launch_lstm_backward(pl, l, lengths, ws, st); }));
+    if (together) ESRNN_TRY(launch_lstm_backward_together(pl, lengths, ws, st));
     ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, true, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_bwd, st,
                         [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, grad_weights, st); }));

@@ -83,6 +83,11 @@ struct Plan {
     size_t together_words;   // the words by which the layers of one launch follow each other (lstm_together.h), cleared by the
                          // set-up: in the place of the outputs O, which come when those layers are done
     int together_groups; // workgroups of that launch
+    // The same for the reverse pass, whose last launch runs the network's first layers.  The words lie in the place of the
+    // output stage's operands, which are packed again in every forward pass; cleared when the output stage is done, and at the end
+    // of every reverse pass.
+    int together_bwd, together_groups_bwd;
+    size_t together_words_bwd;
     int together_fwd;    // so many first layers of the forward pass run in one launch (0: every layer in one of its own)
     size_t lvl, S1, S2, u, v, gu, gv;   // [T][Bt]
     size_t X, Z;         // TL(4*IT), TL(OP)
@@ -102,6 +107,12 @@ struct Plan {
     int forward_groups(const LayerPlan &lp) const { return (lp.narrow_fwd ? 4 * NB : NB) * lp.chains; }        // workgroups of the forward kernel
     size_t es_window_floats;   // prefix of the workspace used by the smoothing and window stages alone
     size_t total_floats;
+};
+
+// words by which the layers of a launch follow each other, a cache line each: to be cleared by the 256 threads of a workgroup
+struct TogetherWords {
+    unsigned *at;
+    int n;
 };
 
 // device-side scalars computed from lengths, and from weights
@@ -153,6 +164,8 @@ hipError_t launch_lstm_forward_together_wide(const Plan &pl, const int32_t *leng
                                              const ForwardMode &mode, hipStream_t st);
 hipError_t launch_lstm_forward_together_forecast(const Plan &pl, const int32_t *lengths, const float *weights, float *ws,
                                                  const ForwardMode &mode, hipStream_t st);
+// the first Plan::together_bwd layers of the network
+hipError_t launch_lstm_backward_together(const Plan &pl, const int32_t *lengths, float *ws, hipStream_t st);
 // 4-series kernels for layers with few workgroups (called by the two launchers above and below)
 hipError_t launch_lstm_forward_narrow(const Plan &pl, int layer, const int32_t *lengths, const float *weights,
                                       float *ws, hipStream_t st);

@@ -530,6 +530,7 @@ struct LossArgs {
     const Scalars *sc;
     float lambda, lambda_cs;
     float *loss;
+    TogetherWords words;        // of the reverse pass, in the place of operands that are not needed any more
 };
 
 // sum over the workgroup of a value per thread, in a fixed order
@@ -546,6 +547,7 @@ __device__ __forceinline__ double block_sum(double v, double *s_wave)
 
 __device__ void loss_body(const LossArgs &a, double *s_wave)
 {
+    clear_words(a.words, kWordStride);
     double pin = 0.0, lv = 0.0, cs = 0.0;
     for (int i = threadIdx.x; i < a.n_pin; i += 256) pin += (double)a.pin[i];
     for (int i = threadIdx.x; i < a.n_lv; i += 256) lv += (double)a.lv[i];
@@ -629,7 +631,8 @@ hipError_t launch_loss_and_forecasts(const Plan &pl, const int32_t *lengths, flo
 {
     const esrnn_config &c = pl.cfg;
     const LossArgs la{ws + pl.loss_partial, ws + pl.loss_partial + pl.head_blocks, ws + pl.cs_partial, pl.head_blocks, pl.es_blocks,
-                      pl.n_cs_partial, reinterpret_cast<const Scalars *>(ws + pl.scalars), c.lambda_lv, c.lambda_cs, loss};
+                      pl.n_cs_partial, reinterpret_cast<const Scalars *>(ws + pl.scalars), c.lambda_lv, c.lambda_cs, loss,
+                      TogetherWords{reinterpret_cast<unsigned *>(ws + pl.together_words_bwd), pl.together_bwd ? 1 + pl.together_groups_bwd : 0}};
     const long long tiles = forecasts ? (long long)pl.P * pl.NB : 0;
     forecast_kernel<<<(unsigned)(1 + (tiles + 3) / 4), 256, 0, st>>>(
         ws + pl.O, ws + pl.u, ws + pl.S1, ws + pl.S2, lengths, reinterpret_cast<const int32_t *>(ws + pl.pmax), forecasts,

@@ -93,27 +93,21 @@ struct TileHome {
 // eight waves, 257 / 319 / 340 us with thirteen; hidden 40, 72 steps: 52 us with eight, 56 us with ten).
 constexpr int fwd_waves(int HT) { return HT <= 10 ? 8 : HT; }
 
-template <int HT, int KXT, int W>
-struct FwdLds {
-    char h[2][tt_b_quads((HT + 1) / 2) * 1024];         // parts of h_{p-d}, by position parity
-    char x[2][tt_b_quads((KXT + 1) / 2) * 1024];        // parts of x_p
-    f32x4 rest[HT][4];                                  // what the rounding of that left out of the bias
-    float cs[W];
-};
-
 // One workgroup of W waves: series tile bt, residue classes chain, chain + chains, ...
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the block
 // input, writes the block output); STASH: a reverse pass may follow - without it gates and cell states stay on chip, and
 // only the residue classes that are asked for are computed.  (An instantiation of its own: a switch at run time cost the
 // layers of a training step 3 us each.)  LATER: the layer below runs in the same launch (lstm_together.h).
 template <int HT, int KXT, int W, bool CP, bool OUT, bool STASH, bool LATER>
-__device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<HT, KXT, W> &lds, int bt, int chain, int chains,
-                                                  const Progress &progress)
+__device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, int chain, int chains, const Progress &progress)
 {
     constexpr int NPX = (KXT + 1) / 2, NPH = (HT + 1) / 2;
     constexpr int AX = tt_a_quads(NPX), AH = tt_a_quads(NPH), BX = tt_b_quads(NPX), BH = tt_b_quads(NPH);
     constexpr int MTW = (HT + W - 1) / W, XTW = (KXT + W - 1) / W;   // unit tiles and input tiles per wave
     static_assert(W == 8 || (MTW == 1 && XTW == 1), "tile s + W j lies in segment j, or there is one tile");
+    __shared__ __align__(16) char h_lds[2][BH * 1024];               // parts of h_{p-d}, by position parity
+    __shared__ __align__(16) char x_lds[2][BX * 1024];               // parts of x_p
+    __shared__ f32x4 rest_lds[HT][4];                                // what the rounding of that left out of the bias
 
     const int lane = threadIdx.x & 63;
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave index, known to be uniform
@@ -145,11 +139,11 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
             // (nothing is left out of an infinite one, and inf - inf would be NaN)
             rest[r] = __builtin_isinf(scaled[j][r]) ? 0.0f : __builtin_fmaf(b[r], k, -scaled[j][r]) * (1.0f / k);
         }
-        if ((lane & 15) == 0 && s + W * j < HT) lds.rest[mt][lane >> 4] = rest;
+        if ((lane & 15) == 0 && s + W * j < HT) rest_lds[mt][lane >> 4] = rest;
     }
     // halves of pairs that no tile fills stay zero
-    for (int i = threadIdx.x; i < 2 * BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(lds.h)[i] = 0u;
-    for (int i = threadIdx.x; i < 2 * BX * 256; i += 64 * W) reinterpret_cast<unsigned *>(lds.x)[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(h_lds)[i] = 0u;
+    for (int i = threadIdx.x; i < 2 * BX * 256; i += 64 * W) reinterpret_cast<unsigned *>(x_lds)[i] = 0u;
 
     // positions below this take part in the loss for this lane's series (CP only)
     int n_valid = 0;
@@ -183,7 +177,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
         auto store_x = [&](int buf, const float (&v)[XTW]) {
             static_for<0, NX>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
-                TileHome<NPX, SX + j>::store(lds.x[buf], x_at[j], splittable(LATER ? below.checked(v[j]) : v[j]));
+                TileHome<NPX, SX + j>::store(x_lds[buf], x_at[j], splittable(LATER ? below.checked(v[j]) : v[j]));
             });
         };
         auto load_res = [&](int p, float (&v)[MTW]) {
@@ -201,13 +195,13 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
             return v;
         };
         f32x4 acc[MTW];
-        // acc = Wx x (+ the rest of the bias), from the parts in lds.x[buf]
+        // acc = Wx x (+ the rest of the bias), from the parts in x_lds[buf]
         auto input_part = [&](int buf) {
             u32x4 b[BX];
 #pragma unroll
-            for (int q = 0; q < BX; ++q) b[q] = read_quad(lds.x[buf], q);
+            for (int q = 0; q < BX; ++q) b[q] = read_quad(x_lds[buf], q);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) acc[j] = lds.rest[min(s + W * j, HT - 1)][lane >> 4];
+            for (int j = 0; j < NJ; ++j) acc[j] = rest_lds[min(s + W * j, HT - 1)][lane >> 4];
             static_for<0, tt_mfmas(NPX)>([&](auto ic) {
                 constexpr TtPair t = tt_mfma(NPX, decltype(ic)::value);
 #pragma unroll
@@ -228,7 +222,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
             load_x(r, xv);
             load_x(r + a.d, x1);
             __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
-            for (int i = threadIdx.x; i < BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(lds.h[0])[i] = 0u;
+            for (int i = threadIdx.x; i < BH * 256; i += 64 * W) reinterpret_cast<unsigned *>(h_lds[0])[i] = 0u;
             store_x(0, xv);
             store_x(1, x1);
             load_x(r + 2 * a.d, xv);
@@ -238,7 +232,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
             load_res(r + a.d, res1);
             lds_barrier();
             input_part(0);
-            lds_barrier();              // lds.x[0] is written again in the first position
+            lds_barrier();              // x_lds[0] is written again in the first position
 
             int par = 0;
             for (int p = r; p < Pt; p += a.d, par ^= 1) {
@@ -249,7 +243,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
                 {
                     u32x4 b[BH];
 #pragma unroll
-                    for (int q = 0; q < BH; ++q) b[q] = read_quad(lds.h[par], q);
+                    for (int q = 0; q < BH; ++q) b[q] = read_quad(h_lds[par], q);
                     static_for<0, tt_mfmas(NPH)>([&](auto ic) {
                         constexpr TtPair t = tt_mfma(NPH, decltype(ic)::value);
 #pragma unroll
@@ -267,7 +261,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
                     const float hn = go * tanh_f(cn);
                     creg[j] = cn;
                     if constexpr (CP) csq += p < n_valid ? cn * cn : 0.0f;
-                    TileHome<NPH, SH + j>::store(lds.h[par ^ 1], h_at[j], hn);
+                    TileHome<NPH, SH + j>::store(h_lds[par ^ 1], h_at[j], hn);
                     // gates and cell state are read again only by the reverse pass: streaming stores
                     if constexpr (STASH) {
                         buf_store4<true>(make_rsrc(a.gates + (pb * HT + mt) * 256), lane16, f32x4{gi, gf, gg, go});
@@ -300,12 +294,13 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
     else if (kTwo && s >= 8) with_x(integral_constant<int, MTW>{}, integral_constant<int, kTwo ? 1 : 0>{});
     else with_x(integral_constant<int, MTW>{}, integral_constant<int, 0>{});
     if constexpr (CP) {
+        __shared__ float s_cs[W];
         const float tot = wave_sum(csq);
-        if (lane == 0) lds.cs[s] = tot;
+        if (lane == 0) s_cs[s] = tot;
         __syncthreads();
         if (threadIdx.x == 0 && (!LATER || a.cs_partial)) {
             float t = 0.0f;
-            for (int i = 0; i < W; ++i) t += lds.cs[i];
+            for (int i = 0; i < W; ++i) t += s_cs[i];
             a.cs_partial[bt * chains + chain] = t;
         }
     }
@@ -314,8 +309,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, FwdLds<H
 template <int HT, int KXT, bool CP, bool OUT, bool STASH>
 __global__ void __launch_bounds__(64 * fwd_waves(HT), 4) lstm_forward_kernel(LstmFwdArgs a)
 {
-    __shared__ __align__(16) FwdLds<HT, KXT, fwd_waves(HT)> lds;
-    lstm_forward_body<HT, KXT, fwd_waves(HT), CP, OUT, STASH, false>(a, lds, blockIdx.x, blockIdx.y, gridDim.y, Progress{});
+    lstm_forward_body<HT, KXT, fwd_waves(HT), CP, OUT, STASH, false>(a, blockIdx.x, blockIdx.y, gridDim.y, Progress{});
 }
 
 template <int HT, int KXT, bool OUT>

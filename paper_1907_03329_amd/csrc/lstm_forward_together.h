@@ -27,30 +27,23 @@ enum { kAllNarrow, kWideStash, kWideNoStash };
 template <int HT, int KXT, bool CP, int KIND>
 __global__ void __launch_bounds__(2 * kNT) lstm_forward_together_kernel(FwdTogetherArgs t)
 {
-    using Narrow = NarrowFwdLds<HT, KXT, false, kFirst>;
-    using Later = NarrowFwdLds<HT, HT, true, kLater>;
-    using Wide = FwdLds<HT, HT, 8>;
-    constexpr size_t bytes = std::max({sizeof(Narrow), sizeof(Later), sizeof(NarrowFwdLds<HT, HT, false, kLater>),
-                                       KIND == kAllNarrow ? size_t(0) : sizeof(Wide)});
-    __shared__ __align__(16) char lds[bytes];
     __shared__ unsigned ticket;
     const Place at = draw_place(t.places, &ticket);
     const int l = at.layer, d = t.places.d[l], bt = at.bt, q = at.q, chain = at.chain;
     const bool wide = KIND != kAllNarrow && l == t.places.layers - 1;
     const Progress progress = progress_of(t.places, at, l - 1);
-    auto as = [&](auto *type) -> decltype(*type) { return reinterpret_cast<decltype(*type)>(lds); };
     if (l == 0) {
-        lstm_forward_narrow_body<HT, KXT, CP, false, kFirst>(t.narrow[0], as((Narrow *)nullptr), bt, q, chain, d, progress);
+        lstm_forward_narrow_body<HT, KXT, CP, false, kFirst>(t.narrow[0], bt, q, chain, d, progress);
     } else if (wide) {
         if constexpr (KIND != kAllNarrow) {
             constexpr bool stash = KIND == kWideStash;
-            if (t.wide.out) lstm_forward_body<HT, HT, 8, CP, true, stash, true>(t.wide, as((Wide *)nullptr), bt, chain, d, progress);
-            else lstm_forward_body<HT, HT, 8, CP, false, stash, true>(t.wide, as((Wide *)nullptr), bt, chain, d, progress);
+            if (t.wide.out) lstm_forward_body<HT, HT, 8, CP, true, stash, true>(t.wide, bt, chain, d, progress);
+            else lstm_forward_body<HT, HT, 8, CP, false, stash, true>(t.wide, bt, chain, d, progress);
         }
     } else if (t.narrow[l].out) {
-        lstm_forward_narrow_body<HT, HT, CP, true, kLater>(t.narrow[l], as((Later *)nullptr), bt, q, chain, d, progress);
+        lstm_forward_narrow_body<HT, HT, CP, true, kLater>(t.narrow[l], bt, q, chain, d, progress);
     } else {
-        lstm_forward_narrow_body<HT, HT, CP, false, kLater>(t.narrow[l], as((NarrowFwdLds<HT, HT, false, kLater> *)nullptr), bt, q, chain, d, progress);
+        lstm_forward_narrow_body<HT, HT, CP, false, kLater>(t.narrow[l], bt, q, chain, d, progress);
     }
 }
 

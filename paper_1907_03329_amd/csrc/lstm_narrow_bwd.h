@@ -3,6 +3,7 @@
 #pragma once
 
 #include "lstm_narrow_common.h"
+#include "lstm_together.h"
 
 namespace esrnn {
 
@@ -54,32 +55,47 @@ struct NarrowBwdArgs {
 // per compute unit: a chain wave is bound by the instructions it issues, and the SIMDs have the other waves' work while it
 // waits.  (With requests, staging and input gradient on the chain waves the first layer of 512 hourly series took 491 us,
 // now 440; that of 501 monthly ones 247 us, now 221; that of 16 quarterly ones 43.6 us, now 39.7.)
-template <int HT, int KXT, bool CP, bool SPLIT>
-__global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 2 : 1) lstm_backward_narrow_kernel(NarrowBwdArgs a)
+// MODE: kLater, layers of one launch (lstm_together.h): this layer waits for the one above it, and its positions are counted; kLast,
+// nobody waits for this one.
+constexpr int narrow_bwd_slots(bool split) { return split ? 8 : 4; }   // two chunks where one wave writes and another reads
+
+template <int HT, int KXT, bool SPLIT>
+struct NarrowBwdLds {                                   // (references: an object each where nothing else has to fit)
+    static constexpr int KX = 4 * KXT, HP = 4 * HT, KT4 = KX + HP;
+    static constexpr int CH = 4;                        // positions per chunk of staged operands
+    static constexpr int NG = (KT4 + 63) / 64;          // groups of 64 columns of [x ; h]
+    static constexpr int CT = (KT4 + 15) / 16;          // 16-column tiles of dW
+    float (&da_all)[2][HP * 16];             // [unit][series][gate]
+    float (&part)[2][kNW][NG * 64 * 4];        // partial W^T da of every wave [column][series]
+    f32x4 (&lc)[narrow_bwd_slots(SPLIT)][2][kNT];   // per thread: activated gates; c, c_{p-d}, two gradient sources
+    float (&xhc)[2][CH][CT * 64];                        // [column of x_p ; h_{p-d}][series]
+    static constexpr size_t at_part = sizeof(float) * 2 * HP * 16, at_lc = at_part + sizeof(float) * 2 * kNW * NG * 64 * 4,
+                            at_xhc = at_lc + sizeof(f32x4) * narrow_bwd_slots(SPLIT) * 2 * kNT, bytes = at_xhc + sizeof(float) * 2 * CH * CT * 64;
+    static __device__ __forceinline__ NarrowBwdLds in(char *at)
+    {
+        return {reinterpret_cast<float (&)[2][HP * 16]>(*at), reinterpret_cast<float (&)[2][kNW][NG * 64 * 4]>(at[at_part]),
+                reinterpret_cast<f32x4 (&)[narrow_bwd_slots(SPLIT)][2][kNT]>(at[at_lc]), reinterpret_cast<float (&)[2][CH][CT * 64]>(at[at_xhc])};
+    }
+};
+
+// One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ...
+template <int HT, int KXT, bool CP, bool SPLIT, int MODE>
+__device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a, const NarrowBwdLds<HT, KXT, SPLIT> &lds, int bt, int q,
+                                                          int chain, int chains, const Progress &progress)
 {
-    constexpr int KX = 4 * KXT, HP = 4 * HT, KT4 = KX + HP;
-    constexpr int CH = 4;                        // positions per chunk of staged operands
-    constexpr int NG = (KT4 + 63) / 64;          // groups of 64 columns of [x ; h]
-    constexpr int CT = (KT4 + 15) / 16;          // 16-column tiles of dW
+    using Lds = NarrowBwdLds<HT, KXT, SPLIT>;
+    static_assert(SPLIT || MODE == kAlone, "");
+    constexpr bool kWaits = MODE != kAlone, kCounts = MODE == kLater;
+    constexpr int KX = Lds::KX, HP = Lds::HP, KT4 = Lds::KT4, CH = Lds::CH, NG = Lds::NG, CT = Lds::CT;
     constexpr int MTW = (HT + kNW - 1) / kNW;    // 16-row tiles of dW per wave (a row tile = 4 units x 4 gates)
     constexpr int XH_PER = (4 * KT4 + kNT - 1) / kNT;
-    __shared__ __align__(16) float da_all[2][HP * 16];           // [unit][series][gate]
-    __shared__ __align__(16) float part[2][kNW][NG * 64 * 4];    // partial W^T da of every wave [column][series]
-    constexpr int SLOTS = SPLIT ? 2 * CH : CH;   // positions of staged per-thread operands (one wave writes, another reads: two chunks)
-    __shared__ __align__(16) f32x4 lc[SLOTS][2][kNT];            // per thread: activated gates; c, c_{p-d}, two gradient sources
-    __shared__ float xhc[2][CH][CT * 64];                        // [column of x_p ; h_{p-d}][series]
+    constexpr int SLOTS = narrow_bwd_slots(SPLIT);
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = SPLIT ? (wv & (kNW - 1)) : wv;
     const bool dw_wave = SPLIT && wv >= kNW;
     const int blk = lane >> 2, j = lane & 3;
-    // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
-    // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
-    // quarters of ONE tile, so they land on the same XCD at about the same time and a row is fetched from
-    // HBM once, not four times (measured before: 2.3-2.8 times the algorithmic bytes).
-    const int bt = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7), q = (blockIdx.x >> 3) & 3;
-    if (bt >= a.NB) return;     // the grid is padded to whole groups of 32 (before any barrier)
     // All four workgroups of a 16-series tile stop at the tile's longest series: what lies beyond is
     // neither computed here nor read by any later kernel.
     const int Pt = a.pmax[bt];
@@ -99,10 +115,10 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
 #pragma unroll
         for (int nb = 0; nb < CT; ++nb) dw[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 dbacc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int e = threadIdx.x; e < 2 * CH * CT * 64; e += SPLIT ? 2 * kNT : kNT) (&xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
+    for (int e = threadIdx.x; e < 2 * CH * CT * 64; e += SPLIT ? 2 * kNT : kNT) (&lds.xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
 
     auto store_dw = [&]() {
-        const size_t partix = (size_t)(4 * bt + q) * gridDim.y + blockIdx.y;
+        const size_t partix = (size_t)(4 * bt + q) * chains + chain;
 #pragma unroll
         for (int t = 0; t < MTW; ++t) {
             const int mt = w + kNW * t;
@@ -118,6 +134,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     };
     // ---- requests and staging of a chunk: the c * CH + ii-th positions from the end of a chain that ends at p_last and has
     // n positions (requests past the chain repeat the last)
+    Below above(progress);
     f32x4 s_gt[CH], s_o[CH];     // (native vectors: arrays of the HIP float4 class do not stay in registers)
     float s_xh[CH][XH_PER];
     auto load_chunk = [&](int c, int n, int p_last) {
@@ -128,7 +145,9 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
             const size_t pbd = (size_t)(p >= a.d ? p - a.d : p) * a.NB + bt;
             const size_t e = pb * (HP * 16) + lane_off;
             s_gt[ii] = reinterpret_cast<const f32x4 *>(a.gates)[e];
-            s_o[ii] = f32x4{a.c[e], a.c[pbd * (HP * 16) + lane_off], a.gsrc[0][e], a.gsrc[1][e]};
+            const float g0 = kWaits ? buf_load_shared(make_rsrc(a.gsrc[0] + pb * (HP * 16)), 4 * lane_off, 0) : a.gsrc[0][e];
+            const float g1 = kWaits ? buf_load_shared(make_rsrc(a.gsrc[1] + pb * (HP * 16)), 4 * lane_off, 0) : a.gsrc[1][e];
+            s_o[ii] = f32x4{a.c[e], a.c[pbd * (HP * 16) + lane_off], g0, g1};
 #pragma unroll
             for (int k = 0; k < XH_PER; ++k) {
                 const int el = min(tid + k * kNT, 4 * KT4 - 1);
@@ -146,31 +165,35 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
         for (int ii = 0; ii < CH; ++ii) {
             const bool has_prev = p_last - min(c * CH + ii, n - 1) * a.d >= a.d;
             const int slot = SPLIT ? (c & 1) * CH + ii : ii;
-            lc[slot][0][tid] = s_gt[ii];
-            lc[slot][1][tid] = s_o[ii];
+            lds.lc[slot][0][tid] = s_gt[ii];
+            if constexpr (kWaits) s_o[ii][2] = above.checked(s_o[ii][2]);
+            lds.lc[slot][1][tid] = s_o[ii];
 #pragma unroll
             for (int k = 0; k < XH_PER; ++k) {
                 const int el = tid + k * kNT;
-                if (el < 4 * KT4) xhc[c & 1][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
+                if (el < 4 * KT4) lds.xhc[c & 1][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
             }
         }
     };
     // ---- sum and store of one position's input gradient
     auto input_gradient = [&](int p, int par) {
-        const float dxv = (part[par][0][dx_el] + part[par][1][dx_el]) + (part[par][2][dx_el] + part[par][3][dx_el]);
-        (a.gdst + ((size_t)p * a.NB + bt) * (KX * 16))[(dx_el >> 2) * 16 + 4 * q + (dx_el & 3)] = dxv;
+        const float dxv = (lds.part[par][0][dx_el] + lds.part[par][1][dx_el]) + (lds.part[par][2][dx_el] + lds.part[par][3][dx_el]);
+        float *to = a.gdst + ((size_t)p * a.NB + bt) * (KX * 16);
+        const int at = (dx_el >> 2) * 16 + 4 * q + (dx_el & 3);
+        if constexpr (kCounts) buf_store_shared(make_rsrc(to), 4 * at, 0, dxv);
+        else to[at] = dxv;
     };
-    // ---- C: weight gradient of one position, k = the four series; da in da_all[par], [x ; h] in xhc[cpar][ii]
+    // ---- C: weight gradient of one position, k = the four series; da in lds.da_all[par], [x ; h] in lds.xhc[cpar][ii]
     auto step_c = [&](int par, int cpar, int ii) {
         float xb[CT];
 #pragma unroll
-        for (int nb = 0; nb < CT; ++nb) xb[nb] = xhc[cpar][ii][64 * nb + xb_off];
+        for (int nb = 0; nb < CT; ++nb) xb[nb] = lds.xhc[cpar][ii][64 * nb + xb_off];
 #pragma unroll
         for (int t = 0; t < MTW; ++t) {
             const int mt = w + kNW * t;
             if (mt < HT) {
                 // row 4*gate + u of the tile is gate `gate` of unit 4*mt + u
-                const float ar = da_all[par][64 * mt + ar_off];
+                const float ar = lds.da_all[par][64 * mt + ar_off];
 #pragma unroll
                 for (int nb = 0; nb < CT; ++nb) dw[t][nb] = mfma16(ar, xb[nb], dw[t][nb]);
             }
@@ -179,29 +202,56 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     if constexpr (SPLIT) {
         if (dw_wave) {
             // the same barriers as the chain waves below: start of a chain, first staging, one per position
-            for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
+            for (int r0 = chain; r0 < a.d && r0 < Pt; r0 += chains) {
                 const int n = (Pt - r0 + a.d - 1) / a.d, p_last = r0 + (n - 1) * a.d;
+                // the layer above has all of a chunk before it is requested
+                auto await_chunk = [&](int c) {
+                    if constexpr (kWaits) above.wait_falling(p_last - min(c * CH + CH - 1, n - 1) * a.d, Pt);
+                };
+                auto complete_but = [&](auto stores) {
+                    if constexpr (kCounts) stores_complete_but<decltype(stores)::value>();
+                };
+                auto count = [&](int positions) {
+                    if constexpr (kCounts) progress.publish(max(positions, 0) * a.d, w == 0);
+                };
+                using std::integral_constant;
+                await_chunk(0);
                 load_chunk(0, n, p_last);
                 __syncthreads();
                 flush_chunk(0, n, p_last);
                 lds_barrier();
                 int c = 0;
                 for (; (c + 1) * CH <= n; ++c) {
+                    // (what a wave stores behind the input gradient that is counted next: another one, and in between a count)
+                    complete_but(integral_constant<int, 2>{});
+                    await_chunk(c + 1);
                     load_chunk(c + 1, n, p_last);
                     static_for<0, CH>([&](auto iic) {
                         constexpr int ii = decltype(iic)::value;
-                        // (the chain reads a position's operands in the interval before it)
-                        if constexpr (ii == CH - 2) flush_chunk(c + 1, n, p_last);
-                        lds_barrier();
                         const int i = c * CH + ii;
+                        // (the chain reads a position's operands in the interval before it)
+                        if constexpr (ii == CH - 2) {
+                            flush_chunk(c + 1, n, p_last);
+                            complete_but(integral_constant<int, 1>{});
+                        }
+                        if constexpr (ii == CH - 1) complete_but(integral_constant<int, 2>{});
+                        lds_barrier();
+                        if constexpr (ii != 1) count(i - 1);
                         step_c(i & 1, c & 1, ii);
                         input_gradient(p_last - i * a.d, i & 1);
                     });
                 }
                 for (int i = c * CH; i < n; ++i) {
+                    complete_but(integral_constant<int, 1>{});
                     lds_barrier();
+                    count(i - 1);
                     step_c(i & 1, c & 1, i - c * CH);
                     input_gradient(p_last - i * a.d, i & 1);
+                }
+                if constexpr (kCounts) {
+                    stores_complete_but<0>();
+                    lds_barrier();
+                    count(n);
                 }
             }
             store_dw();
@@ -222,10 +272,10 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
         const int col = bt * kTileN + 4 * q + j;
         const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
         n_valid = len - a.I - a.H + 1;
-        pen = a.two_lambda_cs * a.sc->inv_n_cs;
+        pen = MODE == kAlone || a.sc ? a.two_lambda_cs * a.sc->inv_n_cs : 0.0f;
     }
 
-    for (int r0 = blockIdx.y; r0 < a.d && r0 < Pt; r0 += gridDim.y) {
+    for (int r0 = chain; r0 < a.d && r0 < Pt; r0 += chains) {
         const int n = (Pt - r0 + a.d - 1) / a.d;
         const int p_last = r0 + (n - 1) * a.d;
         if constexpr (!SPLIT) load_chunk(0, n, p_last);
@@ -236,8 +286,8 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
 
         // per-thread operands of the first position; those of position i+1 are read before the barrier
         // that ends position i
-        f32x4 gt = lc[0][0][tid];      // activated input, forget, candidate, output gate
-        f32x4 o = lc[0][1][tid];       // c, c_{p-d}, gradient sources
+        f32x4 gt = lds.lc[0][0][tid];      // activated input, forget, candidate, output gate
+        f32x4 o = lds.lc[0][1][tid];       // c, c_{p-d}, gradient sources
         // One position: the i-th from the end of the chain, staged in slot ii of the chunk buffers of parity
         // cpar; the per-thread operands of the next position are in slot `next`.  `staged` runs after they
         // have been read and before the barrier (the staging of the next chunk goes there).
@@ -260,7 +310,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
             da[3] = dh_o * tc * (1.0f - gt[3]);
             dcreg = dc_f;
             if (valid) dbacc += da;
-            *reinterpret_cast<f32x4 *>(&da_all[par][16 * unit + 4 * j]) = da;    // for step C
+            *reinterpret_cast<f32x4 *>(&lds.da_all[par][16 * unit + 4 * j]) = da;    // for step C
             // ---- B: partial W^T da over the k-steps (unit, gate) of this wave; da of unit u is
             // broadcast from the registers of block u.  Two chains of dependent instructions: the two
             // column groups, or with one group two accumulators (more would cost the second resident
@@ -285,17 +335,17 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
             // lane l of group g holds column 64g + l for the four series
 #pragma unroll
             for (int g = 0; g < NG; ++g)
-                *reinterpret_cast<f32x4 *>(&part[par][w][(64 * g + lane) * 4]) =
+                *reinterpret_cast<f32x4 *>(&lds.part[par][w][(64 * g + lane) * 4]) =
                     kBwdAcc == 2 ? acc[g][0] + acc[g][1] : acc[g][0];
             // per-thread operands of the next position (staged at least one barrier ago)
-            gt = lc[next][0][tid];
-            o = lc[next][1][tid];
+            gt = lds.lc[next][0][tid];
+            o = lds.lc[next][1][tid];
             staged();
             lds_barrier();
             // ---- sums of the four partials: recurrent dh of this lane; input gradient
             {
                 const int e = 4 * (KX + unit) + j;
-                dhreg = (part[par][0][e] + part[par][1][e]) + (part[par][2][e] + part[par][3][e]);
+                dhreg = (lds.part[par][0][e] + lds.part[par][1][e]) + (lds.part[par][2][e] + lds.part[par][3][e]);
             }
             if constexpr (!SPLIT) {         // (the other waves' work where there are some)
                 input_gradient(p, par);
@@ -310,6 +360,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
                 position(i + 1, 0, 0, (i + 2) & (SLOTS - 1), [] {});
             }
             if (i < n) position(i, 0, 0, 0, [] {});
+            if constexpr (kCounts) lds_barrier();       // (the last input gradients are in memory)
             continue;
         }
         // Whole chunks: one straight run of instructions each.  The operands of the next chunk are requested
@@ -331,7 +382,7 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     }
 
     if constexpr (!SPLIT) store_dw();
-    const size_t partix = (size_t)(4 * bt + q) * gridDim.y + blockIdx.y;
+    const size_t partix = (size_t)(4 * bt + q) * chains + chain;
     // bias gradient: sum over the four series (the lanes of a quad)
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
@@ -347,6 +398,23 @@ __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 
     }
 }
 
+template <int HT, int KXT, bool CP, bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 2 : 1) lstm_backward_narrow_kernel(NarrowBwdArgs a)
+{
+    using Lds = NarrowBwdLds<HT, KXT, SPLIT>;
+    __shared__ __align__(16) float da_all[2][Lds::HP * 16];
+    __shared__ __align__(16) float part[2][kNW][Lds::NG * 64 * 4];
+    __shared__ __align__(16) f32x4 lc[narrow_bwd_slots(SPLIT)][2][kNT];
+    __shared__ float xhc[2][Lds::CH][Lds::CT * 64];
+    // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
+    // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
+    // quarters of ONE tile, so they land on the same XCD at about the same time and a row is fetched from
+    // HBM once, not four times (measured before: 2.3-2.8 times the algorithmic bytes).
+    const int bt = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7), q = (blockIdx.x >> 3) & 3;
+    if (bt >= a.NB) return;     // the grid is padded to whole groups of 32 (before any barrier)
+    lstm_backward_narrow_body<HT, KXT, CP, SPLIT, kAlone>(a, Lds{da_all, part, lc, xhc}, bt, q, blockIdx.y, gridDim.y, Progress{});
+}
+
 template <int HT, int KXT, bool SPLIT>
 hipError_t run_nbwd(const NarrowBwdArgs &a, int chains, hipStream_t st)
 {
@@ -356,8 +424,7 @@ hipError_t run_nbwd(const NarrowBwdArgs &a, int chains, hipStream_t st)
     return hipGetLastError();
 }
 
-template <bool SPLIT>
-hipError_t launch_narrow_bwd(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st)
+inline NarrowBwdArgs narrow_backward_args(const Plan &pl, int layer, const int32_t *lengths, float *ws)
 {
     const LayerPlan &lp = pl.layer[layer];
     NarrowBwdArgs a{};
@@ -374,6 +441,14 @@ hipError_t launch_narrow_bwd(const Plan &pl, int layer, const int32_t *lengths, 
     a.gdst = ws + lp.gdst; a.dw_partial = ws + lp.dw_partial; a.db_partial = ws + lp.db_partial;
     a.P = pl.P; a.NB = pl.NB; a.d = lp.dil;
     a.pmax = reinterpret_cast<const int32_t *>(ws + pl.pmax);
+    return a;
+}
+
+template <bool SPLIT>
+hipError_t launch_narrow_bwd(const Plan &pl, int layer, const int32_t *lengths, float *ws, hipStream_t st)
+{
+    const LayerPlan &lp = pl.layer[layer];
+    const NarrowBwdArgs a = narrow_backward_args(pl, layer, lengths, ws);
 #define X(HT_, KXT_) if (pl.HT == HT_ && lp.KXT == KXT_) return run_nbwd<HT_, KXT_, SPLIT>(a, lp.chains_bwd, st);
     ESRNN_LSTM_SHAPES(X)
 #undef X

@@ -36,36 +36,24 @@ struct NarrowFwdArgs {
 // (13 scalar instructions a position instead of some 20 scalar and vector ones for addresses): 327 -> 290 us for 512 hourly
 // series, 114 -> 108 us for 501 monthly ones, 27.7 -> 25.7 us for 16 quarterly ones.
 //
-// What a launch's layers leave for each other (lstm_together.h): kAlone, nothing; kFirst, this layer's positions are counted;
-// kLater, it also waits for the layer below.
-enum { kAlone, kFirst, kLater };
-
 // positions per chunk of staged inputs: fewer where a chunk cannot be requested before the layer below has all of it
 constexpr int narrow_fwd_chunk(int mode) { return mode == kLater ? 4 : 8; }
-
-template <int HT, int KXT, bool OUT, int MODE>
-struct NarrowFwdLds {
-    static constexpr int KX = 4 * KXT, HP = 4 * HT, CH = narrow_fwd_chunk(MODE);
-    static constexpr int XG = (KX + 15) / 16, HG = (HP + 15) / 16;      // groups of 16 columns (one register each)
-    // inputs x_p of a chunk of positions [column][series], by chunk parity (+ 64 floats that take the writes of
-    // the threads with no input row, so that staging is the same instruction stream in every thread)
-    float xc[2][CH][XG * 64 + 64];
-    float rc[OUT ? 2 : 1][OUT ? CH : 1][kNT];       // residual input of a thread's (unit, series), likewise
-    float hb[2][HG * 64];                           // h_{p-d} [unit][series], by position parity
-    f32x4 half[2][kNW][64];                         // input half, by position parity
-    float cs[kNW];
-};
 
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ... (of several layers in one launch:
 // its only one).
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
 // block input, writes the block output).
 template <int HT, int KXT, bool CP, bool OUT, int MODE>
-__device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a, NarrowFwdLds<HT, KXT, OUT, MODE> &lds, int bt, int q,
-                                                         int chain, int chains, const Progress &progress)
+__device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a, int bt, int q, int chain, int chains, const Progress &progress)
 {
-    using Lds = NarrowFwdLds<HT, KXT, OUT, MODE>;
-    constexpr int KX = Lds::KX, HP = Lds::HP, CH = Lds::CH, XG = Lds::XG, HG = Lds::HG;
+    constexpr int KX = 4 * KXT, HP = 4 * HT, CH = narrow_fwd_chunk(MODE);
+    constexpr int XG = (KX + 15) / 16, HG = (HP + 15) / 16;   // groups of 16 columns (one register each)
+    // inputs x_p of a chunk of positions [column][series], by chunk parity (+ 64 floats that take the writes of
+    // the threads with no input row, so that staging is the same instruction stream in every thread)
+    __shared__ float xc[2][CH][XG * 64 + 64];
+    __shared__ float rc[OUT ? 2 : 1][OUT ? CH : 1][kNT];      // residual input of a thread's (unit, series), likewise
+    __shared__ float hb[2][HG * 64];            // h_{p-d} [unit][series], by position parity
+    __shared__ f32x4 half[2][kNW][64];          // input half, by position parity
     // positions whose stores may still be under way when the next one is counted: a position of a first layer takes less
     // time than a store
     constexpr int kBehind = MODE == kFirst ? 3 : 1, kStores = OUT ? 4 : 3;
@@ -80,8 +68,8 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     // element of this lane inside the TL(HP) block of one (position, series tile)
     const int lane_off = unit * 16 + 4 * q + j;
     // columns past KX / HP in the last group of 16 are never written: zero once (their weights do not exist)
-    for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += 2 * kNT) (&lds.xc[0][0][0])[e] = 0.0f;
-    for (int e = threadIdx.x; e < 2 * HG * 64; e += 2 * kNT) (&lds.hb[0][0])[e] = 0.0f;
+    for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += 2 * kNT) (&xc[0][0][0])[e] = 0.0f;
+    for (int e = threadIdx.x; e < 2 * HG * 64; e += 2 * kNT) (&hb[0][0])[e] = 0.0f;
 
     if (wave >= kNW) {
         // =========================== input waves ===========================
@@ -122,22 +110,22 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             auto flush_chunk = [&](int c) {
 #pragma unroll
                 for (int ii = 0; ii < CH; ++ii) {
-                    lds.xc[c & 1][ii][x_slot] = MODE == kLater ? below.checked(xs[ii]) : xs[ii];
-                    if constexpr (OUT) lds.rc[c & 1][ii][tid] = rs[ii];
+                    xc[c & 1][ii][x_slot] = MODE == kLater ? below.checked(xs[ii]) : xs[ii];
+                    if constexpr (OUT) rc[c & 1][ii][tid] = rs[ii];
                 }
             };
             // input half of the position in slot ii of the chunk of parity cpar, left for the position of parity par
             auto input_half = [&](int cpar, int ii, int par) {
                 float vx[XG];
 #pragma unroll
-                for (int m = 0; m < XG; ++m) vx[m] = lds.xc[cpar][ii][64 * m + lane];
+                for (int m = 0; m < XG; ++m) vx[m] = xc[cpar][ii][64 * m + lane];
                 f32x4 acc0 = f32x4{bias, bias, bias, bias}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
                 static_for<0, KX / 2>([&](auto ic) {
                     constexpr int k = 2 * decltype(ic)::value;
                     acc0 = mfma4_bcast<k % 16>(vx[k / 16], wx[k], acc0);
                     acc1 = mfma4_bcast<(k + 1) % 16>(vx[k / 16], wx[k + 1], acc1);
                 });
-                lds.half[par][w][lane] = acc0 + acc1;
+                half[par][w][lane] = acc0 + acc1;
             };
             await_chunk(0);
             load_chunk(0);
@@ -194,7 +182,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
         const int n = (Pt - r + a.d - 1) / a.d;
         float creg = 0.0f;
         __syncthreads();
-        for (int e = tid; e < 4 * HP; e += kNT) lds.hb[0][e] = 0.0f;    // start of a chain: zero state
+        for (int e = tid; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;    // start of a chain: zero state
         lds_barrier();
         lds_barrier();
         // What a position leaves in memory is stored while the next one waits for its first operands from LDS, through
@@ -224,11 +212,11 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             // h_{p-d} of the four series: lane (b, s) of register m holds unit 16m + b of series s
             float vh[HG];
 #pragma unroll
-            for (int m = 0; m < HG; ++m) vh[m] = lds.hb[par][64 * m + lane];
+            for (int m = 0; m < HG; ++m) vh[m] = hb[par][64 * m + lane];
             // two accumulators: consecutive instructions never depend on each other (measured: one, three and four are
             // slower)
-            f32x4 acc0 = lds.half[par][w][lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-            const float res = OUT ? lds.rc[OUT ? (i / CH) & 1 : 0][OUT ? i % CH : 0][tid] : 0.0f;
+            f32x4 acc0 = half[par][w][lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float res = OUT ? rc[OUT ? (i / CH) & 1 : 0][OUT ? i % CH : 0][tid] : 0.0f;
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!decltype(firstc)::value) store();
             __builtin_amdgcn_sched_barrier(0);
@@ -247,7 +235,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             const float hn = go * tanh_f(cn);
             creg = cn;
             if constexpr (CP) csq += (valid && p < n_valid) ? cn * cn : 0.0f;
-            lds.hb[par ^ 1][4 * unit + j] = hn;
+            hb[par ^ 1][4 * unit + j] = hn;
             gates = f32x4{gi, gf, gg, go};
             cell = cn;
             hidden = hn;
@@ -270,25 +258,25 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
         }
     }
     if constexpr (CP) {
+        __shared__ float s_cs[kNW];
         const float tot = wave_sum(csq);
-        if (lane == 0) lds.cs[w] = tot;
+        if (lane == 0) s_cs[w] = tot;
         __syncthreads();
         if (threadIdx.x == 0 && (MODE == kAlone || a.cs_partial))
-            a.cs_partial[(4 * bt + q) * chains + chain] = (lds.cs[0] + lds.cs[1]) + (lds.cs[2] + lds.cs[3]);
+            a.cs_partial[(4 * bt + q) * chains + chain] = (s_cs[0] + s_cs[1]) + (s_cs[2] + s_cs[3]);
     }
 }
 
 template <int HT, int KXT, bool CP, bool OUT>
 __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdArgs a)
 {
-    __shared__ NarrowFwdLds<HT, KXT, OUT, kAlone> lds;
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
     // quarters of ONE tile, so they land on the same XCD at about the same time and a row is fetched from
     // HBM once, not four times (measured before: 2.3-2.8 times the algorithmic bytes).
     const int bt = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7), q = (blockIdx.x >> 3) & 3;
     if (bt >= a.NB) return;     // the grid is padded to whole groups of 32 (before any barrier)
-    lstm_forward_narrow_body<HT, KXT, CP, OUT, kAlone>(a, lds, bt, q, blockIdx.y, gridDim.y, Progress{});
+    lstm_forward_narrow_body<HT, KXT, CP, OUT, kAlone>(a, bt, q, blockIdx.y, gridDim.y, Progress{});
 }
 
 template <int HT, int KXT, bool OUT>

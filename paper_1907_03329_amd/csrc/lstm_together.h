@@ -95,7 +95,11 @@ __device__ __forceinline__ Progress progress_of(const Places &t, const Place &p,
     return g;
 }
 
-// What a wave knows of the layer below.
+// What a layer of a launch does for the others: kAlone, nothing; kFirst, its positions are counted; kLater, it also waits for the
+// layer before it; kLast, it waits only.
+enum { kAlone, kFirst, kLater, kLast };
+
+// What a wave knows of the layer before its own (the one below, in the reverse pass the one above).
 struct Below {
     const Progress &g;
     unsigned word, first;               // this lane's word, and the first position of its class
@@ -111,6 +115,19 @@ struct Below {
     __device__ __forceinline__ void wait(int p)
     {
         for (int i = 0; __ballot((int)first + have > p) != ~0ull; ++i) {
+            asm volatile("" ::: "memory");
+            if (i == 1 << 22) { lost = true; break; }
+            __builtin_amdgcn_s_sleep(kPollSleep);
+            look();
+        }
+        asm volatile("" ::: "memory");
+    }
+    // the same where positions fall from the last one, positions - 1, to 0: every class from its own last position
+    __device__ __forceinline__ void wait_falling(int p, int positions)
+    {
+        if (!g.below) return;
+        const int r = (int)first, d = g.d, last = r < positions ? r + (positions - 1 - r) / d * d : -1;
+        for (int i = 0; __ballot(last - have < p) != ~0ull; ++i) {
             asm volatile("" ::: "memory");
             if (i == 1 << 22) { lost = true; break; }
             __builtin_amdgcn_s_sleep(kPollSleep);

@@ -311,6 +311,20 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     const HeadPack hp = head_pack_layout(pl);
     pl.head_fwd_pack = ws.take(hp.fwd_total);
     pl.head_bwd_pack = ws.take(hp.bwd_total);
+    // Layers of the reverse pass in one launch, likewise.  (With three or more blocks a launch of its own sums gradients.)
+    {
+        int n = 0, total = 0;
+        for (; cfg.n_blocks < 3 && n < std::min(L, kTogetherMost); ++n) {
+            const LayerPlan &lp = pl.layer[n];
+            const int here = pl.partial_groups(lp);
+            if (!lp.split_bwd || lp.chains_bwd < lp.dil || lp.dil > 64 || total + here > together_groups) break;
+            if ((size_t)(1 + total + here) * kWordStride > pl.head_bwd_pack - pl.head_fwd_pack + hp.bwd_total) break;
+            total += here;
+        }
+        pl.together_bwd = n > 1 ? n : 0;
+        pl.together_groups_bwd = n > 1 ? total : 0;
+        pl.together_words_bwd = pl.head_fwd_pack;
+    }
     pl.head_dw_stride = (pl.MO * pl.MA + pl.MA * pl.MA) * 256 + 4 * pl.OT + 4 * pl.HT;
     pl.head_dw_stride = (pl.head_dw_stride + 63) & ~63;
     pl.head_dw_partial = ws.take((size_t)pl.head_blocks * pl.head_dw_stride);

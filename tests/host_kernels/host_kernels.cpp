@@ -153,6 +153,7 @@ static int step(const Plan &pl, const std::vector<int> &lens)
         RUN(-1, launch_loss_and_forecasts(pl, n, ws, loss, in_sample, nullptr));
         if (!reverse) continue;
         for (int l = pl.L - 1; l >= 0; --l) RUN(l, launch_lstm_backward(pl, l, n, ws, nullptr));
+        if (pl.together_bwd) RUN(pl.together_bwd, launch_lstm_backward_together(pl, n, ws, nullptr));
         RUN(-1, launch_window_backward(pl, n, ws, true, nullptr));
         RUN(-1, launch_es_backward(pl, y, n, es, ws, grad_es, grad_weights, nullptr));
     }
@@ -194,7 +195,7 @@ int main(int argc, char **argv)
         for (int l = 0; l < pl.L; ++l)
             printf("layer %d dilation %d narrow %d %d chains %d %d\n", l, pl.layer[l].dil, pl.layer[l].narrow_fwd,
                    pl.layer[l].narrow_bwd, pl.layer[l].chains, pl.layer[l].chains_bwd);
-        printf("together %d\n", pl.together_fwd);
+        printf("together %d %d\n", pl.together_fwd, pl.together_bwd);
         return 0;
     }
     float *ws = memory<float>(pl.total_floats);

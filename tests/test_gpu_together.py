@@ -22,6 +22,7 @@ CASES = {
     "few_positions": dict(B=33, T=16, blocks=((1, 2), (9, 3))),
     "nine_positions": dict(B=33, T=20, blocks=((1, 1), (1, 2))),
     "many_layers": dict(B=18, T=40, blocks=((1, 2, 1), (2, 1, 3), (1, 2, 1))),
+    "hidden_50": dict(B=21, hidden=50, I=12, blocks=((1, 3), (2, 6))),
     "hidden_8": dict(B=50, hidden=8, blocks=((1, 2), (3,))),
     "hidden_30": dict(B=100, hidden=30, I=6, blocks=((1, 2), (2, 6))),
     "hidden_64": dict(B=36, hidden=64, I=40, T=90, blocks=((1, 2), (4,))),
@@ -45,6 +46,8 @@ def results(cfg, together, monkeypatch, repeat):
     for _ in range(repeat):
         step.forward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
         step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        if repeat > 1:      # (a reverse pass may be run again)
+            step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
         got = [step.loss, step.forecasts, step.grad_es_params, step.grad_weights]
         got = [t.cpu().numpy().copy() for t in got]
         ahead = torch.clamp(dev["lengths"] - cfg.H, min=cfg.I + max(cfg.m1, 2))

@@ -44,7 +44,7 @@ def without_launches(text):
 
 PARTS = ["lstm_backward_kernels", "lstm_backward_large_kernels", "lstm_forward_kernels", "lstm_forward_residual_kernels",
          "lstm_narrow_kernels", "lstm_narrow_fwd_residual_kernels", "lstm_narrow_bwd_kernels", "lstm_narrow_bwd_split_kernels",
-         "lstm_together_kernels", "lstm_together_wide_kernels", "lstm_together_forecast_kernels", "lstm_kernels", "es_kernels", "head_kernels"]
+         "lstm_together_kernels", "lstm_together_wide_kernels", "lstm_together_forecast_kernels", "lstm_together_reverse_kernels", "lstm_kernels", "es_kernels", "head_kernels"]
 
 
 @pytest.fixture(scope="module")
@@ -168,7 +168,7 @@ def test_waves_of_the_recursions_with_the_largest_rings(program):
 @pytest.mark.parametrize("hidden,window", SHAPES)
 def test_waves_of_layers_in_one_launch_are_ordered(program, hidden, window):
     T = window + 3 + 17
-    for lam, dilations, together in ((0.1, (1, 2, 1), 3), (0, (1, 8), 2)):
+    for lam, dilations, together in ((0.1, (1, 2), "2 2"), (0, (1, 8), "2 0")):
         out = subprocess.run([program, "plan"] + [str(a) for a in (64, T, window, 3, hidden, lam, "all") + dilations],
                              env=dict(os.environ, ESRNN_NARROW_BELOW="20"), capture_output=True, text=True, check=True).stdout
         assert f"together {together}" in out
