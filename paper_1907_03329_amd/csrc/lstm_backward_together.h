@@ -1,8 +1,8 @@
 // Last layers of the reverse pass, the first ones of the network, in one launch, each behind the one above (see
 // lstm_together.h): 4-series layers with eight waves a workgroup.  The kernel template and its launcher.
 //
-// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 103 us and three gaps between launches -> 70 us
-// (the step 188 -> 154 us).  What bounds it is the first layer's chain, 40 us, and per layer the positions between an input
+// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 103 us and three gaps between launches -> 69 us
+// (the step 188 -> 152 us).  What bounds it is the first layer's chain, 40 us, and per layer the positions between an input
 // gradient and its count, a store, a look and a load past the caches, and a chunk of the layer below.
 #pragma once
 
@@ -20,8 +20,8 @@ struct BwdTogetherArgs {
 template <int HT, int KXT, bool CP>
 __global__ void __launch_bounds__(2 * kNT) lstm_backward_together_kernel(BwdTogetherArgs t)
 {
-    using Last = NarrowBwdLds<HT, KXT, true>;
-    using Later = NarrowBwdLds<HT, HT, true>;
+    using Last = NarrowBwdLds<HT, KXT, true, kLast>;
+    using Later = NarrowBwdLds<HT, HT, true, kLater>;
     // (arrays next to each other for both kinds of layers do not fit)
     constexpr size_t bytes = std::max(Last::bytes, Later::bytes);
     __shared__ __align__(16) char lds[bytes];

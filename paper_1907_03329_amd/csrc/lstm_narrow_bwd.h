@@ -57,39 +57,46 @@ struct NarrowBwdArgs {
 // now 440; that of 501 monthly ones 247 us, now 221; that of 16 quarterly ones 43.6 us, now 39.7.)
 // MODE: kLater, layers of one launch (lstm_together.h): this layer waits for the one above it, and its positions are counted; kLast,
 // nobody waits for this one.
-constexpr int narrow_bwd_slots(bool split) { return split ? 8 : 4; }   // two chunks where one wave writes and another reads
+// Positions per chunk of staged operands, and places for them: two chunks where one wave writes and another reads.  Fewer in layers
+// that follow another one in their launch, which request a chunk when the layer above has all of it (16 quarterly series, step 155.5
+// -> 152.3 us, 100 178.5 -> 176.5 us); but not in the launch's last layer, whose chain of neighbouring positions has no time
+// for a round trip every two of them (161.5 us; 20 hourly series 1017 -> 1176 us).
+constexpr int narrow_bwd_chunk(int mode) { return mode == kLater ? 2 : 4; }
+// Chunks of [x ; h] rows held: with two positions a chunk the next one is staged while step C of the one before the present is under way.
+constexpr int narrow_bwd_rows(int mode) { return narrow_bwd_chunk(mode) == 2 ? 4 : 2; }
+constexpr int narrow_bwd_slots(bool split, int mode) { return (split ? 2 : 1) * narrow_bwd_chunk(mode); }
 
-template <int HT, int KXT, bool SPLIT>
+template <int HT, int KXT, bool SPLIT, int MODE>
 struct NarrowBwdLds {                                   // (references: an object each where nothing else has to fit)
     static constexpr int KX = 4 * KXT, HP = 4 * HT, KT4 = KX + HP;
-    static constexpr int CH = 4;                        // positions per chunk of staged operands
+    static constexpr int CH = narrow_bwd_chunk(MODE);
     static constexpr int NG = (KT4 + 63) / 64;          // groups of 64 columns of [x ; h]
     static constexpr int CT = (KT4 + 15) / 16;          // 16-column tiles of dW
     float (&da_all)[2][HP * 16];             // [unit][series][gate]
     float (&part)[2][kNW][NG * 64 * 4];        // partial W^T da of every wave [column][series]
-    f32x4 (&lc)[narrow_bwd_slots(SPLIT)][2][kNT];   // per thread: activated gates; c, c_{p-d}, two gradient sources
-    float (&xhc)[2][CH][CT * 64];                        // [column of x_p ; h_{p-d}][series]
+    f32x4 (&lc)[narrow_bwd_slots(SPLIT, MODE)][2][kNT];   // per thread: activated gates; c, c_{p-d}, two gradient sources
+    float (&xhc)[narrow_bwd_rows(MODE)][CH][CT * 64];                        // [column of x_p ; h_{p-d}][series]
     static constexpr size_t at_part = sizeof(float) * 2 * HP * 16, at_lc = at_part + sizeof(float) * 2 * kNW * NG * 64 * 4,
-                            at_xhc = at_lc + sizeof(f32x4) * narrow_bwd_slots(SPLIT) * 2 * kNT, bytes = at_xhc + sizeof(float) * 2 * CH * CT * 64;
+                            at_xhc = at_lc + sizeof(f32x4) * narrow_bwd_slots(SPLIT, MODE) * 2 * kNT, bytes = at_xhc + sizeof(float) * narrow_bwd_rows(MODE) * CH * CT * 64;
     static __device__ __forceinline__ NarrowBwdLds in(char *at)
     {
         return {reinterpret_cast<float (&)[2][HP * 16]>(*at), reinterpret_cast<float (&)[2][kNW][NG * 64 * 4]>(at[at_part]),
-                reinterpret_cast<f32x4 (&)[narrow_bwd_slots(SPLIT)][2][kNT]>(at[at_lc]), reinterpret_cast<float (&)[2][CH][CT * 64]>(at[at_xhc])};
+                reinterpret_cast<f32x4 (&)[narrow_bwd_slots(SPLIT, MODE)][2][kNT]>(at[at_lc]), reinterpret_cast<float (&)[narrow_bwd_rows(MODE)][CH][CT * 64]>(at[at_xhc])};
     }
 };
 
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ...
 template <int HT, int KXT, bool CP, bool SPLIT, int MODE>
-__device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a, const NarrowBwdLds<HT, KXT, SPLIT> &lds, int bt, int q,
+__device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a, const NarrowBwdLds<HT, KXT, SPLIT, MODE> &lds, int bt, int q,
                                                           int chain, int chains, const Progress &progress)
 {
-    using Lds = NarrowBwdLds<HT, KXT, SPLIT>;
+    using Lds = NarrowBwdLds<HT, KXT, SPLIT, MODE>;
     static_assert(SPLIT || MODE == kAlone, "");
     constexpr bool kWaits = MODE != kAlone, kCounts = MODE == kLater;
     constexpr int KX = Lds::KX, HP = Lds::HP, KT4 = Lds::KT4, CH = Lds::CH, NG = Lds::NG, CT = Lds::CT;
     constexpr int MTW = (HT + kNW - 1) / kNW;    // 16-row tiles of dW per wave (a row tile = 4 units x 4 gates)
     constexpr int XH_PER = (4 * KT4 + kNT - 1) / kNT;
-    constexpr int SLOTS = narrow_bwd_slots(SPLIT);
+    constexpr int SLOTS = narrow_bwd_slots(SPLIT, MODE), ROWS = narrow_bwd_rows(MODE);
 
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -115,7 +122,7 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
 #pragma unroll
         for (int nb = 0; nb < CT; ++nb) dw[t][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 dbacc = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int e = threadIdx.x; e < 2 * CH * CT * 64; e += SPLIT ? 2 * kNT : kNT) (&lds.xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
+    for (int e = threadIdx.x; e < ROWS * CH * CT * 64; e += SPLIT ? 2 * kNT : kNT) (&lds.xhc[0][0][0])[e] = 0.0f;   // columns past KT4 stay zero
 
     auto store_dw = [&]() {
         const size_t partix = (size_t)(4 * bt + q) * chains + chain;
@@ -171,7 +178,7 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
 #pragma unroll
             for (int k = 0; k < XH_PER; ++k) {
                 const int el = tid + k * kNT;
-                if (el < 4 * KT4) lds.xhc[c & 1][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
+                if (el < 4 * KT4) lds.xhc[c & (ROWS - 1)][ii][el] = (el < 4 * KX || has_prev) ? s_xh[ii][k] : 0.0f;
             }
         }
     };
@@ -236,8 +243,8 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
                         }
                         if constexpr (ii == CH - 1) complete_but(integral_constant<int, 2>{});
                         lds_barrier();
-                        if constexpr (ii != 1) count(i - 1);
-                        step_c(i & 1, c & 1, ii);
+                        if constexpr (CH == 2 || ii != 1) count(i - 1);
+                        step_c(i & 1, c & (ROWS - 1), ii);
                         input_gradient(p_last - i * a.d, i & 1);
                     });
                 }
@@ -245,7 +252,7 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
                     complete_but(integral_constant<int, 1>{});
                     lds_barrier();
                     count(i - 1);
-                    step_c(i & 1, c & 1, i - c * CH);
+                    step_c(i & 1, c & (ROWS - 1), i - c * CH);
                     input_gradient(p_last - i * a.d, i & 1);
                 }
                 if constexpr (kCounts) {
@@ -401,10 +408,10 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
 template <int HT, int KXT, bool CP, bool SPLIT>
 __global__ void __launch_bounds__(SPLIT ? 2 * kNT : kNT, (!SPLIT && HT <= 10) ? 2 : 1) lstm_backward_narrow_kernel(NarrowBwdArgs a)
 {
-    using Lds = NarrowBwdLds<HT, KXT, SPLIT>;
+    using Lds = NarrowBwdLds<HT, KXT, SPLIT, kAlone>;
     __shared__ __align__(16) float da_all[2][Lds::HP * 16];
     __shared__ __align__(16) float part[2][kNW][Lds::NG * 64 * 4];
-    __shared__ __align__(16) f32x4 lc[narrow_bwd_slots(SPLIT)][2][kNT];
+    __shared__ __align__(16) f32x4 lc[narrow_bwd_slots(SPLIT, kAlone)][2][kNT];
     __shared__ float xhc[2][Lds::CH][Lds::CT * 64];
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
