@@ -67,7 +67,8 @@ __device__ __forceinline__ Place draw_place(const Places &t, unsigned *slot)
 {
     if (threadIdx.x == 0) *slot = atomicAdd(t.words, 1u);
     __syncthreads();
-    const int ticket = min(__builtin_amdgcn_readfirstlane((int)*slot), t.first[t.layers] - 1);
+    // (unsigned: in a workspace whose words were not cleared a ticket is any number, and every place has to be in the launch)
+    const int ticket = (int)min((unsigned)__builtin_amdgcn_readfirstlane((int)*slot), (unsigned)t.first[t.layers] - 1u);
     int l = 0;
     while (ticket >= t.first[l + 1]) ++l;
     const int groups = t.NB * t.quarters[l], x = ticket - t.first[l], chain = x / groups, y = x - chain * groups;

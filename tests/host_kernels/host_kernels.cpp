@@ -9,6 +9,7 @@
 //        host_kernels plan ... the same: what the plan chose per layer, nothing is run
 //        host_kernels step B T I H hidden m1 m2 lambda_cs lengths dilation [dilation ...]: all kernels of a training step and of
 //        a forecast; lengths: of every 64 series (a wave's bounds are those of its own lane here), separated by commas
+//        host_kernels uncleared ... the same, with what a workspace may hold in the words of the launches of several layers
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -120,7 +121,7 @@ void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *)
 using namespace esrnn;
 
 // every kernel of a training step, with and without a reverse pass to come, and of a forecast
-static int step(const Plan &pl, const std::vector<int> &lens)
+static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
 {
     float *ws = memory<float>(pl.total_floats);
     const float *y = memory<float>((size_t)pl.T * pl.B), *es = memory<float>((size_t)pl.K * pl.B), *weights = memory<float>(pl.n_weights);
@@ -137,6 +138,10 @@ static int step(const Plan &pl, const std::vector<int> &lens)
         exit(1);
     };
 #define RUN(layer, call) (snprintf(g_what, sizeof g_what, "%s, layer %d", #call, layer), run(#call, layer, call))
+    // (the reverse pass given a workspace that no forward pass has run in: its words are whatever is there)
+    auto words = [&](size_t at, int groups) {
+        if (uncleared) std::fill_n(reinterpret_cast<unsigned *>(ws + at), (size_t)(1 + groups) * kWordStride, 0xbf80bf80u);
+    };
     for (int pass = 0; pass < 3; ++pass) {
         const bool reverse = pass == 0, predict = pass == 2;
         const ForwardMode mode{reverse, predict ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr, predict};
@@ -144,6 +149,7 @@ static int step(const Plan &pl, const std::vector<int> &lens)
         RUN(-1, launch_es_forward(pl, y, predict ? shorter : lengths, es, weights, ws, mode, nullptr));
         RUN(-1, launch_window_forward(pl, nullptr, ws, nullptr));
         for (int l = 0; l < pl.L; ++l) RUN(l, launch_lstm_forward(pl, l, n, weights, ws, mode, nullptr));
+        words(pl.together_words, pl.together_groups);
         if (pl.together_fwd) RUN(pl.together_fwd, launch_lstm_forward_together(pl, n, weights, ws, mode, nullptr));
         if (predict) {
             RUN(-1, launch_head_last(pl, n, ws, ahead, nullptr));
@@ -153,6 +159,7 @@ static int step(const Plan &pl, const std::vector<int> &lens)
         RUN(-1, launch_loss_and_forecasts(pl, n, ws, loss, in_sample, nullptr));
         if (!reverse) continue;
         for (int l = pl.L - 1; l >= 0; --l) RUN(l, launch_lstm_backward(pl, l, n, ws, nullptr));
+        words(pl.together_words_bwd, pl.together_groups_bwd);
         if (pl.together_bwd) RUN(pl.together_bwd, launch_lstm_backward_together(pl, n, ws, nullptr));
         RUN(-1, launch_window_backward(pl, n, ws, true, nullptr));
         RUN(-1, launch_es_backward(pl, y, n, es, ws, grad_es, grad_weights, nullptr));
@@ -170,7 +177,8 @@ int main(int argc, char **argv)
     if (argc < 9) return 2;
     esrnn_config c{};
     static Plan pl;
-    if (!strcmp(argv[1], "step")) {
+    const bool uncleared = !strcmp(argv[1], "uncleared");
+    if (uncleared || !strcmp(argv[1], "step")) {
         c.B = atoi(argv[2]); c.T = atoi(argv[3]); c.I = atoi(argv[4]); c.H = atoi(argv[5]); c.hidden = atoi(argv[6]);
         c.m1 = atoi(argv[7]); c.m2 = atoi(argv[8]); c.lambda_cs = (float)atof(argv[9]);
         c.n_seas = (c.m1 > 0) + (c.m2 > 0);
@@ -181,7 +189,7 @@ int main(int argc, char **argv)
         c.n_blocks = argc - 11;
         for (int i = 0; i < c.n_blocks; ++i) { c.layers_in_block[i] = 1; c.dilation[i][0] = atoi(argv[11 + i]); }
         if (c.B % 64 || build_plan(c, pl) != ESRNN_OK) { printf("refused\n"); return 1; }
-        return step(pl, lens);
+        return step(pl, lens, uncleared);
     }
     c.B = atoi(argv[1]); c.T = atoi(argv[2]); c.I = atoi(argv[3]); c.H = atoi(argv[4]); c.hidden = atoi(argv[5]);
     c.lambda_cs = (float)atof(argv[6]);

@@ -116,8 +116,8 @@ def test_kernel_kind_follows_the_measured_limits(program, series, dilation):
         assert chosen(program, hidden, series, dilation) == [(int(groups < 65), int(groups < 160))]
 
 
-def run_step(program, narrow, *args):
-    r = subprocess.run([program, "step"] + [str(a) for a in args], env=dict(os.environ, ESRNN_NARROW_BELOW=str(narrow)),
+def run_step(program, narrow, *args, how="step"):
+    r = subprocess.run([program, how] + [str(a) for a in args], env=dict(os.environ, ESRNN_NARROW_BELOW=str(narrow)),
                        capture_output=True, text=True)
     return r.returncode, r.stdout.strip()
 
@@ -173,3 +173,10 @@ def test_waves_of_layers_in_one_launch_are_ordered(program, hidden, window):
                              env=dict(os.environ, ESRNN_NARROW_BELOW="20"), capture_output=True, text=True, check=True).stdout
         assert f"together {together}" in out
         assert run_step(program, 20, 64, T, window, 3, hidden, min(T, 4), 0, lam, f"{T},{window + 9}", *dilations) == (0, "ok")
+
+
+# what a bf16 pair of packed operands looks like as a ticket: its top bit is set
+@pytest.mark.parametrize("hidden,narrow", [(8, 100000), (40, 100000), (50, 20)])
+def test_places_stay_in_the_launch_whatever_the_ticket(program, hidden, narrow):
+    T = 12 + 3 + 9
+    assert run_step(program, narrow, 64, T, 12 if hidden > 8 else 8, 3, hidden, 4, 0, 0, T, 1, 2, how="uncleared") == (0, "ok")
