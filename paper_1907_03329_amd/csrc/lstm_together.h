@@ -10,7 +10,8 @@
 // Every wait ends.  Workgroups take their places by ticket, in the order in which the layers run: whoever waits, waits for lower
 // tickets only, which have been drawn by workgroups that are running, and the lowest one of those that have not ended waits
 // for nobody.  That does not depend on the order of dispatch, nor on how many workgroups the chip holds.  (A wait that goes on
-// for seconds all the same is given up, and what the wave reads from then on is NaN: the loss shows it.)
+// for seconds all the same, because calls overlap on one workspace, is given up, once for all that this wave reads from then on,
+// which is NaN: loss and forecasts show it, in the reverse pass the gradients.)
 //
 // What it costs: words of several workgroups in one cache line, and all lanes storing the same one, made every position wait
 // (512 hourly series, the first two layers: 4800 us); a line each and one lane that stores: 365 us (as two launches 433 us).
@@ -28,6 +29,7 @@ namespace esrnn {
 namespace {
 
 constexpr int kPollSleep = 4;       // (times 64 clocks)
+constexpr int kMostLooks = 1 << 22; // (seconds)
 
 // Memory operations of this wave are complete, but for the last N.
 template <int N>
@@ -115,9 +117,9 @@ struct Below {
     // until position p is complete in every class of the layer below
     __device__ __forceinline__ void wait(int p)
     {
-        for (int i = 0; __ballot((int)first + have > p) != ~0ull; ++i) {
+        for (int i = lost ? kMostLooks : 0; __ballot((int)first + have > p) != ~0ull; ++i) {
             asm volatile("" ::: "memory");
-            if (i == 1 << 22) { lost = true; break; }
+            if (i == kMostLooks) { lost = true; break; }
             __builtin_amdgcn_s_sleep(kPollSleep);
             look();
         }
@@ -128,9 +130,9 @@ struct Below {
     {
         if (!g.below) return;
         const int r = (int)first, d = g.d, last = r < positions ? r + (positions - 1 - r) / d * d : -1;
-        for (int i = 0; __ballot(last - have < p) != ~0ull; ++i) {
+        for (int i = lost ? kMostLooks : 0; __ballot(last - have < p) != ~0ull; ++i) {
             asm volatile("" ::: "memory");
-            if (i == 1 << 22) { lost = true; break; }
+            if (i == kMostLooks) { lost = true; break; }
             __builtin_amdgcn_s_sleep(kPollSleep);
             look();
         }

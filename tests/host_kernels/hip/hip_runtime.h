@@ -65,7 +65,9 @@ typedef const char *__amdgpu_buffer_rsrc_t;
 #define __builtin_amdgcn_readfirstlane(x) (x)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
 #define __builtin_amdgcn_s_setprio(x) ((void)0)
-#define __builtin_amdgcn_s_sleep(x) ((void)0)
+void host_sleep();                              // host_kernels.cpp: before every look at another workgroup's words
+unsigned long long host_ballot(bool complete);  // whether what is waited for is there
+#define __builtin_amdgcn_s_sleep(x) host_sleep()
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) (v)

@@ -1,7 +1,8 @@
 // Runs the kernels on the CPU, thread by thread, and checks what does not depend on values:
 //   every access lies in the workspace, in an input or output at its size, in the launch's LDS, or in the program itself;
 //   every wave of a workgroup meets the same barriers (or none: it has ended before the first one);
-//   between two barriers no wave touches LDS that another one writes (what is never read may be written by all).
+//   between two barriers no wave touches LDS that another one writes (what is never read may be written by all);
+//   a wave that has given up a wait for another workgroup waits no more.
 // The interval between two barriers that an access falls into, and its address, depend on the wave, the lane and the
 // shape alone, so the threads need not run side by side.
 //
@@ -27,6 +28,8 @@ std::vector<Range> g_memory;        // what the kernels may touch beside LDS, th
 const char *g_stack;
 size_t g_dynamic_lds;
 int g_wave, g_interval;
+bool g_stuck;                       // nothing that a wave waits for ever comes (else it is always there)
+int g_looks;                        // of this thread, while it waited
 char g_what[96];
 struct Use { unsigned short readers, writers; };
 std::unordered_map<size_t, std::vector<Use>> g_lds;      // by address / 2, then by interval
@@ -81,6 +84,11 @@ X(1, uint8_t) X(2, uint16_t) X(4, uint32_t) X(8, uint64_t) X(16, __uint128_t)
 #undef X
 
 void host_barrier() { ++g_interval; }
+unsigned long long host_ballot(bool complete) { return complete || !g_stuck ? ~0ull : 0; }
+void host_sleep()
+{
+    if (++g_looks > HOST_MOST_LOOKS) fail("a wave waits again after it has given up a wait");
+}
 void host_global(const void *at, int bytes)
 {
     if (!known(static_cast<const char *>(at), bytes)) fail("access outside the workspace, the inputs and the outputs");
@@ -97,7 +105,7 @@ void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *)
             for (int t = 0; t < threads; ++t) {
                 threadIdx.x = t;
                 g_wave = t / 64;
-                g_interval = 0;
+                g_interval = g_looks = 0;
                 thread(context);
                 if (barriers > 0 && g_interval > 0 && barriers != g_interval) fail("waves meet different numbers of barriers");
                 barriers = std::max(barriers, g_interval);
@@ -140,6 +148,7 @@ static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
 #define RUN(layer, call) (snprintf(g_what, sizeof g_what, "%s, layer %d", #call, layer), run(#call, layer, call))
     // (the reverse pass given a workspace that no forward pass has run in: its words are whatever is there)
     auto words = [&](size_t at, int groups) {
+        g_stuck = uncleared;
         if (uncleared) std::fill_n(reinterpret_cast<unsigned *>(ws + at), (size_t)(1 + groups) * kWordStride, 0xbf80bf80u);
     };
     for (int pass = 0; pass < 3; ++pass) {
