@@ -268,7 +268,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
                         buf_store<true>(r_c, lane4, mt * 256, cn);
                     }
                     buf_store(r_hid, lane4, mt * 256, hn);
-                    if constexpr (OUT) buf_store(make_rsrc(a.out + pb * HT * 64), lane4, mt * 256, res[j] + hn);
+                    if constexpr (OUT) buf_store(make_rsrc(a.out + pb * HT * 64), lane4, mt * 256, (LATER ? below.checked(res[j]) : res[j]) + hn);
                 });
                 input_part(par ^ 1);
                 store_x(par, xv);

@@ -111,7 +111,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
 #pragma unroll
                 for (int ii = 0; ii < CH; ++ii) {
                     xc[c & 1][ii][x_slot] = MODE == kLater ? below.checked(xs[ii]) : xs[ii];
-                    if constexpr (OUT) rc[c & 1][ii][tid] = rs[ii];
+                    if constexpr (OUT) rc[c & 1][ii][tid] = MODE == kLater ? below.checked(rs[ii]) : rs[ii];
                 }
             };
             // input half of the position in slot ii of the chunk of parity cpar, left for the position of parity par

@@ -2,7 +2,7 @@
 //   every access lies in the workspace, in an input or output at its size, in the launch's LDS, or in the program itself;
 //   every wave of a workgroup meets the same barriers (or none: it has ended before the first one);
 //   between two barriers no wave touches LDS that another one writes (what is never read may be written by all);
-//   a wave that has given up a wait for another workgroup waits no more.
+//   a wave that has given up a wait for another workgroup waits no more, and what it reads from then on is NaN.
 // The interval between two barriers that an access falls into, and its address, depend on the wave, the lane and the
 // shape alone, so the threads need not run side by side.
 //
@@ -11,6 +11,7 @@
 //        host_kernels step B T I H hidden m1 m2 lambda_cs lengths dilation [dilation ...]: all kernels of a training step and of
 //        a forecast; lengths: of every 64 series (a wave's bounds are those of its own lane here), separated by commas
 //        host_kernels uncleared ... the same, with what a workspace may hold in the words of the launches of several layers
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -159,7 +160,13 @@ static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
         RUN(-1, launch_window_forward(pl, nullptr, ws, nullptr));
         for (int l = 0; l < pl.L; ++l) RUN(l, launch_lstm_forward(pl, l, n, weights, ws, mode, nullptr));
         words(pl.together_words, pl.together_groups);
-        if (pl.together_fwd) RUN(pl.together_fwd, launch_lstm_forward_together(pl, n, weights, ws, mode, nullptr));
+        if (pl.together_fwd) {
+            // (sums of the residual input and a state that is not formed here: the input's NaN has to show in them)
+            const size_t out = pl.layer[pl.together_fwd - 1].out, size = (size_t)pl.P * pl.NB * pl.HT * 64;
+            if (out) std::fill_n(ws + out, size, 0.0f);
+            RUN(pl.together_fwd, launch_lstm_forward_together(pl, n, weights, ws, mode, nullptr));
+            if (uncleared && out && std::none_of(ws + out, ws + out + size, [](float v) { return v != v; })) fail("no NaN after a wait was given up");
+        }
         if (predict) {
             RUN(-1, launch_head_last(pl, n, ws, ahead, nullptr));
             continue;

@@ -183,7 +183,7 @@ def test_waves_of_layers_in_one_launch_are_ordered(program, hidden, window):
 
 
 # what a bf16 pair of packed operands looks like as a ticket: its top bit is set; and as a count: it never comes
-@pytest.mark.parametrize("hidden,narrow", [(8, 100000), (8, 20), (40, 100000), (50, 20)])
-def test_places_and_waits_end_whatever_the_words(program, hidden, narrow):
+@pytest.mark.parametrize("hidden,narrow,dilation", [(8, 100000, 2), (8, 20, 8), (40, 100000, 2), (50, 20, 8)])
+def test_places_and_waits_end_whatever_the_words(program, hidden, narrow, dilation):
     T = 12 + 3 + 9
-    assert run_step(program, narrow, 64, T, 12 if hidden > 8 else 8, 3, hidden, 4, 0, 0, T, 1, 2, how="uncleared") == (0, "ok")
+    assert run_step(program, narrow, 64, T, 12 if hidden > 8 else 8, 3, hidden, 4, 0, 0, T, 1, dilation, how="uncleared") == (0, "ok")
