@@ -39,6 +39,14 @@ struct NarrowFwdArgs {
 // positions per chunk of staged inputs: fewer where a chunk cannot be requested before the layer below has all of it
 constexpr int narrow_fwd_chunk(int mode) { return mode == kLater ? 4 : 8; }
 
+// Input half of the pre-activations, by position parity: one object for all kinds of layers of a kernel, each of which has
+// arrays of its own otherwise (hidden 64, three kinds and two of 16 series: 131 200 bytes, past the 128 KB that are safe).
+__device__ __forceinline__ f32x4 (&input_halves())[2][kNW][64]
+{
+    __shared__ f32x4 half[2][kNW][64];
+    return half;
+}
+
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ... (of several layers in one launch:
 // its only one).
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
@@ -53,7 +61,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     __shared__ float xc[2][CH][XG * 64 + 64];
     __shared__ float rc[OUT ? 2 : 1][OUT ? CH : 1][kNT];      // residual input of a thread's (unit, series), likewise
     __shared__ float hb[2][HG * 64];            // h_{p-d} [unit][series], by position parity
-    __shared__ f32x4 half[2][kNW][64];          // input half, by position parity
+    f32x4 (&half)[2][kNW][64] = input_halves();
     // positions whose stores may still be under way when the next one is counted: a position of a first layer takes less
     // time than a store
     constexpr int kBehind = MODE == kFirst ? 3 : 1, kStores = OUT ? 4 : 3;

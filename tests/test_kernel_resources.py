@@ -13,8 +13,8 @@ BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
 @pytest.fixture(scope="module")
-def scratch(tmp_path_factory):
-    """{kernel: bytes of scratch per lane}"""
+def resources(tmp_path_factory):
+    """{kernel: (bytes of scratch per lane, bytes of static LDS)}"""
     if not os.path.exists(binding.LIB_PATH):
         build.build()
     data = open(binding.LIB_PATH, "rb").read()
@@ -31,16 +31,22 @@ def scratch(tmp_path_factory):
             path.write_bytes(data[at + offset:at + offset + size])
             notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
             names = re.findall(r"^\s+\.name:\s+(_Z\S+)\s*$", notes, re.M)
-            sizes = re.findall(r"^\s+\.private_segment_fixed_size:\s+(\d+)\s*$", notes, re.M)
-            assert len(names) == len(sizes)
-            out.update(zip(names, map(int, sizes)))
+            sizes = [[int(v) for v in re.findall(rf"^\s+\.{kind}_segment_fixed_size:\s+(\d+)\s*$", notes, re.M)]
+                     for kind in ("private", "group")]
+            assert len(names) == len(sizes[0]) == len(sizes[1])
+            out.update(zip(names, zip(*sizes)))
         at = data.find(BUNDLE, at + 1)
     return out
 
 
-def test_rows_requested_ahead_stay_in_registers(scratch):
+def test_rows_requested_ahead_stay_in_registers(resources):
     """Smoothing recursions: a wave's requests for observations, chunks of steps ahead, have constant places.  In scratch
     (as when their steps are calls and not inlined) every one of them is waited for: 43 -> 82 us for 240 steps at period 1."""
-    kernels = {k: v for k, v in scratch.items() if re.search(r"es_(forward|forward_long|backward)_kernel", k)}
+    kernels = {k: v for k, (v, _) in resources.items() if re.search(r"es_(forward|forward_long|backward)_kernel", k)}
     assert len(kernels) == 14       # forward: 9 of seasonalities and steps per group, 2 for long periods; reverse: 3
     assert not {k: v for k, v in kernels.items() if v}
+
+
+def test_static_lds_stays_within_128_kb(resources):
+    """An output-stage shape with 135 KB of static LDS has launched without an error and computed wrong outputs."""
+    assert not {k: lds for k, (_, lds) in resources.items() if lds > 128 * 1024}
