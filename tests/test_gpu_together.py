@@ -33,6 +33,8 @@ CASES = {
 
 
 def results(cfg, together, monkeypatch, repeat):
+    """Per pass: loss, forecasts, gradients, out-of-sample forecasts, and all arrays of the training step (its workspace, bit by bit).
+    Every pass finds NaN wherever it has not written yet, and so does whoever reads there too early."""
     if together is None:
         monkeypatch.delenv("ESRNN_TOGETHER", raising=False)
     else:
@@ -42,17 +44,24 @@ def results(cfg, together, monkeypatch, repeat):
     step = binding.TrainingStep(cfg)
     if cfg.n_cat:
         step.set_categories(dev["categories"])
+    view = binding.esrnn_workspace_buffer(step.handle, "O", 0)
+    outputs = slice(view.offset_bytes // 4, view.offset_bytes // 4 + int(np.prod([int(d) for d in view.dims[:3]])))
+    ahead = torch.clamp(dev["lengths"] - cfg.H, min=cfg.I + max(cfg.m1, 2))
     out = []
     for _ in range(repeat):
+        step.workspace.fill_(float("nan"))
         step.forward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
         step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
-        if repeat > 1:      # (a reverse pass may be run again)
-            step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
         got = [step.loss, step.forecasts, step.grad_es_params, step.grad_weights]
         got = [t.cpu().numpy().copy() for t in got]
-        ahead = torch.clamp(dev["lengths"] - cfg.H, min=cfg.I + max(cfg.m1, 2))
+        arrays = step.workspace.view(torch.int32).clone()
+        arrays[outputs] = 0     # (rows past a tile's last position hold whatever was there before)
+        step.grad_weights.fill_(float("nan"))       # (a reverse pass may be run again)
+        step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        assert np.array_equal(step.grad_weights.cpu().numpy(), got[3])
+        step.workspace.fill_(float("nan"))
         got.append(step.predict(dev["y"], ahead, dev["es_params"], dev["weights"]).cpu().numpy().copy())
-        out.append(got)
+        out.append((got, arrays))
     step.close()
     return out
 
@@ -60,8 +69,10 @@ def results(cfg, together, monkeypatch, repeat):
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_layers_of_one_launch_are_those_of_several(case, monkeypatch):
     cfg = synth.CONFIGS["quarterly"].with_(**CASES[case])
-    want, = results(cfg, "0", monkeypatch, 1)
+    (want, want_arrays), = results(cfg, "0", monkeypatch, 1)
     assert all(np.isfinite(w).all() for w in want)
-    for got in results(cfg, None, monkeypatch, 3):
+    for got, arrays in results(cfg, None, monkeypatch, 3):
         for name, g, w in zip(("loss", "forecasts", "grad_es", "grad_weights", "ahead"), got, want):
             assert np.array_equal(g, w), name
+        # (the words of the reverse pass, cleared, lie where the output stage's operands were)
+        assert int(((arrays != want_arrays) & (arrays != 0)).sum()) == 0
