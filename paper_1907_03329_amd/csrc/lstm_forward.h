@@ -147,7 +147,9 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
 
     // positions below this take part in the loss for this lane's series (CP only)
     int n_valid = 0;
-    float csq = 0.0f;
+    // sums of squared cell states, as the waves of the layer's own launch have them: by tile where they have one each
+    constexpr int CS = W < fwd_waves(HT) ? MTW : 1;
+    float csq[CS] = {};
     if constexpr (CP) {
         const int col = bt * kTileN + (lane & 15);
         const int len = col < a.B ? min(max(a.lengths[col], 0), a.T) : 0;
@@ -260,7 +262,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
                     const float cn = gf * creg[j] + gi * gg;
                     const float hn = go * tanh_f(cn);
                     creg[j] = cn;
-                    if constexpr (CP) csq += p < n_valid ? cn * cn : 0.0f;
+                    if constexpr (CP) csq[CS > 1 ? j : 0] += p < n_valid ? cn * cn : 0.0f;
                     TileHome<NPH, SH + j>::store(h_lds[par ^ 1], h_at[j], hn);
                     // gates and cell state are read again only by the reverse pass: streaming stores
                     if constexpr (STASH) {
@@ -294,13 +296,17 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
     else if (kTwo && s >= 8) with_x(integral_constant<int, MTW>{}, integral_constant<int, kTwo ? 1 : 0>{});
     else with_x(integral_constant<int, MTW>{}, integral_constant<int, 0>{});
     if constexpr (CP) {
-        __shared__ float s_cs[W];
-        const float tot = wave_sum(csq);
-        if (lane == 0) s_cs[s] = tot;
+        constexpr int N = fwd_waves(HT);
+        __shared__ float s_cs[W * CS];
+#pragma unroll
+        for (int j = 0; j < CS; ++j) {
+            const float tot = wave_sum(csq[j]);
+            if (lane == 0) s_cs[s + W * j] = tot;
+        }
         __syncthreads();
         if (threadIdx.x == 0 && (!LATER || a.cs_partial)) {
             float t = 0.0f;
-            for (int i = 0; i < W; ++i) t += s_cs[i];
+            for (int i = 0; i < N; ++i) t += s_cs[i];
             a.cs_partial[bt * chains + chain] = t;
         }
     }

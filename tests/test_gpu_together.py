@@ -28,6 +28,7 @@ CASES = {
     "hidden_64": dict(B=36, hidden=64, I=40, T=90, blocks=((1, 2), (4,))),
     "hidden_64_16_series": dict(B=300, hidden=64, I=40, T=90, blocks=((1, 4), (4,))),
     "penalty": dict(B=70, hidden=50, I=12, blocks=((1, 3), (2, 6)), lambda_c=0.3, n_cat=6),
+    "penalty_16_series_layer_starts_a_block": dict(B=400, hidden=50, I=12, blocks=((1,), (5,)), lambda_c=0.3, n_cat=6),
     "penalty_16_series": dict(B=501, hidden=50, I=12, blocks=((1, 3), (2, 6)), lambda_c=0.3, n_cat=6),
 }
 
