@@ -326,8 +326,9 @@ esrnn_status esrnn_workspace_buffer(const esrnn_handle *h, int32_t which, int32_
  * host) and adds their elapsed times to per-stage totals; call it once after
  * each pair.  esrnn_profile_read copies the totals in milliseconds and the
  * number of collected launches into host arrays of esrnn_profile_stage_count
- * entries.  Enabling resets the totals.  While enabled, every layer has a launch of its own (small batches run several
- * in one otherwise).
+ * entries.  Enabling resets the totals.  Small batches run several layers in
+ * one launch, which is a stage of its own (lstm_forward_l0_to_l3); the stages
+ * of those layers then have no launches.
  */
 esrnn_status esrnn_profile_enable(esrnn_handle *h, int32_t on);
 esrnn_status esrnn_profile_stage_count(const esrnn_handle *h, int32_t *n);

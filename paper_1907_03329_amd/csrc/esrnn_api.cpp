@@ -27,6 +27,7 @@ struct esrnn_handle {
     // stage indices
     int st_es_fwd, st_win_fwd, st_lstm_fwd[kMaxLayers], st_head, st_fc;
     int st_lstm_bwd[kMaxLayers], st_win_bwd, st_es_bwd;
+    int st_together_fwd, st_together_bwd;      // (where the plan has such launches)
     const int32_t *categories;   // device array of the caller, or null
     bool forward_only;           // esrnn_forward skips the reverse pass of the output stage; esrnn_backward is refused
 };
@@ -58,13 +59,13 @@ hipError_t run_stage(esrnn_handle *h, int idx, hipStream_t st, F &&launch)
     return e;
 }
 
-// All layers of the forward pass.  (Stages are timed one by one, so with profiling on every layer has a launch of its own.)
+// All layers of the forward pass.
 hipError_t lstm_layers(esrnn_handle *h, const int32_t *lengths, const float *weights, float *ws, const ForwardMode &mode, hipStream_t st)
 {
     const Plan &pl = h->plan;
     int l = 0;
-    if (pl.together_fwd && !h->profiling) {
-        const hipError_t e = launch_lstm_forward_together(pl, lengths, weights, ws, mode, st);
+    if (pl.together_fwd) {
+        const hipError_t e = run_stage(h, h->st_together_fwd, st, [&] { return launch_lstm_forward_together(pl, lengths, weights, ws, mode, st); });
         if (e != hipSuccess) return e;
         l = pl.together_fwd;
     }
@@ -103,10 +104,12 @@ esrnn_status esrnn_create(const esrnn_config *cfg, esrnn_handle **out)
     const Plan &pl = h->plan;
     h->st_es_fwd = add_stage(h, "es_forward", 0);
     h->st_win_fwd = add_stage(h, "window_forward", 0);
+    if (pl.together_fwd) h->st_together_fwd = add_stage(h, "lstm_forward_l0_to_l%d", pl.together_fwd - 1);
     for (int l = 0; l < pl.L; ++l) h->st_lstm_fwd[l] = add_stage(h, "lstm_forward_l%d", l);
     h->st_head = add_stage(h, "head_forward_backward", 0);
     h->st_fc = add_stage(h, "forecasts", 0);
     for (int l = pl.L - 1; l >= 0; --l) h->st_lstm_bwd[l] = add_stage(h, "lstm_backward_l%d", l);
+    if (pl.together_bwd) h->st_together_bwd = add_stage(h, "lstm_backward_l0_to_l%d", pl.together_bwd - 1);
     h->st_win_bwd = add_stage(h, "window_backward", 0);
     h->st_es_bwd = add_stage(h, "es_backward", 0);
     *out = h;
@@ -215,10 +218,9 @@ esrnn_status esrnn_backward(esrnn_handle *h, const float *y, const int32_t *leng
     const Plan &pl = h->plan;
     float *ws = static_cast<float *>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int together = h->profiling ? 0 : pl.together_bwd;
-    for (int l = pl.L - 1; l >= together; --l)
+    for (int l = pl.L - 1; l >= pl.together_bwd; --l)
         ESRNN_TRY(run_stage(h, h->st_lstm_bwd[l], st, [&] { return launch_lstm_backward(pl, l, lengths, ws, st); }));
-    if (together) ESRNN_TRY(launch_lstm_backward_together(pl, lengths, ws, st));
+    if (pl.together_bwd) ESRNN_TRY(run_stage(h, h->st_together_bwd, st, [&] { return launch_lstm_backward_together(pl, lengths, ws, st); }));
     ESRNN_TRY(run_stage(h, h->st_win_bwd, st, [&] { return launch_window_backward(pl, lengths, ws, true, st); }));
     ESRNN_TRY(run_stage(h, h->st_es_bwd, st,
                         [&] { return launch_es_backward(pl, y, lengths, es_params, ws, grad_es_params, grad_weights, st); }));

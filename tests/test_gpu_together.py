@@ -77,3 +77,23 @@ def test_layers_of_one_launch_are_those_of_several(case, monkeypatch):
             assert np.array_equal(g, w), name
         # (the words of the reverse pass, cleared, lie where the output stage's operands were)
         assert int(((arrays != want_arrays) & (arrays != 0)).sum()) == 0
+
+
+def test_profiling_times_the_launches_of_the_step():
+    """The stages that are timed are those that a step runs, and timing them changes no result."""
+    cfg = synth.CONFIGS["quarterly"].with_(B=16)
+    inp = synth.make_inputs(cfg, seed=3, ragged=True)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in inp.items()}
+    step = binding.TrainingStep(cfg)
+    results = []
+    for on in (False, True):
+        binding.esrnn_profile_enable(step.handle, on)
+        step.forward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        step.backward(dev["y"], dev["lengths"], dev["es_params"], dev["weights"])
+        results.append([t.cpu().numpy().copy() for t in (step.loss, step.forecasts, step.grad_es_params, step.grad_weights)])
+    binding.esrnn_profile_collect(step.handle)
+    stages = {name: count for name, _, count in binding.esrnn_profile_read(step.handle) if count}
+    assert stages == dict.fromkeys(["es_forward", "window_forward", "lstm_forward_l0_to_l3", "head_forward_backward", "forecasts",
+                                    "lstm_backward_l0_to_l3", "window_backward", "es_backward"], 1)
+    assert all(np.array_equal(a, b) for a, b in zip(*results))
+    step.close()
