@@ -243,7 +243,7 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
                         }
                         if constexpr (ii == CH - 1) complete_but(integral_constant<int, 2>{});
                         lds_barrier();
-                        if constexpr (CH == 2 || ii != 1) count(i - 1);
+                        count(i - 1);
                         step_c(i & 1, c & (ROWS - 1), ii);
                         input_gradient(p_last - i * a.d, i & 1);
                     });

@@ -25,17 +25,6 @@ struct NarrowFwdArgs {
     int B, T, I, H;
 };
 
-// Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the next
-// position's pre-activations (with the bias), which does not depend on it: the chain then has 4 HT instead of
-// 4 (KXT + HT) matrix instructions a position, and no request of its own.  Both kinds meet the same barriers.
-// 512 hourly series, first layer (24 + 40 columns, 649 positions): 348 -> 331 us (333 -> 317 us for 333); 501 monthly ones
-// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  (Three
-// accumulators, which need no wait states between the matrix instructions: 340 us.)  What bounds it is the issue of one
-// wave and what the input wave of its SIMD takes from it: without the input half 264 of 327 us.  Gates in the rows of sixteen
-// lanes, which four instructions transpose (26 between the lanes of a quad), and stores through pointers that move on
-// (13 scalar instructions a position instead of some 20 scalar and vector ones for addresses): 327 -> 290 us for 512 hourly
-// series, 114 -> 108 us for 501 monthly ones, 27.7 -> 25.7 us for 16 quarterly ones.
-//
 // positions per chunk of staged inputs: fewer where a chunk cannot be requested before the layer below has all of it
 constexpr int narrow_fwd_chunk(int mode) { return mode == kLater ? 4 : 8; }
 
@@ -47,6 +36,17 @@ __device__ __forceinline__ f32x4 (&input_halves())[2][kNW][64]
     return half;
 }
 
+// Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the next
+// position's pre-activations (with the bias), which does not depend on it: the chain then has 4 HT instead of
+// 4 (KXT + HT) matrix instructions a position, and no request of its own.  Both kinds meet the same barriers.
+// 512 hourly series, first layer (24 + 40 columns, 649 positions): 348 -> 331 us (333 -> 317 us for 333); 501 monthly ones
+// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  (Three
+// accumulators, which need no wait states between the matrix instructions: 340 us.)  What bounds it is the issue of one
+// wave and what the input wave of its SIMD takes from it: without the input half 264 of 327 us.  Gates in the rows of sixteen
+// lanes, which four instructions transpose (26 between the lanes of a quad), and stores through pointers that move on
+// (13 scalar instructions a position instead of some 20 scalar and vector ones for addresses): 327 -> 290 us for 512 hourly
+// series, 114 -> 108 us for 501 monthly ones, 27.7 -> 25.7 us for 16 quarterly ones.
+//
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ... (of several layers in one launch:
 // its only one).
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the

@@ -255,13 +255,14 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     // Steps in us, launches of one layer / this rule / up to 512 workgroups: quarterly 40 series 218 / 161 / 162, 100 223 / 177 /
     // 189, 300 244 / 217 / 220, 700 281 / 282 / 296, 1024 313 / 315 / 326; yearly 100 124 / 112 / 114, 500 139 / 137 / 145;
     // monthly 40 649 / 475 / 443, 100 646 / 534 / 540, 250 713 / 617 / 622, 700 1065 / 1063 / 1099; hourly 20 1355 / 1017 / 1017,
-    // 100 1368 / 1138 / 1144, 250 1524 / 1474 / 1591.
+    // 100 1368 / 1138 / 1144, 250 1524 / 1474 / 1591.  (Up to 512 is faster for 40 monthly series alone, whose fourth forward layer
+    // then joins: 264 workgroups.  One limit for both directions; they were not measured apart.)
     {
         int n = 0, total = 0;
         for (; n < std::min(L, kTogetherMost); ++n) {
             const LayerPlan &lp = pl.layer[n];
             const int here = pl.forward_groups(lp);
-            if (lp.chains < std::min(lp.dil, pl.P) || total + here > together_groups) break;
+            if (lp.chains < lp.dil || total + here > together_groups) break;
             if (n == 0 && !lp.narrow_fwd) break;
             if (n > 0 && (!pl.layer[n - 1].narrow_fwd || pl.layer[n - 1].dil * (lp.narrow_fwd ? 1 : 4) > 64)) break;
             // (in front of the words lie the masks of a forecast)
