@@ -15,6 +15,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -30,9 +31,8 @@ PEAK_HBM_GBS = 8000.0           # MI355X HBM3E peak
 # (FETCH x 2.0, WRITE x 1.0): profiles/hbm_traffic_<workload>_B<batch>.txt.  Valid for that workload and batch only.
 MEASURED_TRAFFIC_BYTES = {
     ('tiny_quarterly', 16): {
-        "es_forward": 2.324e+06, "window_forward": 1.53e+05, "lstm_forward_l0": 1.037e+06, "lstm_forward_l1": 1.244e+06,
-        "lstm_forward_l2": 1.24e+06, "lstm_forward_l3": 1.554e+06, "head_forward_backward": 1.05e+06, "forecasts": 1.559e+05,
-        "lstm_backward_l3": 3.175e+06, "lstm_backward_l2": 2.355e+06, "lstm_backward_l1": 2.101e+06, "lstm_backward_l0": 1.338e+06,
+        "es_forward": 2.348e+06, "window_forward": 1.53e+05, "lstm_forward_l0_to_l3": 7.38e+06,
+        "head_forward_backward": 1.052e+06, "forecasts": 1.58e+05, "lstm_backward_l0_to_l3": 1.194e+07,
         "window_backward": 5.584e+06, "es_backward": 2.709e+06,
     },
     ('quarterly', 4096): {
@@ -54,10 +54,10 @@ MEASURED_TRAFFIC_BYTES = {
         "window_backward": 8.38e+07, "es_backward": 6.392e+06,
     },
     ('hourly', 512): {
-        "es_forward": 1.212e+07, "window_forward": 9.854e+07, "lstm_forward_l0": 4.218e+08, "lstm_forward_l1": 3.731e+08, "lstm_forward_l2": 3.732e+08,
-        "lstm_forward_l3": 4.801e+08, "head_forward_backward": 3.033e+08, "forecasts": 1.318e+08, "lstm_backward_l3": 4.798e+08,
-        "lstm_backward_l2": 4.916e+08, "lstm_backward_l1": 5.394e+08, "lstm_backward_l0": 4.417e+08, "window_backward": 2.425e+08,
-        "es_backward": 1.327e+07,
+        "es_forward": 1.214e+07, "window_forward": 9.854e+07, "lstm_forward_l0_to_l1": 9.004e+08, "lstm_forward_l2": 3.731e+08,
+        "lstm_forward_l3": 4.8e+08, "head_forward_backward": 3.034e+08, "forecasts": 1.318e+08, "lstm_backward_l3": 4.798e+08,
+        "lstm_backward_l2": 4.916e+08, "lstm_backward_l1": 5.394e+08, "lstm_backward_l0": 4.417e+08,
+        "window_backward": 2.424e+08, "es_backward": 1.327e+07,
     },
 }
 
@@ -86,6 +86,12 @@ def weight_partials(cfg):
 REDUCE_SPLITS = 16      # partial sums that the first stage of the weight-gradient reduction leaves
 
 
+def stage_layers(name):
+    """Layers of the LSTM stage `name`: one, or of a launch of several (lstm_forward_l0_to_l3) all of them."""
+    numbers = [int(n) for n in re.findall(r"_l(\d+)", name)]
+    return range(numbers[0], numbers[-1] + 1)
+
+
 def stage_model(cfg, name, network=True):
     """Algorithmic work of one launch of a stage: (bound, amount, unit).
 
@@ -99,9 +105,7 @@ def stage_model(cfg, name, network=True):
     P = T - I - H + 1
     n_seas = cfg.n_seas
     if name.startswith("lstm_forward_l") or name.startswith("lstm_backward_l"):
-        layer = int(name.rsplit("l", 1)[1])
-        k = (I + cfg.n_cat if layer == 0 else h) + h
-        per = 2 * k * 4 * h
+        per = sum(2 * ((I + cfg.n_cat if layer == 0 else h) + h) * 4 * h for layer in stage_layers(name))
         if name.startswith("lstm_backward"):
             per *= 2                      # transposed contraction + weight gradient
         return "mfma", float(per) * B * P, "flop"
@@ -127,23 +131,22 @@ def stage_model(cfg, name, network=True):
 
 
 def lstm_stash_bytes(cfg, name):
-    """Algorithmic HBM bytes of one LSTM layer launch (fp32): the forward pass reads its input and writes the
+    """Algorithmic HBM bytes of one LSTM launch (fp32), a layer or several: the forward pass reads its input and writes the
     activation stash (four activated gates, cell state, hidden state per unit); the reverse pass reads the
     stash, the previous cell and hidden state, the input and the arriving gradient, and writes the input
     gradient.  The last layer of a block >= 1 also reads the block input and writes the block output."""
     B, I, H, h = cfg.B, cfg.I, cfg.H, cfg.hidden
     P = cfg.T - I - H + 1
-    layer = int(name.rsplit("l", 1)[1])
-    k_in = I + cfg.n_cat if layer == 0 else h
-    ends, n = [], 0
+    ends, n, per = [], 0, 0
     for blk in cfg.blocks:
         n += len(blk)
         ends.append(n - 1)
-    residual = layer in ends[1:]
-    if name.startswith("lstm_forward"):
-        per = k_in + 6 * h + (2 * h if residual else 0)
-    else:
-        per = 6 * h + 2 * h + k_in + h + k_in
+    for layer in stage_layers(name):
+        k_in = I + cfg.n_cat if layer == 0 else h
+        if name.startswith("lstm_forward"):
+            per += k_in + 6 * h + (2 * h if layer in ends[1:] else 0)
+        else:
+            per += 6 * h + 2 * h + k_in + h + k_in
     return 4.0 * per * B * P
 
 
