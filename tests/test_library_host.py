@@ -10,6 +10,7 @@ import pytest
 from oracle import oracle
 from paper_1907_03329_amd import binding, synth
 from paper_1907_03329_amd.synth import CONFIGS, Config
+from tests.test_gpu_together import CASES as SHARED_LAUNCHES, shared
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -157,3 +158,16 @@ def test_workspaces_at_the_size_of_the_built_in_one(lib, monkeypatch, B, T, I, H
     h = binding.esrnn_create(bad(B=B, T=T, I=I, H=H, hidden=hidden, blocks=blocks))
     assert binding.esrnn_workspace_bytes(h) <= 32 << 20
     binding.esrnn_destroy(h)
+
+
+@pytest.mark.parametrize("case", sorted(SHARED_LAUNCHES))
+def test_layers_share_launches_where_the_rule_says(lib, case, monkeypatch):
+    """What the GPU test of these cases compares is really a launch of several layers."""
+    launches, fields = SHARED_LAUNCHES[case]
+    cfg = CONFIGS["quarterly"].with_(**fields)
+    for variable, want in ((None, launches), ("0", (0, 0))):
+        if variable:
+            monkeypatch.setenv("ESRNN_TOGETHER", variable)
+        h = binding.esrnn_create(cfg)
+        assert shared(h) == want
+        binding.esrnn_destroy(h)
