@@ -40,20 +40,29 @@ void host_launch(dim3 grid, int threads, size_t dynamic_lds, F &&f)
 
 // ---- device builtins: addresses and barriers are those of the device, arithmetic across lanes is not formed ----
 void host_barrier();                            // host_kernels.cpp
-void host_global(const void *at, int bytes);    // stops the program if it lies outside the workspace
+struct host_rsrc { const char *base; unsigned bytes; };
+void host_read(host_rsrc r, unsigned at, int shared, void *to, int bytes);      // host_kernels.cpp, likewise
+void host_write(host_rsrc r, unsigned at, int shared, const void *from, int bytes);
+void host_wait(int but);                        // until this thread's stores are complete but for the last so many
 template <class V>
-inline V &host_buffer(const char *r, unsigned bytes)
+inline V host_load(host_rsrc r, unsigned at, int aux)
 {
-    host_global(r + bytes, sizeof(V));
-    return *reinterpret_cast<V *>(const_cast<char *>(r + bytes));
+    V v;
+    host_read(r, at, aux & 16, &v, sizeof(V));
+    return v;
+}
+template <class V>
+inline void host_store(const V &v, host_rsrc r, unsigned at, int aux)
+{
+    host_write(r, at, aux & 16, &v, sizeof(V));
 }
 typedef unsigned host_b128 __attribute__((ext_vector_type(4)));
-typedef const char *__amdgpu_buffer_rsrc_t;
-#define __builtin_amdgcn_make_buffer_rsrc(base, stride, range, flags) static_cast<const char *>(base)
-#define __builtin_amdgcn_raw_buffer_load_b32(r, lane, tile, aux) host_buffer<unsigned>(r, (lane) + (tile))
-#define __builtin_amdgcn_raw_buffer_load_b128(r, lane, tile, aux) host_buffer<host_b128>(r, (lane) + (tile))
-#define __builtin_amdgcn_raw_buffer_store_b32(v, r, lane, tile, aux) (host_buffer<unsigned>(r, (lane) + (tile)) = (v))
-#define __builtin_amdgcn_raw_buffer_store_b128(v, r, lane, tile, aux) (host_buffer<host_b128>(r, (lane) + (tile)) = (v))
+typedef host_rsrc __amdgpu_buffer_rsrc_t;
+#define __builtin_amdgcn_make_buffer_rsrc(base, stride, range, flags) host_rsrc{static_cast<const char *>(base), (unsigned)(range)}
+#define __builtin_amdgcn_raw_buffer_load_b32(r, lane, tile, aux) host_load<unsigned>(r, (lane) + (tile), aux)
+#define __builtin_amdgcn_raw_buffer_load_b128(r, lane, tile, aux) host_load<host_b128>(r, (lane) + (tile), aux)
+#define __builtin_amdgcn_raw_buffer_store_b32(v, r, lane, tile, aux) host_store<unsigned>(v, r, (lane) + (tile), aux)
+#define __builtin_amdgcn_raw_buffer_store_b128(v, r, lane, tile, aux) host_store<host_b128>(v, r, (lane) + (tile), aux)
 #define __syncthreads() host_barrier()
 #define __ballot(x) ((void)(x), ~0ull)
 #define __shfl_xor(v, off, width) (v)
@@ -66,9 +75,9 @@ typedef const char *__amdgpu_buffer_rsrc_t;
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
 #define __builtin_amdgcn_s_setprio(x) ((void)0)
 void host_sleep();                              // host_kernels.cpp: before every look at another workgroup's words
-unsigned long long host_ballot(bool complete);  // whether what is waited for is there
+unsigned long long host_ballot(bool complete);  // until what is waited for is there
 #define __builtin_amdgcn_s_sleep(x) host_sleep()
-#define __builtin_amdgcn_s_waitcnt(x) ((void)0)
+#define __builtin_amdgcn_s_waitcnt(x) host_wait(((x) & 15) | ((x) >> 14 & 3) << 4)
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
 #define __builtin_amdgcn_update_dpp(old, v, control, rows, banks, bound) (v)
 struct host_pair { unsigned v[2]; unsigned operator[](int i) const { return v[i]; } };

@@ -2,6 +2,8 @@
 //   every access lies in the workspace, in an input or output at its size, in the launch's LDS, or in the program itself;
 //   every wave of a workgroup meets the same barriers (or none: it has ended before the first one);
 //   between two barriers no wave touches LDS that another one writes (what is never read may be written by all);
+//   what a workgroup reads of another one of its launch was stored past the caches, and complete when the position was counted that
+//   the reading wave has waited for, however late every count shows;
 //   a wave that has given up a wait for another workgroup waits no more, and what it reads from then on is NaN.
 // The interval between two barriers that an access falls into, and its address, depend on the wave, the lane and the
 // shape alone, so the threads need not run side by side.
@@ -15,6 +17,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
+#include <tuple>
 #include <unordered_map>
 #include <vector>
 
@@ -29,8 +33,33 @@ std::vector<Range> g_memory;        // what the kernels may touch beside LDS, th
 const char *g_stack;
 size_t g_dynamic_lds;
 int g_wave, g_interval;
-bool g_stuck;                       // nothing that a wave waits for ever comes (else it is always there)
+bool g_stuck;                       // nothing that a wave waits for ever comes
 int g_looks;                        // of this thread, while it waited
+
+// ---- launches whose workgroups follow each other: they run one after the other here, in the order of their tickets ----
+struct Launch {
+    bool on = false;
+    const char *ws = nullptr, *words = nullptr, *words_end = nullptr;
+    std::vector<int> writer;                    // per float of the workspace: the workgroup that wrote it, and
+    std::vector<int> count;                     // the first count of it that covers that store (kNever: none does)
+    std::unordered_map<int, const char *> word; // by workgroup
+    std::unordered_map<const char *, std::vector<int>> counts;     // by word: all that it has held, rising
+} g_launch;
+constexpr int kNever = 1 << 30;
+struct Stored { int at, seq, interval; bool shared; };
+struct Counted { int interval, value; };
+// of the workgroup that runs
+int g_group;
+std::vector<Counted> g_counted;
+std::unordered_map<int, int> g_complete;        // float of the workspace: interval in which its store is known to be complete
+struct Need { int wave, wait, value; const char *word; };
+std::vector<Need> g_needs;                      // what its waves have read: (wave, wait before it) has to have seen value in word
+std::map<std::tuple<int, int, const char *>, int> g_seen;          // what they saw
+// of the thread that runs
+std::vector<Stored> g_stored;
+int g_issued, g_waits, g_view;                  // stores so far; waits for another workgroup that have ended; counts seen of its word
+const char *g_word;                             // that it looks at
+bool g_fresh;                                   // the next look shows one count more
 char g_what[96];
 struct Use { unsigned short readers, writers; };
 std::unordered_map<size_t, std::vector<Use>> g_lds;      // by address / 2, then by interval
@@ -60,6 +89,22 @@ bool known(const char *p, int bytes)
 }
 }  // namespace
 
+// an access to the workspace in a launch whose workgroups follow each other
+static void follow(const char *p, int bytes, bool write, bool shared)
+{
+    Launch &l = g_launch;
+    if (!l.on || p < l.ws || p >= l.ws + 4 * l.writer.size() || (p >= l.words && p < l.words_end)) return;
+    for (int at = (int)((p - l.ws) / 4), end = at + std::max(bytes / 4, 1); at < end; ++at) {
+        if (write) {
+            g_stored.push_back({at, g_issued, kNever, shared});
+        } else if (l.writer[at] >= 0 && l.writer[at] != g_group) {
+            if (!shared) fail("another workgroup's data read through the caches");
+            if (l.count[at] == kNever) fail("another workgroup's data read that no count covers");
+            g_needs.push_back({g_wave, g_waits, l.count[at], l.word[l.writer[at]]});
+        }
+    }
+}
+
 __attribute__((section("lds"), aligned(256))) float host_dynamic_lds[40960];     // the most a workgroup has
 extern "C" char __start_lds, __stop_lds, __executable_start, end;
 static void touch(const void *at, int bytes, bool write)
@@ -68,6 +113,7 @@ static void touch(const void *at, int bytes, bool write)
     if (p < &__start_lds || p >= &__stop_lds) {
         const bool own = (p >= &__executable_start && p < &end) || (p >= static_cast<char *>(__builtin_frame_address(0)) && p < g_stack);
         if (!own && !known(p, bytes)) fail("access outside the workspace, the inputs and the outputs");
+        if (!own) follow(p, bytes, write, false);
         return;
     }
     const char *dynamic = reinterpret_cast<const char *>(host_dynamic_lds);
@@ -85,14 +131,94 @@ X(1, uint8_t) X(2, uint16_t) X(4, uint32_t) X(8, uint64_t) X(16, __uint128_t)
 #undef X
 
 void host_barrier() { ++g_interval; }
-unsigned long long host_ballot(bool complete) { return complete || !g_stuck ? ~0ull : 0; }
+
+unsigned long long host_ballot(bool complete)
+{
+    if (!complete) return 0;
+    if (g_launch.on) {
+        g_seen[{g_wave, g_waits + 1, g_word}] = g_view ? g_launch.counts[g_word][g_view - 1] : 0;
+        ++g_waits;
+    }
+    return ~0ull;
+}
 void host_sleep()
 {
-    if (++g_looks > HOST_MOST_LOOKS) fail("a wave waits again after it has given up a wait");
+    if (++g_looks > HOST_MOST_LOOKS) fail(g_stuck ? "a wave waits again after it has given up a wait" : "a wave waits for what never comes");
+    g_fresh = true;
 }
-void host_global(const void *at, int bytes)
+void host_wait(int but)
 {
-    if (!known(static_cast<const char *>(at), bytes)) fail("access outside the workspace, the inputs and the outputs");
+    for (Stored &st : g_stored)
+        if (st.interval == kNever && st.seq < g_issued - but) st.interval = g_interval;
+}
+void host_read(host_rsrc r, unsigned at, int shared, void *to, int bytes)
+{
+    const char *p = r.base + at;
+    if (at + bytes > r.bytes) fail("read past the end of a buffer");
+    if (!known(p, bytes)) fail("access outside the workspace, the inputs and the outputs");
+    memcpy(to, p, bytes);
+    if (g_launch.on && p >= g_launch.words && p < g_launch.words_end) {
+        const std::vector<int> &counts = g_launch.counts[g_word = p];
+        if (g_fresh && g_view < (int)counts.size()) ++g_view;
+        g_fresh = false;
+        const int count = g_view ? counts[g_view - 1] : 0;
+        memcpy(to, &count, bytes);
+    } else {
+        follow(p, bytes, false, shared);
+    }
+}
+void host_write(host_rsrc r, unsigned at, int shared, const void *from, int bytes)
+{
+    char *p = const_cast<char *>(r.base) + at;
+    if (at + bytes <= r.bytes) {        // (else it is dropped)
+        if (!known(p, bytes)) fail("access outside the workspace, the inputs and the outputs");
+        memcpy(p, from, bytes);
+        if (g_launch.on && p >= g_launch.words && p < g_launch.words_end) {
+            int value;
+            memcpy(&value, from, 4);
+            g_launch.word[g_group] = p;
+            std::vector<int> &counts = g_launch.counts[p];
+            if (!shared || value < (counts.empty() ? 0 : counts.back())) fail("a count that falls, or is kept in a cache");
+            if (counts.empty() || value > counts.back()) counts.push_back(value);
+            g_counted.push_back({g_interval, value});
+        } else {
+            follow(p, bytes, true, shared);
+        }
+    }
+    ++g_issued;
+}
+
+// a thread of the workgroup has ended
+static void thread_done()
+{
+    for (const Stored &st : g_stored) {
+        g_launch.writer[st.at] = g_group;
+        int &complete = g_complete[st.at];
+        complete = std::max(complete, st.shared ? st.interval : kNever);
+    }
+    g_stored.clear();
+    g_issued = g_waits = g_view = 0;
+    g_word = nullptr;
+    g_fresh = false;
+}
+// all threads have
+static void group_done()
+{
+    for (const auto &[at, complete] : g_complete) {
+        g_launch.count[at] = kNever;
+        for (const Counted &c : g_counted)      // (a barrier lies between the wait and the count)
+            if (c.interval > complete) g_launch.count[at] = std::min(g_launch.count[at], c.value);
+    }
+    for (const Need &n : g_needs) {
+        const auto seen = g_seen.find({n.wave, n.wait, n.word});
+        g_wave = n.wave;
+        if (seen == g_seen.end() || seen->second < n.value) fail("another workgroup's data read before they are known to be complete");
+    }
+    g_complete.clear();
+    g_counted.clear();
+    g_needs.clear();
+    g_seen.clear();
+    ++g_group;
 }
 
 void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *), void *context)
@@ -108,6 +234,7 @@ void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *)
                 g_wave = t / 64;
                 g_interval = g_looks = 0;
                 thread(context);
+                if (g_launch.on) thread_done();
                 if (barriers > 0 && g_interval > 0 && barriers != g_interval) fail("waves meet different numbers of barriers");
                 barriers = std::max(barriers, g_interval);
             }
@@ -124,6 +251,7 @@ void host_run(dim3 grid, int threads, size_t dynamic_lds, void (*thread)(void *)
                     }
                 }
             }
+            if (g_launch.on) group_done();
         }
 }
 
@@ -147,11 +275,20 @@ static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
         exit(1);
     };
 #define RUN(layer, call) (snprintf(g_what, sizeof g_what, "%s, layer %d", #call, layer), run(#call, layer, call))
-    // (the reverse pass given a workspace that no forward pass has run in: its words are whatever is there)
-    auto words = [&](size_t at, int groups) {
+    // around a launch of several layers.  (`uncleared`: a reverse pass given a workspace that no forward pass has run in, whose
+    // words are whatever is there)
+    auto begin = [&](size_t at, int groups) {
+        unsigned *const words = reinterpret_cast<unsigned *>(ws + at);
+        const size_t n = (size_t)(1 + groups) * kWordStride;
         g_stuck = uncleared;
-        if (uncleared) std::fill_n(reinterpret_cast<unsigned *>(ws + at), (size_t)(1 + groups) * kWordStride, 0xbf80bf80u);
+        if (uncleared) return void(std::fill_n(words, n, 0xbf80bf80u));
+        for (int i = 0; i <= groups; ++i)
+            if (words[i * kWordStride]) fail("words that are not cleared");
+        g_launch = Launch{true, reinterpret_cast<char *>(ws), reinterpret_cast<char *>(words), reinterpret_cast<char *>(words + n),
+                          std::vector<int>(pl.total_floats, -1), std::vector<int>(pl.total_floats, kNever), {}, {}};
+        g_group = 0;
     };
+    auto done = [&] { g_launch.on = false; };
     for (int pass = 0; pass < 3; ++pass) {
         const bool reverse = pass == 0, predict = pass == 2;
         const ForwardMode mode{reverse, predict ? reinterpret_cast<unsigned *>(ws + pl.O) : nullptr, predict};
@@ -159,12 +296,13 @@ static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
         RUN(-1, launch_es_forward(pl, y, predict ? shorter : lengths, es, weights, ws, mode, nullptr));
         RUN(-1, launch_window_forward(pl, nullptr, ws, nullptr));
         for (int l = 0; l < pl.L; ++l) RUN(l, launch_lstm_forward(pl, l, n, weights, ws, mode, nullptr));
-        words(pl.together_words, pl.together_groups);
         if (pl.together_fwd) {
+            begin(pl.together_words, pl.together_groups);
             // (sums of the residual input and a state that is not formed here: the input's NaN has to show in them)
             const size_t out = pl.layer[pl.together_fwd - 1].out, size = (size_t)pl.P * pl.NB * pl.HT * 64;
             if (out) std::fill_n(ws + out, size, 0.0f);
             RUN(pl.together_fwd, launch_lstm_forward_together(pl, n, weights, ws, mode, nullptr));
+            done();
             if (uncleared && out && std::none_of(ws + out, ws + out + size, [](float v) { return v != v; })) fail("no NaN after a wait was given up");
         }
         if (predict) {
@@ -175,8 +313,11 @@ static int step(const Plan &pl, const std::vector<int> &lens, bool uncleared)
         RUN(-1, launch_loss_and_forecasts(pl, n, ws, loss, in_sample, nullptr));
         if (!reverse) continue;
         for (int l = pl.L - 1; l >= 0; --l) RUN(l, launch_lstm_backward(pl, l, n, ws, nullptr));
-        words(pl.together_words_bwd, pl.together_groups_bwd);
-        if (pl.together_bwd) RUN(pl.together_bwd, launch_lstm_backward_together(pl, n, ws, nullptr));
+        if (pl.together_bwd) {
+            begin(pl.together_words_bwd, pl.together_groups_bwd);
+            RUN(pl.together_bwd, launch_lstm_backward_together(pl, n, ws, nullptr));
+            done();
+        }
         RUN(-1, launch_window_backward(pl, n, ws, true, nullptr));
         RUN(-1, launch_es_backward(pl, y, n, es, ws, grad_es, grad_weights, nullptr));
     }

@@ -1,7 +1,7 @@
 """What the kernels' correctness needs beside their arithmetic, checked without a GPU: the kernel sources are built for the
 CPU and run thread by thread (tests/host_kernels/host_kernels.cpp).  Every access has to lie in the workspace or an array
 of the call, every wave has to meet the same barriers, and between two barriers no wave may touch LDS that another one
-writes."""
+writes.  What a workgroup reads of another one of the same launch has to be complete when the count shows that it has waited for."""
 import os
 import re
 import shutil
@@ -180,6 +180,17 @@ def test_waves_of_layers_in_one_launch_are_ordered(program, hidden, window):
                              env=dict(os.environ, ESRNN_NARROW_BELOW="20"), capture_output=True, text=True, check=True).stdout
         assert f"together {together}" in out
         assert run_step(program, 20, 64, T, window, 3, hidden, min(T, 4), 0, lam, f"{T},{window + 9}", *dilations) == (0, "ok")
+
+
+# chains around a chunk of staged operands, and of one position (a horizon whose outputs hold the words all the same)
+@pytest.mark.parametrize("positions", [1, 2, 3, 4, 5, 8, 9, 10])
+def test_chains_of_every_length_in_one_launch(program, positions):
+    T = 4 + 24 + positions - 1
+    for dilations in ((1, 2), (2, 1)) if positions > 1 else ((1, 1),):
+        out = subprocess.run([program, "plan"] + [str(a) for a in (64, T, 4, 24, 40, 0, "all") + dilations], capture_output=True, text=True,
+                             check=True).stdout
+        assert "together 2 2" in out
+        assert run_step(program, 100000, 64, T, 4, 24, 40, 4, 0, 0, T, *dilations) == (0, "ok")
 
 
 # what a bf16 pair of packed operands looks like as a ticket: its top bit is set; and as a count: it never comes
