@@ -31,7 +31,8 @@
  *   - fp32 throughout.  Series values must be strictly positive inside their
  *     length; values past the length are ignored.
  *   - A handle may be used by one thread at a time.  A workspace belongs to one
- *     forward/backward pair at a time.
+ *     forward/backward pair at a time: calls that overlap on one give wrong
+ *     numbers, in small batches perhaps NaN and after some seconds.
  */
 #ifndef ESRNN_H
 #define ESRNN_H

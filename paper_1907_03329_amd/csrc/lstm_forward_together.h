@@ -1,11 +1,12 @@
 // First layers of the network in one launch, each behind the one below (see lstm_together.h): 4-series layers, the last one
 // possibly a 16-series one.  The kernel template and its launcher, included by one translation unit per kind of last layer.
 //
-// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 65 us and three gaps between launches -> 42 us;
-// the first two layers of 512 hourly series 433 -> 365 us (of 333, for forecasts, 396 -> 293 us), of 501 monthly ones 187 -> 137 us.
+// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 65 us and three gaps between launches -> 43 us;
+// the first two layers of 512 hourly series 440 -> 350 us (of 333, for forecasts, 399 -> 292 us), of 501 monthly ones 188 -> 136 us.
 // Whole calls: 7 quarterly series 80 -> 58 us, step of 16 211 -> 188 us, forecasts of 333 hourly ones 540 -> 431 us, step of 512
-// 1770 -> 1740 us.  What bounds it is the first layer's chain; at the end every layer adds what a store, a look and a load past
-// the caches take and a few positions of its own, some 5 us.
+// 1770 -> 1740 us (the third layer, in a launch of its own behind the two, takes 87 us instead of 65).  What bounds it is the first
+// layer's chain; at the end every layer adds what a store, a look and a load past the caches take and a few positions of its own,
+// some 5 us.
 #pragma once
 
 #include "lstm_forward.h"
