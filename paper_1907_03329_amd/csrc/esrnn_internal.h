@@ -48,7 +48,7 @@ struct LayerPlan {
     int chains;          // forward workgroups per series tile (per 4 series if narrow_fwd); each walks the residue classes
                          // r, r+chains, ... (mod dil)
     int chains_bwd;      // the same for the reverse kernel
-    int split_bwd;       // 1: 4-series reverse kernel with eight waves, the weight gradient on waves of its own, one workgroup per compute unit
+    int split_bwd;       // 1: 4-series reverse kernel with twelve waves, staging and weight gradient on waves of their own, one workgroup per compute unit
     int narrow_fwd;      // 1: forward pass on the 4-series kernel (lstm_narrow_fwd.h): wpack_fwd is [4][4*(KXT+HT)][64],
                          // bias_pack unused
     int narrow_bwd;      // 1: reverse pass on the 4-series kernel (lstm_narrow_bwd.h): wpack_bwd is [4][NG][4*HT][64], and the

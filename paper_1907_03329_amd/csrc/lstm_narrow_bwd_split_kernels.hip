@@ -1,4 +1,4 @@
-// 4-series reverse LSTM kernel, eight waves per workgroup: the weight gradient on waves of its own (see
+// 4-series reverse LSTM kernel, twelve waves per workgroup: staging and the weight gradient on waves of their own (see
 // lstm_narrow_bwd.h).
 #include "lstm_narrow_bwd.h"
 

@@ -30,26 +30,28 @@
 // transposed contraction runs on the 4x4x1 instruction with the gate gradients
 // broadcast straight from the registers of the lanes that computed them; the
 // weight gradient contracts over the four series, which is exactly the k = 4 of
-// ONE 16x16x4 instruction per 16x16 tile of dW; the LDS arrays a position writes
+// ONE 16x16x4 instruction per 16x16 tile of dW (or half the k of a bf16 one, over
+// four positions); the LDS arrays a position writes
 // are double-buffered by position parity, which leaves one barrier per
 // position.  Every LDS array is laid out [row][4 series], so that each access
 // of a wave covers consecutive addresses.
 //
 // Waves that carry the recurrence are bound by the instructions they issue, so
-// whatever it does not need is done by four more waves: the inputs and their half
-// of the pre-activations (forward), and in the reverse kernel, where the grid leaves
-// the room, all requests, the weight gradient and the input gradient.
+// whatever it does not need is done by other waves: the inputs and their half
+// of the pre-activations (forward, four more waves), and in the reverse kernel, where
+// the grid leaves the room, all requests and the factors that do not depend on the
+// recurrence (four more), the weight gradient and the input gradient (four more).
 //
 // Global operands.  A position takes a fraction of a microsecond here, less
-// than the latency of HBM, so operands are requested a whole chunk of positions
-// ahead into registers and staged in LDS: the requests for the next chunk go
-// out at the start of a chunk, and at its end the registers are written to LDS.
-// A whole chunk is ONE straight run of instructions (the position loop inside
-// it is unrolled): memory operations complete in order, and only with request
-// and use in the same run does the compiler's wait for a request count the
-// stores issued since instead of waiting for all of them.  (With the request in
-// one loop iteration and the use in another, every chunk waited for its newest
-// stores; a ring of registers with one request per position was slower still.)
+// than the latency of HBM, so operands are requested several positions
+// ahead into registers and staged in LDS.  In the forward kernel the requests for
+// the next chunk of positions go out at the start of a chunk, and at its end the
+// registers are written to LDS; the reverse kernel requests and stages a position
+// in every position, in waves that store nothing.
+// A chunk, or in the reverse kernel a run of four positions, is ONE straight run of
+// instructions (the position loop inside it is unrolled): memory operations complete
+// in order, and only with request and use in the same run does the compiler's wait for
+// a request count the operations issued since instead of waiting for all of them.
 // Lanes past HT repeat the last unit of the wave, operands and addresses alike,
 // and threads without an input row stage into a spare LDS column, so no memory
 // operation sits behind a divergent branch.

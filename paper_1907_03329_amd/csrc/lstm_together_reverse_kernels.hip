@@ -1,9 +1,9 @@
 // Last layers of the reverse pass, the first ones of the network, in one launch, each behind the one above (see
-// lstm_together.h): 4-series layers with eight waves a workgroup.
+// lstm_together.h): 4-series layers with twelve waves a workgroup.
 //
-// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 103 us and three gaps between launches -> 69 us
-// (the step 188 -> 152 us).  What bounds it is the first layer's chain, 40 us, and per layer the positions between an input
-// gradient and its count, a store, a look and a load past the caches, and a chunk of the layer below.
+// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 103 us and three gaps between launches -> 69 us,
+// now 50 us.  What bounds it is the first layer's chain, 31 us, and per layer the positions between an input
+// gradient and its count, a store, a look and a load past the caches.
 
 #include "lstm_narrow_bwd.h"
 
@@ -17,7 +17,7 @@ struct BwdTogetherArgs {
 };
 
 template <int HT, int KXT, bool CP>
-__global__ void __launch_bounds__(2 * kNT) lstm_backward_together_kernel(BwdTogetherArgs t)
+__global__ void __launch_bounds__(narrow_bwd_threads(true)) lstm_backward_together_kernel(BwdTogetherArgs t)
 {
     using Last = NarrowBwdLds<HT, KXT, true, kLast>;
     using Later = NarrowBwdLds<HT, HT, true, kLater>;
@@ -55,8 +55,8 @@ hipError_t launch_lstm_backward_together(const Plan &pl, const int32_t *lengths,
     const bool cp = pl.cfg.lambda_cs != 0.0f;
 #define X(HT_, KXT_)                                                                                                            \
     if (pl.HT == HT_ && pl.layer[0].KXT == KXT_) {                                                                              \
-        if (cp) lstm_backward_together_kernel<HT_, KXT_, true><<<blocks, 2 * kNT, 0, st>>>(t);                                  \
-        else lstm_backward_together_kernel<HT_, KXT_, false><<<blocks, 2 * kNT, 0, st>>>(t);                                    \
+        if (cp) lstm_backward_together_kernel<HT_, KXT_, true><<<blocks, narrow_bwd_threads(true), 0, st>>>(t);                                  \
+        else lstm_backward_together_kernel<HT_, KXT_, false><<<blocks, narrow_bwd_threads(true), 0, st>>>(t);                                    \
         return hipGetLastError();                                                                                               \
     }
     ESRNN_LSTM_SHAPES(X)

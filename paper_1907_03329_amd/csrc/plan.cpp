@@ -229,8 +229,8 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.narrow_bwd = wide_groups < narrow_bwd_below ? 1 : 0;
         lp.chains = chains_for(lp.narrow_fwd ? 4 * pl.NB : pl.NB, 512);
         const int groups = lp.narrow_bwd ? 4 * pl.NB : pl.NB;
-        // The 4-series reverse kernel has two workgroups per compute unit, or one of eight waves, the weight gradient
-        // on waves of its own: the faster kind where the grid has no more than that.
+        // The 4-series reverse kernel has two workgroups per compute unit, or one of twelve waves, staging and weight gradient
+        // on waves of their own: the faster kind where the grid has no more than that.
         lp.chains_bwd = lp.narrow_bwd ? chains_for(groups, 512) : wide_reverse_chains(groups, most_chains);
         lp.split_bwd = lp.narrow_bwd && groups * lp.chains_bwd <= 256 ? 1 : 0;
         // The forward operands lie where the first reduction stage of the weight gradient comes at the end of the reverse
