@@ -138,15 +138,28 @@ struct PackLstmArgs {
 };
 
 // Operands of the 4-series kernels.  v_mfma_f32_4x4x1: lane l supplies A[l%4] of block l/4.
-//   forward  [wave][column k of x ; h][lane]: gate l/16 of unit wave*HT + min(l%16, HT-1) (the lanes past HT
-//            repeat the last unit, so that all lanes do the same work on the same addresses)
+//   forward  [wave][column k of h][lane]: gate l/16 of unit wave*HT + min(l%16, HT-1) (the lanes past HT
+//            repeat the last unit, so that all lanes do the same work on the same addresses); then those of x on the bf16 pipe,
+//            three parts of W (three_term.h) as [wave][column tile][quads of x][lane][dword], column c = 16*tile + l%16 is gate c/HT
+//            of unit wave*HT + c%HT
 //   reverse  [wave][group g][k-step 4*u + gate][lane]: W[gate, unit wave*HT + u][column 64*g + l]
 __device__ __forceinline__ void pack_forward_narrow(const PackLstmArgs &a, int block, int n_blocks)
 {
-    const int KT4 = 4 * (a.KXT + a.HT), n = 4 * KT4 * 64;
+    const int HP = 4 * a.HT, n = 4 * HP * 64;
     for (int idx = block * 256 + threadIdx.x; idx < n; idx += n_blocks * 256) {
-        const int lane = idx & 63, k = (idx >> 6) % KT4, w = (idx >> 6) / KT4;
-        a.fwd[idx] = a.at_row(lane >> 4, w * a.HT + min(lane & 15, a.HT - 1), k);
+        const int lane = idx & 63, k = (idx >> 6) % HP, w = (idx >> 6) / HP;
+        a.fwd[idx] = a.at(lane >> 4, w * a.HT + min(lane & 15, a.HT - 1), false, k);
+    }
+    const int np = (a.KXT + 1) / 2, quads = tt_a_quads(np), tiles = (a.HT + 3) / 4, nx = 4 * tiles * quads * 256;
+    unsigned *const x = reinterpret_cast<unsigned *>(a.fwd + n);
+    for (int idx = block * 256 + threadIdx.x; idx < nx; idx += n_blocks * 256) {
+        const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, t = (idx >> 8) / quads % tiles, w = (idx >> 8) / (quads * tiles);
+        const int c = 16 * t + (lane & 15), gate = c / a.HT, unit = w * a.HT + c % a.HT, k = lane >> 4;
+        const TtDword part = tt_a_dword(np, q, d);
+        const bool exists = c < HP;
+        const Parts p = split_pair(exists ? splittable(a.at(gate, unit, true, 8 * part.pair + k)) : 0.0f,
+                                   exists ? splittable(a.at(gate, unit, true, 8 * part.pair + 4 + k)) : 0.0f);
+        x[idx] = part_of(p, part.part);
     }
 }
 __device__ __forceinline__ void pack_backward_narrow(const PackLstmArgs &a, int block, int n_blocks)

@@ -6,7 +6,8 @@
 // Whole calls: 7 quarterly series 80 -> 58 us, step of 16 211 -> 188 us, forecasts of 333 hourly ones 540 -> 431 us, step of 512
 // 1770 -> 1740 us (the third layer, in a launch of its own behind the two, takes 87 us instead of 65).  What bounds it is the first
 // layer's chain; at the end every layer adds what a store, a look and a load past the caches take and a few positions of its own,
-// some 5 us.
+// some 5 us.  512 hourly series: the first layer alone in this launch 285 us, 338 us beside a second one that waits for nothing, 363 us as
+// it is; looks half as often change that by 3 % and cost small batches more.
 #pragma once
 
 #include "lstm_forward.h"
@@ -29,6 +30,8 @@ template <int HT, int KXT, bool CP, int KIND>
 __global__ void __launch_bounds__(2 * kNT) lstm_forward_together_kernel(FwdTogetherArgs t)
 {
     __shared__ unsigned ticket;
+    // (32 KB of input halves, and what is known of the rest: all 4-series layers 46 - 48 KB, with a 16-series one 50 - 98)
+    alone_on_compute_unit<KIND == kAllNarrow ? 45 * 1024 : HT == 2 ? 50 * 1024 : HT == 8 ? 68 * 1024 : HT == 10 ? 77 * 1024 : 96 * 1024>();
     const Place at = draw_place(t.places, &ticket);
     const int l = at.layer, d = t.places.d[l], bt = at.bt, q = at.q, chain = at.chain;
     const bool wide = KIND != kAllNarrow && l == t.places.layers - 1;

@@ -604,6 +604,7 @@ __global__ void __launch_bounds__(narrow_bwd_threads(SPLIT), (!SPLIT && HT <= 10
     __shared__ __align__(16) typename Lds::Part part;
     __shared__ __align__(16) typename Lds::Staged lc;
     __shared__ __align__(16) typename Lds::Rows xh;
+    if constexpr (SPLIT) alone_on_compute_unit<(int)Lds::bytes>();
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
     // quarters of ONE tile, so they land on the same XCD at about the same time and a row is fetched from

@@ -12,12 +12,13 @@
 // ("blocks") per instruction, one k-step.  Lane l belongs to block l/4; it
 // supplies A[l%4] and B[l%4] of its block and holds D[0..3][l%4].  With its
 // broadcast control (cbsz = 4, abid = b) all sixteen blocks take the A values
-// of block b.  Here A carries the ACTIVATIONS of the four series for one input
+// of block b.  Here A carries the ACTIVATIONS of the four series for one
 // column, broadcast from the block whose four lanes hold them, and B carries
 // the weights: lane 16 g + u of a wave holds gate g of hidden unit u.  One
-// instruction advances 16 units x 4 gates x 4 series by one input column, and no
-// operand has to be replicated over the blocks: a wave reads [x_p ; h_{p-d}] of
-// the four series from LDS with one 4-byte load per 16 columns.  Four waves
+// instruction advances 16 units x 4 gates x 4 series by one column, and no
+// operand has to be replicated over the blocks: a wave reads h_{p-d} of
+// the four series from LDS with one 4-byte load per 16 columns.  (The input half
+// comes from other waves, lstm_narrow_fwd.h.)  Four waves
 // share the units; wave w owns w*HT .. w*HT+HT-1 (HT <= 16; the padded
 // hidden size is 4*HT).  A lane ends up with one gate of one unit for the four
 // series; a transpose between components and rows of sixteen lanes (four
@@ -44,17 +45,15 @@
 //
 // Global operands.  A position takes a fraction of a microsecond here, less
 // than the latency of HBM, so operands are requested several positions
-// ahead into registers and staged in LDS.  In the forward kernel the requests for
-// the next chunk of positions go out at the start of a chunk, and at its end the
-// registers are written to LDS; the reverse kernel requests and stages a position
-// in every position, in waves that store nothing.
-// A chunk, or in the reverse kernel a run of four positions, is ONE straight run of
+// ahead into registers.  The forward kernel requests the inputs of
+// four positions at a time, one or two such groups ahead; the reverse kernel requests a
+// position and stages one in LDS in every position, in waves that store nothing.
+// A run of four positions is ONE straight run of
 // instructions (the position loop inside it is unrolled): memory operations complete
 // in order, and only with request and use in the same run does the compiler's wait for
 // a request count the operations issued since instead of waiting for all of them.
-// Lanes past HT repeat the last unit of the wave, operands and addresses alike,
-// and threads without an input row stage into a spare LDS column, so no memory
-// operation sits behind a divergent branch.
+// Lanes past HT repeat the last unit of the wave, operands and addresses alike, so no
+// request sits behind a divergent branch.
 //
 // All tensors keep the layouts of the 16-series kernels (TL(R) tiles of 16
 // series), so layers of both kinds mix freely and the weight-gradient
@@ -109,6 +108,20 @@ __device__ __forceinline__ void row_transpose(f32x4 &v)
     swap32(v0, v2);
     swap32(v1, v3);
     v = f32x4{v0, v1, v2, v3};
+}
+
+// LDS that a kernel takes only so that no two of its workgroups share a compute unit: more than half of the 160 KB together with the
+// `used` bytes that it needs.  Grids of at most one workgroup per compute unit do not spread by themselves, and chains that share
+// their SIMDs slow each other down: two forward layers for forecasts of 333 hourly series 294 -> 275 us, first layers of 1024
+// quarterly ones (256 workgroups) 31.5 -> 30.1 us.
+template <int used>
+__device__ __forceinline__ void alone_on_compute_unit()
+{
+    constexpr int enough = 84 * 1024;
+    if constexpr (used < enough) {
+        __shared__ char rest[enough - used];
+        asm volatile("" ::"v"((__attribute__((address_space(3))) char *)rest));
+    }
 }
 
 // workgroups along x: groups of 32 = 8 tiles x 4 quarters

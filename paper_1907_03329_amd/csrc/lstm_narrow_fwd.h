@@ -5,13 +5,15 @@
 
 #include "lstm_narrow_common.h"
 #include "lstm_together.h"
+#include "three_term.h"
 
 namespace esrnn {
 
 namespace {
 
 struct NarrowFwdArgs {
-    const float *wpack;   // [4][KT4][64]  weight operands: wave, input column, lane (gate l/16 of unit l%16 of the wave)
+    const float *wpack;   // [4][4*HT][64] weights of h: wave, column, lane (gate l/16 of unit l%16 of the wave), then
+                          // [4][column tiles][quads][64][4] those of x: columns (gate, unit of the wave), split in three
     const float *bias;    // caller's bias vector [4h]
     const float *xsrc;    // TL(4*KXT)
     float *gates;         // TL(HP) x [4]
@@ -25,27 +27,29 @@ struct NarrowFwdArgs {
     int B, T, I, H;
 };
 
-// positions per chunk of staged inputs: fewer where a chunk cannot be requested before the layer below has all of it
-constexpr int narrow_fwd_chunk(int mode) { return mode == kLater ? 4 : 8; }
+// positions whose input half is formed together: the 16 rows of a matrix instruction are four positions of four series
+constexpr int kInputGroup = 4;
 
-// Input half of the pre-activations, by position parity: one object for all kinds of layers of a kernel, each of which has
-// arrays of its own otherwise (hidden 64, three kinds and two of 16 series: 131 200 bytes, past the 128 KB that are safe).
-__device__ __forceinline__ f32x4 (&input_halves())[2][kNW][64]
+// Input half of the pre-activations, two groups of positions: one object for all kinds of layers of a kernel, each of which has
+// arrays of its own otherwise.
+__device__ __forceinline__ f32x4 (&input_halves())[2][kInputGroup][kNW][64]
 {
-    __shared__ f32x4 half[2][kNW][64];
+    __shared__ f32x4 half[2][kInputGroup][kNW][64];
     return half;
 }
 
-// Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the next
-// position's pre-activations (with the bias), which does not depend on it: the chain then has 4 HT instead of
-// 4 (KXT + HT) matrix instructions a position, and no request of its own.  Both kinds meet the same barriers.
-// 512 hourly series, first layer (24 + 40 columns, 649 positions): 348 -> 331 us (333 -> 317 us for 333); 501 monthly ones
-// (20 + 50 columns, 211 positions): 123 -> 115 us; 16 quarterly ones (4 + 40 columns, 61 positions): 30.3 -> 27.7 us.  (Three
-// accumulators, which need no wait states between the matrix instructions: 340 us.)  What bounds it is the issue of one
-// wave and what the input wave of its SIMD takes from it: without the input half 264 of 327 us.  Gates in the rows of sixteen
-// lanes, which four instructions transpose (26 between the lanes of a quad), and stores through pointers that move on
-// (13 scalar instructions a position instead of some 20 scalar and vector ones for addresses): 327 -> 290 us for 512 hourly
-// series, 114 -> 108 us for 501 monthly ones, 27.7 -> 25.7 us for 16 quarterly ones.
+// Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the
+// pre-activations (with the bias), which does not depend on it, on the bf16 matrix pipe: x of four positions and four series is
+// the 16 rows of one operand, a wave's gates and units the columns of the other, and a lane ends up with what one lane of the chain
+// wave takes, four series of a gate and unit.  The chain then has 4 HT matrix instructions a position, and no request of its own.
+// Both kinds meet the same barriers.
+// What bounds it: the chain, 230 of 268 us without stores and input half (512 hourly series, first layer, 24 + 40 columns, 649
+// positions): some 150 ns a position from the state's LDS write over the barrier to its read, 40 matrix instructions of 3.7 ns,
+// the gates.  Without the stores alone 253 us, without five of six of the input waves' products 257 us.  Input half with fp32 products a
+// position at a time (24 of them, which share the issue with the chain's vector instructions): 301 us; 501 monthly series (20 + 50
+// columns, 211 positions) 111 -> 103 us, 16 quarterly ones (4 + 40 columns, 61 positions) 26.1 -> 25.0 us, their second layer (40 + 40)
+// 18.7 -> 17.1 us.  Tried: stores spread over the matrix instructions (272 instead of 268 us), three accumulators instead of two,
+// contraction split over the rows of a wave, ten waves (nothing gained: the barrier takes longer, 186 ns instead of 150).
 //
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ... (of several layers in one launch:
 // its only one).
@@ -54,14 +58,12 @@ __device__ __forceinline__ f32x4 (&input_halves())[2][kNW][64]
 template <int HT, int KXT, bool CP, bool OUT, int MODE>
 __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a, int bt, int q, int chain, int chains, const Progress &progress)
 {
-    constexpr int KX = 4 * KXT, HP = 4 * HT, CH = narrow_fwd_chunk(MODE);
-    constexpr int XG = (KX + 15) / 16, HG = (HP + 15) / 16;   // groups of 16 columns (one register each)
-    // inputs x_p of a chunk of positions [column][series], by chunk parity (+ 64 floats that take the writes of
-    // the threads with no input row, so that staging is the same instruction stream in every thread)
-    __shared__ float xc[2][CH][XG * 64 + 64];
-    __shared__ float rc[OUT ? 2 : 1][OUT ? CH : 1][kNT];      // residual input of a thread's (unit, series), likewise
+    constexpr int KX = 4 * KXT, HP = 4 * HT;
+    constexpr int HG = (HP + 15) / 16;          // groups of 16 columns (one register each)
+    constexpr int kStoreStep = 1;          // pairs of matrix instructions between two stores
+    __shared__ float rc[OUT ? 2 : 1][OUT ? kInputGroup : 1][kNT];      // residual input of a thread's (unit, series), by group of positions
     __shared__ float hb[2][HG * 64];            // h_{p-d} [unit][series], by position parity
-    f32x4 (&half)[2][kNW][64] = input_halves();
+    f32x4 (&half)[2][kInputGroup][kNW][64] = input_halves();
     // positions whose stores may still be under way when the next one is counted: a position of a first layer takes less
     // time than a store
     constexpr int kBehind = MODE == kFirst ? 3 : 1, kStores = OUT ? 4 : 3;
@@ -75,91 +77,135 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     const int unit = w * HT + min(blk, HT - 1);     // lanes past HT repeat the last unit
     // element of this lane inside the TL(HP) block of one (position, series tile)
     const int lane_off = unit * 16 + 4 * q + j;
-    // columns past KX / HP in the last group of 16 are never written: zero once (their weights do not exist)
-    for (int e = threadIdx.x; e < 2 * CH * (XG * 64 + 64); e += 2 * kNT) (&xc[0][0][0])[e] = 0.0f;
+    // columns past HP in the last group of 16 are never written: zero once (their weights do not exist)
     for (int e = threadIdx.x; e < 2 * HG * 64; e += 2 * kNT) (&hb[0][0])[e] = 0.0f;
 
     if (wave >= kNW) {
         // =========================== input waves ===========================
-        float wx[KX];
+        // x (16 rows: position, series) times W_x^T (columns: gate, unit of the wave), on the bf16 matrix pipe (three_term.h)
+        constexpr int NP = (KXT + 1) / 2, AQ = tt_a_quads(NP), BQ = tt_b_quads(NP), TILES = (HT + 3) / 4;
+        const u32x4 *wpack = reinterpret_cast<const u32x4 *>(a.wpack + (size_t)kNW * HP * 64) + (size_t)w * TILES * AQ * 64 + lane;
+        u32x4 wx[TILES][AQ];
+        float bias[TILES];
+        int to[TILES];              // where a column goes: gate in rows of sixteen lanes
 #pragma unroll
-        for (int k = 0; k < KX; ++k) wx[k] = a.wpack[((size_t)w * (KX + HP) + k) * 64 + lane];
-        // before the transpose a lane holds gate j of its unit for the four series
-        const float bias = unit < a.h ? a.bias[j * a.h + unit] : 0.0f;
-        // cooperative input load: thread t < 4*KX brings row t/4 of series t%4 (the others repeat row 0)
-        const bool x_thread = tid < 4 * KX;
-        const int x_off = (x_thread ? tid >> 2 : 0) * 16 + 4 * q + (tid & 3);
-        const int x_slot = x_thread ? tid : XG * 64 + lane;
+        for (int t = 0; t < TILES; ++t) {
+#pragma unroll
+            for (int m = 0; m < AQ; ++m) wx[t][m] = wpack[(t * AQ + m) * 64];
+            const int c = 16 * t + blk, gate = c / HT, u = w * HT + c % HT;
+            bias[t] = c < HP && u < a.h ? a.bias[gate * a.h + u] : 0.0f;
+            to[t] = c < HP ? 16 * gate + c % HT : -1;
+        }
         Below below(progress);
         for (int r = chain; r < a.d && r < Pt; r += chains) {
             const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
-            float xs[CH], rs[CH];
-            auto load_chunk = [&](int c) {
+            float xs[2 * NP], rs[kInputGroup];
+            // requests of the four positions from the i-th on (past the chain its last)
+            auto request = [&](int i) {
+                // before them, the layer below has all of it
+                if constexpr (MODE == kLater) below.wait(r + min(i + kInputGroup - 1, n - 1) * a.d);
+                const int first = min(i, n - 1), mine = min(i + (blk >> 2), n - 1) - first;     // this lane's position (not before the first)
+                const size_t tile = (size_t)(r + first * a.d) * a.NB + bt;
+                const int at = j * 16 + 4 * q + (blk & 3);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (MODE == kLater) {
+                    // (d NB is at most 256 workgroups here: 32 bits)
+                    const buf_rsrc x = make_rsrc(a.xsrc + tile * (KX * 16));
+                    const int from = 4 * (mine * a.d * a.NB * (KX * 16) + at);
 #pragma unroll
-                for (int ii = 0; ii < CH; ++ii) {
-                    const size_t tile = (size_t)(r + min(c * CH + ii, n - 1) * a.d) * a.NB + bt;
-                    if constexpr (MODE == kLater) {
-                        xs[ii] = buf_load_shared(make_rsrc(a.xsrc + tile * (KX * 16)), 4 * x_off, 0);
-                        rs[ii] = OUT ? buf_load_shared(make_rsrc(a.resid + tile * (HP * 16)), 4 * lane_off, 0) : 0.0f;
-                    } else {
-                        xs[ii] = (a.xsrc + tile * (KX * 16))[x_off];
-                        rs[ii] = OUT ? (a.resid + tile * (HP * 16))[lane_off] : 0.0f;
+                    for (int k = 0; k < 2 * NP; ++k) xs[k] = k < KXT ? buf_load_shared(x, from, 256 * k) : 0.0f;
+                } else {
+                    const float *x = a.xsrc + (tile + (size_t)(mine * a.d) * a.NB) * (KX * 16) + at;
+#pragma unroll
+                    for (int k = 0; k < 2 * NP; ++k) xs[k] = k < KXT ? x[64 * k] : 0.0f;
+                }
+                if constexpr (OUT) {
+#pragma unroll
+                    for (int g = 0; g < kInputGroup; ++g) {
+                        const buf_rsrc res = make_rsrc(a.resid + ((size_t)(r + min(i + g, n - 1) * a.d) * a.NB + bt) * (HP * 16));
+                        rs[g] = MODE == kLater ? buf_load_shared(res, 4 * lane_off, 0) : buf_load(res, 4 * lane_off, 0);
                     }
                 }
+                __builtin_amdgcn_sched_barrier(0);
             };
-            // before a chunk is requested: the layer below has all of it
-            auto await_chunk = [&](int c) {
-                if constexpr (MODE == kLater) below.wait(r + min(c * CH + CH - 1, n - 1) * a.d);
+            // what has been requested in parts, as operands; residual inputs in LDS
+            u32x4 xq[BQ];
+            auto arrive = [&](int par) {
+                Parts p[4 * ((NP + 3) / 4)];
+                auto value = [&](int k) { return splittable(MODE == kLater ? below.checked(xs[k]) : xs[k]); };
+#pragma unroll
+                for (int k = 0; k < 4 * ((NP + 3) / 4); ++k) p[k] = k < NP ? split_pair(value(2 * k), 2 * k + 1 < KXT ? value(2 * k + 1) : 0.0f) : Parts{0, 0, 0};
+                static_for<0, BQ>([&](auto qc) {
+                    constexpr int b = decltype(qc)::value, full = tt_full(NP), rest = b - 3 * full;
+                    static_for<0, 4>([&](auto dc) {
+                        constexpr int d = decltype(dc)::value;
+                        constexpr int pair = rest < 0 ? 4 * (b / 3) + d : 4 * full + (tt_rest(NP) == 2 ? d & 1 : 0);
+                        constexpr int part = rest < 0 ? b % 3 : tt_rest(NP) == 1 ? d % 3 : rest == 0 ? d / 2 : d < 2 ? 2 : 0;
+                        xq[b][d] = part_of(p[pair], part);
+                    });
+                });
+                if constexpr (OUT) {
+#pragma unroll
+                    for (int g = 0; g < kInputGroup; ++g) rc[par][g][tid] = MODE == kLater ? below.checked(rs[g]) : rs[g];
+                }
+            };
+            // column tiles [from, end), left for the group of parity par: a lane has position j, its column, and four series
+            auto products = [&](auto from, auto end, int par) {
+                static_for<decltype(from)::value, decltype(end)::value>([&](auto tc) {
+                    constexpr int t = decltype(tc)::value;
+                    // (two sums: a chain of half the length)
+                    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+                    static_for<0, tt_mfmas(NP)>([&](auto ic) {
+                        constexpr int i = decltype(ic)::value;
+                        constexpr TtPair m = tt_mfma(NP, i);
+                        acc[i % 2] = mfma_bf16(xq[m.b], wx[t][m.a], acc[i % 2]);
+                    });
+                    const f32x4 sum = acc[0] + acc[1];
+                    if (to[t] >= 0) half[par][j][w][to[t]] = f32x4{sum[0] + bias[t], sum[1] + bias[t], sum[2] + bias[t], sum[3] + bias[t]};
+                });
             };
             // after the barrier of the i-th position
             auto count = [&](int i) {
                 if constexpr (MODE != kAlone) progress.publish(max(i - kBehind, 0) * a.d, w == 0);
             };
-            auto flush_chunk = [&](int c) {
-#pragma unroll
-                for (int ii = 0; ii < CH; ++ii) {
-                    xc[c & 1][ii][x_slot] = MODE == kLater ? below.checked(xs[ii]) : xs[ii];
-                    if constexpr (OUT) rc[c & 1][ii][tid] = MODE == kLater ? below.checked(rs[ii]) : rs[ii];
-                }
-            };
-            // input half of the position in slot ii of the chunk of parity cpar, left for the position of parity par
-            auto input_half = [&](int cpar, int ii, int par) {
-                float vx[XG];
-#pragma unroll
-                for (int m = 0; m < XG; ++m) vx[m] = xc[cpar][ii][64 * m + lane];
-                f32x4 acc0 = f32x4{bias, bias, bias, bias}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-                static_for<0, KX / 2>([&](auto ic) {
-                    constexpr int k = 2 * decltype(ic)::value;
-                    acc0 = mfma4_bcast<k % 16>(vx[k / 16], wx[k], acc0);
-                    acc1 = mfma4_bcast<(k + 1) % 16>(vx[k / 16], wx[k + 1], acc1);
-                });
-                half[par][w][lane] = acc0 + acc1;
-            };
-            await_chunk(0);
-            load_chunk(0);
+            using std::integral_constant;
+            constexpr integral_constant<int, 0> none;
+            constexpr integral_constant<int, TILES> all;
+            request(0);
             __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
-            flush_chunk(0);
+            arrive(0);
+            if constexpr (MODE != kLater) request(kInputGroup);
+            products(none, all, 0);
             lds_barrier();
-            input_half(0, 0, 0);
-            lds_barrier();
-            // Whole chunks: the body of a chunk is one straight run of instructions, and requests are staged in the run that
-            // issued them, two positions before its end: the first position of the next chunk is formed in the last one.
-            int c = 0;
-            for (; (c + 1) * CH <= n; ++c) {
-                await_chunk(c + 1);
-                load_chunk(c + 1);              // (row indices stop at the chain's last position)
-                static_for<0, CH>([&](auto iic) {
-                    constexpr int ii = decltype(iic)::value;
-                    if constexpr (ii == CH - 2) flush_chunk(c + 1);
-                    if constexpr (ii == CH - 1) input_half((c + 1) & 1, 0, 0);
-                    else input_half(c & 1, ii + 1, (ii + 1) & 1);
+            // Four positions are one straight run of instructions, in which the next four's input half is formed.  A layer that
+            // follows another one requests them here, else they have been requested in the run before.
+            int i = 0, par = 1;
+            if (int groups = n / kInputGroup) do {
+                static_for<0, kInputGroup>([&](auto kc) {
+                    constexpr int k = decltype(kc)::value;
+                    if constexpr (MODE == kLater) {
+                        if constexpr (k == 0) request(i + kInputGroup);
+                        if constexpr (k == 2) {
+                            arrive(par);
+                            products(none, integral_constant<int, TILES / 2>{}, par);
+                        }
+                        if constexpr (k == 3) products(integral_constant<int, TILES / 2>{}, all, par);
+                    } else {
+                        if constexpr (k == 0) {
+                            arrive(par);
+                            request(i + 2 * kInputGroup);
+                        } else {
+                            products(integral_constant<int, (k - 1) * TILES / 3>{}, integral_constant<int, k * TILES / 3>{}, par);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);      // (a third of the products in every position, not all in one)
                     lds_barrier();
-                    count(c * CH + ii);
+                    count(i + k);
                 });
-            }
-            // the last, partial chunk
-            for (int i = c * CH; i < n; ++i) {
-                input_half(c & 1, min(i + 1 - c * CH, CH - 1), (i + 1) & 1);
+                i += kInputGroup;
+                par ^= 1;
+            } while (--groups);
+            for (; i < n; ++i) {
                 lds_barrier();
                 count(i);
             }
@@ -178,7 +224,8 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     const bool valid = blk < HT;
     float wh[HP];
 #pragma unroll
-    for (int k = 0; k < HP; ++k) wh[k] = a.wpack[((size_t)w * (KX + HP) + KX + k) * 64 + lane];
+    for (int k = 0; k < HP; ++k) wh[k] = a.wpack[((size_t)w * HP + k) * 64 + lane];
+    const int half_lane = 16 * j + min(blk, HT - 1);
     int n_valid = 0;
     float csq = 0.0f;
     if constexpr (CP) {
@@ -192,44 +239,52 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
         __syncthreads();
         for (int e = tid; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;    // start of a chain: zero state
         lds_barrier();
-        lds_barrier();
         // What a position leaves in memory is stored while the next one waits for its first operands from LDS, through
         // scalar pointers that move on by a position.
         f32x4 gates;
         float cell, hidden, output;
         const size_t first = ((size_t)r * a.NB + bt) * (HP * 16), step = (size_t)a.d * a.NB * (HP * 16);
         float *at_gates = a.gates + 4 * first, *at_c = a.c + first, *at_hid = a.hid + first, *at_out = OUT ? a.out + first : nullptr;
-        auto store = [&]() {
-            buf_store4<true>(make_rsrc(at_gates), 16 * lane_off, gates);
-            buf_store(make_rsrc(at_c), 4 * lane_off, 0, cell);     // (plain: the four quarter-row writes of a tile then merge in L2)
-            if constexpr (MODE == kAlone) {
-                buf_store(make_rsrc(at_hid), 4 * lane_off, 0, hidden);
-                if (OUT) buf_store(make_rsrc(at_out), 4 * lane_off, 0, output);
-            } else {
-                buf_store_shared(make_rsrc(at_hid), 4 * lane_off, 0, hidden);
-                if (OUT) buf_store_shared(make_rsrc(at_out), 4 * lane_off, 0, output);
+        auto store = [&](auto partc) {
+            constexpr int part = decltype(partc)::value;
+            if constexpr (part == 0) {
+                buf_store4<true>(make_rsrc(at_gates), 16 * lane_off, gates);
+                at_gates += 4 * step;
             }
-            at_gates += 4 * step;
-            at_c += step;
-            at_hid += step;
-            if (OUT) at_out += step;
+            if constexpr (part == 1) {
+                buf_store(make_rsrc(at_c), 4 * lane_off, 0, cell);     // (plain: the four quarter-row writes of a tile then merge in L2)
+                at_c += step;
+            }
+            if constexpr (part == 2) {
+                if constexpr (MODE == kAlone) buf_store(make_rsrc(at_hid), 4 * lane_off, 0, hidden);
+                else buf_store_shared(make_rsrc(at_hid), 4 * lane_off, 0, hidden);
+                at_hid += step;
+            }
+            if constexpr (OUT && part == 3) {
+                if constexpr (MODE == kAlone) buf_store(make_rsrc(at_out), 4 * lane_off, 0, output);
+                else buf_store_shared(make_rsrc(at_out), 4 * lane_off, 0, output);
+                at_out += step;
+            }
         };
-        auto position = [&](int i, auto parc, auto firstc) {
-            constexpr int par = decltype(parc)::value;
-            const int p = r + i * a.d;
+        int p = r, group = 0;           // (parity of the group of positions)
+        auto position = [&](auto kc, auto firstc) {
+            constexpr int k = decltype(kc)::value, par = k & 1;
             // h_{p-d} of the four series: lane (b, s) of register m holds unit 16m + b of series s
             float vh[HG];
 #pragma unroll
             for (int m = 0; m < HG; ++m) vh[m] = hb[par][64 * m + lane];
             // two accumulators: consecutive instructions never depend on each other (measured: one, three and four are
             // slower)
-            f32x4 acc0 = half[par][w][lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
-            const float res = OUT ? rc[OUT ? (i / CH) & 1 : 0][OUT ? i % CH : 0][tid] : 0.0f;
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (!decltype(firstc)::value) store();
-            __builtin_amdgcn_sched_barrier(0);
+            f32x4 acc0 = half[group][k][w][half_lane], acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
+            const float res = OUT ? rc[OUT ? group : 0][OUT ? k : 0][tid] : 0.0f;
             static_for<0, HP / 2>([&](auto ic) {
-                constexpr int k = 2 * decltype(ic)::value;
+                constexpr int i = decltype(ic)::value, k = 2 * i;
+                // (a store between two matrix instructions: 275 -> 268 us)
+                if constexpr (!decltype(firstc)::value && i % kStoreStep == 0 && i / kStoreStep < 4) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    store(std::integral_constant<int, i / kStoreStep>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 acc0 = mfma4_bcast<k % 16>(vh[k / 16], wh[k], acc0);
                 acc1 = mfma4_bcast<(k + 1) % 16>(vh[k / 16], wh[k + 1], acc1);
             });
@@ -248,18 +303,27 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             cell = cn;
             hidden = hn;
             output = res + hn;
+            p += a.d;
             if constexpr (MODE != kAlone) stores_complete_but<kBehind * kStores>();
             lds_barrier();
         };
         using std::integral_constant;
-        position(0, integral_constant<int, 0>{}, std::true_type{});
-        int i = 1;
-        for (; i + 1 < n; i += 2) {
-            position(i, integral_constant<int, 1>{}, std::false_type{});
-            position(i + 1, integral_constant<int, 0>{}, std::false_type{});
+        // (the first position has nothing to store yet)
+        position(integral_constant<int, 0>{}, std::true_type{});
+        int left = n - 1;
+        while (left > 0) {
+            // positions 1, 2, 3 of a group and 0 of the next one
+            position(integral_constant<int, 1>{}, std::false_type{});
+            if (left == 1) break;
+            position(integral_constant<int, 2>{}, std::false_type{});
+            if (left == 2) break;
+            position(integral_constant<int, 3>{}, std::false_type{});
+            if (left == 3) break;
+            group ^= 1;
+            position(integral_constant<int, 0>{}, std::false_type{});
+            left -= 4;
         }
-        if (i < n) position(i, integral_constant<int, 1>{}, std::false_type{});
-        store();
+        static_for<0, 4>(store);
         if constexpr (MODE != kAlone) {
             stores_complete_but<0>();
             lds_barrier();
@@ -284,6 +348,7 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
     // HBM once, not four times (measured before: 2.3-2.8 times the algorithmic bytes).
     const int bt = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7), q = (blockIdx.x >> 3) & 3;
     if (bt >= a.NB) return;     // the grid is padded to whole groups of 32 (before any barrier)
+    alone_on_compute_unit<33 * 1024>();
     lstm_forward_narrow_body<HT, KXT, CP, OUT, kAlone>(a, bt, q, blockIdx.y, gridDim.y, Progress{});
 }
 

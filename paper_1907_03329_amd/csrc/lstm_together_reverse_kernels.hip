@@ -25,6 +25,7 @@ __global__ void __launch_bounds__(narrow_bwd_threads(true)) lstm_backward_togeth
     constexpr size_t bytes = std::max(Last::bytes, Later::bytes);
     __shared__ __align__(16) char lds[bytes];
     __shared__ unsigned ticket;
+    alone_on_compute_unit<(int)bytes>();
     const Place at = draw_place(t.places, &ticket);
     const Progress progress = progress_of(t.places, at, at.layer - 1);
     const int d = t.places.d[at.layer];
