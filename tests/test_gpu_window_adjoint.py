@@ -94,3 +94,43 @@ def test_default_choice_at_many_tiles_agrees_with_the_gather_kernel():
     err = ((a - b).abs().amax(dim=1) / b.abs().amax(dim=1).clamp_min(1e-30)).max().item()
     print(f"  grad_es rows: {err:.2e}", flush=True)
     assert err <= 1e-5, err
+
+
+# three row groups, and as many tiles as fill the chip: the kernel that requests a block ahead, on lengths that end in every place of a
+# block and on tiles without a block, bit for bit what the other one (fewer series tiles) gives for the same series.  (Without the level
+# penalty, whose normaliser counts all series; the comparison of the kernels at 65 536 series above has it.)
+def test_blocks_requested_ahead_give_the_same_sums():
+    import numpy as np
+    import torch
+    from paper_1907_03329_amd import binding, synth
+    cfg = small("ahead", B=16 * 4096, T=40, lambda_lv=0.0)
+    inp = synth.make_inputs(cfg.with_(B=4096), seed=5, ragged=True)
+    rng = np.random.default_rng(6)
+    lengths = np.repeat(rng.integers(cfg.I + cfg.H, cfg.T + 1, size=4096), 16).astype(np.int32)
+    y = np.tile(inp["y"], (1, 16))
+    es = np.tile(inp["es_params"], (1, 16))
+    grads = torch.Generator(device="cuda").manual_seed(7)
+    results = []
+    X = O = None
+    for B in (cfg.B, cfg.B - 16 * 512):
+        c = cfg.with_(B=B)
+        with forced(0):
+            h = binding.esrnn_create(c)
+        ws = torch.full((binding.esrnn_es_window_workspace_bytes(h) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+        dev = [torch.from_numpy(np.ascontiguousarray(v[..., :B])).cuda() for v in (y, lengths, es)]
+        binding.esrnn_es_window_forward(h, *dev, ws)
+        tiles = []
+        for which in ("grad_X", "grad_O"):
+            v = binding.esrnn_workspace_buffer(h, which)
+            P, Bp, R, _ = (int(x) for x in v.dims)
+            tiles.append(ws[v.offset_bytes // 4: v.offset_bytes // 4 + P * Bp * R].view(P, Bp // 16, R, 16))
+        if X is None:
+            X, O = (torch.randn(t.shape, generator=grads, device="cuda") for t in tiles)
+        for t, g in zip(tiles, (X, O)):
+            t.copy_(g[:, :B // 16])
+        out = torch.empty((c.K, B), dtype=torch.float32, device="cuda")
+        binding.esrnn_es_window_backward(h, *dev, ws, out)
+        results.append(out.cpu().numpy())
+        binding.esrnn_destroy(h)
+    assert np.isfinite(results[1]).all()
+    assert np.array_equal(results[0][:, :results[1].shape[1]], results[1])
