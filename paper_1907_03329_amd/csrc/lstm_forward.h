@@ -170,7 +170,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
         static_for<0, NJ>([&](auto jc) { constexpr int j = decltype(jc)::value; h_at[j] = TileHome<NPH, SH + j>::at(s, lane); });
         static_for<0, NX>([&](auto jc) { constexpr int j = decltype(jc)::value; x_at[j] = TileHome<NPX, SX + j>::at(sx, lane); });
         auto load_x = [&](int p, float (&v)[XTW]) {
-            if constexpr (LATER && NX > 0) below.wait(min(p, Pt - 1));
+            if constexpr (LATER && NX > 0) below.wait<kWidePollSleep>(min(p, Pt - 1));
             const buf_rsrc rx = make_rsrc(a.xsrc + ((size_t)min(p, Pt - 1) * a.NB + bt) * (KXT * 64));
 #pragma unroll
             for (int j = 0; j < NX; ++j) v[j] = LATER ? buf_load_shared(rx, lane4, (sx + W * j) * 256) : buf_load(rx, lane4, (sx + W * j) * 256);
@@ -184,7 +184,7 @@ __device__ __forceinline__ void lstm_forward_body(const LstmFwdArgs &a, int bt, 
         };
         auto load_res = [&](int p, float (&v)[MTW]) {
             if constexpr (OUT) {
-                if constexpr (LATER && NX == 0) below.wait(min(p, Pt - 1));
+                if constexpr (LATER && NX == 0) below.wait<kWidePollSleep>(min(p, Pt - 1));
                 const buf_rsrc rr = make_rsrc(a.resid + ((size_t)min(p, Pt - 1) * a.NB + bt) * HT * 64);
 #pragma unroll
                 for (int j = 0; j < NJ; ++j) v[j] = LATER ? buf_load_shared(rr, lane4, (s + W * j) * 256) : buf_load(rr, lane4, (s + W * j) * 256);

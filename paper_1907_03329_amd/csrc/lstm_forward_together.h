@@ -6,8 +6,8 @@
 // Whole calls: 7 quarterly series 80 -> 58 us, step of 16 211 -> 188 us, forecasts of 333 hourly ones 540 -> 431 us, step of 512
 // 1770 -> 1740 us (the third layer, in a launch of its own behind the two, takes 87 us instead of 65).  What bounds it is the first
 // layer's chain; at the end every layer adds what a store, a look and a load past the caches take and a few positions of its own,
-// some 5 us.  512 hourly series: the first layer alone in this launch 285 us, 338 us beside a second one that waits for nothing, 363 us as
-// it is; looks half as often change that by 3 % and cost small batches more.
+// some 5 us.  512 hourly series: the first layer alone in this launch 285 us, 338 us beside a second one that waits for nothing, 355 us as
+// it is.
 #pragma once
 
 #include "lstm_forward.h"

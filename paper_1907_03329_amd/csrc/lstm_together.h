@@ -29,6 +29,10 @@ namespace esrnn {
 namespace {
 
 constexpr int kPollSleep = 4;       // (times 64 clocks)
+// in 16-series layers, whose eight waves all look, four to sixteen words each: first two layers of 512 hourly series 368 - 378 us with 4,
+// 356 with 20, 351 - 360 with 40, 360 with 120; of 501 monthly ones and for forecasts of 333 hourly ones level.  (In 4-series layers, one
+// wave of four words, 40 costs 7 quarterly series 3 us of 41.)
+constexpr int kWidePollSleep = 40;
 constexpr int kMostLooks = 1 << 22; // (seconds)
 
 // Memory operations of this wave are complete, but for the last N.
@@ -117,12 +121,13 @@ struct Below {
     }
     __device__ __forceinline__ void look() { have = __builtin_bit_cast(int, buf_load_shared(make_rsrc(g.below), 4 * kWordStride * word, 0)); }
     // until position p is complete in every class of the layer below
+    template <int pause = kPollSleep>
     __device__ __forceinline__ void wait(int p)
     {
         for (int i = lost ? kMostLooks : 0; __ballot((int)first + have > p) != ~0ull; ++i) {
             asm volatile("" ::: "memory");
             if (i == kMostLooks) { lost = true; break; }
-            __builtin_amdgcn_s_sleep(kPollSleep);
+            __builtin_amdgcn_s_sleep(pause);
             look();
         }
         asm volatile("" ::: "memory");
