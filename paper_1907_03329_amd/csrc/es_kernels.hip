@@ -139,9 +139,9 @@ struct PackLstmArgs {
 
 // Operands of the 4-series kernels.  v_mfma_f32_4x4x1: lane l supplies A[l%4] of block l/4.
 //   forward  [wave][column k of h][lane]: gate l/16 of unit wave*HT + min(l%16, HT-1) (the lanes past HT
-//            repeat the last unit, so that all lanes do the same work on the same addresses); then those of x on the bf16 pipe,
-//            three parts of W (three_term.h) as [wave][column tile][quads of x][lane][dword], column c = 16*tile + l%16 is gate c/HT
-//            of unit wave*HT + c%HT
+//            repeat the last unit, so that all lanes do the same work on the same addresses); then those of x
+//            for v_mfma_f32_16x16x4, [wave][column tile][unit tile k of x][lane]: column c = 16*tile + l%16, gate c/HT of unit
+//            wave*HT + c%HT, row 4*k + l/16 of x
 //   reverse  [wave][group g][k-step 4*u + gate][lane]: W[gate, unit wave*HT + u][column 64*g + l]
 __device__ __forceinline__ void pack_forward_narrow(const PackLstmArgs &a, int block, int n_blocks)
 {
@@ -150,16 +150,11 @@ __device__ __forceinline__ void pack_forward_narrow(const PackLstmArgs &a, int b
         const int lane = idx & 63, k = (idx >> 6) % HP, w = (idx >> 6) / HP;
         a.fwd[idx] = a.at(lane >> 4, w * a.HT + min(lane & 15, a.HT - 1), false, k);
     }
-    const int np = (a.KXT + 1) / 2, quads = tt_a_quads(np), tiles = (a.HT + 3) / 4, nx = 4 * tiles * quads * 256;
-    unsigned *const x = reinterpret_cast<unsigned *>(a.fwd + n);
+    const int tiles = (a.HT + 3) / 4, nx = 4 * tiles * a.KXT * 64;
     for (int idx = block * 256 + threadIdx.x; idx < nx; idx += n_blocks * 256) {
-        const int d = idx & 3, lane = (idx >> 2) & 63, q = (idx >> 8) % quads, t = (idx >> 8) / quads % tiles, w = (idx >> 8) / (quads * tiles);
-        const int c = 16 * t + (lane & 15), gate = c / a.HT, unit = w * a.HT + c % a.HT, k = lane >> 4;
-        const TtDword part = tt_a_dword(np, q, d);
-        const bool exists = c < HP;
-        const Parts p = split_pair(exists ? splittable(a.at(gate, unit, true, 8 * part.pair + k)) : 0.0f,
-                                   exists ? splittable(a.at(gate, unit, true, 8 * part.pair + 4 + k)) : 0.0f);
-        x[idx] = part_of(p, part.part);
+        const int lane = idx & 63, k = (idx >> 6) % a.KXT, t = (idx >> 6) / a.KXT % tiles, w = (idx >> 6) / (a.KXT * tiles);
+        const int c = 16 * t + (lane & 15);
+        a.fwd[n + idx] = c < HP ? a.at(c / a.HT, w * a.HT + c % a.HT, true, 4 * k + (lane >> 4)) : 0.0f;
     }
 }
 __device__ __forceinline__ void pack_backward_narrow(const PackLstmArgs &a, int block, int n_blocks)

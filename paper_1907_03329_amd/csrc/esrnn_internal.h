@@ -49,7 +49,7 @@ struct LayerPlan {
                          // r, r+chains, ... (mod dil)
     int chains_bwd;      // the same for the reverse kernel
     int split_bwd;       // 1: 4-series reverse kernel with twelve waves, staging and weight gradient on waves of their own, one workgroup per compute unit
-    int narrow_fwd;      // 1: forward pass on the 4-series kernel (lstm_narrow_fwd.h): wpack_fwd is [4][4*HT][64] and the parts of W_x,
+    int narrow_fwd;      // 1: forward pass on the 4-series kernel (lstm_narrow_fwd.h): wpack_fwd is [4][4*HT][64] for h and [4][(HT+3)/4][KXT][64] for x,
                          // bias_pack unused
     int narrow_bwd;      // 1: reverse pass on the 4-series kernel (lstm_narrow_bwd.h): wpack_bwd is [4][NG][4*HT][64], and the
                          // weight-gradient partials are indexed by 4*NB*chains_bwd workgroups

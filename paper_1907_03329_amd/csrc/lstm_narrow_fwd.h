@@ -5,7 +5,6 @@
 
 #include "lstm_narrow_common.h"
 #include "lstm_together.h"
-#include "three_term.h"
 
 namespace esrnn {
 
@@ -13,7 +12,7 @@ namespace {
 
 struct NarrowFwdArgs {
     const float *wpack;   // [4][4*HT][64] weights of h: wave, column, lane (gate l/16 of unit l%16 of the wave), then
-                          // [4][column tiles][quads][64][4] those of x: columns (gate, unit of the wave), split in three
+                          // [4][column tiles][KXT][64] those of x: columns (gate, unit of the wave)
     const float *bias;    // caller's bias vector [4h]
     const float *xsrc;    // TL(4*KXT)
     float *gates;         // TL(HP) x [4]
@@ -39,17 +38,18 @@ __device__ __forceinline__ f32x4 (&input_halves())[2][kInputGroup][kNW][64]
 }
 
 // Waves 0-3 carry the recurrence; waves 4-7, on the same SIMDs, bring the inputs and form the input half of the
-// pre-activations (with the bias), which does not depend on it, on the bf16 matrix pipe: x of four positions and four series is
-// the 16 rows of one operand, a wave's gates and units the columns of the other, and a lane ends up with what one lane of the chain
+// pre-activations (with the bias), which does not depend on it: x of four positions and four series is the 16 rows of
+// v_mfma_f32_16x16x4, a wave's gates and units the columns, and a lane ends up with what one lane of the chain
 // wave takes, four series of a gate and unit.  The chain then has 4 HT matrix instructions a position, and no request of its own.
 // Both kinds meet the same barriers.
-// What bounds it: the chain, 230 of 268 us without stores and input half (512 hourly series, first layer, 24 + 40 columns, 649
+// What bounds it: the chain, 230 of 260 us without stores and input half (512 hourly series, first layer, 24 + 40 columns, 649
 // positions): some 150 ns a position from the state's LDS write over the barrier to its read, 40 matrix instructions of 3.7 ns,
-// the gates.  Without the stores alone 253 us, without five of six of the input waves' products 257 us.  Input half with fp32 products a
-// position at a time (24 of them, which share the issue with the chain's vector instructions): 301 us; 501 monthly series (20 + 50
-// columns, 211 positions) 111 -> 103 us, 16 quarterly ones (4 + 40 columns, 61 positions) 26.1 -> 25.0 us, their second layer (40 + 40)
-// 18.7 -> 17.1 us.  Tried: stores spread over the matrix instructions (272 instead of 268 us), three accumulators instead of two,
-// contraction split over the rows of a wave, ten waves (nothing gained: the barrier takes longer, 186 ns instead of 150).
+// the gates.  Input half on the 4x4x1 instruction, a position at a time: 295 us; 512 monthly series (12 + 50 columns, 211 positions)
+// 100 -> 90 us; all layers of 16 quarterly ones in one launch 44 -> 41 us.  With three-term bf16 products the input waves need fewer
+// cycles of the matrix pipe but hold 1.5 times the weights (later layers of hidden 50: 180 registers, and no second workgroup on a compute
+// unit; now 120), and infinite operands become finite ones: 268 us; step of 64 hourly series 10 us more.  Tried: stores spread over the matrix
+// instructions (within 2 %), three accumulators instead of two, contraction split over the rows of a wave, ten waves (nothing gained: the
+// barrier takes longer, 186 ns instead of 150).
 //
 // One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ... (of several layers in one launch:
 // its only one).
@@ -82,24 +82,26 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
 
     if (wave >= kNW) {
         // =========================== input waves ===========================
-        // x (16 rows: position, series) times W_x^T (columns: gate, unit of the wave), on the bf16 matrix pipe (three_term.h)
-        constexpr int NP = (KXT + 1) / 2, AQ = tt_a_quads(NP), BQ = tt_b_quads(NP), TILES = (HT + 3) / 4;
-        const u32x4 *wpack = reinterpret_cast<const u32x4 *>(a.wpack + (size_t)kNW * HP * 64) + (size_t)w * TILES * AQ * 64 + lane;
-        u32x4 wx[TILES][AQ];
+        // x (16 rows: position, series) times W_x^T (columns: gate, unit of the wave)
+        constexpr int TILES = (HT + 3) / 4;
+        const float *wpack = a.wpack + (size_t)kNW * HP * 64 + (size_t)w * TILES * KXT * 64 + lane;
+        float wx[TILES][KXT];
         float bias[TILES];
+        bool real[TILES];           // (infinite inputs times the zeros of a unit that only pads stay out of its state)
         int to[TILES];              // where a column goes: gate in rows of sixteen lanes
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
 #pragma unroll
-            for (int m = 0; m < AQ; ++m) wx[t][m] = wpack[(t * AQ + m) * 64];
+            for (int k = 0; k < KXT; ++k) wx[t][k] = wpack[(t * KXT + k) * 64];
             const int c = 16 * t + blk, gate = c / HT, u = w * HT + c % HT;
-            bias[t] = c < HP && u < a.h ? a.bias[gate * a.h + u] : 0.0f;
+            real[t] = c < HP && u < a.h;
+            bias[t] = real[t] ? a.bias[gate * a.h + u] : 0.0f;
             to[t] = c < HP ? 16 * gate + c % HT : -1;
         }
         Below below(progress);
         for (int r = chain; r < a.d && r < Pt; r += chains) {
             const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
-            float xs[2 * NP], rs[kInputGroup];
+            float xs[KXT], rs[kInputGroup];
             // requests of the four positions from the i-th on (past the chain its last)
             auto request = [&](int i) {
                 // before them, the layer below has all of it
@@ -113,11 +115,11 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                     const buf_rsrc x = make_rsrc(a.xsrc + tile * (KX * 16));
                     const int from = 4 * (mine * a.d * a.NB * (KX * 16) + at);
 #pragma unroll
-                    for (int k = 0; k < 2 * NP; ++k) xs[k] = k < KXT ? buf_load_shared(x, from, 256 * k) : 0.0f;
+                    for (int k = 0; k < KXT; ++k) xs[k] = buf_load_shared(x, from, 256 * k);
                 } else {
                     const float *x = a.xsrc + (tile + (size_t)(mine * a.d) * a.NB) * (KX * 16) + at;
 #pragma unroll
-                    for (int k = 0; k < 2 * NP; ++k) xs[k] = k < KXT ? x[64 * k] : 0.0f;
+                    for (int k = 0; k < KXT; ++k) xs[k] = x[64 * k];
                 }
                 if constexpr (OUT) {
 #pragma unroll
@@ -128,22 +130,11 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
-            // what has been requested in parts, as operands; residual inputs in LDS
-            u32x4 xq[BQ];
+            // what has been requested: operands (in registers of their own, those of the requests are the next ones'), residual inputs in LDS
+            float xq[KXT];
             auto arrive = [&](int par) {
-                Parts p[4 * ((NP + 3) / 4)];
-                auto value = [&](int k) { return splittable(MODE == kLater ? below.checked(xs[k]) : xs[k]); };
 #pragma unroll
-                for (int k = 0; k < 4 * ((NP + 3) / 4); ++k) p[k] = k < NP ? split_pair(value(2 * k), 2 * k + 1 < KXT ? value(2 * k + 1) : 0.0f) : Parts{0, 0, 0};
-                static_for<0, BQ>([&](auto qc) {
-                    constexpr int b = decltype(qc)::value, full = tt_full(NP), rest = b - 3 * full;
-                    static_for<0, 4>([&](auto dc) {
-                        constexpr int d = decltype(dc)::value;
-                        constexpr int pair = rest < 0 ? 4 * (b / 3) + d : 4 * full + (tt_rest(NP) == 2 ? d & 1 : 0);
-                        constexpr int part = rest < 0 ? b % 3 : tt_rest(NP) == 1 ? d % 3 : rest == 0 ? d / 2 : d < 2 ? 2 : 0;
-                        xq[b][d] = part_of(p[pair], part);
-                    });
-                });
+                for (int k = 0; k < KXT; ++k) xq[k] = __builtin_canonicalizef(MODE == kLater ? below.checked(xs[k]) : xs[k]);
                 if constexpr (OUT) {
 #pragma unroll
                     for (int g = 0; g < kInputGroup; ++g) rc[par][g][tid] = MODE == kLater ? below.checked(rs[g]) : rs[g];
@@ -153,15 +144,10 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             auto products = [&](auto from, auto end, int par) {
                 static_for<decltype(from)::value, decltype(end)::value>([&](auto tc) {
                     constexpr int t = decltype(tc)::value;
-                    // (two sums: a chain of half the length)
-                    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-                    static_for<0, tt_mfmas(NP)>([&](auto ic) {
-                        constexpr int i = decltype(ic)::value;
-                        constexpr TtPair m = tt_mfma(NP, i);
-                        acc[i % 2] = mfma_bf16(xq[m.b], wx[t][m.a], acc[i % 2]);
-                    });
-                    const f32x4 sum = acc[0] + acc[1];
-                    if (to[t] >= 0) half[par][j][w][to[t]] = f32x4{sum[0] + bias[t], sum[1] + bias[t], sum[2] + bias[t], sum[3] + bias[t]};
+                    f32x4 sum = f32x4{bias[t], bias[t], bias[t], bias[t]};
+#pragma unroll
+                    for (int k = 0; k < KXT; ++k) sum = mfma16(xq[k], wx[t][k], sum);
+                    if (to[t] >= 0) half[par][j][w][to[t]] = real[t] ? sum : f32x4{0.f, 0.f, 0.f, 0.f};
                 });
             };
             // after the barrier of the i-th position

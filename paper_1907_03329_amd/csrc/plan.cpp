@@ -235,7 +235,7 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
         lp.split_bwd = lp.narrow_bwd && groups * lp.chains_bwd <= 256 ? 1 : 0;
         // The forward operands lie where the first reduction stage of the weight gradient comes at the end of the reverse
         // pass, which does not need them any more and packs none for the next forward pass.
-        const size_t fwd_pack = lp.narrow_fwd ? (size_t)4 * 4 * pl.HT * 64 + (size_t)4 * ceil_div(pl.HT, 4) * tt_a_quads((lp.KXT + 1) / 2) * 256
+        const size_t fwd_pack = lp.narrow_fwd ? (size_t)4 * (4 * pl.HT + ceil_div(pl.HT, 4) * lp.KXT) * 64
                                               : (size_t)pl.HT * (tt_a_quads((lp.KXT + 1) / 2) + tt_a_quads((pl.HT + 1) / 2)) * 256;
         lp.wpack_fwd = lp.dw_reduced = ws.take(std::max((size_t)kReduceSplits * pl.HT * MB * 256, fwd_pack));
         lp.bias_pack = lp.narrow_fwd ? lp.wpack_fwd : ws.take((size_t)pl.HT * 16);   // (unused by the 4-series kernel)
