@@ -30,10 +30,11 @@ struct NarrowFwdArgs {
 constexpr int kInputGroup = 4;
 
 // Input half of the pre-activations, two groups of positions: one object for all kinds of layers of a kernel, each of which has
-// arrays of its own otherwise.
-__device__ __forceinline__ f32x4 (&input_halves())[2][kInputGroup][kNW][64]
+// arrays of its own otherwise.  A place a wave takes the columns that only pad.
+using InputHalves = f32x4[2][kInputGroup][kNW][64 + 1];
+__device__ __forceinline__ InputHalves &input_halves()
 {
-    __shared__ f32x4 half[2][kInputGroup][kNW][64];
+    __shared__ InputHalves half;
     return half;
 }
 
@@ -42,12 +43,14 @@ __device__ __forceinline__ f32x4 (&input_halves())[2][kInputGroup][kNW][64]
 // v_mfma_f32_16x16x4, a wave's gates and units the columns, and a lane ends up with what one lane of the chain
 // wave takes, four series of a gate and unit.  The chain then has 4 HT matrix instructions a position, and no request of its own.
 // Both kinds meet the same barriers.
-// What bounds it: the chain, 230 of 260 us without stores and input half (512 hourly series, first layer, 24 + 40 columns, 649
+// What bounds it: the chain, 230 of 250 us without stores and input half (512 hourly series, first layer, 24 + 40 columns, 649
 // positions): some 150 ns a position from the state's LDS write over the barrier to its read, 40 matrix instructions of 3.7 ns,
 // the gates.  Input half on the 4x4x1 instruction, a position at a time: 295 us; 512 monthly series (12 + 50 columns, 211 positions)
 // 100 -> 90 us; all layers of 16 quarterly ones in one launch 44 -> 41 us.  With three-term bf16 products the input waves need fewer
 // cycles of the matrix pipe but hold 1.5 times the weights (later layers of hidden 50: 180 registers, and no second workgroup on a compute
-// unit; now 120), and infinite operands become finite ones: 268 us; step of 64 hourly series 10 us more.  Tried: stores spread over the matrix
+// unit; now 125), and infinite operands become finite ones: 268 us; step of 64 hourly series 10 us more.  All columns of x requested by every
+// wave: forecasts of 333 hourly series 362 instead of 345 us, forward pass of 64 monthly ones 175.9 instead of 172.6.  (With one unit tile of x,
+// dealt columns cost 16 quarterly series 2 us of 64.)  Tried: stores spread over the matrix
 // instructions (within 2 %), three accumulators instead of two, contraction split over the rows of a wave, ten waves (nothing gained: the
 // barrier takes longer, 186 ns instead of 150).
 //
@@ -55,7 +58,8 @@ __device__ __forceinline__ f32x4 (&input_halves())[2][kInputGroup][kNW][64]
 // its only one).
 // CP: the layer's cell states enter the cell-state penalty; OUT: the layer ends a residual block (reads the
 // block input, writes the block output).
-template <int HT, int KXT, bool CP, bool OUT, int MODE>
+// COUNTED: a first layer counts every so many positions.
+template <int HT, int KXT, bool CP, bool OUT, int MODE, int COUNTED = 1>
 __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a, int bt, int q, int chain, int chains, const Progress &progress)
 {
     constexpr int KX = 4 * KXT, HP = 4 * HT;
@@ -63,7 +67,12 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     constexpr int kStoreStep = 1;          // pairs of matrix instructions between two stores
     __shared__ float rc[OUT ? 2 : 1][OUT ? kInputGroup : 1][kNT];      // residual input of a thread's (unit, series), by group of positions
     __shared__ float hb[2][HG * 64];            // h_{p-d} [unit][series], by position parity
-    f32x4 (&half)[2][kInputGroup][kNW][64] = input_halves();
+    InputHalves &half = input_halves();
+    // Every input wave needs all columns of x.  Each requests a quarter of them, a position before the products, and they meet in LDS; a
+    // layer that follows another one has no position to spare, and every wave of it requests them all.
+    constexpr bool kDealt = MODE != kLater && KXT > 1;
+    constexpr int NX = kDealt ? (KXT + kNW - 1) / kNW : KXT;
+    __shared__ float x_dealt[kDealt ? KXT : 1][64];     // [unit tile][lane of the operand]
     // positions whose stores may still be under way when the next one is counted: a position of a first layer takes less
     // time than a store
     constexpr int kBehind = MODE == kFirst ? 3 : 1, kStores = OUT ? 4 : 3;
@@ -79,6 +88,8 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     const int lane_off = unit * 16 + 4 * q + j;
     // columns past HP in the last group of 16 are never written: zero once (their weights do not exist)
     for (int e = threadIdx.x; e < 2 * HG * 64; e += 2 * kNT) (&hb[0][0])[e] = 0.0f;
+    if (a.h < HP)
+        for (int e = threadIdx.x; e < 2 * kInputGroup * kNW * (64 + 1); e += 2 * kNT) (&half[0][0][0][0])[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     if (wave >= kNW) {
         // =========================== input waves ===========================
@@ -87,21 +98,22 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
         const float *wpack = a.wpack + (size_t)kNW * HP * 64 + (size_t)w * TILES * KXT * 64 + lane;
         float wx[TILES][KXT];
         float bias[TILES];
-        bool real[TILES];           // (infinite inputs times the zeros of a unit that only pads stay out of its state)
-        int to[TILES];              // where a column goes: gate in rows of sixteen lanes
+        // where a column goes: gate in rows of sixteen lanes.  (What a unit that only pads has there stays zero: infinite inputs times its
+        // weights of zero would be its state.)
+        int to[TILES];
 #pragma unroll
         for (int t = 0; t < TILES; ++t) {
 #pragma unroll
             for (int k = 0; k < KXT; ++k) wx[t][k] = wpack[(t * KXT + k) * 64];
             const int c = 16 * t + blk, gate = c / HT, u = w * HT + c % HT;
-            real[t] = c < HP && u < a.h;
-            bias[t] = real[t] ? a.bias[gate * a.h + u] : 0.0f;
-            to[t] = c < HP ? 16 * gate + c % HT : -1;
+            const bool exists = c < HP && u < a.h;
+            bias[t] = exists ? a.bias[gate * a.h + u] : 0.0f;
+            to[t] = exists ? 16 * gate + c % HT : 64;
         }
         Below below(progress);
         for (int r = chain; r < a.d && r < Pt; r += chains) {
             const int n = (Pt - r + a.d - 1) / a.d;            // positions of this chain: r, r+d, ...
-            float xs[KXT], rs[kInputGroup];
+            float xs[NX], rs[kInputGroup];
             // requests of the four positions from the i-th on (past the chain its last)
             auto request = [&](int i) {
                 // before them, the layer below has all of it
@@ -115,11 +127,11 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                     const buf_rsrc x = make_rsrc(a.xsrc + tile * (KX * 16));
                     const int from = 4 * (mine * a.d * a.NB * (KX * 16) + at);
 #pragma unroll
-                    for (int k = 0; k < KXT; ++k) xs[k] = buf_load_shared(x, from, 256 * k);
+                    for (int k = 0; k < NX; ++k) xs[k] = buf_load_shared(x, from, 256 * k);
                 } else {
                     const float *x = a.xsrc + (tile + (size_t)(mine * a.d) * a.NB) * (KX * 16) + at;
 #pragma unroll
-                    for (int k = 0; k < KXT; ++k) xs[k] = x[64 * k];
+                    for (int k = 0; k < NX; ++k) xs[k] = x[64 * (kDealt ? min(w + kNW * k, KXT - 1) : k)];
                 }
                 if constexpr (OUT) {
 #pragma unroll
@@ -130,14 +142,25 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                 }
                 __builtin_amdgcn_sched_barrier(0);
             };
-            // what has been requested: operands (in registers of their own, those of the requests are the next ones'), residual inputs in LDS
+            // what has been requested: operands (in LDS, or in registers of their own, those of the requests are the next ones'), residual
+            // inputs in LDS
             float xq[KXT];
             auto arrive = [&](int par) {
 #pragma unroll
-                for (int k = 0; k < KXT; ++k) xq[k] = __builtin_canonicalizef(MODE == kLater ? below.checked(xs[k]) : xs[k]);
+                for (int k = 0; k < NX; ++k) {
+                    if constexpr (!kDealt) xq[k] = __builtin_canonicalizef(MODE == kLater ? below.checked(xs[k]) : xs[k]);
+                    else if (w + kNW * k < KXT) x_dealt[w + kNW * k][lane] = xs[k];
+                }
                 if constexpr (OUT) {
 #pragma unroll
                     for (int g = 0; g < kInputGroup; ++g) rc[par][g][tid] = MODE == kLater ? below.checked(rs[g]) : rs[g];
+                }
+            };
+            // (behind a barrier after the arrival)
+            auto collect = [&]() {
+                if constexpr (kDealt) {
+#pragma unroll
+                    for (int k = 0; k < KXT; ++k) xq[k] = x_dealt[k][lane];
                 }
             };
             // column tiles [from, end), left for the group of parity par: a lane has position j, its column, and four series
@@ -147,7 +170,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                     f32x4 sum = f32x4{bias[t], bias[t], bias[t], bias[t]};
 #pragma unroll
                     for (int k = 0; k < KXT; ++k) sum = mfma16(xq[k], wx[t][k], sum);
-                    if (to[t] >= 0) half[par][j][w][to[t]] = real[t] ? sum : f32x4{0.f, 0.f, 0.f, 0.f};
+                    half[par][j][w][to[t]] = sum;
                 });
             };
             // after the barrier of the i-th position
@@ -161,6 +184,8 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
             __syncthreads();            // LDS free: initial clearing, or the last position of the previous chain
             arrive(0);
             if constexpr (MODE != kLater) request(kInputGroup);
+            if constexpr (kDealt) lds_barrier();
+            collect();
             products(none, all, 0);
             lds_barrier();
             // Four positions are one straight run of instructions, in which the next four's input half is formed.  A layer that
@@ -181,12 +206,13 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
                             arrive(par);
                             request(i + 2 * kInputGroup);
                         } else {
+                            if constexpr (k == 1) collect();
                             products(integral_constant<int, (k - 1) * TILES / 3>{}, integral_constant<int, k * TILES / 3>{}, par);
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);      // (a third of the products in every position, not all in one)
                     lds_barrier();
-                    count(i + k);
+                    if constexpr (k % COUNTED == 0) count(i + k);
                 });
                 i += kInputGroup;
                 par ^= 1;
@@ -224,6 +250,7 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
         float creg = 0.0f;
         __syncthreads();
         for (int e = tid; e < 4 * HP; e += kNT) hb[0][e] = 0.0f;    // start of a chain: zero state
+        if constexpr (kDealt) lds_barrier();
         lds_barrier();
         // What a position leaves in memory is stored while the next one waits for its first operands from LDS, through
         // scalar pointers that move on by a position.
