@@ -27,11 +27,9 @@ struct FwdTogetherArgs {
 enum { kAllNarrow, kWideStash, kWideNoStash };
 
 template <int HT, int KXT, bool CP, int KIND>
-__global__ void __launch_bounds__(2 * kNT) lstm_forward_together_kernel(FwdTogetherArgs t)
+__global__ void __launch_bounds__(2 * kNT, KIND == kAllNarrow ? 4 : 2) lstm_forward_together_kernel(FwdTogetherArgs t)
 {
     __shared__ unsigned ticket;
-    // (32 KB of input halves, and what is known of the rest: all 4-series layers 46 - 48 KB, with a 16-series one 50 - 98)
-    alone_on_compute_unit<KIND == kAllNarrow ? 45 * 1024 : HT == 2 ? 50 * 1024 : HT == 8 ? 68 * 1024 : HT == 10 ? 77 * 1024 : 96 * 1024>();
     const Place at = draw_place(t.places, &ticket);
     const int l = at.layer, d = t.places.d[l], bt = at.bt, q = at.q, chain = at.chain;
     const bool wide = KIND != kAllNarrow && l == t.places.layers - 1;

@@ -110,10 +110,11 @@ __device__ __forceinline__ void row_transpose(f32x4 &v)
     v = f32x4{v0, v1, v2, v3};
 }
 
-// LDS that a kernel takes only so that no two of its workgroups share a compute unit: more than half of the 160 KB together with the
-// `used` bytes that it needs.  Grids of at most one workgroup per compute unit do not spread by themselves, and chains that share
-// their SIMDs slow each other down: two forward layers for forecasts of 333 hourly series 294 -> 275 us, first layers of 1024
-// quarterly ones (256 workgroups) 31.5 -> 30.1 us.
+// LDS that the twelve-wave reverse kernels take only so that no two of their workgroups share a compute unit: more than half of the 160 KB
+// together with the `used` bytes that they need.  They have at most one workgroup per compute unit; where registers leave room for two,
+// chains would share their SIMDs.  With / without: first layer of 501 monthly series 110 / 119 us, of 512 hourly ones 271 / 266.
+// Forward kernels leave that room: alone on the chip they are as fast, and several streams that serve small requests share compute units
+// (four streams, forward passes of 1024 quarterly series 345 us each round instead of 365, of 64 monthly ones 315 instead of 360).
 template <int used>
 __device__ __forceinline__ void alone_on_compute_unit()
 {

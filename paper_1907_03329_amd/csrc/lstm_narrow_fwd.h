@@ -352,8 +352,9 @@ __device__ __forceinline__ void lstm_forward_narrow_body(const NarrowFwdArgs &a,
     }
 }
 
+// (four waves a SIMD, two workgroups a compute unit)
 template <int HT, int KXT, bool CP, bool OUT>
-__global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdArgs a)
+__global__ void __launch_bounds__(2 * kNT, 4) lstm_forward_narrow_kernel(NarrowFwdArgs a)
 {
     // The four workgroups of a 16-series tile share every 64-byte row of the tile.  Consecutive workgroup
     // ids go round the 8 XCDs, each with its own L2: ids x, x+8, x+16, x+24 of a group of 32 are the four
@@ -361,7 +362,6 @@ __global__ void __launch_bounds__(2 * kNT) lstm_forward_narrow_kernel(NarrowFwdA
     // HBM once, not four times (measured before: 2.3-2.8 times the algorithmic bytes).
     const int bt = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7), q = (blockIdx.x >> 3) & 3;
     if (bt >= a.NB) return;     // the grid is padded to whole groups of 32 (before any barrier)
-    alone_on_compute_unit<33 * 1024>();
     lstm_forward_narrow_body<HT, KXT, CP, OUT, kAlone>(a, bt, q, blockIdx.y, gridDim.y, Progress{});
 }
 

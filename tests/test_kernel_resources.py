@@ -13,8 +13,8 @@ BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
 
 
 @pytest.fixture(scope="module")
-def resources(tmp_path_factory):
-    """{kernel: (bytes of scratch per lane, bytes of static LDS)}"""
+def notes(tmp_path_factory):
+    """{kernel: (bytes of scratch per lane, bytes of static LDS, registers)}"""
     if not os.path.exists(binding.LIB_PATH):
         build.build()
     data = open(binding.LIB_PATH, "rb").read()
@@ -31,12 +31,18 @@ def resources(tmp_path_factory):
             path.write_bytes(data[at + offset:at + offset + size])
             notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
             names = re.findall(r"^\s+\.name:\s+(_Z\S+)\s*$", notes, re.M)
-            sizes = [[int(v) for v in re.findall(rf"^\s+\.{kind}_segment_fixed_size:\s+(\d+)\s*$", notes, re.M)]
-                     for kind in ("private", "group")]
-            assert len(names) == len(sizes[0]) == len(sizes[1])
+            sizes = [[int(v) for v in re.findall(rf"^\s+\.{kind}:\s+(\d+)\s*$", notes, re.M)]
+                     for kind in ("private_segment_fixed_size", "group_segment_fixed_size", "vgpr_count")]
+            assert all(len(names) == len(s) for s in sizes)
             out.update(zip(names, zip(*sizes)))
         at = data.find(BUNDLE, at + 1)
     return out
+
+
+@pytest.fixture(scope="module")
+def resources(notes):
+    """{kernel: (bytes of scratch per lane, bytes of static LDS)}"""
+    return {k: v[:2] for k, v in notes.items()}
 
 
 def test_rows_requested_ahead_stay_in_registers(resources):
@@ -50,3 +56,16 @@ def test_rows_requested_ahead_stay_in_registers(resources):
 def test_static_lds_stays_within_128_kb(resources):
     """An output-stage shape with 135 KB of static LDS has launched without an error and computed wrong outputs."""
     assert not {k: lds for k, (_, lds) in resources.items() if lds > 128 * 1024}
+
+
+def test_forward_workgroups_of_several_streams_share_a_compute_unit(notes):
+    """4-series forward kernels, eight waves each: two fit into the 160 KB and 512 registers a SIMD, so that streams run side by side."""
+    kernels = {k: v for k, v in notes.items() if re.search(r"lstm_forward_narrow_kernel|lstm_forward_together_kernelI(Li\d+E){2}Lb\dELi0E", k)}
+    assert len(kernels) == 14 * (4 + 2)
+    assert not {k: (lds, registers) for k, (_, lds, registers) in kernels.items() if lds > 80 * 1024 or registers > 128}
+
+
+def test_twelve_wave_workgroups_have_a_compute_unit_each(notes):
+    kernels = {k: lds for k, (_, lds, _) in notes.items() if re.search(r"lstm_backward_(narrow_kernelI(Li\d+E){2}Lb\dELb1E|together)", k)}
+    assert len(kernels) == 14 * (2 + 2)
+    assert not {k: lds for k, lds in kernels.items() if lds <= 80 * 1024}
