@@ -100,7 +100,9 @@ struct NarrowBwdLds {                                   // (references: an objec
     }
 };
 
-// One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ...
+// One workgroup: quarter q of series tile bt, residue classes chain, chain + chains, ...  (With twelve waves one class: a grid with fewer
+// chains than classes is too large for them.  Without the loops over classes the first layer of 501 monthly series takes 115 us instead
+// of 110, of 512 hourly ones as long.)
 template <int HT, int KXT, bool CP, bool SPLIT, int MODE>
 __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a, const NarrowBwdLds<HT, KXT, SPLIT, MODE> &lds, int bt, int q,
                                                           int chain, int chains, const Progress &progress)
@@ -112,10 +114,11 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
     constexpr int KX = Lds::KX, HP = Lds::HP, KT4 = Lds::KT4, NG = Lds::NG, CT = Lds::CT;
     constexpr bool kThree = Lds::kThree;
     constexpr int kAhead = narrow_bwd_gradient_sets(MODE);
-    // 16-row tiles of dW per wave (a row tile = 4 units x 4 gates).  On the bf16 pipe, tiles that are left when every wave has as many
-    // are shared by kShare waves, which take every kShare-th column tile of it.
+    // 16-row tiles of dW per wave (a row tile = 4 units x 4 gates).  With twelve waves, tiles that are left when every wave has as many are
+    // shared by kShare waves, which take every kShare-th column tile of it.  (A whole one more in the first wave: up to 12 registers in
+    // scratch memory at hidden 50, layers of one launch.  With four waves it is the other way round.)
     constexpr int MTW = (HT + kNW - 1) / kNW;
-    constexpr int kLeft = kThree ? HT % kNW : 0, kFull = kThree ? HT / kNW : MTW, kShare = kLeft ? kNW / kLeft : 1, CL = kLeft ? (CT + kShare - 1) / kShare : 1;
+    constexpr int kLeft = SPLIT ? HT % kNW : 0, kFull = SPLIT ? HT / kNW : MTW, kShare = kLeft ? kNW / kLeft : 1, CL = kLeft ? (CT + kShare - 1) / kShare : 1;
     static_assert(kLeft != 3, "tiles that are left are shared by 4 or 2 waves");
     // elements (column, series) of [x ; h] that a thread brings: number tid, and tid + kNT where there are as many
     constexpr bool kTwo = 4 * KT4 > kNT;
@@ -165,7 +168,7 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
         };
 #pragma unroll
         for (int t = 0; t < kFull; ++t)
-            if (w + kNW * t < HT) {
+            if (SPLIT || w + kNW * t < HT) {
 #pragma unroll
                 for (int nb = 0; nb < CT; ++nb) store(w + kNW * t, nb, dw[t][nb]);
             }
@@ -312,15 +315,19 @@ __device__ __forceinline__ void lstm_backward_narrow_body(const NarrowBwdArgs &a
             float xb[CT];
 #pragma unroll
             for (int nb = 0; nb < CT; ++nb) xb[nb] = lds.xh[k][64 * nb + xb_off];
+            // row 4*gate + u of a tile mt is gate `gate` of unit 4*mt + u
 #pragma unroll
-            for (int t = 0; t < MTW; ++t) {
-                const int mt = w + kNW * t;
-                if (mt < HT) {
-                    // row 4*gate + u of the tile is gate `gate` of unit 4*mt + u
-                    const float ar = lds.da_all[par][64 * mt + ar_off];
+            for (int t = 0; t < kFull; ++t) {
+                if (SPLIT || w + kNW * t < HT) {
+                    const float ar = lds.da_all[par][64 * (w + kNW * t) + ar_off];
 #pragma unroll
                     for (int nb = 0; nb < CT; ++nb) dw[t][nb] = mfma16(ar, xb[nb], dw[t][nb]);
                 }
+            }
+            if constexpr (kLeft > 0) {
+                const float ar = lds.da_all[par][64 * left_tile + ar_off];
+#pragma unroll
+                for (int nb = 0; nb < CL; ++nb) dw_left[nb] = mfma16(ar, lds.xh[k][64 * min(left_col + kShare * nb, CT - 1) + xb_off], dw_left[nb]);
             }
         }
     };

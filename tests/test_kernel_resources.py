@@ -69,3 +69,9 @@ def test_twelve_wave_workgroups_have_a_compute_unit_each(notes):
     kernels = {k: lds for k, (_, lds, _) in notes.items() if re.search(r"lstm_backward_(narrow_kernelI(Li\d+E){2}Lb\dELb1E|together)", k)}
     assert len(kernels) == 14 * (2 + 2)
     assert not {k: lds for k, lds in kernels.items() if lds <= 80 * 1024}
+
+
+def test_recurrences_of_4_series_layers_have_no_scratch(resources):
+    kernels = {k: v for k, (v, _) in resources.items() if re.search(r"lstm_(forward|backward)_(narrow|together)_kernel", k)}
+    assert len(kernels) == 14 * (4 + 4 + 5 + 2)
+    assert not {k: v for k, v in kernels.items() if v}

@@ -123,13 +123,27 @@ def test_kernel_kind_follows_the_measured_limits(program, series, dilation):
         assert chosen(program, hidden, series, dilation) == [(int(groups < 65), int(groups < 160))]
 
 
+@pytest.mark.parametrize("narrow", ["", "100000"])
+@pytest.mark.parametrize("series", [1, 40, 256, 500, 1024, 1500])
+def test_twelve_wave_workgroups_have_one_class_each(program, series, narrow):
+    env = {k: v for k, v in os.environ.items() if k != "ESRNN_NARROW_BELOW"}
+    for hidden, T in ((40, 12), (40, 60), (64, 60)):
+        for dilations in ((1, 2, 3), (5, 16, 60), (255, 256, 700)):
+            out = subprocess.run([program, "plan", str(series), str(T), "4", "3", str(hidden), "0", "all"] + [str(d) for d in dilations],
+                                 env=dict(env, ESRNN_NARROW_BELOW=narrow) if narrow else env, capture_output=True, text=True, check=True).stdout
+            for d, found in zip(dilations, re.findall(r"dilation \d+ narrow \d (\d) chains \d+ (\d+)", out), strict=True):
+                four_series, chains = (int(v) for v in found)
+                if four_series and 4 * -(-series // 16) * chains <= 256:
+                    assert chains == min(d, T - 6)
+
+
 def run_step(program, narrow, *args, how="step"):
     r = subprocess.run([program, how] + [str(a) for a in args], env=dict(os.environ, ESRNN_NARROW_BELOW=str(narrow)),
                        capture_output=True, text=True)
     return r.returncode, r.stdout.strip()
 
 
-# 4-series kernels: chains around a chunk (forward 8 positions, reverse 4) and two, tiles of few positions, and the output stage and
+# 4-series kernels: chains around a group of four positions and two, tiles of few positions, and the output stage and
 # everything else of a step beside them
 @pytest.mark.parametrize("hidden,window", SHAPES)
 def test_waves_of_the_4_series_kernels_are_ordered(program, hidden, window):
@@ -182,7 +196,7 @@ def test_waves_of_layers_in_one_launch_are_ordered(program, hidden, window):
         assert run_step(program, 20, 64, T, window, 3, hidden, min(T, 4), 0, lam, f"{T},{window + 9}", *dilations) == (0, "ok")
 
 
-# chains around a chunk of staged operands, and of one position (a horizon whose outputs hold the words all the same)
+# chains around a group of four positions, and of one position (a horizon whose outputs hold the words all the same)
 @pytest.mark.parametrize("positions", [1, 2, 3, 4, 5, 8, 9, 10])
 def test_chains_of_every_length_in_one_launch(program, positions):
     T = 4 + 24 + positions - 1
