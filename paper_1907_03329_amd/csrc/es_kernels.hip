@@ -1216,7 +1216,7 @@ __global__ void __launch_bounds__(256, NQ > 0 ? 4 : 1) window_backward_stream_ke
                     const bool is_x = e < QX;
                     const int r = 4 * (is_x ? e : e - QX) + g;
                     ok[e] = r < (is_x ? I : H);
-                    // (rows that do not count add nothing to the slot of the window's first one)
+                    // (the address of a row that does not count, which is not accessed: that of the window's first one)
                     at[e] = ((s0 + sp + (ok[e] ? (is_x ? r : I + r) : 0)) & mask) * 16 + n;
                     val[e] = is_x ? q.w[sp][e] : -q.w[sp][e];
                 }
@@ -1265,8 +1265,13 @@ __global__ void __launch_bounds__(256, NQ > 0 ? 4 : 1) window_backward_stream_ke
 
     for (int s0 = -((I + 2) & ~3); s0 < T; s0 += 4) {      // output block: gv[s0 .. s0+3], gu[s0+I-1 .. s0+I+2]
         if constexpr (NQ > 0)
-            if (s0 == 0 && Pt >= 4 && !pads) {
+            if (s0 == 0 && Pt >= 4) {
                 streamed();
+                if (pads && pad_col < Bp)
+                    for (int s = 0; s < (Pt & ~3); ++s) {
+                        a.gv[(size_t)s * Bp + pad_col] = 0.0f;
+                        a.gu[(size_t)(s + I - 1) * Bp + pad_col] = 0.0f;
+                    }
                 s0 = Pt & ~3;
                 if (s0 >= T) break;
             }
@@ -1770,12 +1775,7 @@ hipError_t launch_window_backward(const Plan &pl, const int32_t *lengths, float 
         a.blocks = (pl.NB + 3) / 4;
         const unsigned grid = (unsigned)(a.blocks + jobs.blocks);
         const size_t lds = (size_t)4 * a.R * 16 * sizeof(float);
-        // The kernel that requests a block ahead has four waves on a SIMD, 4096 on the chip, the other one six.  Adjoint in us, the
-        // other one / this one: 65 536 quarterly series (4096 waves) 75 / 57, 131 072 (8192) 22 less of 352, but 70 000 (4375: two
-        // rounds) 15 more of 135.  So where the last round is nearly full.  Four row groups (yearly) take more registers than there
-        // are: 4 to 6 more of 97 and 198 us.
-        const int round = 4096, rounds = (pl.NB + round - 1) / round;
-        if ((pl.I + 3) / 4 + (pl.H + 3) / 4 == 3 && 10ll * pl.NB >= 9ll * rounds * round) window_backward_stream_kernel<3><<<grid, 256, lds, st>>>(a, jobs);
+        if (pl.window_ahead) window_backward_stream_kernel<3><<<grid, 256, lds, st>>>(a, jobs);
         else window_backward_stream_kernel<0><<<grid, 256, lds, st>>>(a, jobs);
         return hipGetLastError();
     }

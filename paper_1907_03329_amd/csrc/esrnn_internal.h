@@ -70,6 +70,7 @@ struct Plan {
     int OT, MO, OP;      // horizon: unit tiles, 16-row MFMA tiles, rows of the Z / O / gO tiles (4*OT)
     int MA;              // 16-row tiles of the hidden dimension in "unit-tile" order: ceil(HT/4)
     int window_stream;   // window adjoint: 1 = streaming kernel (many series tiles), 0 = gather kernel
+    int window_ahead;    // streaming: 1 = the next block's rows are requested while this one's are added up (three row groups)
     int L;
     int K;               // rows of es_params
     int row_gamma1, row_gamma2, row_s1, row_s2;

@@ -42,8 +42,19 @@ constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwa
 // time step and series).  Gather against streaming in us: quarterly shape at 1024 / 2048 / 4096 / 8192 tiles 21 / 35 / 77 / 157
 // and 52 / 58 / 77 / 155, yearly 14 / 22 / 37 / 81 and 28 / 33 / 40 / 85, monthly 131 / 257 / 497 / 979 and 274 / 324 / 440 / 949;
 // a wave of the streaming kernel is a chain of dependent memory round trips and needs about sixteen waves per SIMD to
-// hide them.
+// hide them.  (Of the kernel that requests nothing ahead.)
 constexpr int kWindowStreamFromDefault = 4096;
+
+// Row groups of four that hold the elements of a window position.
+int window_row_groups(int I, int H) { return ceil_div(I, 4) + ceil_div(H, 4); }
+
+// Series tiles from which windows of three row groups take the streaming kernel that requests a block ahead; with four groups
+// (yearly) two blocks are more registers than there are (97 and 198 us at 4096 and 8192 tiles: 4 to 6 us slower); fewer were not measured.  Reverse pass of smoothing and windows in us, gathered /
+// streamed / with a block ahead, quarterly shape: 3072 tiles 59 / 75 / 55, 3333 66 / 86 / 65, 3584 74 / 85 / 64, 4096 92 / 93 / 72, 4375
+// 100 / 105 / 98, 5120 115 / 105 / 105, 8192 188 / 184 / 157, 12 289 273 / 274 / 236, 32 768 734 / 643 / 584; with 40 steps instead of 72 3333 40 / 50 /
+// 42, 3584 42 / 48 / 40, 4375 49 / 56 / 55; windows of 3 + 5 and of 6 + 4 alike.
+constexpr int kWindowAheadFrom = 3600;
+bool window_ahead_pays(int tiles, int I, int H) { return window_row_groups(I, H) == 3 && tiles >= kWindowAheadFrom; }
 
 // Chains of the 16-series reverse kernels, which have one workgroup per compute unit: the fewest that take the least
 // time, counted in rounds of 256 workgroups times classes each walks (80 groups, four classes: 320 workgroups with
@@ -107,7 +118,11 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     // The window adjoint streams tile by tile from this many series tiles on (one wave per tile needs enough
     // tiles to hide memory latency); ESRNN_WINDOW_STREAM_FROM overrides, for measurements.
     int window_stream_from = kWindowStreamFromDefault;
-    if (const char *env = std::getenv("ESRNN_WINDOW_STREAM_FROM")) window_stream_from = std::atoi(env);
+    bool default_stream = true;
+    if (const char *env = std::getenv("ESRNN_WINDOW_STREAM_FROM")) {
+        window_stream_from = std::atoi(env);
+        default_stream = false;
+    }
     // At most so many workgroups in a launch of several layers; ESRNN_TOGETHER overrides (0: every layer in a launch of its own),
     // for measurements.
     int together_groups = kTogetherGroups;
@@ -134,7 +149,11 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     pl.B = cfg.B; pl.T = cfg.T; pl.I = cfg.I; pl.H = cfg.H; pl.h = cfg.hidden; pl.C = cfg.n_categories;
     pl.P = cfg.T - cfg.I - cfg.H + 1;
     pl.NB = ceil_div(cfg.B, kTileN);
-    pl.window_stream = pl.NB >= window_stream_from ? 1 : 0;
+    bool ahead = window_ahead_pays(pl.NB, pl.I, pl.H);
+    pl.window_stream = pl.NB >= window_stream_from || (default_stream && ahead) ? 1 : 0;
+    // ESRNN_WINDOW_AHEAD overrides where the adjoint streams (0: never, 1: wherever there are three row groups), for measurements.
+    if (const char *env = std::getenv("ESRNN_WINDOW_AHEAD")) ahead = std::atoi(env) && window_row_groups(pl.I, pl.H) == 3;
+    pl.window_ahead = pl.window_stream && ahead ? 1 : 0;
     pl.Bp = pl.NB * kTileN;
     pl.Bt = ceil_div(cfg.B, 64) * 64;
     pl.HT = pick_ht(cfg.hidden);

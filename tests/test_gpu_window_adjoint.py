@@ -134,3 +134,26 @@ def test_blocks_requested_ahead_give_the_same_sums():
         binding.esrnn_destroy(h)
     assert np.isfinite(results[1]).all()
     assert np.array_equal(results[0][:, :results[1].shape[1]], results[1])
+
+
+# the same kernel on every way that three row groups are split and filled, on chains without a block, of one and of several, on every
+# number of tiles modulo four (the last tile clears the columns that pad the batch to 64), against the other streaming kernel bit for bit
+@pytest.mark.parametrize("I,H,n_cat", [(4, 8, 0), (3, 5, 0), (1, 7, 0), (6, 4, 0), (8, 1, 0), (5, 3, 6), (4, 8, 6)])
+@pytest.mark.parametrize("B,positions", [(1, 3), (17, 4), (37, 5), (64, 8), (70, 13), (113, 26)])
+def test_blocks_requested_ahead_on_every_shape_of_three_row_groups(I, H, n_cat, B, positions, monkeypatch):
+    import numpy as np
+    from paper_1907_03329_amd import binding, synth
+    cfg = small("ahead", B=B, T=I + H + positions - 1, I=I, H=H, m1=2, hidden=30 if n_cat else 8, blocks=((1,),), n_cat=n_cat)
+    inp = synth.make_inputs(cfg, seed=B, ragged=positions > 4)
+    got = []
+    for ahead in "01":
+        monkeypatch.setenv("ESRNN_WINDOW_STREAM_FROM", "0")
+        monkeypatch.setenv("ESRNN_WINDOW_AHEAD", ahead)
+        step = gc.run_gpu(cfg, inp)
+        views = [step.buffer(k).cpu().numpy() for k in ("grad_u", "grad_v")]
+        v = binding.esrnn_workspace_buffer(step.handle, "grad_u", 0)
+        padded = step.workspace[v.offset_bytes // 4: v.offset_bytes // 4 + int(v.dims[0]) * int(v.dims[1])].view(int(v.dims[0]), -1)
+        got.append(views + [padded[:, 16 * -(-B // 16):].cpu().numpy(), step.grad_es_params.cpu().numpy()])
+        step.close()
+    assert all(np.isfinite(a).all() and np.array_equal(a, b) for a, b in zip(*got))
+    assert not got[1][2].any()
