@@ -1,13 +1,11 @@
 // First layers of the network in one launch, each behind the one below (see lstm_together.h): 4-series layers, the last one
 // possibly a 16-series one.  The kernel template and its launcher, included by one translation unit per kind of last layer.
 //
-// What it gives (a launch a layer -> one launch): 16 quarterly series, four layers 65 us and three gaps between launches -> 43 us;
-// the first two layers of 512 hourly series 440 -> 350 us (of 333, for forecasts, 399 -> 292 us), of 501 monthly ones 188 -> 136 us.
-// Whole calls: 7 quarterly series 80 -> 58 us, step of 16 211 -> 188 us, forecasts of 333 hourly ones 540 -> 431 us, step of 512
-// 1770 -> 1740 us (the third layer, in a launch of its own behind the two, takes 87 us instead of 65).  What bounds it is the first
-// layer's chain; at the end every layer adds what a store, a look and a load past the caches take and a few positions of its own,
-// some 5 us.  512 hourly series: the first layer alone in this launch 285 us, 338 us beside a second one that waits for nothing, 355 us as
-// it is.
+// What it gives (a launch a layer -> one launch), steps: at the rule in plan.cpp; the first two layers of 512 hourly series 400 -> 333 us, of 501 monthly
+// ones 171 -> 136, forecasts of 512 hourly ones 470 -> 382.  What bounds it is the first layer's chain; at the end every layer adds what a
+// store, a look and a load past the caches take and a few positions of its own, some 5 us.  A first layer alone in this launch, without
+// counts, takes 105 us for 512 monthly series and 90 in a launch of its own (quarters of a tile on the same XCD there), 275 for 512 hourly ones;
+// beside it the 16-series layer's stores cost another 30 and 50 us.
 #pragma once
 
 #include "lstm_forward.h"

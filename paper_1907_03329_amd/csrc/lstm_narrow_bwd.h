@@ -61,6 +61,8 @@ struct NarrowBwdArgs {
 // quarterly series (4 + 40 columns, 61 positions): eight waves, operands in chunks of four positions, step C in fp32 445, 224, 45; step C
 // in bf16 alone 497, 236, 52 (the eight waves' second half became longer still); operands staged position by position, and
 // factors of step A formed there 391, 188, 46; twelve waves 302, 172, 36; staging ahead of step C (s_setprio) 292, 169, 35.5.
+// The kind with four waves, which has all of it on the chain waves, gained from staging by position too: hidden 64, two layers of 61 positions,
+// 68 groups 217 -> 191 us, 130 groups 324 -> 284, dilation two 68 groups 116 -> 104.
 // MODE: kLater, layers of one launch (lstm_together.h): this layer waits for the one above it, and its positions are counted; kLast,
 // nobody waits for this one.
 // Staging.  Every position of a chain stages one (the factors that the chain waves need of it, its row of [x ; h]) and requests one:

@@ -47,7 +47,7 @@
 // than the latency of HBM, so operands are requested several positions
 // ahead into registers.  The forward kernel requests the inputs of
 // four positions at a time, one or two such groups ahead; the reverse kernel requests a
-// position and stages one in LDS in every position, in waves that store nothing.
+// position and stages one in LDS in every position, with twelve waves in some that store nothing.
 // A run of four positions is ONE straight run of
 // instructions (the position loop inside it is unrolled): memory operations complete
 // in order, and only with request and use in the same run does the compiler's wait for

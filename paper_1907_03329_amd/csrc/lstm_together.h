@@ -15,8 +15,7 @@
 //
 // What it costs: words of several workgroups in one cache line, and all lanes storing the same one, made every position wait
 // (512 hourly series, the first two layers: 4800 us); a line each and one lane that stores: 350 us (as two launches 440 us).
-// Longer pauses between two looks, fewer positions between a store and its count and chunks of two positions change less than
-// 1 %.  Places dealt so that a tile's workgroups share an XCD, as in the launches of one layer, are slower (517 us), also with
+// Fewer positions between a store and its count change less than 1 %; pauses between two looks: at kWidePollSleep.  Places dealt so that a tile's workgroups share an XCD, as in the launches of one layer, are slower (517 us), also with
 // data handed on in whole cache lines (534 us): what is written through by one workgroup and read past the caches by another
 // is better not in the same L2.
 #pragma once

@@ -25,18 +25,20 @@ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Layers whose 16-series grid has fewer workgroups than this run on the 4-series kernels, separately for the two
 // directions: with four times the workgroups a chip that is not full carries a quarter of the memory traffic on each.
-// Measured on two layers of the same dilation, 61 positions (window 4) and 151 (window 12), in us (16-series kernel
-// against 4-series kernel, second layer, 61 positions unless stated; at 64 and less the 4-series kernels are the faster
-// ones or level, except at hidden 8: 21 / 24 and 26 / 27 at 64):
+// Measured on two layers of the same dilation, 61 positions (window 4) and 151 (window 12), in us with the events around a launch (16-series
+// kernel against 4-series kernel, second layer, 61 positions unless stated; at 64 and less the 4-series kernels are the faster
+// ones):
 //   hidden   groups 68 (dilation 2)                72 (dilation 1)                    128 (dilation 1)
-//      8     forward 13 / 19, reverse 16 / 22      21 / 32,  26 / 38                  22 / 34,  28 / 39
-//     30     22 / 32,  32 / 38                     38 / 56,  55 / 68                  39 / 58,  56 / 70
-//     40     30 / 36,  42 / 58                     54 / 64,  74 / 105                 55 / 66,  75 / 107
-//     50     39 / 43,  66 / 98                     71 / 77,  121 / 179                72 / 79,  123 / 184
-//     60     42 / 48,  189 / 115                   77 / 87,  363 / 212                79 / 91,  366 / 218
-// and with 151 positions alike; first layers with few inputs are nearest to the line (151 positions, 72 groups: hidden 30
-// 105 / 106, hidden 50 129 / 132, 222 / 216).  Above hidden 52 the reverse pass of 16 series is the fp32 kernel, which loses up
-// to 148 groups (369 / 323 us); at 160 it depends on the dilation (one 371 / 324, eight 57 / 64).
+//      8     forward 13 / 16, reverse 16 / 22      21 / 26,  27 / 38                  22 / 27,  28 / 39
+//     30     23 / 25,  32 / 38                     39 / 43,  55 / 65                  39 / 44,  56 / 68
+//     40     31 / 32,  43 / 56                     54 / 51,  74 / 99                  55 / 60,  75 / 102
+//     50     40 / 38,  68 / 92                     72 / 67,  122 / 167                73 / 71,  123 / 172
+//     60     43 / 44,  188 / 104                   77 / 79,  364 / 189                80 / 82,  372 / 194
+// and with 151 positions alike (hidden 40, 72 groups: 124 / 114, 172 / 229).  The line is where the first 4-series kernels lost in both
+// directions; now their forward pass is up to 10 % faster at 68 and 72 groups of hidden 40 and 50 and slower at 128, and first layers of hidden 50
+// are faster in reverse (72 groups, 151 positions 224 / 184).  Above hidden 52 the reverse pass of 16 series is the fp32 kernel, which
+// loses up to 176 groups of dilation one (160: 372 / 289 us, 200: 374 / 376); at 160 it depends on the dilation (eight: 57 / 60, and
+// 121 / 108 with 151 positions).
 constexpr int kNarrowForwardBelow = 65, kNarrowBackwardBelow = 65, kNarrowBackwardBelowFp32 = 160;
 // Series tiles from which the window adjoint streams (one wave per tile) instead of gathering (one thread per
 // time step and series).  Gather against streaming in us: quarterly shape at 1024 / 2048 / 4096 / 8192 tiles 21 / 35 / 77 / 157
@@ -271,11 +273,11 @@ esrnn_status build_plan(const esrnn_config &cfg, Plan &pl)
     }
     // First layers in one launch: every workgroup has one class, so that positions rise in all of them, there is a compute unit for
     // each, and a lane for every word that a workgroup looks at.  16-series layers count no positions: one can only be the last.
-    // Steps in us, launches of one layer / this rule / up to 512 workgroups: quarterly 40 series 218 / 161 / 162, 100 223 / 177 /
-    // 189, 300 244 / 217 / 220, 700 281 / 282 / 296, 1024 313 / 315 / 326; yearly 100 124 / 112 / 114, 500 139 / 137 / 145;
-    // monthly 40 649 / 475 / 443, 100 646 / 534 / 540, 250 713 / 617 / 622, 700 1065 / 1063 / 1099; hourly 20 1355 / 1017 / 1017,
-    // 100 1368 / 1138 / 1144, 250 1524 / 1474 / 1591.  (Up to 512 is faster for 40 monthly series alone, whose fourth forward layer
-    // then joins: 264 workgroups.  One limit for both directions; they were not measured apart.)
+    // Steps in us, launches of one layer / this rule: quarterly 40 series 188 / 134, 100 192 / 151, 300 218 / 196, 700 264 / 264, 1024 298 / 299;
+    // yearly 100 111 / 99, 500 123 / 124; monthly 40 519 / 387, 100 527 / 448, 250 606 / 547, 700 981 / 983; hourly 20 1026 / 819, 100
+    // 1054 / 939, 250 1204 / 1198.  Up to 512 workgroups, with the kernels of eight waves before these: faster for 40 monthly series alone (475 /
+    // 443, whose fourth forward layer then joins: 264 workgroups), else level or up to 8 % slower.  (One limit for both directions; they
+    // were not measured apart.)
     {
         int n = 0, total = 0;
         for (; n < std::min(L, kTogetherMost); ++n) {

@@ -3,8 +3,9 @@ de-seasonalised log series and of the log level) against the float64 CPU oracle.
 
 The library gathers per (time, series) at small batches and streams tile by tile at large ones; the
 choice is made from the number of 16-series tiles when a handle is created (environment variable
-ESRNN_WINDOW_STREAM_FROM: 0 = stream always, a large number = never).  Both kernels are forced onto every
-shape here, ragged lengths included, and compared on every series and time step (grad_u, grad_v) and in
+ESRNN_WINDOW_STREAM_FROM: 0 = stream always, a large number = never), and windows of three row groups may
+take a streaming kernel that requests a block ahead (ESRNN_WINDOW_AHEAD: 0 = never, 1 = wherever it streams).
+Gather and streaming are forced onto every shape here, ragged lengths included, and compared on every series and time step (grad_u, grad_v) and in
 what follows from them (gradients of the smoothing parameters)."""
 import os
 
@@ -63,7 +64,7 @@ def test_each_window_adjoint_kernel_on_every_shape(shape, kind):
 
 
 def test_default_choice_at_many_tiles_agrees_with_the_gather_kernel():
-    """65536 quarterly series (4096 tiles) is where the default turns to the streaming kernel.  The oracle
+    """65536 quarterly series (4096 tiles) stream by default, a block requested ahead.  The oracle
     cannot run that size in the time of a test; both kernels are compared with it on every shape above,
     and here with each other on the full-size batch: the same sums in a different order."""
     import numpy as np
@@ -96,7 +97,7 @@ def test_default_choice_at_many_tiles_agrees_with_the_gather_kernel():
     assert err <= 1e-5, err
 
 
-# three row groups, and as many tiles as fill the chip: the kernel that requests a block ahead, on lengths that end in every place of a
+# three row groups, and more than 3600 tiles: the kernel that requests a block ahead, on lengths that end in every place of a
 # block and on tiles without a block, bit for bit what the other one (fewer series tiles) gives for the same series.  (Without the level
 # penalty, whose normaliser counts all series; the comparison of the kernels at 65 536 series above has it.)
 def test_blocks_requested_ahead_give_the_same_sums():
